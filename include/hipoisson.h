@@ -171,9 +171,9 @@ enum {
 /* Create a plan for one problem (the initialisation of Section 3.2.1): grid
  * geometry, eigenvalue tables or the Green's spectrum (computed in FP64 on
  * the GPU for unbounded problems), twiddle tables, workspaces.  Any cell count
- * is accepted (Section 2.3.2): transform lengths with prime factors above 5
- * run a direct stage per such prime (R multiply-adds per output), so they are
- * slower than 2^a 3^b 5^c lengths; a length above 8192 (FP32) or 4096 (FP64),
+ * is accepted (Section 2.3.2): prime factors R of a transform length above 13
+ * (FP32) or 7 (FP64) run a stage of about R multiply-adds per output, so such
+ * lengths are slower than others; a length above 8192 (FP32) or 4096 (FP64),
  * or a doubled free-space length above 4096 (the Green's function is
  * transformed in FP64), returns HP_E_UNSUPPORTED.  Returns HP_E_ARG / HP_E_UNSUPPORTED for
  * descriptors it cannot serve.  Blocking. */

@@ -111,51 +111,121 @@ void r2r_ops(int bc, int grid, int n, int* xf, int* xb, int* L, double* c) {
   else { *xf = X_DCT2; *xb = X_DCT3; *L = 2 * n; *c = 2.0 * n; }
 }
 
-bool factorize(int L, int* radix, int* nstage) {
+// Accepted transform lengths: at most kMaxStages factors 8, 4, 2, 3, 5 (taken
+// greedily) and primes.
+bool length_ok(int L) {
   if (L < 1) return false;
   int s = 0, r = L;
-  while (r > 1) {
-    int f = 0;
+  for (; r > 1; ++s) {
+    int f;
     if (r % 8 == 0) f = 8;
     else if (r % 4 == 0) f = 4;
     else if (r % 2 == 0) f = 2;
     else if (r % 3 == 0) f = 3;
     else if (r % 5 == 0) f = 5;
     else {
-      // the smallest prime factor (> 5): a direct prime-radix stage
       f = 7;
       while (r % f != 0 && (long long)f * f <= r) f += 2;
       if (r % f != 0) f = r;
     }
     if (s >= kMaxStages) return false;
-    radix[s++] = f;
     r /= f;
   }
-  *nstage = s;
   return true;
 }
 
-// Complex elements per thread of a general-kernel FFT stage (PassArgs.big).
-int maxe(int prec, int big) { return (big ? 32 : 16) / (prec == 0 ? 1 : 2); }
-
-// Pick the tile width P (power of two) for a pass; returns 0 if nothing fits.
-// lds(P) gives the LDS bytes, nfft(P) the transforms per FFT call.
-template <class F1, class F2>
-int choose_P(int want, int minP, int Np, int L, int prec, int big, F1 lds, F2 nfft, int* lds_out) {
-  int cap = 1;
-  while (cap < Np) cap <<= 1;
-  int P = want;
-  if (P > cap) P = cap < minP ? minP : cap;
-  const int budgets[2] = {64 * 1024, 160 * 1024};
-  for (int b = 0; b < 2; ++b) {
-    for (int q = P; q >= minP; q >>= 1) {
-      if ((long long)nfft(q) * L <= (long long)maxe(prec, big) * kThreads && lds(q) <= budgets[b]) {
-        *lds_out = (int)lds(q);
-        return q;
+// Radices of a general pass (a.L, a.P, a.big set): the fewest stages, then the
+// smallest sum, among the factorisations whose every stage fits the threads'
+// registers at this tile width (general_fits).  A stage costs two barriers
+// and a trip of the whole tile through LDS whatever its radix, so two stages
+// of radix 16 and 15 beat four of radix 8, 5, 3 and 2.  Prime factors above the
+// register radices come first (their stage is cheapest without twiddles),
+// then the radices in descending order (the first stage has no twiddles).
+bool choose_radices(PassArgs& a, int prec) {
+  const int top = max_radix(prec);
+  int big[kMaxStages], nbig = 0, rest = a.L;
+  // the primes above `top` divided out: split `rest` over 2..top
+  {
+    int r = a.L;
+    for (int f = 2; (long long)f * f <= r; ++f)
+      while (r % f == 0) {
+        if (f > top) {
+          if (nbig >= kMaxStages) return false;
+          big[nbig++] = f;
+        }
+        r /= f;
       }
+    if (r > top) {
+      if (nbig >= kMaxStages) return false;
+      big[nbig++] = r;
     }
+    for (int i = 0; i < nbig; ++i) rest /= big[i];
   }
-  return 0;
+  int best[kMaxStages], nbest = -1, sum_best = 0, cur[kMaxStages];
+  auto fits = [&](int n) {
+    PassArgs t = a;
+    t.nstage = nbig + n;
+    for (int i = 0; i < nbig; ++i) t.radix[i] = big[i];
+    for (int i = 0; i < n; ++i) t.radix[nbig + i] = cur[i];
+    return general_fits(t, prec);
+  };
+  auto search = [&](auto&& self, int r, int limit, int n, int sum) -> void {
+    if (r == 1) {
+      if (nbest < 0 || n < nbest || (n == nbest && sum < sum_best)) {
+        if (!fits(n)) return;
+        nbest = n;
+        sum_best = sum;
+        for (int i = 0; i < n; ++i) best[i] = cur[i];
+      }
+      return;
+    }
+    if (nbig + n >= kMaxStages || (nbest >= 0 && n >= nbest)) return;
+    for (int f = std::min(limit, r); f >= 2; --f) {
+      if (r % f) continue;
+      cur[n] = f;
+      self(self, r / f, f, n + 1, sum + f);
+    }
+  };
+  search(search, rest, top, 0, 0);
+  if (nbest < 0) return false;
+  a.nstage = nbig + nbest;
+  for (int i = 0; i < nbig; ++i) a.radix[i] = big[i];
+  for (int i = 0; i < nbest; ++i) a.radix[nbig + i] = best[i];
+  return true;
+}
+
+// Tile width, register budget, radices and LDS of a general pass.
+//
+// The widest tile up to `want` pencils that fits 64 KB of LDS (two workgroups
+// per CU at least) with the smaller register budget, then 160 KB, then the
+// larger budget for the tiles of long transforms.  Where that leaves the chip
+// short of workgroups the tile is narrowed (kFillTiles): a pass of fewer tiles
+// than CUs takes as long as one tile does (FP64 periodic 2D of about 200 x 250
+// points, 16 and 5 tiles: 151 -> 38 us together with the stages above).
+constexpr int kFillTiles = 256;  // one workgroup per CU
+constexpr int kNarrowest = 4;    // pencils a tile is narrowed to
+
+bool choose_tile(PassArgs& a, int prec, int want, int minP) {
+  int cap = 1;
+  while (cap < a.Np) cap <<= 1;
+  const int top = std::min(want, std::max(cap, minP));
+  for (int big = 0; big < 2; ++big)
+    for (int budget : {64 * 1024, 160 * 1024})
+      for (int P = top; P >= minP; P >>= 1) {
+        a.P = P;
+        a.big = big;
+        if (!choose_radices(a, prec)) continue;
+        a.lds_bytes = general_lds_bytes(a, P, prec);
+        if (a.lds_bytes > budget) continue;
+        while (P / 2 >= std::max(minP, kNarrowest) && (long long)((a.Np + P - 1) / P) * a.No < kFillTiles) {
+          P >>= 1;
+          a.P = P;
+          if (!choose_radices(a, prec)) return false;
+          a.lds_bytes = general_lds_bytes(a, P, prec);
+        }
+        return true;
+      }
+  return false;
 }
 
 // ---------------------------------------------------------- validation
@@ -227,15 +297,15 @@ hp_status validate(const hp_desc* d) {
       if (axis_bc(*d, a) == HP_NEUMANN && d->grid == HP_REGULAR && d->nc[a] < 2)
         return fail(nullptr, HP_E_ARG, "Neumann regular derivatives need 2 cells per axis");
   }
-  // any transform length whose radix stages (2, 3, 4, 5, 8 and primes) number at
-  // most kMaxStages, up to the largest tile of one pencil
+  // any transform length of at most kMaxStages factors, up to the largest tile
+  // of one pencil
   for (int a = 0; a < d->ndim; ++a) {
     const int n = unknowns(axis_bc(*d, a), d->grid, (int)d->nc[a]);
-    int L = n, xf, xb, rad[kMaxStages], ns;
+    int L = n, xf, xb;
     double c;
     if (r2r_plan(*d)) r2r_ops(axis_bc(*d, a), d->grid, n, &xf, &xb, &L, &c);
     if (unb || axis_bc(*d, a) == HP_UNBOUNDED) L = 2 * n;
-    if (!factorize(L, rad, &ns))
+    if (!length_ok(L))
       return fail(nullptr, HP_E_UNSUPPORTED,
                   "transform length " + std::to_string(L) + " needs too many radix stages");
     if ((long long)L > (long long)(d->prec == 0 ? 32 : 16) * kMaxLenThreads)
@@ -515,7 +585,6 @@ hp_status green_spectrum(hp_plan p, Problem& P) {
       a.n = M[axis];
       a.nin = M[axis];
       a.nout = axis == 2 ? K2 : M[axis];
-      if (!factorize(a.L, a.radix, &a.nstage)) { restore(); return fail(p, HP_E_UNSUPPORTED, "Green's length"); }
       const void* tw;
       hp_status s = twiddles(p, a.L, &tw);
       if (s != HP_OK) { restore(); return s; }
@@ -529,12 +598,6 @@ hp_status green_spectrum(hp_plan p, Problem& P) {
         a.out_sj = 1; a.out_sp = K2; a.out_so = (long long)M[1] * K2;
         a.Np = M[1]; a.No = M[0];
         a.in_jfast = a.out_jfast = 1;
-        int lds;
-        a.big = 1;
-        a.P = choose_P(16, 2, a.Np, a.L, 1, 1,
-                       [&](int q) { return (long long)(q / 2) * a.L * 16 + (long long)q * a.nin * 8; },
-                       [&](int q) { return q / 2; }, &lds);
-        a.lds_bytes = lds;
       } else {
         a.in[0] = spec;
         a.out[0] = spec;
@@ -543,13 +606,8 @@ hp_status green_spectrum(hp_plan p, Problem& P) {
         a.in_so = a.out_so = axis == 1 ? (long long)M[1] * K2 : K2;
         a.Np = K2; a.No = axis == 1 ? M[0] : M[1];
         a.in_jfast = a.out_jfast = 0;
-        int lds;
-        a.big = 1;
-        a.P = choose_P(8, 1, a.Np, a.L, 1, 1, [&](int q) { return (long long)q * a.L * 16; },
-                       [&](int q) { return q; }, &lds);
-        a.lds_bytes = lds;
       }
-      if (a.P == 0) { restore(); return fail(p, HP_E_UNSUPPORTED, "Green's transform does not fit"); }
+      if (!choose_tile(a, 1, axis == 2 ? 16 : 8, axis == 2 ? 2 : 1)) { restore(); return fail(p, HP_E_UNSUPPORTED, "Green's transform does not fit"); }
       hipError_t e = launch_pass(a, 1, 1, p->stream);
       if (e != hipSuccess) { restore(); return fail(p, HP_E_DEVICE, std::string("Green's pass: ") + hipGetErrorString(e)); }
     }
@@ -818,65 +876,27 @@ unsigned long long general_key(const PassArgs& a, int prec, int want, int minP, 
   return tune_hash(v, (int)(sizeof(v) / sizeof(v[0])));
 }
 
-// Fill the FFT fields of a pass for length L; P from the LDS model.  A tuned
+// Fill the FFT fields of a pass for length L (choose_tile).  A tuned
 // configuration (radix order, tile width, register budget) replaces the
 // default when it fits this pass; otherwise the default stands.
-hp_status finish_pass_with(hp_plan p, PassArgs& a, int want, int minP, int lds_kind,
-                           const Tune* tn) {
-  if (tn) {
-    a.nstage = tn->nstage;
-    for (int s = 0; s < tn->nstage; ++s) a.radix[s] = tn->radix[s];
-    want = tn->P;
-  } else if (!factorize(a.L, a.radix, &a.nstage)) {
-    return fail(p, HP_E_UNSUPPORTED, "length");
-  }
+hp_status finish_pass_with(hp_plan p, PassArgs& a, int want, int minP, const Tune* tn) {
   const void* tw;
   HP_TRY(twiddles(p, a.L, &tw));
   a.tw = tw;
-  const long long cs = 2 * (long long)p->es, es = p->es;
-  int lds = 0;
-  auto nfft_pair = [](int q) { return q / 2; };
-  auto nfft_one = [](int q) { return q; };
-  // the smaller register budget first (more resident waves), the larger one
-  // when a tile of this length does not fit it
-  for (int big = tn ? tn->big : 0; big < (tn ? tn->big + 1 : 2); ++big) {
-    a.big = big;
-    switch (lds_kind) {
-      case 0:  // one-way complex
-        a.P = choose_P(want, minP, a.Np, a.L, p->prec, big, [&](int q) { return (long long)q * a.L * cs; }, nfft_one, &lds);
-        break;
-      case 1:  // one-way real input (pairs)
-        a.P = choose_P(want, 2, a.Np, a.L, p->prec, big,
-                       [&](int q) { return (long long)(q / 2) * a.L * cs + (long long)q * a.nin * es; }, nfft_pair, &lds);
-        break;
-      case 2:  // one-way C2R (pairs, complex staging)
-        a.P = choose_P(want, 2, a.Np, a.L, p->prec, big,
-                       [&](int q) { return (long long)(q / 2) * a.L * cs + (long long)q * a.nin * cs; }, nfft_pair, &lds);
-        break;
-      case 3:  // r2r sandwich
-        a.P = choose_P(want, 2, a.Np, a.L, p->prec, big,
-                       [&](int q) { return (long long)(q / 2) * a.L * cs + (long long)q * a.nin * es; }, nfft_pair, &lds);
-        break;
-      case 4: {  // c2c sandwich: (nS + 1) complex tiles
-        const int nS = diff_is_adjoint(a.diff) ? a.n_out : a.n_in;
-        a.P = choose_P(want, minP, a.Np, a.L, p->prec, big,
-                       [&](int q) { return (long long)(nS + 1) * q * a.L * cs; }, nfft_one, &lds);
-      } break;
-      case 5: {  // paired c2c sandwich (1D periodic)
-        const int nS = a.n_in;
-        a.P = choose_P(want, 2, a.Np, a.L, p->prec, big,
-                       [&](int q) {
-                         return (long long)nS * (q / 2) * a.L * cs +
-                                std::max((long long)(q / 2) * a.L * cs, (long long)q * a.nin * es);
-                       },
-                       nfft_pair, &lds);
-      } break;
-    }
-    if (a.P > 0) break;
+  if (tn) {
+    a.nstage = tn->nstage;
+    for (int s = 0; s < tn->nstage; ++s) a.radix[s] = tn->radix[s];
+    a.P = tn->P;
+    a.big = tn->big;
+    a.lds_bytes = general_lds_bytes(a, a.P, p->prec);
+    int cap = 1;
+    while (cap < a.Np) cap <<= 1;
+    if (a.P < minP || a.P > std::max(cap, minP) || !general_fits(a, p->prec) || a.lds_bytes > 160 * 1024)
+      return HP_E_UNSUPPORTED;  // does not fit: caller takes the default
+    return HP_OK;
   }
-  if (tn && a.P != tn->P) return HP_E_UNSUPPORTED;  // does not fit: caller takes the default
-  if (a.P == 0) return fail(p, HP_E_UNSUPPORTED, "pass of length " + std::to_string(a.L) + " does not fit in LDS");
-  a.lds_bytes = lds;
+  if (!choose_tile(a, p->prec, want, minP))
+    return fail(p, HP_E_UNSUPPORTED, "pass of length " + std::to_string(a.L) + " does not fit in LDS");
   return HP_OK;
 }
 
@@ -888,13 +908,13 @@ hp_status finish_pass(hp_plan p, PassArgs& a, int want, int minP, long long lds_
   if (it != p->tuned.end() && it->second.fast == FAST_NONE &&
       radix_ok(a.L, it->second.radix, it->second.nstage)) {
     PassArgs t = a;
-    if (finish_pass_with(p, t, want, minP, lds_kind, &it->second) == HP_OK) {
+    if (finish_pass_with(p, t, want, minP, &it->second) == HP_OK) {
       a = t;
       a.tune_key = key;
       return HP_OK;
     }
   }
-  HP_TRY(finish_pass_with(p, a, want, minP, lds_kind, nullptr));
+  HP_TRY(finish_pass_with(p, a, want, minP, nullptr));
   a.tune_key = key;
   return HP_OK;
 }

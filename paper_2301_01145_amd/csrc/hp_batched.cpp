@@ -125,7 +125,7 @@ hp_status batched_setup(hp_plan p) {
   }
   // items: pass level by pass level, problems in order, tiles in order
   std::vector<int> first(lists.size(), 0);
-  int npass = 0, maxlev = 0, lds = 0, big = 0;
+  int npass = 0, maxlev = 0, lds = 0, big = 0, gen = 0;
   for (size_t q = 0; q < lists.size(); ++q) {
     first[q] = npass;
     npass += (int)lists[q].size();
@@ -133,9 +133,11 @@ hp_status batched_setup(hp_plan p) {
     for (auto& r : lists[q]) {
       lds = std::max(lds, r.a.lds_bytes);
       big = std::max(big, r.a.big);
+      gen = std::max(gen, general_mode(r.a, p->prec));
     }
   }
   p->batch_big = big;
+  p->batch_gen = gen;
   const int per_item = batch_tiles_of(p);
   std::vector<BatchItem> items;
   p->batch_groups.clear();
@@ -198,7 +200,7 @@ hp_status batched_setup(hp_plan p) {
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return plan_fail(p, HP_E_DEVICE, "device query failed");
-  const int per_cu = p->batch_wf ? batched_wf_blocks_per_cu(xf, lds) : batched_blocks_per_cu(lds, p->prec, big);
+  const int per_cu = p->batch_wf ? batched_wf_blocks_per_cu(xf, lds) : batched_blocks_per_cu(lds, p->prec, gen);
   p->batch_grid = std::max(1, std::min(p->batch_nitems, per_cu * cus));
   // level form: streams and events for the groups of a level (the most
   // groups in one level - 1 forked streams; a fork and the joins per level)
@@ -330,7 +332,7 @@ hp_status batched_solve(hp_plan p) {
           : launch_batched((const PassArgs*)p->batch_probs, (const BatchItem*)p->batch_items,
                            p->batch_nitems, p->batch_counters, p->batch_ncounters,
                            (int*)(p->batch_counters + p->batch_ncounters), p->batch_grid,
-                           p->batch_lds, p->prec, p->batch_big, p->stream);
+                           p->batch_lds, p->prec, p->batch_gen, p->stream);
   if (e != hipSuccess)
     return plan_fail(p, HP_E_DEVICE, std::string("batched launch: ") + hipGetErrorString(e));
   p->solved = true;

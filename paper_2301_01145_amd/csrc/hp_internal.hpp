@@ -94,6 +94,7 @@ struct PassArgs {
   int nunk[3];             // unknown counts per logical axis
   int lds_bytes;
   int big;                 // general kernels: 1 = the larger per-thread register budget
+  int prime_table;         // general kernels: the prime stage's factors are in LDS
   // wavefront-FFT kernels of the free-space path (0: general pass)
   int fast;                // FAST_* below
   int un[3];               // physical (undoubled) sizes n_a
@@ -191,6 +192,15 @@ int fast_tile(int fast, int L, int prec);
 // Tile widths a wavefront-FFT pass is built for.
 bool fast_tile_ok(int fast, int L, int P, int prec);
 
+// General kernels (hp_kernels.hip): the largest radix with a register stage
+// (larger prime factors run the prime stage), whether a pass's radices fit the
+// threads' registers at its tile width and budget, the LDS bytes of a tile of
+// P pencils, and the kernel mode the pass needs (batched plans run one mode
+// for all passes: the largest).
+int max_radix(int prec);
+bool general_fits(const PassArgs& a, int prec);
+int general_lds_bytes(PassArgs& a, int P, int prec);  // sets a.prime_table
+int general_mode(const PassArgs& a, int prec);
 // Launch one pass over `grid_y` independent field groups.
 hipError_t launch_pass(const PassArgs& a, int prec, int grid_y, hipStream_t s);
 // Free-space kernel of the plan (Section 2.5.2 readings) in `dim` = 1, 2 or
@@ -265,7 +275,7 @@ hipError_t launch_zero_mode_noalloc(const PassArgs* a, const void* const* f, int
 // to 1 if a dependency wait exceeds its spin limit (the item is then skipped).
 hipError_t launch_batched(const PassArgs* passes, const BatchItem* items, int nitems,
                           unsigned* counters, int ncounters, int* err, int grid, int lds,
-                          int prec, int big, hipStream_t s);
+                          int prec, int mode, hipStream_t s);
 // Batched persistent solve on the wavefront kernels (FP32, transform lengths
 // 64, 96, 128, 192, 256; hp_bounded.hip).  Passes carry fast = FAST_R2R_C /
 // FAST_R2R_S / FAST_R2R_SW, the wavefront twiddles and P = 32; xf is the
@@ -296,5 +306,5 @@ struct BatchGroup {
 hipError_t launch_batched_group(int xf, const PassArgs* passes, const BatchItem* items,
                                 const BatchGroup& g, int* err, hipStream_t s);
 // Resident workgroups per CU of the persistent kernel with `lds` bytes of LDS.
-int batched_blocks_per_cu(int lds, int prec, int big);
+int batched_blocks_per_cu(int lds, int prec, int mode);
 }  // namespace hp

@@ -3,11 +3,23 @@
 // One launch transforms every pencil (1D line) of a field along one axis.  A
 // workgroup of 256 threads takes a tile of P pencils: it loads the tile from
 // HBM with unit-stride runs (along the pencil when the pencil is contiguous,
-// across pencils otherwise), builds the complex FFT input in LDS, runs a
-// mixed-radix (2/3/4/5/8, and any larger prime as a direct stage) Stockham
-// FFT in LDS and writes the result with
-// unit-stride runs again.  The strides of the input and output sides are
-// independent, so a pass can also transpose.
+// across pencils otherwise) straight into the complex FFT input in LDS, runs a
+// mixed-radix Stockham FFT there (radices 2..16 in FP32, 2..10 in FP64, any
+// larger prime by a stage of its own) and writes the result with unit-stride
+// runs again.  The strides of the input and output sides are independent, so
+// a pass can also transpose.
+//
+// What bounds them: at the sizes of one solve (1 to 16 million points, resident
+// in the 256 MB cache) a pass is one or two rounds of workgroups, each a chain
+// of load, stages (two barriers and a trip through LDS each) and store, so its
+// time is the length of that chain, not bytes or flops.  Hence few stages of
+// large radix, no run-time divisions, no raw copy of the tile beside the FFT
+// input, LDS rows that every access pattern takes without bank conflicts, and
+// tiles narrowed where there are fewer of them than CUs.  Measured on one
+// MI355X, whole solves, against stages of radix <= 8 with a raw tile and direct
+// prime sums: 120 x 96 x 80 FP64 Neumann 123 -> 83 us, 96 x 80 x 100 FP64 free
+// space 139 -> 97 us, 128^3 FP32 semi-unbounded gradient 381 -> 239 us, 127^3
+// FP32 periodic (a prime) 971 -> 111 us.
 //
 // The sandwich pass (last axis of the forward transform) loads, transforms,
 // multiplies by the spectral multiplier (Table 1 eigenvalues or the Green's
@@ -19,22 +31,112 @@
 
 #include "hp_device.hpp"
 #include "hp_faces.hpp"
+#include "hp_gendft.hpp"
 #include "hp_internal.hpp"
 
 namespace hp {
 
+// ----------------------------------------------------------- index helpers
+// Quotients by run-time divisors d <= 8192 of small numbers (x d < 2^32), one
+// multiply instead of the division sequence: m = ceil(2^32 / d).
+__device__ __forceinline__ unsigned div_magic(int d) { return 0xffffffffu / (unsigned)d + 1u; }
+__device__ __forceinline__ int div_by(int x, int d, unsigned m) {
+  return d > 1 ? (int)__umulhi((unsigned)x, m) : x;
+}
+
+// ------------------------------------------------------------- LDS tile
+// The FFT data of a tile: element m of transform f (a pencil pair, or a
+// complex pencil) at row m, column f.  Rows hold nf = 2^lg transforms and, from
+// two on, one pad element: consecutive lanes take consecutive columns, so
+// every access of a stage is a set of whole rows whatever its stride, and the
+// accesses along m (rows read one column at a time) step over all banks.
+// Pointers carry the LDS address space, so that functions that are not inlined
+// use LDS instructions and not generic ones.
+#define HP_LDS __attribute__((address_space(3)))
+#define HP_GLB __attribute__((address_space(1)))
+template <typename T>
+struct V2 {
+  typedef T t __attribute__((ext_vector_type(2)));
+  // the same in global memory, aligned to one element only
+  typedef T u __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+};
+template <typename T>
+using GC = const HP_GLB typename V2<T>::t*;  // complex table or field in global memory
+template <typename T>
+__device__ __forceinline__ GC<T> glb(const void* p) {
+  return (GC<T>)p;
+}
+template <typename T>
+__device__ __forceinline__ C2<T> ldc(GC<T> p, long long i) {
+  const typename V2<T>::t v = p[i];
+  return {v.x, v.y};
+}
+template <typename T>
+__device__ __forceinline__ void stc(void* p, long long i, C2<T> c) {
+  typename V2<T>::t v;
+  v.x = c.re;
+  v.y = c.im;
+  ((HP_GLB typename V2<T>::t*)p)[i] = v;
+}
+template <typename T>
+struct LTile {
+  HP_LDS typename V2<T>::t* z;
+  int S, lg;
+  __device__ __forceinline__ C2<T> get(int i) const {
+    const typename V2<T>::t v = z[i];
+    return {v.x, v.y};
+  }
+  __device__ __forceinline__ void put(int i, C2<T> c) const {
+    typename V2<T>::t v;
+    v.x = c.re;
+    v.y = c.im;
+    z[i] = v;
+  }
+};
+__host__ __device__ constexpr int tile_row(int nf) { return nf > 1 ? nf + 1 : 1; }
+
+template <typename T>
+__device__ __forceinline__ LTile<T> lds_tile(unsigned char* smem, int nf, int L, int index) {
+  LTile<T> z;
+  z.lg = 31 - __builtin_clz((unsigned)nf);
+  z.S = tile_row(nf);
+  z.z = (HP_LDS typename V2<T>::t*)smem + (size_t)index * L * z.S;
+  return z;
+}
+
 // ------------------------------------------------------------- Stockham FFT
-// One radix-R stage over `nfft` transforms of length L stored contiguously in
-// LDS.  Butterfly j of a transform reads x[j + t L/R] (t < R), twiddles input
-// t by W_{Ns R}^{t k} (k = j mod Ns), and writes output t' to
-// (j / Ns) Ns R + k + t' Ns.  All reads finish (barrier) before any write, so
-// the stage is in place.
-template <typename T, int R, int MAXE, bool INV>
-__device__ __attribute__((noinline)) void fft_stage(C2<T>* Z, int L, int nfft, int Ns, int twstep,
-                                          const C2<T>* __restrict__ tw) {
-  constexpr int MB = (MAXE + R - 1) / R;
+// Kernel modes.  Complex elements per thread of one stage: 16 (FP32) / 8
+// (FP64), fewer registers and more resident waves, or (GM_BIG) 32 / 16 for
+// tiles of long transforms.  GM_SMALL has no prime stage, whose accumulators
+// would set the registers of every kernel that holds it (FP64: 184 against
+// 82, two resident waves per SIMD against five).
+enum GenMode : int { GM_SMALL = 0, GM_PRIME = 1, GM_BIG = 2 };
+template <typename T, int MODE>
+struct Maxe {
+  static constexpr int v = (MODE == GM_BIG ? 32 : 16) / (sizeof(T) == 8 ? 2 : 1);
+};
+
+// Butterflies of radix R a thread holds: rounded down in the smaller budget
+// (its registers are the kernel's), up in the larger one (every length fits).
+template <typename T>
+__host__ __device__ constexpr int stage_slots(int R, int maxe) {
+  return maxe > (sizeof(T) == 4 ? 16 : 8) ? (maxe + R - 1) / R : (maxe / R > 1 ? maxe / R : 1);
+}
+
+// One radix-R stage over the nf transforms of a tile.  Butterfly j of a
+// transform reads x[j + t L/R] (t < R), twiddles input t by W_{Ns R}^{t k}
+// (k = j mod Ns; no twiddles in the first stage, Ns = 1), and writes output t'
+// to (j / Ns) Ns R + k + t' Ns.  All reads finish (barrier) before any write,
+// so the stage is in place.
+template <typename T, int R, int MAXE>
+__device__ __attribute__((noinline)) void fft_stage(LTile<T> Z, int L, int Ns, GC<T> tw) {
+  constexpr int MB = stage_slots<T>(R, MAXE);
   const int nbl = L / R;
-  const int total = nfft * nbl;
+  const int total = nbl << Z.lg;
+  const int mask = (1 << Z.lg) - 1;
+  const unsigned mN = div_magic(Ns);
+  const int twstep = nbl / Ns;
+  const int rstep = nbl * Z.S, wstep = Ns * Z.S;
   C2<T> v[MB][R];
   int ob[MB];
 #pragma unroll
@@ -42,123 +144,190 @@ __device__ __attribute__((noinline)) void fft_stage(C2<T>* Z, int L, int nfft, i
     const int idx = threadIdx.x + b * kThreads;
     ob[b] = -1;
     if (idx < total) {
-      const int f = idx / nbl;
-      const int j = idx - f * nbl;
-      const int k = j % Ns;
-      const C2<T>* src = Z + f * L + j;
+      const int f = idx & mask, j = idx >> Z.lg;
+      const int k = j - div_by(j, Ns, mN) * Ns;
+      const int src = j * Z.S + f;
 #pragma unroll
-      for (int t = 0; t < R; ++t) {
-        C2<T> x = src[t * nbl];
-        if (t > 0 && k > 0) {
-          C2<T> w = tw[t * k * twstep];
-          if (INV) w.im = -w.im;
-          x = cmul(x, w);
-        }
-        v[b][t] = x;
+      for (int t = 0; t < R; ++t) v[b][t] = Z.get(src + t * rstep);
+      if (Ns > 1) {
+        const int e = k * twstep;
+#pragma unroll
+        for (int t = 1; t < R; ++t) v[b][t] = cmul(v[b][t], ldc<T>(tw, t * e));
       }
-      ob[b] = f * L + (j - k) * R + k;
+      ob[b] = ((j - k) * R + k) * Z.S + f;
     }
   }
   __syncthreads();
 #pragma unroll
   for (int b = 0; b < MB; ++b) {
     if (ob[b] >= 0) {
-      dftR<T, R, INV>(v[b]);
+      dft_any<T, R>(v[b]);
 #pragma unroll
-      for (int t = 0; t < R; ++t) Z[ob[b] + t * Ns] = v[b][t];
+      for (int t = 0; t < R; ++t) Z.put(ob[b] + t * wstep, v[b][t]);
     }
   }
   __syncthreads();
 }
 
-// One stage of a prime radix R > 5 (lengths with a prime factor that the fixed
-// radices do not cover).  Output t' of butterfly j (k = j mod Ns) is the
-// R-term sum  sum_t x[j + t L/R] W_{Ns R}^{t (k + t' Ns)}: the stage twiddle
-// W_{Ns R}^{t k} and the R-point DFT factor W_R^{t t'} in one table entry.
-// It costs R multiply-adds per output instead of O(log R), which is what a
-// direct DFT of a prime length costs.  One output per thread slot (the tile
-// holds at most kThreads * MAXE elements); all reads finish (barrier) before
-// any write, so the stage is in place like the fixed-radix ones.
-template <typename T, int MAXE, bool INV>
-__device__ __attribute__((noinline)) void fft_stage_prime(C2<T>* Z, int L, int nfft, int R, int Ns,
-                                                          int twstep, const C2<T>* __restrict__ tw) {
-  const int nbl = L / R;
-  const int total = nfft * L;
-  C2<T> v[MAXE];
-  int ob[MAXE];
+// One stage of a prime radix R that has no register DFT, by the even and odd
+// parts of the butterfly's inputs (s_t = x_t + x_{R-t}, d_t = x_t - x_{R-t}
+// after the stage twiddles):
+//   X_u, X_{R-u} = x_0 + sum_t s_t cos(2 pi t u / R) -+ i sum_t d_t sin(2 pi t u / R),
+// t = 1 .. h = (R - 1) / 2, a quarter of the products of the direct sum and
+// half its terms per accumulator.  First the parts replace the inputs in
+// place (each pair belongs to one thread); then a thread accumulates kPrimeB
+// values u of one butterfly, so one read of s_t and d_t serves 4 kPrimeB
+// multiply-adds, the factors coming from a table of R values in LDS; the
+// outputs are written after all reads.
+constexpr int kPrimeB = 4;
+// TABLE false: the factors come from the twiddle table instead (tiles that
+// leave no LDS for them: coupled fields of lengths above 4096).
+template <typename T, int MAXE, bool TABLE>
+__device__ __attribute__((noinline)) void fft_stage_prime(LTile<T> Z, HP_LDS typename V2<T>::t* wR,
+                                                          int L, int R, int Ns, GC<T> tw) {
+  // items per thread: blocks of kPrimeB outputs u of one butterfly (the last
+  // block of a butterfly may be partly unused: at most 1.5 slots per element)
+  constexpr int MBP = MAXE * 3 / 16 > 2 ? MAXE * 3 / 16 : 2;
+  const int nbl = L / R, h = (R - 1) / 2;
+  const int mask = (1 << Z.lg) - 1;
+  const int twstep = nbl / Ns;
+  const int rstep = nbl * Z.S;
+  const unsigned mN = div_magic(Ns), mB = div_magic(nbl);
+  if constexpr (TABLE)
+    for (int e = threadIdx.x; e < R; e += kThreads) {
+      const C2<T> w = ldc<T>(tw, e * nbl);
+      typename V2<T>::t c;
+      c.x = w.re;
+      c.y = -w.im;  // (cos, sin) of 2 pi e / R
+      wR[e] = c;
+    }
+  const int total1 = (nbl * h) << Z.lg;
+  for (int idx = threadIdx.x; idx < total1; idx += kThreads) {
+    const int f = idx & mask, r = idx >> Z.lg;
+    const int t1 = div_by(r, nbl, mB), j = r - t1 * nbl;
+    const int t = t1 + 1;
+    const int ia = j * Z.S + f + t * rstep, ib = j * Z.S + f + (R - t) * rstep;
+    C2<T> x = Z.get(ia), y = Z.get(ib);
+    if (Ns > 1) {
+      const int e = (j - div_by(j, Ns, mN) * Ns) * twstep;
+      x = cmul(x, ldc<T>(tw, t * e));
+      y = cmul(y, ldc<T>(tw, (R - t) * e));
+    }
+    Z.put(ia, cadd(x, y));
+    Z.put(ib, csub(x, y));
+  }
+  __syncthreads();
+  const int nb = (h + 1 + kPrimeB - 1) / kPrimeB;
+  const int total = (nbl * nb) << Z.lg;
+  C2<T> C[MBP][kPrimeB], D[MBP][kPrimeB];
+  int ob[MBP], u0[MBP];
 #pragma unroll
-  for (int b = 0; b < MAXE; ++b) {
+  for (int b = 0; b < MBP; ++b) {
     const int idx = threadIdx.x + b * kThreads;
     ob[b] = -1;
+    u0[b] = 0;
     if (idx < total) {
-      const int f = idx / L;
-      const int r = idx - f * L;
-      const int j = r / R, tp = r - j * R;  // butterfly j, output t'
-      const int k = j % Ns;
-      const C2<T>* src = Z + f * L + j;
-      // exponent of W_L for term t: t (k + t' Ns) twstep mod L, stepped by e1 < L
-      const int e1 = (k + tp * Ns) * twstep;
-      int e = 0;
-      C2<T> acc = {(T)0, (T)0};
-      for (int t = 0; t < R; ++t) {
-        C2<T> w = tw[e];
-        if (INV) w.im = -w.im;
-        acc = cadd(acc, cmul(src[t * nbl], w));
-        e += e1;
-        if (e >= L) e -= L;
+      const int f = idx & mask, r = idx >> Z.lg;
+      const int ub = div_by(r, nbl, mB), j = r - ub * nbl;
+      const int k = j - div_by(j, Ns, mN) * Ns;
+      u0[b] = ub * kPrimeB;
+      ob[b] = ((j - k) * R + k) * Z.S + f;
+      const int src = j * Z.S + f;
+      const C2<T> x0 = Z.get(src);
+      unsigned e[kPrimeB];
+#pragma unroll
+      for (int q = 0; q < kPrimeB; ++q) {
+        C[b][q] = x0;
+        D[b][q] = {(T)0, (T)0};
+        e[q] = 0;
       }
-      v[b] = acc;
-      ob[b] = f * L + (j - k) * R + k + tp * Ns;
+      int ia = src, ib = src + R * rstep;
+#pragma unroll 1
+      for (int t = 1; t <= h; ++t) {
+        ia += rstep;
+        ib -= rstep;
+        const C2<T> s = Z.get(ia), d = Z.get(ib);
+#pragma unroll
+        for (int q = 0; q < kPrimeB; ++q) {
+          // t u mod R, stepped by u <= h + kPrimeB - 1 < R
+          e[q] += (unsigned)(u0[b] + q);
+          e[q] = min(e[q], e[q] - (unsigned)R);
+          typename V2<T>::t w;
+          if constexpr (TABLE) {
+            w = wR[e[q]];
+          } else {
+            w = tw[e[q] * nbl];
+            w.y = -w.y;
+          }
+          C[b][q].re += s.re * w.x;
+          C[b][q].im += s.im * w.x;
+          D[b][q].re += d.re * w.y;
+          D[b][q].im += d.im * w.y;
+        }
+      }
     }
   }
   __syncthreads();
 #pragma unroll
-  for (int b = 0; b < MAXE; ++b)
-    if (ob[b] >= 0) Z[ob[b]] = v[b];
+  for (int b = 0; b < MBP; ++b) {
+    if (ob[b] >= 0) {
+#pragma unroll
+      for (int q = 0; q < kPrimeB; ++q) {
+        const int u = u0[b] + q;
+        if (u > h) continue;
+        const C2<T> c = C[b][q], d = D[b][q];
+        Z.put(ob[b] + u * Ns * Z.S, {c.re + d.im, c.im - d.re});
+        if (u > 0) Z.put(ob[b] + (R - u) * Ns * Z.S, {c.re - d.im, c.im + d.re});
+      }
+    }
+  }
   __syncthreads();
 }
 
-// Complex elements per thread of one stage: BIG = 0 holds 16 (FP32) / 8
-// (FP64), fewer registers and more resident waves; BIG = 1 holds 32 / 16 for
-// tiles of long transforms.
-template <typename T, int BIG>
-struct Maxe {
-  static constexpr int v = (BIG ? 32 : 16) / (sizeof(T) == 8 ? 2 : 1);
-};
-
-// Full FFT of nfft transforms in LDS (caller has synchronised the input).
-template <typename T, int BIG, bool INV>
-__device__ void fft_lds(C2<T>* Z, int nfft, const PassArgs& a) {
-  constexpr int ME = Maxe<T, BIG>::v;
-  const C2<T>* tw = (const C2<T>*)a.tw;
+// Forward FFT of the tile's transforms (caller has synchronised the input).
+// A backward FFT is this one with real and imaginary parts exchanged on both
+// sides, which the loads and stores around it do.
+template <typename T, int MODE>
+__device__ __forceinline__ void fft_lds(LTile<T> Z, HP_LDS typename V2<T>::t* wR, const PassArgs& a) {
+  constexpr int ME = Maxe<T, MODE>::v;
+  const GC<T> tw = glb<T>(a.tw);
   const int L = a.L;
   int Ns = 1;
   for (int s = 0; s < a.nstage; ++s) {
     const int R = a.radix[s];
-    const int twstep = L / (Ns * R);
     switch (R) {
-      case 8: fft_stage<T, 8, ME, INV>(Z, L, nfft, Ns, twstep, tw); break;
-      case 4: fft_stage<T, 4, ME, INV>(Z, L, nfft, Ns, twstep, tw); break;
-      case 2: fft_stage<T, 2, ME, INV>(Z, L, nfft, Ns, twstep, tw); break;
-      case 3: fft_stage<T, 3, ME, INV>(Z, L, nfft, Ns, twstep, tw); break;
-      case 5: fft_stage<T, 5, ME, INV>(Z, L, nfft, Ns, twstep, tw); break;
-      default: fft_stage_prime<T, ME, INV>(Z, L, nfft, R, Ns, twstep, tw); break;
+      case 2: fft_stage<T, 2, ME>(Z, L, Ns, tw); break;
+      case 3: fft_stage<T, 3, ME>(Z, L, Ns, tw); break;
+      case 4: fft_stage<T, 4, ME>(Z, L, Ns, tw); break;
+      case 5: fft_stage<T, 5, ME>(Z, L, Ns, tw); break;
+      case 6: fft_stage<T, 6, ME>(Z, L, Ns, tw); break;
+      case 7: fft_stage<T, 7, ME>(Z, L, Ns, tw); break;
+      case 8: fft_stage<T, 8, ME>(Z, L, Ns, tw); break;
+      case 9: fft_stage<T, 9, ME>(Z, L, Ns, tw); break;
+      case 10: fft_stage<T, 10, ME>(Z, L, Ns, tw); break;
+      default:
+        if constexpr (sizeof(T) == 4) {  // (kMaxRadix64: registers)
+          if (R == 11) { fft_stage<T, 11, ME>(Z, L, Ns, tw); break; }
+          if (R == 12) { fft_stage<T, 12, ME>(Z, L, Ns, tw); break; }
+          if (R == 13) { fft_stage<T, 13, ME>(Z, L, Ns, tw); break; }
+          if (R == 14) { fft_stage<T, 14, ME>(Z, L, Ns, tw); break; }
+          if (R == 15) { fft_stage<T, 15, ME>(Z, L, Ns, tw); break; }
+          if (R == 16) { fft_stage<T, 16, ME>(Z, L, Ns, tw); break; }
+        }
+        if constexpr (MODE == GM_BIG) {
+          if (!a.prime_table) { fft_stage_prime<T, ME, false>(Z, wR, L, R, Ns, tw); break; }
+        }
+        if constexpr (MODE != GM_SMALL) fft_stage_prime<T, ME, true>(Z, wR, L, R, Ns, tw);
+        break;
     }
     Ns *= R;
   }
 }
 
-__device__ __forceinline__ bool xform_inverse_fft(int x) {
+constexpr bool xform_inverse_fft(int x) {
   return x == X_C2C_B || x == X_C2R || x == X_PAIR_B || x == X_DCT3 || x == X_DST3;
 }
-__device__ __forceinline__ bool xform_real_in(int x) {
-  return x == X_R2C || x == X_PAIR_F || x == X_DST1 || x == X_DST2 || x == X_DST3 ||
-         x == X_DCT1 || x == X_DCT2 || x == X_DCT3 || x == X_DHT;
-}
-__device__ __forceinline__ bool xform_real_out(int x) {
-  return x == X_C2R || x == X_PAIR_B || x == X_DST1 || x == X_DST2 || x == X_DST3 ||
-         x == X_DCT1 || x == X_DCT2 || x == X_DCT3 || x == X_DHT;
-}
+__device__ __forceinline__ bool xform_complex_in(int x) { return x == X_C2C_F || x == X_C2C_B; }
 
 // ----------------------------------------------------------- tile addressing
 struct Tile {
@@ -174,420 +343,472 @@ __device__ __forceinline__ Tile tile_of(const PassArgs& a) {
   return t;
 }
 
-// Element e of a P x cnt tile -> (p, j), unit stride runs on the memory side.
-__device__ __forceinline__ void tile_pj(int e, int P, int cnt, int jfast, int& p, int& j) {
+// Element e of a tile of nf = 2^lg columns and cnt rows -> (column, row):
+// runs along the rows (jfast: the pencil axis is contiguous in memory) or
+// across the columns.
+__device__ __forceinline__ void tile_fj(int e, int lg, int cnt, unsigned mc, int jfast, int& f, int& j) {
   if (jfast) {
-    p = e / cnt;
-    j = e - p * cnt;
+    f = div_by(e, cnt, mc);
+    j = e - f * cnt;
   } else {
-    j = e / P;
-    p = e - j * P;
+    j = e >> lg;
+    f = e - (j << lg);
   }
 }
 
 // ---------------------------------------------------------------- loading
 // Each thread takes kLoadBatch elements per round and issues all their loads
 // before the first is used, so a tile costs one memory latency per round
-// instead of one per element.
+// instead of one per element.  The values go straight to their places in the
+// FFT input: the symmetric extension of a real-to-real transform is written
+// while loading, so there is no raw copy of the tile.
 constexpr int kLoadBatch = 4;
 
-// Complex pencils straight into Z[p][m], zero beyond nin.
 template <typename T>
-__device__ void load_c2c(C2<T>* Z, const void* src, const PassArgs& a, const Tile& t) {
-  const C2<T>* in = (const C2<T>*)src;
-  const int cnt = a.nin;
-  const int total = a.P * cnt;
-  const long long obase = (long long)t.o * a.in_so + (long long)t.p0 * a.in_sp;
-  for (int e0 = threadIdx.x; e0 < total; e0 += kLoadBatch * kThreads) {
-    C2<T> v[kLoadBatch];
-    int pp[kLoadBatch], jj[kLoadBatch];
-#pragma unroll
-    for (int u = 0; u < kLoadBatch; ++u) {
-      const int e = e0 + u * kThreads;
-      tile_pj(min(e, total - 1), a.P, cnt, a.in_jfast, pp[u], jj[u]);
-      // unconditional load from a clamped (in-tile) address; the pencils
-      // beyond np are zeroed where the values are kept
-      v[u] = in[obase + (long long)min(pp[u], t.np - 1) * a.in_sp + (long long)jj[u] * a.in_sj];
-    }
-#pragma unroll
-    for (int u = 0; u < kLoadBatch; ++u)
-      if (e0 + u * kThreads < total) Z[pp[u] * a.L + jj[u]] = pp[u] < t.np ? v[u] : C2<T>{(T)0, (T)0};
-  }
-  for (int e = threadIdx.x; e < a.P * (a.L - cnt); e += kThreads) {
-    const int p = e / (a.L - cnt);
-    const int m = cnt + (e - p * (a.L - cnt));
-    Z[p * a.L + m] = {(T)0, (T)0};
+__device__ __forceinline__ void zero_rows(LTile<T> Z, int m0, int m1) {
+  const int total = (m1 - m0) << Z.lg;
+  for (int e = threadIdx.x; e < total; e += kThreads) {
+    const int m = e >> Z.lg;
+    Z.put((m0 + m) * Z.S + e - (m << Z.lg), {(T)0, (T)0});
   }
 }
 
-// Real pencils into R[p][j] (j < nin), with boundary terms when present.
-template <typename T>
-__device__ void load_real(T* R, const void* src, const PassArgs& a, const Tile& t, bool faces) {
-  const T* in = (const T*)src;
-  const int cnt = a.nin;
-  const int total = a.P * cnt;
-  const long long obase = (long long)t.o * a.in_so + (long long)t.p0 * a.in_sp;
-  for (int e0 = threadIdx.x; e0 < total; e0 += kLoadBatch * kThreads) {
-    T v[kLoadBatch];
-    int pp[kLoadBatch], jj[kLoadBatch];
-#pragma unroll
-    for (int u = 0; u < kLoadBatch; ++u) {
-      const int e = e0 + u * kThreads;
-      tile_pj(min(e, total - 1), a.P, cnt, a.in_jfast, pp[u], jj[u]);
-      v[u] = in[obase + (long long)min(pp[u], t.np - 1) * a.in_sp + (long long)jj[u] * a.in_sj];
-    }
-    if (faces) {
-#pragma unroll
-      for (int u = 0; u < kLoadBatch; ++u)
-        if (e0 + u * kThreads < total && pp[u] < t.np)
-          v[u] = (T)((double)v[u] + face_terms<T>(a, jj[u], t.p0 + pp[u], t.o));
-    }
-#pragma unroll
-    for (int u = 0; u < kLoadBatch; ++u)
-      if (e0 + u * kThreads < total) R[pp[u] * cnt + jj[u]] = pp[u] < t.np ? v[u] : (T)0;
-  }
-}
-
-// Half spectra (complex, nin = L/2 + 1) into R[p][k].
-template <typename T>
-__device__ void load_half(C2<T>* R, const void* src, const PassArgs& a, const Tile& t) {
-  const C2<T>* in = (const C2<T>*)src;
-  const int cnt = a.nin;
-  const int total = a.P * cnt;
-  const long long obase = (long long)t.o * a.in_so + (long long)t.p0 * a.in_sp;
-  for (int e0 = threadIdx.x; e0 < total; e0 += kLoadBatch * kThreads) {
-    C2<T> v[kLoadBatch];
-    int pp[kLoadBatch], jj[kLoadBatch];
-#pragma unroll
-    for (int u = 0; u < kLoadBatch; ++u) {
-      const int e = e0 + u * kThreads;
-      tile_pj(min(e, total - 1), a.P, cnt, a.in_jfast, pp[u], jj[u]);
-      v[u] = in[obase + (long long)min(pp[u], t.np - 1) * a.in_sp + (long long)jj[u] * a.in_sj];
-    }
-#pragma unroll
-    for (int u = 0; u < kLoadBatch; ++u)
-      if (e0 + u * kThreads < total) R[pp[u] * cnt + jj[u]] = pp[u] < t.np ? v[u] : C2<T>{(T)0, (T)0};
-  }
-}
-
-// Build the complex FFT input Z[f][m] (f = pencil pair) from real pencils R.
-// (XC: the transform type as a compile-time constant; build_from_real below
-// branches once per call instead of once per element)
+// FFT input of transform XC from element s of the pair (a + ib) in column f:
+//   DST-I   [0, x_0..x_{n-1}, 0, -x_{n-1}..-x_0]
+//   DCT-I   [x_0..x_{n-1}, x_{n-2}..x_1]
+//   DCT-II  [x_0..x_{n-1}, x_{n-1}..x_0] (DST-II: (-1)^s x_s)
+//   DCT-III e^{+i pi s/2n} x_s below n, 0 at n, the conjugate twist above
+//           (DST-III: x reversed), for the backward FFT (parts exchanged)
+//   others  x_s (rows beyond the input zeroed by extend_zeros)
 template <typename T, int XC>
-__device__ void build_from_real_x(C2<T>* Z, const T* R, const PassArgs& a, int nfft) {
-  constexpr int x = XC;
-  const int L = a.L, n = a.n, cnt = a.nin;
-  const C2<T>* q = (const C2<T>*)a.qtw;
-  for (int e = threadIdx.x; e < nfft * L; e += kThreads) {
-    const int f = e / L;
-    const int m = e - f * L;
-    const T* ra = R + (2 * f) * cnt;
-    const T* rb = ra + cnt;
-    C2<T> z = {(T)0, (T)0};
-    switch (x) {
-      case X_R2C:
-      case X_PAIR_F:
-      case X_DHT:
-        if (m < cnt) z = {ra[m], rb[m]};
-        break;
-      case X_DST1:  // [0, x_0..x_{n-1}, 0, -x_{n-1}..-x_0]
-        if (m >= 1 && m <= n) z = {ra[m - 1], rb[m - 1]};
-        else if (m > n + 1) z = {-ra[L - m - 1], -rb[L - m - 1]};
-        break;
-      case X_DCT1: {  // [x_0..x_{n-1}, x_{n-2}..x_1]
-        const int s = m < n ? m : L - m;
-        z = {ra[s], rb[s]};
-      } break;
-      case X_DCT2:
-      case X_DST2: {  // [x_0..x_{n-1}, x_{n-1}..x_0], DST-II with (-1)^j
-        const int s = m < n ? m : L - 1 - m;
-        z = {ra[s], rb[s]};
-        if (x == X_DST2 && (s & 1)) z = {-z.re, -z.im};
-      } break;
-      case X_DCT3:
-      case X_DST3: {  // e^{+i pi j/2n} (a_j + i b_j), j < n; 0 at n; conjugate twist above
-        if (m == n) break;
-        const int s = m < n ? m : L - m;
-        const int src = (x == X_DST3) ? n - 1 - s : s;
-        C2<T> v = {ra[src], rb[src]};
-        C2<T> w = q[s];  // e^{-i pi s / 2n}
-        if (m < n) w.im = -w.im;
-        z = cmul(v, w);
-      } break;
-      default:
-        break;
-    }
-    Z[e] = z;
+__device__ __forceinline__ void extend(LTile<T> Z, int f, int s, C2<T> v, const PassArgs& a) {
+  const int L = a.L, n = a.n;
+  auto put = [&](int m, C2<T> z) { Z.put(m * Z.S + f, z); };
+  if constexpr (XC == X_DST1) {
+    put(s + 1, v);
+    put(L - 1 - s, {-v.re, -v.im});
+  } else if constexpr (XC == X_DCT1) {
+    put(s, v);
+    if (s > 0 && s < n - 1) put(L - s, v);
+  } else if constexpr (XC == X_DCT2 || XC == X_DST2) {
+    if (XC == X_DST2 && (s & 1)) v = {-v.re, -v.im};
+    put(s, v);
+    put(L - 1 - s, v);
+  } else if constexpr (XC == X_DCT3 || XC == X_DST3) {
+    const int m = XC == X_DST3 ? n - 1 - s : s;
+    const C2<T> w = ldc<T>(glb<T>(a.qtw), m);  // e^{-i pi m / 2n}
+    const C2<T> lo = cmul(v, cconj(w)), hi = cmul(v, w);
+    put(m, {lo.im, lo.re});
+    if (m > 0) put(L - m, {hi.im, hi.re});
+  } else {
+    put(s, v);
   }
 }
 
-template <typename T>
-__device__ void build_from_real(C2<T>* Z, const T* R, int x, const PassArgs& a, int nfft) {
-  switch (x) {
-    case X_R2C: build_from_real_x<T, X_R2C>(Z, R, a, nfft); break;
-    case X_PAIR_F: build_from_real_x<T, X_PAIR_F>(Z, R, a, nfft); break;
-    case X_DST1: build_from_real_x<T, X_DST1>(Z, R, a, nfft); break;
-    case X_DST2: build_from_real_x<T, X_DST2>(Z, R, a, nfft); break;
-    case X_DST3: build_from_real_x<T, X_DST3>(Z, R, a, nfft); break;
-    case X_DCT1: build_from_real_x<T, X_DCT1>(Z, R, a, nfft); break;
-    case X_DCT2: build_from_real_x<T, X_DCT2>(Z, R, a, nfft); break;
-    case X_DCT3: build_from_real_x<T, X_DCT3>(Z, R, a, nfft); break;
-    case X_DHT: build_from_real_x<T, X_DHT>(Z, R, a, nfft); break;
-    default: build_from_real_x<T, -1>(Z, R, a, nfft); break;
+// The rows of the FFT input that no element reaches.
+template <typename T, int XC>
+__device__ __forceinline__ void extend_zeros(LTile<T> Z, const PassArgs& a, int cnt) {
+  if constexpr (XC == X_DST1) {
+    zero_rows<T>(Z, 0, 1);
+    zero_rows<T>(Z, a.n + 1, a.n + 2);
+  } else if constexpr (XC == X_DCT3 || XC == X_DST3) {
+    zero_rows<T>(Z, a.n, a.n + 1);
+  } else if constexpr (XC == X_R2C || XC == X_PAIR_F || XC == X_DHT) {
+    zero_rows<T>(Z, cnt, a.L);
   }
 }
 
-// Build Z[f][m] from two half spectra R[2f], R[2f+1] (Hermitian completion).
-template <typename T>
-__device__ void build_from_half(C2<T>* Z, const C2<T>* R, const PassArgs& a, int nfft) {
-  const int L = a.L, cnt = a.nin, half = L / 2;
-  for (int e = threadIdx.x; e < nfft * L; e += kThreads) {
-    const int f = e / L;
-    const int m = e - f * L;
-    const C2<T>* ra = R + (2 * f) * cnt;
-    const C2<T>* rb = ra + cnt;
-    C2<T> A, B;
-    if (m <= half) {
-      A = ra[m];
-      B = rb[m];
-      if (m == 0 || 2 * m == L) {
-        A.im = (T)0;
-        B.im = (T)0;
+__device__ __forceinline__ bool has_face_terms(const PassArgs& a) {
+  return a.face[0][0] || a.face[0][1] || a.face[1][0] || a.face[1][1] || a.face[2][0] || a.face[2][1];
+}
+
+// Whether element j of pencil p or p + 1 is the first or last unknown of an axis.
+__device__ __forceinline__ bool beside_face(const PassArgs& a, int j, int p, int o) {
+  bool hit = false;
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    const int hi = a.nunk[b] - 1;
+    if (a.ax_j == b) hit |= j <= 0 || j >= hi;
+    if (a.ax_p == b) hit |= p <= 0 || p + 1 >= hi;
+    if (a.ax_o == b) hit |= o <= 0 || o >= hi;
+  }
+  return hit;
+}
+
+// Real pencils, two per column, with boundary terms when present (first
+// passes only: forward transforms).
+template <typename T, int XC>
+__device__ __forceinline__ void load_real_x(LTile<T> Z, const void* src, const PassArgs& a, const Tile& t, bool faces) {
+  const int cnt = a.nin, jfast = a.in_jfast;
+  const int total = cnt << Z.lg;
+  const unsigned mc = div_magic(cnt);
+  const HP_GLB T* in = (const HP_GLB T*)src + (long long)t.o * a.in_so + (long long)t.p0 * a.in_sp;
+  // adjacent pencils adjacent in memory, every pair complete: one load a pair
+  const bool pairs = a.in_sp == 1 && !jfast && (t.np & 1) == 0;
+  for (int e0 = threadIdx.x; e0 < total; e0 += kLoadBatch * kThreads) {
+    C2<T> v[kLoadBatch];
+    int ff[kLoadBatch], jj[kLoadBatch];
+    // unconditional loads from clamped (in-tile) addresses; the pencils
+    // beyond np are zeroed where the values are kept
+    if (pairs) {
+#pragma unroll
+      for (int u = 0; u < kLoadBatch; ++u) {
+        tile_fj(min(e0 + u * kThreads, total - 1), Z.lg, cnt, mc, 0, ff[u], jj[u]);
+        const typename V2<T>::u w =
+            *(const HP_GLB typename V2<T>::u*)(in + (long long)jj[u] * a.in_sj + min(2 * ff[u], t.np - 2));
+        v[u] = {w.x, w.y};
       }
     } else {
-      A = cconj(ra[L - m]);
-      B = cconj(rb[L - m]);
+#pragma unroll
+      for (int u = 0; u < kLoadBatch; ++u) {
+        tile_fj(min(e0 + u * kThreads, total - 1), Z.lg, cnt, mc, jfast, ff[u], jj[u]);
+        const HP_GLB T* row = in + (long long)jj[u] * a.in_sj;
+        v[u].re = row[(long long)min(2 * ff[u], t.np - 1) * a.in_sp];
+        v[u].im = row[(long long)min(2 * ff[u] + 1, t.np - 1) * a.in_sp];
+      }
     }
-    Z[e] = {A.re - B.im, A.im + B.re};
+#pragma unroll
+    for (int u = 0; u < kLoadBatch; ++u) {
+      if (e0 + u * kThreads >= total) continue;
+      const int p = 2 * ff[u];
+      extend<T, XC>(Z, ff[u], jj[u], {p < t.np ? v[u].re : (T)0, p + 1 < t.np ? v[u].im : (T)0}, a);
+    }
+  }
+  extend_zeros<T, XC>(Z, a, cnt);
+  if (faces) {
+    // boundary terms: the elements next to a face are read back from their
+    // (first) place in the FFT input and extended again
+    __syncthreads();
+    for (int e = threadIdx.x; e < total; e += kThreads) {
+      int f, j;
+      tile_fj(e, Z.lg, cnt, mc, 0, f, j);
+      const int p = 2 * f;
+      if (p >= t.np || !beside_face(a, j, t.p0 + p, t.o)) continue;
+      C2<T> v = Z.get((XC == X_DST1 ? j + 1 : j) * Z.S + f);
+      if (XC == X_DST2 && (j & 1)) v = {-v.re, -v.im};
+      v.re = (T)((double)v.re + face_terms<T>(a, j, t.p0 + p, t.o));
+      if (p + 1 < t.np) v.im = (T)((double)v.im + face_terms<T>(a, j, t.p0 + p + 1, t.o));
+      extend<T, XC>(Z, f, j, v, a);
+    }
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ void load_real(LTile<T> Z, const void* src, int x, const PassArgs& a, const Tile& t, bool faces) {
+  switch (x) {
+    case X_DST1: load_real_x<T, X_DST1>(Z, src, a, t, faces); break;
+    case X_DST2: load_real_x<T, X_DST2>(Z, src, a, t, faces); break;
+    case X_DST3: load_real_x<T, X_DST3>(Z, src, a, t, faces); break;
+    case X_DCT1: load_real_x<T, X_DCT1>(Z, src, a, t, faces); break;
+    case X_DCT2: load_real_x<T, X_DCT2>(Z, src, a, t, faces); break;
+    case X_DCT3: load_real_x<T, X_DCT3>(Z, src, a, t, faces); break;
+    default: load_real_x<T, X_R2C>(Z, src, a, t, faces); break;  // R2C, paired, Hartley: as they are
+  }
+}
+
+// Complex pencils, one per column, zero beyond nin; swap: for the backward FFT.
+template <typename T>
+__device__ __forceinline__ void load_c2c(LTile<T> Z, const void* src, const PassArgs& a, const Tile& t, bool swap) {
+  const int cnt = a.nin, jfast = a.in_jfast;
+  const int total = cnt << Z.lg;
+  const unsigned mc = div_magic(cnt);
+  const GC<T> in = glb<T>(src) + (long long)t.o * a.in_so + (long long)t.p0 * a.in_sp;
+  for (int e0 = threadIdx.x; e0 < total; e0 += kLoadBatch * kThreads) {
+    C2<T> v[kLoadBatch];
+    int ff[kLoadBatch], jj[kLoadBatch];
+#pragma unroll
+    for (int u = 0; u < kLoadBatch; ++u) {
+      tile_fj(min(e0 + u * kThreads, total - 1), Z.lg, cnt, mc, jfast, ff[u], jj[u]);
+      v[u] = ldc<T>(in, (long long)min(ff[u], t.np - 1) * a.in_sp + (long long)jj[u] * a.in_sj);
+    }
+#pragma unroll
+    for (int u = 0; u < kLoadBatch; ++u) {
+      if (e0 + u * kThreads >= total) continue;
+      const C2<T> w = ff[u] < t.np ? v[u] : C2<T>{(T)0, (T)0};
+      Z.put(jj[u] * Z.S + ff[u], swap ? C2<T>{w.im, w.re} : w);
+    }
+  }
+  zero_rows<T>(Z, cnt, a.L);
+}
+
+// Half spectra A, B (L/2 + 1 bins) of the two pencils of a column, completed
+// to A + iB by Hermitian symmetry, for the backward FFT.
+template <typename T>
+__device__ __forceinline__ void load_half(LTile<T> Z, const void* src, const PassArgs& a, const Tile& t) {
+  const int cnt = a.nin, jfast = a.in_jfast, L = a.L;
+  const int total = cnt << Z.lg;
+  const unsigned mc = div_magic(cnt);
+  const GC<T> in = glb<T>(src) + (long long)t.o * a.in_so + (long long)t.p0 * a.in_sp;
+  constexpr int U = kLoadBatch / 2;
+  for (int e0 = threadIdx.x; e0 < total; e0 += U * kThreads) {
+    C2<T> va[U], vb[U];
+    int ff[U], jj[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      tile_fj(min(e0 + u * kThreads, total - 1), Z.lg, cnt, mc, jfast, ff[u], jj[u]);
+      const GC<T> row = in + (long long)jj[u] * a.in_sj;
+      va[u] = ldc<T>(row, (long long)min(2 * ff[u], t.np - 1) * a.in_sp);
+      vb[u] = ldc<T>(row, (long long)min(2 * ff[u] + 1, t.np - 1) * a.in_sp);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (e0 + u * kThreads >= total) continue;
+      const int m = jj[u], p = 2 * ff[u];
+      const bool self = m == 0 || 2 * m == L;
+      C2<T> A = p < t.np ? va[u] : C2<T>{(T)0, (T)0}, B = p + 1 < t.np ? vb[u] : C2<T>{(T)0, (T)0};
+      if (self) A.im = B.im = (T)0;
+      Z.put(m * Z.S + ff[u], {A.im + B.re, A.re - B.im});
+      if (!self) Z.put((L - m) * Z.S + ff[u], {B.re - A.im, A.re + B.im});
+    }
   }
 }
 
 // ---------------------------------------------------------------- storing
-// Value of output element (pencil p, index k) computed from the transformed Z.
-template <typename T>
-__device__ __forceinline__ T real_out(const C2<T>* Z, int x, const PassArgs& a, int p, int k) {
-  const int f = p >> 1;
-  const bool second = p & 1;
-  const C2<T>* z = Z + f * a.L;
-  switch (x) {
-    case X_DST1: {
-      C2<T> v = z[k + 1];
-      return second ? v.re : -v.im;
-    }
-    case X_DCT1:
-    case X_DCT3:
-    case X_C2R:
-    case X_PAIR_B: {
-      C2<T> v = z[k];
-      return second ? v.im : v.re;
-    }
-    case X_DST3: {
-      C2<T> v = z[k];
-      T r = second ? v.im : v.re;
-      return (k & 1) ? -r : r;
-    }
-    case X_DCT2:
-    case X_DST2: {
-      const int kk = (x == X_DST2) ? a.n - 1 - k : k;
-      C2<T> v = cmul(z[kk], ((const C2<T>*)a.qtw)[kk]);
-      return second ? v.im : v.re;
-    }
-    case X_DHT: {
-      // Z = X_a + i X_b with X_a, X_b Hermitian; H = Re X - Im X per pencil
-      const C2<T> u = z[k], w = z[k == 0 ? 0 : a.L - k];
-      return second ? (T)0.5 * ((u.im + w.im) + (u.re - w.re))
-                    : (T)0.5 * ((u.re + w.re) - (u.im - w.im));
-    }
-    default:
-      return (T)0;
+// Output k of the two pencils of column f from the transformed tile.
+template <typename T, int XC>
+__device__ __forceinline__ C2<T> real_out(LTile<T> Z, const PassArgs& a, int f, int k) {
+  if constexpr (XC == X_DST1) {
+    const C2<T> v = Z.get((k + 1) * Z.S + f);
+    return {-v.im, v.re};
+  } else if constexpr (XC == X_DCT1) {
+    return Z.get(k * Z.S + f);
+  } else if constexpr (XC == X_DCT2 || XC == X_DST2) {
+    const int kk = XC == X_DST2 ? a.n - 1 - k : k;
+    return cmul(Z.get(kk * Z.S + f), ldc<T>(glb<T>(a.qtw), kk));
+  } else if constexpr (XC == X_DHT) {
+    // Z = X_a + i X_b with X_a, X_b Hermitian; H = Re X - Im X per pencil
+    const C2<T> u = Z.get(k * Z.S + f), w = Z.get((k == 0 ? 0 : a.L - k) * Z.S + f);
+    return {(T)0.5 * ((u.re + w.re) - (u.im - w.im)), (T)0.5 * ((u.im + w.im) + (u.re - w.re))};
+  } else {  // DCT-III, DST-III, C2R, paired backward: the parts exchanged back
+    const C2<T> v = Z.get(k * Z.S + f);
+    if (XC == X_DST3 && (k & 1)) return {-v.im, -v.re};
+    return {v.im, v.re};
   }
-}
-
-template <typename T>
-__device__ __forceinline__ C2<T> half_out(const C2<T>* Z, const PassArgs& a, int p, int k) {
-  const int f = p >> 1;
-  const C2<T>* z = Z + f * a.L;
-  C2<T> zk = z[k];
-  C2<T> zc = cconj(z[k == 0 ? 0 : a.L - k]);
-  if (p & 1) {  // (zk - zc) / (2 i)
-    C2<T> d = csub(zk, zc);
-    return {d.im * (T)0.5, -d.re * (T)0.5};
-  }
-  C2<T> s = cadd(zk, zc);
-  return {s.re * (T)0.5, s.im * (T)0.5};
 }
 
 template <typename T, int XC>
-__device__ void store_out_x(const C2<T>* Z, void* dst, const PassArgs& a, const Tile& t) {
-  constexpr int x = XC;
-  const int cnt = a.nout;
-  const int total = a.P * cnt;
-  const long long obase = (long long)t.o * a.out_so + (long long)t.p0 * a.out_sp;
+__device__ __forceinline__ void store_real_x(LTile<T> Z, void* dst, const PassArgs& a, const Tile& t) {
+  const int cnt = a.nout, jfast = a.out_jfast;
+  const int total = cnt << Z.lg;
+  const unsigned mc = div_magic(cnt);
+  HP_GLB T* out = (HP_GLB T*)dst + (long long)t.o * a.out_so + (long long)t.p0 * a.out_sp;
+  const bool pairs = a.out_sp == 1 && !jfast && (t.np & 1) == 0;
   for (int e = threadIdx.x; e < total; e += kThreads) {
-    int p, k;
-    tile_pj(e, a.P, cnt, a.out_jfast, p, k);
-    if (p >= t.np) continue;
-    const long long off = obase + (long long)p * a.out_sp + (long long)k * a.out_sj;
-    if (x == X_C2C_F || x == X_C2C_B) {
-      ((C2<T>*)dst)[off] = Z[p * a.L + k];
-    } else if (x == X_R2C) {
-      ((C2<T>*)dst)[off] = half_out(Z, a, p, k);
+    int f, k;
+    tile_fj(e, Z.lg, cnt, mc, jfast, f, k);
+    if (2 * f >= t.np) continue;
+    const C2<T> v = real_out<T, XC>(Z, a, f, k);
+    HP_GLB T* row = out + (long long)k * a.out_sj;
+    if (pairs) {
+      typename V2<T>::u w;
+      w.x = v.re;
+      w.y = v.im;
+      *(HP_GLB typename V2<T>::u*)(row + 2 * f) = w;
     } else {
-      ((T*)dst)[off] = real_out(Z, x, a, p, k);
+      row[(long long)(2 * f) * a.out_sp] = v.re;
+      if (2 * f + 1 < t.np) row[(long long)(2 * f + 1) * a.out_sp] = v.im;
     }
   }
 }
 
+// Complex pencils (swap: the parts exchanged back after a backward FFT).
 template <typename T>
-__device__ void store_out(const C2<T>* Z, int x, void* dst, const PassArgs& a, const Tile& t) {
+__device__ __forceinline__ void store_c2c(LTile<T> Z, void* dst, const PassArgs& a, const Tile& t, bool swap) {
+  const int cnt = a.nout, jfast = a.out_jfast;
+  const int total = cnt << Z.lg;
+  const unsigned mc = div_magic(cnt);
+  C2<T>* out = (C2<T>*)dst + (long long)t.o * a.out_so + (long long)t.p0 * a.out_sp;
+  for (int e = threadIdx.x; e < total; e += kThreads) {
+    int f, k;
+    tile_fj(e, Z.lg, cnt, mc, jfast, f, k);
+    if (f >= t.np) continue;
+    const C2<T> v = Z.get(k * Z.S + f);
+    stc<T>(out, (long long)f * a.out_sp + (long long)k * a.out_sj, swap ? C2<T>{v.im, v.re} : v);
+  }
+}
+
+// Half spectra of the two pencils of every column (X_R2C).
+template <typename T>
+__device__ __forceinline__ void store_half(LTile<T> Z, void* dst, const PassArgs& a, const Tile& t) {
+  const int cnt = a.nout, jfast = a.out_jfast;
+  const int total = cnt << Z.lg;
+  const unsigned mc = div_magic(cnt);
+  C2<T>* out = (C2<T>*)dst + (long long)t.o * a.out_so + (long long)t.p0 * a.out_sp;
+  for (int e = threadIdx.x; e < total; e += kThreads) {
+    int f, k;
+    tile_fj(e, Z.lg, cnt, mc, jfast, f, k);
+    if (2 * f >= t.np) continue;
+    const C2<T> zk = Z.get(k * Z.S + f), zc = cconj(Z.get((k == 0 ? 0 : a.L - k) * Z.S + f));
+    const C2<T> s = cadd(zk, zc), d = csub(zk, zc);
+    C2<T>* row = out + (long long)k * a.out_sj;
+    stc<T>(row, (long long)(2 * f) * a.out_sp, {s.re * (T)0.5, s.im * (T)0.5});
+    // (zk - zc) / (2 i)
+    if (2 * f + 1 < t.np) stc<T>(row, (long long)(2 * f + 1) * a.out_sp, {d.im * (T)0.5, -d.re * (T)0.5});
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ void store_out(LTile<T> Z, int x, void* dst, const PassArgs& a, const Tile& t) {
   switch (x) {
-    case X_C2C_F: store_out_x<T, X_C2C_F>(Z, dst, a, t); break;
-    case X_C2C_B: store_out_x<T, X_C2C_B>(Z, dst, a, t); break;
-    case X_R2C: store_out_x<T, X_R2C>(Z, dst, a, t); break;
-    case X_C2R: store_out_x<T, X_C2R>(Z, dst, a, t); break;
-    case X_PAIR_B: store_out_x<T, X_PAIR_B>(Z, dst, a, t); break;
-    case X_DST1: store_out_x<T, X_DST1>(Z, dst, a, t); break;
-    case X_DST2: store_out_x<T, X_DST2>(Z, dst, a, t); break;
-    case X_DST3: store_out_x<T, X_DST3>(Z, dst, a, t); break;
-    case X_DCT1: store_out_x<T, X_DCT1>(Z, dst, a, t); break;
-    case X_DCT2: store_out_x<T, X_DCT2>(Z, dst, a, t); break;
-    case X_DCT3: store_out_x<T, X_DCT3>(Z, dst, a, t); break;
-    case X_DHT: store_out_x<T, X_DHT>(Z, dst, a, t); break;
-    default: store_out_x<T, -1>(Z, dst, a, t); break;
+    case X_C2C_F: store_c2c<T>(Z, dst, a, t, false); break;
+    case X_C2C_B: store_c2c<T>(Z, dst, a, t, true); break;
+    case X_R2C: store_half<T>(Z, dst, a, t); break;
+    case X_DST1: store_real_x<T, X_DST1>(Z, dst, a, t); break;
+    case X_DST2: store_real_x<T, X_DST2>(Z, dst, a, t); break;
+    case X_DST3: store_real_x<T, X_DST3>(Z, dst, a, t); break;
+    case X_DCT1: store_real_x<T, X_DCT1>(Z, dst, a, t); break;
+    case X_DCT2: store_real_x<T, X_DCT2>(Z, dst, a, t); break;
+    case X_DHT: store_real_x<T, X_DHT>(Z, dst, a, t); break;
+    default: store_real_x<T, X_DCT3>(Z, dst, a, t); break;  // DCT-III, C2R, paired backward
   }
 }
 
 // -------------------------------------------------------- spectral multiply
+// Spectral indices per logical axis.
+struct KIdx {
+  int k0, k1, k2;
+};
+
 template <typename T>
-__device__ __forceinline__ T multiplier(const PassArgs& a, const int k[3]) {
+__device__ __forceinline__ T multiplier(const PassArgs& a, const KIdx& k) {
   if (a.mult == M_EIGEN) {
-    double lam = a.lam[0][k[0]];
-    if (a.lam[1]) lam += a.lam[1][k[1]];
-    if (a.lam[2]) lam += a.lam[2][k[2]];
+    double lam = ((const HP_GLB double*)a.lam[0])[k.k0];
+    if (a.lam[1]) lam += ((const HP_GLB double*)a.lam[1])[k.k1];
+    if (a.lam[2]) lam += ((const HP_GLB double*)a.lam[2])[k.k2];
     return lam == 0.0 ? (T)0 : (T)(a.norm / lam);
   }
   if (a.mult == M_GREEN) {
-    const int i0 = min(k[0], a.gM[0] - k[0]);
-    const int i1 = min(k[1], a.gM[1] - k[1]);
-    return ((const T*)a.green)[(long long)i0 * a.g_s[0] + (long long)i1 * a.g_s[1] +
-                               (long long)k[2] * a.g_s[2]];
+    const int i0 = min(k.k0, a.gM[0] - k.k0);
+    const int i1 = min(k.k1, a.gM[1] - k.k1);
+    return ((const HP_GLB T*)a.green)[(long long)i0 * a.g_s[0] + (long long)i1 * a.g_s[1] +
+                                      (long long)k.k2 * a.g_s[2]];
   }
   return (T)1;
 }
 
 // Spectral indices of element m of pencil p (tile-relative pencils beyond the
 // last one are clamped: their values are never stored).
-__device__ __forceinline__ void spectral_index(const PassArgs& a, int m, int p, int o, int k[3]) {
+__device__ __forceinline__ KIdx spectral_index(const PassArgs& a, int m, int p, int o) {
   p = min(p, a.Np - 1);
-  k[0] = k[1] = k[2] = 0;
-  if (a.ax_j >= 0) k[a.ax_j] = m;
-  if (a.ax_p >= 0) k[a.ax_p] = p;
-  if (a.ax_o >= 0) k[a.ax_o] = o;
+  auto of = [&](int ax) { return a.ax_j == ax ? m : (a.ax_p == ax ? p : (a.ax_o == ax ? o : 0)); };
+  return {of(0), of(1), of(2)};
 }
 
 template <typename T>
-__device__ __forceinline__ T kval(const PassArgs& a, int axis, const int k[3]) {
-  return ((const T*)a.kvec[axis])[k[axis]];
+__device__ __forceinline__ T kval(const PassArgs& a, int axis, const KIdx& k) {
+  return ((const HP_GLB T*)a.kvec[axis])[axis == 0 ? k.k0 : (axis == 1 ? k.k1 : k.k2)];
 }
 
 // ------------------------------------------------------------ pass bodies
-template <typename T, int BIG>
-__device__ void oneway(const PassArgs& a, unsigned char* smem, const Tile& t, int field) {
+template <typename T, int MODE>
+__device__ __forceinline__ void oneway(const PassArgs& a, unsigned char* smem, const Tile& t, int field) {
   if (!a.in[field]) return;  // absent field (zero upstream gradient): uniform per block
-  C2<T>* Z = (C2<T>*)smem;
   const int x = a.xf;
-  const bool pair = xform_real_in(x) || x == X_C2R;
-  const int nfft = pair ? a.P / 2 : a.P;
-  const bool faces = a.face[0][0] || a.face[0][1] || a.face[1][0] || a.face[1][1] ||
-                     a.face[2][0] || a.face[2][1];
-  unsigned char* rbuf = smem + (size_t)nfft * a.L * sizeof(C2<T>);
-  if (x == X_C2C_F || x == X_C2C_B) {
-    load_c2c<T>(Z, a.in[field], a, t);
-  } else if (x == X_C2R) {
-    load_half<T>((C2<T>*)rbuf, a.in[field], a, t);
-    __syncthreads();
-    build_from_half<T>(Z, (const C2<T>*)rbuf, a, nfft);
-  } else {
-    load_real<T>((T*)rbuf, a.in[field], a, t, faces);
-    __syncthreads();
-    build_from_real<T>(Z, (const T*)rbuf, x, a, nfft);
-  }
+  const bool cplx = xform_complex_in(x);
+  const int nf = cplx ? a.P : a.P / 2;
+  const LTile<T> Z = lds_tile<T>(smem, nf, a.L, 0);
+  if (cplx) load_c2c<T>(Z, a.in[field], a, t, x == X_C2C_B);
+  else if (x == X_C2R) load_half<T>(Z, a.in[field], a, t);
+  else load_real<T>(Z, a.in[field], x, a, t, has_face_terms(a));
   __syncthreads();
-  if (xform_inverse_fft(x)) fft_lds<T, BIG, true>(Z, nfft, a);
-  else fft_lds<T, BIG, false>(Z, nfft, a);
+  fft_lds<T, MODE>(Z, Z.z + (size_t)a.L * Z.S, a);
   store_out<T>(Z, x, a.out[field], a, t);
 }
 
-// Real-to-real sandwich (Dirichlet / Neumann): forward R2R, multiply by the
-// FD2 / PS multiplier, backward R2R, along the same axis.
-template <typename T, int BIG>
-__device__ void sandwich_r2r(const PassArgs& a, unsigned char* smem, const Tile& t, int field) {
-  const int nfft = a.P / 2;
-  C2<T>* Z = (C2<T>*)smem;
-  T* R = (T*)(smem + (size_t)nfft * a.L * sizeof(C2<T>));
-  const bool faces = a.face[0][0] || a.face[0][1] || a.face[1][0] || a.face[1][1] ||
-                     a.face[2][0] || a.face[2][1];
-  load_real<T>(R, a.in[field], a, t, faces);
+// Spectral values of the forward transform XF times the multiplier, as the
+// input of the backward transform XB.  In place without a barrier: output k
+// is read from bins that only its own thread replaces (the sine and cosine
+// transforms read one bin below n and write it and its mirror above n; a
+// Hartley output reads bins k and L - k, both handled by one thread).
+template <typename T, int XF, int XB>
+__device__ __forceinline__ void multiply_r2r(LTile<T> Z, const PassArgs& a, const Tile& t) {
+  const int rows = XF == X_DHT ? a.n / 2 + 1 : a.n;
+  const int total = rows << Z.lg;
+  auto scaled = [&](C2<T> s, int m, int f) {
+    return C2<T>{s.re * multiplier<T>(a, spectral_index(a, m, t.p0 + 2 * f, t.o)),
+                 s.im * multiplier<T>(a, spectral_index(a, m, t.p0 + 2 * f + 1, t.o))};
+  };
+  for (int e = threadIdx.x; e < total; e += kThreads) {
+    const int m = e >> Z.lg, f = e - (m << Z.lg);
+    const C2<T> v = scaled(real_out<T, XF>(Z, a, f, m), m, f);
+    if constexpr (XF == X_DHT) {
+      const int mm = m == 0 ? 0 : a.L - m;
+      if (mm != m) {
+        const C2<T> w = scaled(real_out<T, XF>(Z, a, f, mm), mm, f);
+        extend<T, XB>(Z, f, mm, w, a);
+      }
+    }
+    extend<T, XB>(Z, f, m, v, a);
+  }
+  extend_zeros<T, XB>(Z, a, a.n);
+}
+
+// Real-to-real sandwich (Dirichlet / Neumann / Hartley): forward R2R, multiply
+// by the FD2 / PS multiplier, backward R2R, along the same axis.
+template <typename T, int MODE>
+__device__ __forceinline__ void sandwich_r2r(const PassArgs& a, unsigned char* smem, const Tile& t, int field) {
+  const LTile<T> Z = lds_tile<T>(smem, a.P / 2, a.L, 0);
+  HP_LDS typename V2<T>::t* wR = Z.z + (size_t)a.L * Z.S;
+  load_real<T>(Z, a.in[field], a.xf, a, t, has_face_terms(a));
   __syncthreads();
-  build_from_real<T>(Z, R, a.xf, a, nfft);
-  __syncthreads();
-  if (xform_inverse_fft(a.xf)) fft_lds<T, BIG, true>(Z, nfft, a);
-  else fft_lds<T, BIG, false>(Z, nfft, a);
-  // spectral values times the multiplier, back into R (same [p][k] layout)
-  for (int e = threadIdx.x; e < a.P * a.n; e += kThreads) {
-    const int p = e / a.n;
-    const int m = e - p * a.n;
-    int k[3];
-    spectral_index(a, m, t.p0 + p, t.o, k);
-    R[e] = real_out<T>(Z, a.xf, a, p, m) * multiplier<T>(a, k);
+  fft_lds<T, MODE>(Z, wR, a);
+  switch (a.xf) {
+    case X_DST1: multiply_r2r<T, X_DST1, X_DST1>(Z, a, t); break;
+    case X_DST2: multiply_r2r<T, X_DST2, X_DST3>(Z, a, t); break;
+    case X_DCT1: multiply_r2r<T, X_DCT1, X_DCT1>(Z, a, t); break;
+    case X_DCT2: multiply_r2r<T, X_DCT2, X_DCT3>(Z, a, t); break;
+    default: multiply_r2r<T, X_DHT, X_DHT>(Z, a, t); break;
   }
   __syncthreads();
-  build_from_real<T>(Z, R, a.xb, a, nfft);
-  __syncthreads();
-  if (xform_inverse_fft(a.xb)) fft_lds<T, BIG, true>(Z, nfft, a);
-  else fft_lds<T, BIG, false>(Z, nfft, a);
+  fft_lds<T, MODE>(Z, wR, a);
   store_out<T>(Z, a.xb, a.out[field], a, t);
 }
 
 // Complex sandwich (periodic after R2C, unbounded, 1D periodic pairs):
-// every coupled field of the tile is resident: S_c (P x L each) plus a work
-// buffer W for derivative outputs.
-template <typename T, int BIG>
-__device__ void sandwich_c2c(const PassArgs& a, unsigned char* smem, const Tile& t) {
+// every coupled field of the tile is resident: S_c (one LDS tile each) plus a
+// work tile W where there are derivative inputs or outputs.
+template <typename T, int MODE>
+__device__ __forceinline__ void sandwich_c2c(const PassArgs& a, unsigned char* smem, const Tile& t) {
   const bool pair = a.xf == X_PAIR_F;
-  const int nfft = pair ? a.P / 2 : a.P;
+  const int nf = pair ? a.P / 2 : a.P;
   const int L = a.L;
-  const int tileC = nfft * L;
   const bool adj = diff_is_adjoint(a.diff);
   const int nS = adj ? a.n_out : a.n_in;
   // independent fields (no derivative coupling) take their field from blockIdx.y
   const int fb = (a.diff == D_NONE) ? (int)blockIdx.y : 0;
-  C2<T>* S = (C2<T>*)smem;
-  C2<T>* W = S + (size_t)nS * tileC;
-  T* R = (T*)W;  // raw real pencils (pair mode; W is free while loading)
+  const LTile<T> S = lds_tile<T>(smem, nf, L, 0);
+  const LTile<T> W = lds_tile<T>(smem, nf, L, a.diff == D_NONE ? 0 : nS);
+  const int tileC = L * S.S;  // LDS elements of a tile
+  HP_LDS typename V2<T>::t* wR = S.z + (size_t)(a.diff == D_NONE ? nS : nS + 1) * tileC;
+  const int total = L << S.lg;
+  const unsigned mL = div_magic(L);
+  auto tile = [&](int c) { return LTile<T>{S.z + (size_t)c * tileC, S.S, S.lg}; };
 
-  auto load_into = [&](C2<T>* dst, const void* src) {
-    if (pair) {
-      load_real<T>(R, src, a, t, false);
-      __syncthreads();
-      build_from_real<T>(dst, R, X_PAIR_F, a, nfft);
-    } else {
-      load_c2c<T>(dst, src, a, t);
-    }
+  auto load_into = [&](LTile<T> dst, const void* src) {
+    if (pair) load_real<T>(dst, src, X_PAIR_F, a, t, false);
+    else load_c2c<T>(dst, src, a, t, false);
     __syncthreads();
-    fft_lds<T, BIG, false>(dst, nfft, a);
+    fft_lds<T, MODE>(dst, wR, a);
+  };
+  // element e of a tile -> column f, bin m (rows first: the multipliers' rows
+  // are contiguous along m)
+  auto each = [&](auto&& body) {
+    for (int e = threadIdx.x; e < total; e += kThreads) {
+      const int f = div_by(e, L, mL), m = e - f * L;
+      body(m * S.S + f, spectral_index(a, m, t.p0 + f, t.o));
+    }
   };
 
   for (int c = 0; c < nS; ++c) {
     if (a.in[fb + c]) {
-      load_into(S + (size_t)c * tileC, a.in[fb + c]);
+      load_into(tile(c), a.in[fb + c]);
     } else {
-      for (int e = threadIdx.x; e < tileC; e += kThreads) S[(size_t)c * tileC + e] = {(T)0, (T)0};
+      zero_rows<T>(tile(c), 0, L);
       __syncthreads();
     }
   }
   // spectral Laplacian: the first derivative i k_b (Nyquist zeroed) twice per axis
-  auto lap_of = [&](const int k[3]) -> T {
+  auto lap_of = [&](const KIdx& k) -> T {
     T s = (T)0;
     for (int b = 0; b < 3; ++b)
       if (a.kvec[b]) {
@@ -604,38 +825,39 @@ __device__ void sandwich_c2c(const PassArgs& a, unsigned char* smem, const Tile&
       const void* src = a.in[nS + i];
       if (!src) continue;
       load_into(W, src);
-      for (int e = threadIdx.x; e < tileC; e += kThreads) {
-        const int f = e / L;
-        const int m = e - f * L;
-        int k[3];
-        spectral_index(a, m, t.p0 + f, t.o, k);
-        const C2<T> g = W[e];
+      each([&](int z, const KIdx& k) {
+        const C2<T> g = W.get(z);
+        auto acc = [&](int c, C2<T> v) {
+          const int q = z + c * tileC;
+          S.put(q, cadd(S.get(q), v));
+        };
         if (a.diff == D_ADJ_CURL && nS == 1) {
           // 2D curl of a scalar, (d_y, -d_x): its transpose is -d_y g_0 + d_x g_1
           const T kk = i == 0 ? -kval<T>(a, 1, k) : kval<T>(a, 0, k);
-          S[e] = cadd(S[e], cscale(cmuli(g), kk));
+          acc(0, cscale(cmuli(g), kk));
         } else if (a.diff == D_ADJ_CURL) {
           // (C g)_c = i(k_{c+1} g_{c+2} - k_{c+2} g_{c+1}): g_i enters
           // component i+1 with +i k_{i+2} and component i+2 with -i k_{i+1}
           const int c1 = (i + 1) % 3, c2 = (i + 2) % 3;
           const T kc1 = kval<T>(a, c1, k), kc2 = kval<T>(a, c2, k);
-          C2<T> ig = cmuli(g);
-          S[(size_t)c1 * tileC + e] = cadd(S[(size_t)c1 * tileC + e], cscale(ig, kc2));
-          S[(size_t)c2 * tileC + e] = csub(S[(size_t)c2 * tileC + e], cscale(ig, kc1));
+          const C2<T> ig = cmuli(g);
+          acc(c1, cscale(ig, kc2));
+          acc(c2, cscale(ig, -kc1));
         } else if (a.diff == D_ADJ_DIV) {
           const C2<T> ig = cmuli(g);
-          for (int c = 0; c < nS; ++c)
-            S[(size_t)c * tileC + e] = csub(S[(size_t)c * tileC + e], cscale(ig, kval<T>(a, c, k)));
+          for (int c = 0; c < nS; ++c) acc(c, cscale(ig, -kval<T>(a, c, k)));
         } else if (a.diff == D_ADJ_NABLA) {
-          S[(size_t)i * tileC + e] = cadd(S[(size_t)i * tileC + e], cscale(g, lap_of(k)));
+          acc(i, cscale(g, lap_of(k)));
         } else {
-          const T ka = kval<T>(a, i, k);
-          S[e] = csub(S[e], cscale(cmuli(g), ka));
+          acc(0, cscale(cmuli(g), -kval<T>(a, i, k)));
         }
-      }
+      });
       __syncthreads();
     }
   }
+  // The multiplied spectra S keep their parts in place while derivative
+  // outputs still read them, and are exchanged for the backward FFT otherwise.
+  const bool derivs = a.diff == D_GRAD || a.diff == D_CURL || a.diff == D_DIV || a.diff == D_NABLA;
   if (a.mult == M_GREEN_ROWS || a.mult == M_GREEN_ROWS_ODD) {
     // Paired real pencils 2f, 2f + 1 of the tile belong to different bounded
     // modes, so they take different real-even Green's rows G_a, G_b.  The FFT
@@ -646,101 +868,110 @@ __device__ void sandwich_c2c(const PassArgs& a, unsigned char* smem, const Tile&
     // (bins i b_a, i b_b, b odd in m): Z'_m = i (A Z_m + B conj Z_-m) and
     // Z'_-m = -i (A Z_-m + B conj Z_m), A, B from b_a, b_b at m.
     const int half = L / 2;
+    const unsigned mh = div_magic(half + 1);
     const bool odd = a.mult == M_GREEN_ROWS_ODD;
     auto row = [&](int p, int m) -> T {
       p = min(p, a.Np - 1);
       long long off = (long long)m * a.g_s[a.ax_j] + (long long)p * a.g_s[a.ax_p];
       if (a.ax_o >= 0) off += (long long)t.o * a.g_s[a.ax_o];
-      return ((const T*)a.green)[off];
+      return ((const HP_GLB T*)a.green)[off];
     };
-    for (int e = threadIdx.x; e < nfft * (half + 1); e += kThreads) {
-      const int f = e / (half + 1);
+    for (int e = threadIdx.x; e < ((half + 1) << S.lg); e += kThreads) {
+      const int f = div_by(e, half + 1, mh);
       const int m = e - f * (half + 1);
       const int mm = m == 0 ? 0 : L - m;
       const T ga = row(t.p0 + 2 * f, m), gb = row(t.p0 + 2 * f + 1, m);
       const T A = (T)0.5 * (ga + gb), B = (T)0.5 * (ga - gb);
-      C2<T>* z = S + (size_t)f * L;
-      const C2<T> zm = z[m], zmm = z[mm];
-      const C2<T> ym = cadd(cscale(zm, A), cscale(cconj(zmm), B));
-      const C2<T> ymm = cadd(cscale(zmm, A), cscale(cconj(zm), B));
+      const int im = m * S.S + f, imm = mm * S.S + f;
+      const C2<T> zm = S.get(im), zmm = S.get(imm);
+      C2<T> ym = cadd(cscale(zm, A), cscale(cconj(zmm), B));
+      C2<T> ymm = cadd(cscale(zmm, A), cscale(cconj(zm), B));
       if (odd) {
-        z[m] = cmuli(ym);
-        if (mm != m) z[mm] = cscale(cmuli(ymm), (T)-1);
-      } else {
-        z[m] = ym;
-        if (mm != m) z[mm] = ymm;
+        ym = cmuli(ym);
+        ymm = cscale(cmuli(ymm), (T)-1);
       }
+      S.put(im, {ym.im, ym.re});
+      if (mm != m) S.put(imm, {ymm.im, ymm.re});
     }
   } else {
     // multiply by the spectral multiplier
-    for (int e = threadIdx.x; e < tileC; e += kThreads) {
-      const int f = e / L;
-      const int m = e - f * L;
-      int k[3];
-      spectral_index(a, m, t.p0 + f, t.o, k);
+    each([&](int z, const KIdx& k) {
       const T mu = multiplier<T>(a, k);
-      for (int c = 0; c < nS; ++c) S[(size_t)c * tileC + e] = cscale(S[(size_t)c * tileC + e], mu);
-    }
+      for (int c = 0; c < nS; ++c) {
+        const C2<T> v = cscale(S.get(z + c * tileC), mu);
+        S.put(z + c * tileC, derivs ? v : C2<T>{v.im, v.re});
+      }
+    });
   }
   __syncthreads();
   const int xb = pair ? X_PAIR_B : X_C2C_B;
   // derivative outputs (forward GRAD / CURL) through W, then psi in place
-  if (a.diff == D_GRAD || a.diff == D_CURL || a.diff == D_DIV || a.diff == D_NABLA) {
+  if (derivs) {
     const int nd = a.n_out - a.n_in;
     for (int d = 0; d < nd; ++d) {
-      for (int e = threadIdx.x; e < tileC; e += kThreads) {
-        const int f = e / L;
-        const int m = e - f * L;
-        int k[3];
-        spectral_index(a, m, t.p0 + f, t.o, k);
+      each([&](int z, const KIdx& k) {
         C2<T> v;
         if (a.diff == D_GRAD) {
-          v = cscale(cmuli(S[e]), kval<T>(a, d, k));
+          v = cscale(cmuli(S.get(z)), kval<T>(a, d, k));
         } else if (a.diff == D_DIV) {
           C2<T> acc = {(T)0, (T)0};
-          for (int c = 0; c < a.n_in; ++c)
-            acc = cadd(acc, cscale(S[(size_t)c * tileC + e], kval<T>(a, c, k)));
+          for (int c = 0; c < a.n_in; ++c) acc = cadd(acc, cscale(S.get(z + c * tileC), kval<T>(a, c, k)));
           v = cmuli(acc);
         } else if (a.diff == D_NABLA) {
-          v = cscale(S[(size_t)d * tileC + e], lap_of(k));
+          v = cscale(S.get(z + d * tileC), lap_of(k));
         } else if (a.n_in == 1) {
           // 2D curl of a scalar: (d_y psi, -d_x psi)
-          v = cscale(cmuli(S[e]), d == 0 ? kval<T>(a, 1, k) : -kval<T>(a, 0, k));
+          v = cscale(cmuli(S.get(z)), d == 0 ? kval<T>(a, 1, k) : -kval<T>(a, 0, k));
         } else {
           const int c1 = (d + 1) % 3, c2 = (d + 2) % 3;
-          v = cmuli(csub(cscale(S[(size_t)c2 * tileC + e], kval<T>(a, c1, k)),
-                         cscale(S[(size_t)c1 * tileC + e], kval<T>(a, c2, k))));
+          v = cmuli(csub(cscale(S.get(z + c2 * tileC), kval<T>(a, c1, k)),
+                         cscale(S.get(z + c1 * tileC), kval<T>(a, c2, k))));
         }
-        W[e] = v;
-      }
+        W.put(z, {v.im, v.re});
+      });
       __syncthreads();
-      fft_lds<T, BIG, true>(W, nfft, a);
+      fft_lds<T, MODE>(W, wR, a);
       store_out<T>(W, xb, a.out[a.n_in + d], a, t);
       __syncthreads();
     }
+    for (int c = 0; c < nS; ++c)
+      each([&](int z, const KIdx&) {
+        const C2<T> v = S.get(z + c * tileC);
+        S.put(z + c * tileC, {v.im, v.re});
+      });
+    __syncthreads();
   }
   for (int c = 0; c < nS; ++c) {
-    fft_lds<T, BIG, true>(S + (size_t)c * tileC, nfft, a);
-    store_out<T>(S + (size_t)c * tileC, xb, a.out[fb + c], a, t);
+    fft_lds<T, MODE>(tile(c), wR, a);
+    store_out<T>(tile(c), xb, a.out[fb + c], a, t);
   }
 }
 
-template <typename T, int BIG>
-__global__ void __launch_bounds__(kThreads) k_oneway(const PassArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  oneway<T, BIG>(a, smem, tile_of(a), blockIdx.y);
+// The pass descriptor where the launch put it (the kernels' only argument).
+// Read as a parameter it is copied to scratch memory once its uses are many.
+__device__ __forceinline__ const PassArgs& kernel_args() {
+  return *(const PassArgs*)(const __attribute__((address_space(4))) PassArgs*)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
-template <typename T, int BIG>
-__global__ void __launch_bounds__(kThreads) k_sandwich_c2c(const PassArgs a) {
+template <typename T, int MODE>
+__global__ void __launch_bounds__(kThreads) k_oneway(const PassArgs) {
   extern __shared__ __align__(16) unsigned char smem[];
-  sandwich_c2c<T, BIG>(a, smem, tile_of(a));
+  const PassArgs& a = kernel_args();
+  oneway<T, MODE>(a, smem, tile_of(a), blockIdx.y);
 }
 
-template <typename T, int BIG>
-__global__ void __launch_bounds__(kThreads) k_sandwich_r2r(const PassArgs a) {
+template <typename T, int MODE>
+__global__ void __launch_bounds__(kThreads) k_sandwich_c2c(const PassArgs) {
   extern __shared__ __align__(16) unsigned char smem[];
-  sandwich_r2r<T, BIG>(a, smem, tile_of(a), blockIdx.y);
+  const PassArgs& a = kernel_args();
+  sandwich_c2c<T, MODE>(a, smem, tile_of(a));
+}
+
+template <typename T, int MODE>
+__global__ void __launch_bounds__(kThreads) k_sandwich_r2r(const PassArgs) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const PassArgs& a = kernel_args();
+  sandwich_r2r<T, MODE>(a, smem, tile_of(a), blockIdx.y);
 }
 
 template <auto K>
@@ -761,29 +992,98 @@ static void allow_lds() {
   }
 }
 
-template <typename T, int BIG>
+template <typename T, int MODE>
 static void launch_t(const PassArgs& a, dim3 grid, hipStream_t s) {
-  allow_lds<k_oneway<T, BIG>>();
-  allow_lds<k_sandwich_c2c<T, BIG>>();
-  allow_lds<k_sandwich_r2r<T, BIG>>();
-  if (a.kind == PK_ONEWAY)
-    hipLaunchKernelGGL((k_oneway<T, BIG>), grid, dim3(kThreads), a.lds_bytes, s, a);
-  else if (a.xf == X_C2C_F || a.xf == X_PAIR_F)
-    hipLaunchKernelGGL((k_sandwich_c2c<T, BIG>), grid, dim3(kThreads), a.lds_bytes, s, a);
-  else
-    hipLaunchKernelGGL((k_sandwich_r2r<T, BIG>), grid, dim3(kThreads), a.lds_bytes, s, a);
+  if (a.kind == PK_ONEWAY) {
+    allow_lds<k_oneway<T, MODE>>();
+    hipLaunchKernelGGL((k_oneway<T, MODE>), grid, dim3(kThreads), a.lds_bytes, s, a);
+  } else if (a.xf == X_C2C_F || a.xf == X_PAIR_F) {
+    allow_lds<k_sandwich_c2c<T, MODE>>();
+    hipLaunchKernelGGL((k_sandwich_c2c<T, MODE>), grid, dim3(kThreads), a.lds_bytes, s, a);
+  } else {
+    allow_lds<k_sandwich_r2r<T, MODE>>();
+    hipLaunchKernelGGL((k_sandwich_r2r<T, MODE>), grid, dim3(kThreads), a.lds_bytes, s, a);
+  }
+}
+
+// Radices of the register stages (fft_lds); a larger one runs the prime stage.
+int max_radix(int prec) { return prec == 0 ? 16 : 10; }
+
+static int gen_mode(const PassArgs& a, int prec) {
+  if (a.big) return GM_BIG;
+  for (int s = 0; s < a.nstage; ++s)
+    if (a.radix[s] > max_radix(prec)) return GM_PRIME;
+  return GM_SMALL;
+}
+
+int general_mode(const PassArgs& a, int prec) { return gen_mode(a, prec); }
+
+template <typename T>
+static void launch_mode(const PassArgs& a, int mode, dim3 grid, hipStream_t s) {
+  if (mode == GM_BIG) launch_t<T, GM_BIG>(a, grid, s);
+  else if (mode == GM_PRIME) launch_t<T, GM_PRIME>(a, grid, s);
+  else launch_t<T, GM_SMALL>(a, grid, s);
+}
+
+// Every stage of the pass has room for its butterflies in the threads'
+// registers, and the tile (with the prime stage's table) in LDS.
+bool general_fits(const PassArgs& a, int prec) {
+  const int maxe = (a.big ? 32 : 16) / (prec == 0 ? 1 : 2);
+  const bool cplx = a.xf == X_C2C_F || a.xf == X_C2C_B;
+  const long long nf = cplx ? a.P : a.P / 2;
+  if (nf < 1 || (nf & (nf - 1)) || a.L < 1 || a.L > 8192 || a.nin > a.L + 1 || a.nout > a.L + 1) return false;
+  long long prod = 1;
+  for (int s = 0; s < a.nstage; ++s) {
+    const int R = a.radix[s];
+    if (R < 2) return false;
+    prod *= R;
+    if (a.L % prod != 0) return false;
+    const long long nbl = a.L / R;
+    if (R <= max_radix(prec)) {
+      if (nf * nbl > (long long)(prec == 0 ? stage_slots<float>(R, maxe) : stage_slots<double>(R, maxe)) * kThreads)
+        return false;
+    } else {
+      if (R % 2 == 0) return false;
+      const long long nb = ((R - 1) / 2 + 1 + kPrimeB - 1) / kPrimeB;
+      if (nf * nbl * nb > (long long)std::max(2, maxe * 3 / 16) * kThreads) return false;
+    }
+  }
+  return prod == a.L;
+}
+
+// LDS bytes of a general pass of tile width P: its FFT tiles (nS coupled
+// fields and a work tile where derivatives couple them) and the table of the
+// largest prime stage (left out, a.prime_table = 0, where it would not fit).
+int general_lds_bytes(PassArgs& a, int P, int prec) {
+  const bool cplx = a.xf == X_C2C_F || a.xf == X_C2C_B;
+  const int nf = cplx ? P : P / 2;
+  int tiles = 1;
+  if (a.kind == PK_SANDWICH && (cplx || a.xf == X_PAIR_F)) {
+    const int nS = diff_is_adjoint(a.diff) ? a.n_out : a.n_in;
+    tiles = a.diff == D_NONE ? nS : nS + 1;
+  }
+  int table = 0;
+  for (int s = 0; s < a.nstage; ++s)
+    if (a.radix[s] > max_radix(prec)) table = std::max(table, a.radix[s]);
+  const long long cs = prec == 0 ? 8 : 16, data = (long long)tiles * a.L * tile_row(nf) * cs;
+  a.prime_table = table > 0;
+  if (a.big && data + table * cs > 160 * 1024) {
+    a.prime_table = 0;
+    table = 0;
+  }
+  return (int)std::min<long long>(data + table * cs, 1 << 30);
 }
 
 hipError_t launch_pass(const PassArgs& a, int prec, int grid_y, hipStream_t s) {
+  PassArgs chk = a;
+  if (!general_fits(a, prec) || general_lds_bytes(chk, a.P, prec) > a.lds_bytes ||
+      chk.prime_table != a.prime_table)
+    return hipErrorInvalidValue;
   const int tiles = ((a.Np + a.P - 1) / a.P) * a.No;
   dim3 grid(tiles, grid_y);
-  if (prec == 0) {
-    if (a.big) launch_t<float, 1>(a, grid, s);
-    else launch_t<float, 0>(a, grid, s);
-  } else {
-    if (a.big) launch_t<double, 1>(a, grid, s);
-    else launch_t<double, 0>(a, grid, s);
-  }
+  const int mode = gen_mode(a, prec);
+  if (prec == 0) launch_mode<float>(a, mode, grid, s);
+  else launch_mode<double>(a, mode, grid, s);
   return hipGetLastError();
 }
 
@@ -798,7 +1098,7 @@ __global__ void k_zero_counters(unsigned* c, int n, int* err) {
   if (blockIdx.x == 0 && threadIdx.x == 0) err[0] = 0;
 }
 
-template <typename T, int BIG>
+template <typename T, int MODE>
 __global__ void __launch_bounds__(kThreads) k_batched(const PassArgs* passes, const BatchItem* items,
                                                       int nitems, unsigned* counters, int* err) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -843,8 +1143,8 @@ __global__ void __launch_bounds__(kThreads) k_batched(const PassArgs* passes, co
         t.o = tile / tiles_p;
         t.p0 = (tile - t.o * tiles_p) * a.P;
         t.np = min(a.P, a.Np - t.p0);
-        if (a.kind == PK_ONEWAY) oneway<T, BIG>(a, smem, t, 0);
-        else sandwich_r2r<T, BIG>(a, smem, t, 0);
+        if (a.kind == PK_ONEWAY) oneway<T, MODE>(a, smem, t, 0);
+        else sandwich_r2r<T, MODE>(a, smem, t, 0);
         __syncthreads();  // LDS reuse by the next tile
       }
     }
@@ -858,15 +1158,16 @@ __global__ void __launch_bounds__(kThreads) k_batched(const PassArgs* passes, co
   }
 }
 
-int batched_blocks_per_cu(int lds, int prec, int big) {
+template <typename T>
+static hipError_t batched_occupancy(int* n, int lds, int mode) {
+  if (mode == GM_BIG) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_batched<T, GM_BIG>, kThreads, lds);
+  if (mode == GM_PRIME) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_batched<T, GM_PRIME>, kThreads, lds);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_batched<T, GM_SMALL>, kThreads, lds);
+}
+
+int batched_blocks_per_cu(int lds, int prec, int mode) {
   int n = 0;
-  hipError_t e;
-  if (prec == 0)
-    e = big ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batched<float, 1>, kThreads, lds)
-            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batched<float, 0>, kThreads, lds);
-  else
-    e = big ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batched<double, 1>, kThreads, lds)
-            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batched<double, 0>, kThreads, lds);
+  const hipError_t e = prec == 0 ? batched_occupancy<float>(&n, lds, mode) : batched_occupancy<double>(&n, lds, mode);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return 1;
@@ -874,26 +1175,29 @@ int batched_blocks_per_cu(int lds, int prec, int big) {
   return n > 0 ? n : 1;
 }
 
-template <typename T, int BIG>
+template <typename T, int MODE>
 static void launch_batched_t(const PassArgs* passes, const BatchItem* items, int nitems,
                              unsigned* counters, int* err, int grid, int lds, hipStream_t s) {
-  allow_lds<k_batched<T, BIG>>();
-  hipLaunchKernelGGL((k_batched<T, BIG>), dim3(grid), dim3(kThreads), lds, s, passes, items, nitems,
+  allow_lds<k_batched<T, MODE>>();
+  hipLaunchKernelGGL((k_batched<T, MODE>), dim3(grid), dim3(kThreads), lds, s, passes, items, nitems,
                      counters, err);
+}
+
+template <typename T>
+static void launch_batched_mode(const PassArgs* passes, const BatchItem* items, int nitems, unsigned* counters,
+                                int* err, int grid, int lds, int mode, hipStream_t s) {
+  if (mode == GM_BIG) launch_batched_t<T, GM_BIG>(passes, items, nitems, counters, err, grid, lds, s);
+  else if (mode == GM_PRIME) launch_batched_t<T, GM_PRIME>(passes, items, nitems, counters, err, grid, lds, s);
+  else launch_batched_t<T, GM_SMALL>(passes, items, nitems, counters, err, grid, lds, s);
 }
 
 hipError_t launch_batched(const PassArgs* passes, const BatchItem* items, int nitems,
                           unsigned* counters, int ncounters, int* err, int grid, int lds,
-                          int prec, int big, hipStream_t s) {
+                          int prec, int mode, hipStream_t s) {
   hipLaunchKernelGGL(k_zero_counters, dim3(1 + ncounters / 256), dim3(256), 0, s, counters,
                      ncounters, err);
-  if (prec == 0) {
-    if (big) launch_batched_t<float, 1>(passes, items, nitems, counters, err, grid, lds, s);
-    else launch_batched_t<float, 0>(passes, items, nitems, counters, err, grid, lds, s);
-  } else {
-    if (big) launch_batched_t<double, 1>(passes, items, nitems, counters, err, grid, lds, s);
-    else launch_batched_t<double, 0>(passes, items, nitems, counters, err, grid, lds, s);
-  }
+  if (prec == 0) launch_batched_mode<float>(passes, items, nitems, counters, err, grid, lds, mode, s);
+  else launch_batched_mode<double>(passes, items, nitems, counters, err, grid, lds, mode, s);
   return hipGetLastError();
 }
 

@@ -88,6 +88,7 @@ struct hp_plan_s {
   unsigned* batch_counters = nullptr;
   int batch_nitems = 0, batch_ncounters = 0, batch_grid = 0, batch_lds = 0;
   int batch_big = 0;  // register budget of the persistent kernel (PassArgs.big)
+  int batch_gen = 0;  // general passes: kernel mode of the persistent launch (general_mode)
   // kernels of the batched solve: 0 = general passes in one persistent launch
   // (k_batched); 1 = wavefront tile bodies in one persistent launch
   // (k_batched_wf, forward type batch_xf); 2 = the wavefront tile bodies as
