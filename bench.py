@@ -215,9 +215,9 @@ def neumann_batch64(steps, warmup):
         ntuned, tiles = bs.autotune(reps=5)
     ms_eager = _time(bs.run, steps, warmup, bs.stream)
     ms = _time_graph(bs.run, side, steps, warmup)
-    forms = {0: "one persistent launch, general passes",
-             1: "one persistent launch, wavefront tile bodies",
-             2: "one launch per pass level, transform length and pass kind, wavefront tile bodies"}
+    forms = {0: "one launch per pass level, general passes",
+             1: "one launch per pass level, wavefront tile bodies",
+             2: "one launch per pass level and transform length, wavefront tile bodies"}
     out = {"batches_per_s": 1000 / ms, "problems_per_s": 64000 / ms, "ms": ms,
            "timing": "hipGraph replays of the tuned batch",
            "kernel_form": forms[bs.kernel_mode()], "ms_eager": ms_eager,

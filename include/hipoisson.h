@@ -148,24 +148,25 @@ enum {
   HP_Q_NUM_PASSES = 3,      /* kernel launches of one hp_solve */
   HP_Q_NUM_OUTPUTS = 4,     /* psi components + derivative components */
   HP_Q_NUM_DERIVS = 5,      /* derivative components (gradient or curl) */
-  HP_Q_BATCH_ERROR = 6,     /* batched plans: 1 if the last solve hit a dependency-wait
-                               limit (results invalid), else 0; synchronises */
+  HP_Q_BATCH_ERROR = 6,     /* batched plans: 1 if the last solve's results are invalid
+                               because a wait inside it ran out; always 0 (a solve is a
+                               sequence of launches without such waits); synchronises */
   HP_Q_TUNED_PASSES = 7,    /* pass signatures whose configuration hp_autotune changed */
   HP_Q_TUNE_DEFAULT_MS = 8, /* milliseconds of one solve with the planner's defaults,
                                measured by the last hp_autotune */
   HP_Q_TUNE_BEST_MS = 9,    /* the same with the configuration it kept */
-  HP_Q_BATCH_TILES = 10,    /* batched plans: tiles per work item of the persistent kernel */
+  HP_Q_BATCH_TILES = 10,    /* batched plans: tiles per work item (workgroup) */
   HP_Q_ZERO_MODE = 11,      /* periodic / Neumann plans: the part of the bound source (with its
                                FD2 boundary terms) that the k = 0 projection removes, i.e. the
                                k = 0 coefficient of its forward transform over that of a field
                                of ones (the weighted mean, DCT-I ends weighted 1/2); 0 for a
                                compatible source and for other BCs; 3-component plans give
                                the component of largest magnitude; synchronises */
-  HP_Q_BATCH_KERNEL = 12    /* batched plans: 0 = one persistent launch of the general passes,
-                               1 = one persistent launch of the wavefront-FFT tile bodies (FP32,
-                               every transform length 64, 96, 128, 192 or 256), 2 = the same
-                               tile bodies as one launch per pass level (chosen by hp_autotune
-                               only) */
+  HP_Q_BATCH_KERNEL = 12    /* batched plans: 0 = the general passes, one launch per pass
+                               level; 1 = the wavefront-FFT tile bodies (FP32, every
+                               transform length 64, 96, 128, 192 or 256), one launch per
+                               pass level; 2 = the same tile bodies, one launch per pass
+                               level and transform length (chosen by hp_autotune only) */
 };
 
 /* Create a plan for one problem (the initialisation of Section 3.2.1): grid
@@ -181,11 +182,11 @@ HP_API hp_status hp_plan_create(const hp_desc* desc, hp_stream stream, hp_plan* 
 
 /* A plan over `count` independent problems (descs[0..count-1]); they must
  * share bc, grid, kernel, diff, prec and ndim and may differ in size.  One
- * hp_solve launches a single persistent kernel that runs every pass of every
- * problem.  Supported for bounded, non-periodic, homogeneous problems.  When
- * every transform length of every problem is 64, 96, 128, 192 or 256 (FP32)
- * the launch runs one FFT per wavefront, otherwise the general LDS-staged
- * passes (HP_Q_BATCH_KERNEL; hp_autotune may choose either). */
+ * hp_solve runs every problem's passes level by level, one launch per level
+ * for all problems.  Supported for bounded, non-periodic, homogeneous
+ * problems.  When every transform length of every problem is 64, 96, 128, 192
+ * or 256 (FP32) the launches run one FFT per wavefront, otherwise the general
+ * LDS-staged passes (HP_Q_BATCH_KERNEL; hp_autotune may choose either). */
 HP_API hp_status hp_plan_create_batched(const hp_desc* descs, int count, hp_stream stream, hp_plan* out);
 
 /* Unknown (input) and output point counts per axis of problem `problem`;
@@ -257,7 +258,7 @@ HP_API hp_status hp_pass_stats(hp_plan plan, int max, int* npass, double* ms, do
  * choices are kept only if the whole solve (batched plans: the whole batch,
  * which also decides the work-item size) is faster with them; later solves of
  * this plan use them.  Batched plans keep every pass within the register
- * budget and LDS of the default persistent kernel.  The tuned plan is then run against the default
+ * budget and LDS of the default launches.  The tuned plan is then run against the default
  * on the same pseudo-random input and every output must agree to rounding
  * (relative L2 difference <= 1e-5 FP32, <= 1e-12 FP64); otherwise the tuning
  * is dropped and HP_E_DEVICE returned.  Works on scratch arrays it allocates

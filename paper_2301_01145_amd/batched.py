@@ -1,4 +1,4 @@
-"""Many independent bounded solves in one persistent launch (hp_plan_create_batched)."""
+"""Many independent bounded solves in one plan (hp_plan_create_batched)."""
 from . import _lib
 from ._lib import (hp_autotune, hp_bind_output, hp_input_shape, hp_output_shape,
                    hp_plan_create_batched, hp_plan_destroy, hp_query, hp_set_input, hp_solve)
@@ -59,8 +59,9 @@ class BatchedSolver:
         return bool(hp_query(self.plan, _lib.HP_Q_BATCH_KERNEL))
 
     def kernel_mode(self):
-        """0: general passes in one persistent launch; 1: wavefront tile bodies in
-        one persistent launch; 2: wavefront tile bodies, one launch per pass level."""
+        """0: general passes, one launch per pass level; 1: wavefront tile bodies, one
+        launch per pass level; 2: wavefront tile bodies, one launch per pass level
+        and transform length."""
         return int(hp_query(self.plan, _lib.HP_Q_BATCH_KERNEL))
 
     def error_flag(self):

@@ -1,12 +1,18 @@
-// Batched persistent solve: many independent bounded problems of different
-// sizes in one launch.  The pass list of every problem is the one of the
-// single-problem path (all passes in place in the problem's output array); the
-// persistent kernel walks a global item list (one item = consecutive tiles of
-// one pass) ordered pass level by pass level, with per-pass completion
-// counters as the only dependencies between workgroups.  Where every pass of
-// every problem has a wavefront FFT (FP32, lengths 64, 96, 128, 192, 256) the
-// kernel runs the wavefront tile bodies (k_batched_wf); otherwise the general
-// pass code (k_batched).
+// Batched solve: many independent bounded problems of different sizes.  The
+// pass list of every problem is the one of the single-problem path (all passes
+// in place in the problem's output array); the passes of all problems at one
+// place in their lists form a level, whose work items (one item =
+// consecutive tiles of one pass) are independent and run in one launch.
+// Where every pass of every problem has a wavefront FFT (FP32, lengths 64,
+// 96, 128, 192, 256) the launches run the wavefront tile bodies
+// (k_batched_pass); otherwise the general pass code (k_batched).
+//
+// A single persistent launch with per-pass completion counters, the other way
+// to order the levels, was always slower: the agent-scope release and acquire
+// between dependent items write back and invalidate the L2 caches of all XCDs
+// once per item, a launch boundary once per level (64 Neumann problems of 32
+// to 128 cells per axis: 2430 us persistent, 484 us in launches; one
+// 128^3 problem 656 and 63 us; two of 32^3 101 and 26 us).
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
@@ -85,12 +91,16 @@ int pass_kind(const PassArgs& a, int xf) {
 // Tiles of a pass in the kernel of the plan's mode.
 int mode_tiles(hp_plan p, const PassArgs& a) { return p->batch_wf ? batched_wf_tiles(a) : tiles_of(a); }
 
+// One tile (strided wavefront items: one per group of wavefronts) per item:
+// more lengthen the chain of a workgroup and pay only where many rounds of
+// workgroups share the tables (8 problems: 85 us with 1, 95 with 2 tiles per
+// item; 64 problems: 484 and 467).
 int batch_tiles_per_item() {
   if (const char* e = std::getenv("HP_BATCH_TILES")) {
     const int v = std::atoi(e);
     if (v >= 1 && v <= 64) return v;
   }
-  return 4;
+  return 1;
 }
 const int kBatchTilesPerItem = batch_tiles_per_item();
 
@@ -110,7 +120,7 @@ hp_status batched_setup(hp_plan p) {
   // wavefront tile bodies where every pass allows them (unless the autotuner
   // chose the general passes)
   const int xf = p->batch_mode == 0 ? 0 : wf_family(p, lists);
-  // HP_BATCH_LEVELS=1: the level-launch form by default (as the autotuner may choose)
+  // HP_BATCH_LEVELS=1: a launch per level and length by default (as the autotuner may choose)
   const char* lv = std::getenv("HP_BATCH_LEVELS");
   const bool levels = p->batch_mode == 2 || (p->batch_mode < 0 && lv && std::atoi(lv) == 1);
   p->batch_wf = xf == 0 ? 0 : (levels ? 2 : 1);
@@ -142,47 +152,40 @@ hp_status batched_setup(hp_plan p) {
   std::vector<BatchItem> items;
   p->batch_groups.clear();
   for (int lev = 0; lev < maxlev; ++lev) {
-    // within a level, the problems' passes grouped by transform length and
-    // kind (the level launches run one kernel instance per group; the
-    // persistent kernels take any order within a level)
-    std::vector<std::pair<int, int>> keys;
-    for (size_t q = 0; q < lists.size(); ++q)
-      if (lev < (int)lists[q].size()) keys.push_back({lists[q][lev].a.L, pass_kind(lists[q][lev].a, xf)});
+    // within a level, the problems' passes grouped by kind (and by transform
+    // length in mode 2), longest transforms first: their items take longest
+    std::vector<std::pair<int, int>> keys;  // (kind, -length)
+    for (auto& l : lists)
+      if (lev < (int)l.size()) keys.push_back({pass_kind(l[lev].a, xf), -l[lev].a.L});
     std::sort(keys.begin(), keys.end());
     keys.erase(std::unique(keys.begin(), keys.end()), keys.end());
-    for (auto key : keys) {
-      BatchGroup grp{(int)items.size(), 0, key.first, key.second, 0, lev};
+    for (size_t i = 0; i < keys.size(); ++i) {
+      const auto key = keys[i];
+      const bool open = i > 0 && (p->batch_wf == 0 || (p->batch_wf == 1 && keys[i - 1].first == key.first));
+      if (!open)
+        p->batch_groups.push_back({(int)items.size(), 0, p->batch_wf == 2 ? -key.second : 0, key.first, 0, lev});
+      BatchGroup& grp = p->batch_groups.back();
       for (size_t q = 0; q < lists.size(); ++q) {
-        if (lev >= (int)lists[q].size() || lists[q][lev].a.L != key.first ||
-            pass_kind(lists[q][lev].a, xf) != key.second)
-          continue;
-        grp.lds = std::max(grp.lds, lists[q][lev].a.lds_bytes);
-        const int gp = first[q] + lev;
-        const int dep = lev > 0 ? gp - 1 : -1;
-        const int need = lev > 0 ? mode_tiles(p, lists[q][lev - 1].a) : 0;
-        // consecutive tiles of a pass share one item (one queue step, one
-        // dependency check and one release per item); a wavefront strided item
-        // holds one tile per group of wavefronts for every step
+        if (lev >= (int)lists[q].size()) continue;
         const PassArgs& a = lists[q][lev].a;
+        if (-a.L != key.second || pass_kind(a, xf) != key.first) continue;
+        grp.lds = std::max(grp.lds, a.lds_bytes);
+        // a wavefront strided item holds one tile per group of wavefronts for
+        // every step
         const int nt = mode_tiles(p, a);
         const int step = per_item * (p->batch_wf ? batched_wf_group(a) : 1);
-        for (int t = 0; t < nt; t += step)
-          items.push_back({gp, t, std::min(step, nt - t), dep, need});
+        for (int t = 0; t < nt; t += step) items.push_back({first[q] + lev, t, std::min(step, nt - t)});
       }
       grp.count = (int)items.size() - grp.first;
-      p->batch_groups.push_back(grp);
     }
   }
   p->batch_nitems = (int)items.size();
-  p->batch_ncounters = 1 + npass;
   p->batch_lds = lds;
   // a second setup (after autotuning) replaces the tables of the first
   (void)hipStreamSynchronize(p->stream);
   plan_free(p, p->batch_items);
-  plan_free(p, p->batch_counters);
   plan_free(p, p->batch_probs);
   p->batch_items = p->batch_probs = nullptr;
-  p->batch_counters = nullptr;
   p->batch_uploaded.clear();
   void* d;
   s = plan_alloc(p, items.size() * sizeof(BatchItem), &d);
@@ -190,18 +193,9 @@ hp_status batched_setup(hp_plan p) {
   p->batch_items = d;
   if (hipMemcpy(d, items.data(), items.size() * sizeof(BatchItem), hipMemcpyHostToDevice) != hipSuccess)
     return plan_fail(p, HP_E_DEVICE, "upload of the batched work list failed");
-  s = plan_alloc(p, (size_t)p->batch_ncounters * sizeof(unsigned) + 64, &d);
-  if (s != HP_OK) return s;
-  p->batch_counters = (unsigned*)d;
   s = plan_alloc(p, (size_t)npass * sizeof(PassArgs), &d);
   if (s != HP_OK) return s;
   p->batch_probs = d;
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return plan_fail(p, HP_E_DEVICE, "device query failed");
-  const int per_cu = p->batch_wf ? batched_wf_blocks_per_cu(xf, lds) : batched_blocks_per_cu(lds, p->prec, gen);
-  p->batch_grid = std::max(1, std::min(p->batch_nitems, per_cu * cus));
   // level form: streams and events for the groups of a level (the most
   // groups in one level - 1 forked streams; a fork and the joins per level)
   if (p->batch_wf == 2) {
@@ -235,20 +229,23 @@ hp_status batched_setup(hp_plan p) {
   return HP_OK;
 }
 
-// The level form: one launch per (level, length, kind) group.  The groups of
-// one level are independent (each problem has one pass per level).  While the
-// plan's stream is being captured, all but the first group of a level run on
-// forked streams that wait for the level's start on the plan's stream, and
-// the plan's stream waits for all of them before the next level: the fork and
-// the joins become graph edges, and the replayed graph runs a level's groups
-// concurrently (64 Neumann problems: 0.51 -> 0.44 ms).  Eager solves launch
-// the groups in order on the plan's stream, where the event calls of a fork
-// cost more than the overlap gains.
+// The launches of a solve in level order.  Mode 2 has several groups per level
+// (one per transform length), which are independent (each problem has one
+// pass per level).  While the plan's stream is being captured, all but the
+// first group of a level run on forked streams that wait for the level's
+// start on the plan's stream, and the plan's stream waits for all of them
+// before the next level: the fork and the joins become graph edges, and the
+// replayed graph runs a level's groups concurrently.  Eager solves launch the
+// groups in order on the plan's stream, where the event calls of a fork cost
+// more than the overlap gains.
 hipError_t launch_levels(hp_plan p) {
   const PassArgs* passes = (const PassArgs*)p->batch_probs;
   const BatchItem* items = (const BatchItem*)p->batch_items;
-  int* err = (int*)(p->batch_counters + p->batch_ncounters);
   const std::vector<BatchGroup>& gs = p->batch_groups;
+  auto launch = [&](const BatchGroup& g, hipStream_t s) {
+    return p->batch_wf ? launch_batched_group(p->batch_xf, passes, items, g, s)
+                       : launch_batched(passes, items, g, p->prec, p->batch_gen, s);
+  };
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   const bool capturing =
       hipStreamIsCapturing(p->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusActive;
@@ -266,8 +263,7 @@ hipError_t launch_levels(hp_plan p) {
     }
     for (size_t g = k; g < e; ++g) {
       const hipStream_t s = (fork && g > k) ? p->batch_aux[g - k - 1] : p->stream;
-      if ((r = launch_batched_group(p->batch_xf, passes, items, gs[g], g == 0 ? err : nullptr, s)) != hipSuccess)
-        return r;
+      if ((r = launch(gs[g], s)) != hipSuccess) return r;
     }
     if (fork) {
       for (size_t g = k + 1; g < e; ++g) {
@@ -321,18 +317,7 @@ hp_status batched_solve(hp_plan p) {
       return plan_fail(p, HP_E_DEVICE, "upload of the batched pass table failed");
     p->batch_uploaded = img;
   }
-  hipError_t e =
-      p->batch_wf == 2
-          ? launch_levels(p)
-      : p->batch_wf
-          ? launch_batched_wf(p->batch_xf, (const PassArgs*)p->batch_probs,
-                              (const BatchItem*)p->batch_items, p->batch_nitems, p->batch_counters,
-                              p->batch_ncounters, (int*)(p->batch_counters + p->batch_ncounters),
-                              p->batch_grid, p->batch_lds, p->stream)
-          : launch_batched((const PassArgs*)p->batch_probs, (const BatchItem*)p->batch_items,
-                           p->batch_nitems, p->batch_counters, p->batch_ncounters,
-                           (int*)(p->batch_counters + p->batch_ncounters), p->batch_grid,
-                           p->batch_lds, p->prec, p->batch_gen, p->stream);
+  const hipError_t e = launch_levels(p);
   if (e != hipSuccess)
     return plan_fail(p, HP_E_DEVICE, std::string("batched launch: ") + hipGetErrorString(e));
   p->solved = true;

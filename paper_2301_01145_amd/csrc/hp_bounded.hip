@@ -363,14 +363,11 @@ __global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
   }
 }
 
-// ------------------------------------------ batched persistent solve
-// Every pass of every problem of a batched plan, one persistent launch: a
-// workgroup of kBatchWaves wavefronts takes work items (consecutive tiles of
-// one pass of one problem) from a queue ordered pass level by pass level and
-// waits for the pass it depends on (per-pass completion counters, agent-scope
-// acquire / release), as the general batched kernel does.  The tile bodies
-// are those of kb_contig / kb_strided with the transform length and type as
-// compile-time constants:
+// ------------------------------------------ batched solve
+// A pass level of a batched plan (one pass of every problem) is one launch, one
+// workgroup of kBatchWaves wavefronts per work item (consecutive tiles of one
+// pass of one problem).  The tile bodies are those of kb_contig / kb_strided
+// with the transform length and type as compile-time constants:
 //   contiguous pass: a tile is kBatchWaves * PPW pencil pairs (one per lane
 //     group) taken in (o, pair) order;
 //   strided pass / sandwich: a tile is P = 32 pencils adjacent along the
@@ -450,41 +447,6 @@ __device__ __forceinline__ BwArgs bw_args(const PassArgs& a) {
   return b;
 }
 
-__device__ __forceinline__ BwArgs bw_uniform(const BwArgs& a) {
-  BwArgs b;
-  b.L = uni(a.L);
-  b.fast = uni(a.fast);
-  b.xf = uni(a.xf);
-  b.n = uni(a.n);
-  b.Np = uni(a.Np);
-  b.No = uni(a.No);
-  b.in_sj = uni(a.in_sj);
-  b.in_sp = uni(a.in_sp);
-  b.in_so = uni(a.in_so);
-  b.out_sj = uni(a.out_sj);
-  b.out_sp = uni(a.out_sp);
-  b.out_so = uni(a.out_so);
-  b.in = uni(a.in);
-  b.out = uni(a.out);
-  b.tw = uni(a.tw);
-  b.qtw = uni(a.qtw);
-  b.lam_j = uni(a.lam_j);
-  b.lam_p = uni(a.lam_p);
-  b.lam_o = uni(a.lam_o);
-  b.norm = uni(a.norm);
-  return b;
-}
-
-// The thread index, opaque to the optimiser: everything a tile body derives
-// from it (lane splits, LDS slot addresses) is then computed inside the body
-// instead of being hoisted out of the persistent loop, where the values of
-// every (length, kind) body would stay live together and spill.
-__device__ __forceinline__ int bw_tid() {
-  int t = threadIdx.x;
-  asm volatile("" : "+v"(t));
-  return t;
-}
-
 // Load the twiddles of the pass (and the quarter-wave twists) into LDS.
 template <int L>
 __device__ __forceinline__ void bw_tables(const BwArgs& a, C2<float>* tw, C2<float>* q, int tid) {
@@ -502,7 +464,7 @@ __device__ __forceinline__ void bw_contig(const BwArgs& a, unsigned char* smem, 
   C2<T>* tw = (C2<T>*)smem;
   C2<T>* q = tw + L;
   C2<T>* slots = q + BW<L>::MAXN;
-  const int tid = bw_tid();
+  const int tid = threadIdx.x;
   bw_tables<L>(a, tw, q, tid);
   __syncthreads();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -562,7 +524,7 @@ __device__ __forceinline__ void bw_strided(const BwArgs& a, unsigned char* smem,
   C2<T>* q = tw + L;
   C2<T>* slots = q + MAXN;
   T* tiles = (T*)(slots + kBatchWaves * PPW * slot_len(L));
-  const int tid = bw_tid();
+  const int tid = threadIdx.x;
   bw_tables<L>(a, tw, q, tid);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int sub = wave / W, wv = wave - sub * W;  // tile group and wavefront in it
@@ -639,114 +601,41 @@ __device__ __forceinline__ void bw_strided(const BwArgs& a, unsigned char* smem,
   }
 }
 
-// The persistent kernel calls every tile body as a function of its own (not
-// inlined), so that each is register-allocated on its own: inlined into the
-// loop over items their values stayed live together and spilled.  The
-// arguments are copied into scalar registers on entry (bw_uniform).  The
-// level launches have no loop over items and inline the bodies.
-template <int L, int X>
-__device__ __attribute__((noinline)) void bw_contig_call(const BwArgs* ap, unsigned char* smem,
-                                                         int tile, int ntile) {
-  bw_contig<L, X>(bw_uniform(*ap), smem, tile, ntile);
-}
-template <int L, int XF, int XO, bool SW>
-__device__ __attribute__((noinline)) void bw_strided_call(const BwArgs* ap, unsigned char* smem,
-                                                          int tile, int ntile) {
-  bw_strided<L, XF, XO, SW>(bw_uniform(*ap), smem, tile, ntile);
-}
-
-// One item: ntile tiles of pass a, for the transform pair (XF, XB) of the batch.
-template <int L, int XF, int XB, bool CALL>
-__device__ __forceinline__ void bw_item_L(const BwArgs& a, unsigned char* smem, int tile, int ntile) {
-  if (a.fast == FAST_R2R_C) {
-    if constexpr (CALL) {
-      if (a.xf == XF) bw_contig_call<L, XF>(&a, smem, tile, ntile);
-      else bw_contig_call<L, XB>(&a, smem, tile, ntile);
-    } else {
-      if (a.xf == XF) bw_contig<L, XF>(a, smem, tile, ntile);
-      else bw_contig<L, XB>(a, smem, tile, ntile);
-    }
-  } else if (a.fast == FAST_R2R_S) {
-    if constexpr (CALL) {
-      if (a.xf == XF) bw_strided_call<L, XF, XF, false>(&a, smem, tile, ntile);
-      else bw_strided_call<L, XB, XB, false>(&a, smem, tile, ntile);
-    } else {
-      if (a.xf == XF) bw_strided<L, XF, XF, false>(a, smem, tile, ntile);
-      else bw_strided<L, XB, XB, false>(a, smem, tile, ntile);
-    }
-  } else {
-    if constexpr (CALL) bw_strided_call<L, XF, XB, true>(&a, smem, tile, ntile);
-    else bw_strided<L, XF, XB, true>(a, smem, tile, ntile);
-  }
-}
-
-template <int XF, int XB, bool CALL>
+// One item of kind KIND: 0 / 1 contiguous pass of type XF / XB, 2 / 3 strided
+// pass of type XF / XB, 4 sandwich (XF, multiplier, XB).
+template <int L, int XF, int XB, int KIND>
 __device__ __forceinline__ void bw_item(const BwArgs& a, unsigned char* smem, int tile, int ntile) {
-  switch (a.L) {
-    case 64: bw_item_L<64, XF, XB, CALL>(a, smem, tile, ntile); break;
-    case 96: bw_item_L<96, XF, XB, CALL>(a, smem, tile, ntile); break;
-    case 128: bw_item_L<128, XF, XB, CALL>(a, smem, tile, ntile); break;
-    case 192: bw_item_L<192, XF, XB, CALL>(a, smem, tile, ntile); break;
-    default: bw_item_L<256, XF, XB, CALL>(a, smem, tile, ntile); break;
-  }
+  if constexpr (KIND == 0) bw_contig<L, XF>(a, smem, tile, ntile);
+  else if constexpr (KIND == 1) bw_contig<L, XB>(a, smem, tile, ntile);
+  else if constexpr (KIND == 2) bw_strided<L, XF, XF, false>(a, smem, tile, ntile);
+  else if constexpr (KIND == 3) bw_strided<L, XB, XB, false>(a, smem, tile, ntile);
+  else bw_strided<L, XF, XB, true>(a, smem, tile, ntile);
 }
 
-__global__ void k_bw_zero(unsigned* c, int n, int* err) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) c[i] = 0u;
-  if (blockIdx.x == 0 && threadIdx.x == 0) err[0] = 0;
+__device__ __forceinline__ BatchItem bw_take(const BatchItem* items) {
+  BatchItem bi = items[blockIdx.x];
+  bi.pass = uni(bi.pass);
+  bi.tile = uni(bi.tile);
+  bi.ntile = uni(bi.ntile);
+  return bi;
 }
 
-// Four wavefronts per SIMD: at most 128 VGPRs.
-template <int XF, int XB>
+// One pass level of the batch, every transform length in one launch: the
+// workgroups of a level are independent, so the lengths run side by side and
+// a solve is one launch per level (8 problems of 32 to 128 cells per axis: 85 us
+// against 174 with a launch per level and length; 64 problems: 484 and 609).
+template <int XF, int XB, int KIND>
 __global__ void __launch_bounds__(64 * kBatchWaves, 4)
-    k_batched_wf(const PassArgs* passes, const BatchItem* items, int nitems, unsigned* counters,
-                 int* err) {
+    k_batched_pass(const PassArgs* passes, const BatchItem* items) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_item, s_ok;
-  for (;;) {
-    if (threadIdx.x == 0) s_item = (int)atomicAdd(&counters[0], 1u);
-    __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(s_item);
-    if (it >= nitems) break;
-    BatchItem bi = items[it];
-    bi.pass = uni(bi.pass);
-    bi.tile = uni(bi.tile);
-    bi.ntile = uni(bi.ntile);
-    bi.dep = uni(bi.dep);
-    bi.need = uni(bi.need);
-    if (threadIdx.x == 0) {
-      int ok = 1;
-      if (bi.dep >= 0) {
-        unsigned spins = 0;
-        while (__hip_atomic_load(&counters[1 + bi.dep], __ATOMIC_ACQUIRE,
-                                 __HIP_MEMORY_SCOPE_AGENT) < (unsigned)bi.need) {
-          __builtin_amdgcn_s_sleep(2);
-          // bounded wait: report and skip (also stop at once if another wait failed)
-          if (++spins > (1u << 22) ||
-              __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-            ok = 0;
-            atomicExch(err, 1);
-            break;
-          }
-        }
-      }
-      s_ok = ok;
-    }
-    __syncthreads();
-    const int ok = __builtin_amdgcn_readfirstlane(s_ok);
-    // acquire: the tiles written by the workgroups that completed the pass
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    if (ok) {
-      const BwArgs args = bw_args(passes[bi.pass]);
-      bw_item<XF, XB, true>(args, smem, bi.tile, bi.ntile);
-    }
-    // release: this item's stores before its tiles are counted
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    if (threadIdx.x == 0)
-      __hip_atomic_fetch_add(&counters[1 + bi.pass], (unsigned)bi.ntile, __ATOMIC_RELEASE,
-                             __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
+  const BatchItem bi = bw_take(items);
+  const BwArgs a = bw_args(passes[bi.pass]);
+  switch (a.L) {
+    case 64: bw_item<64, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+    case 96: bw_item<96, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+    case 128: bw_item<128, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+    case 192: bw_item<192, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+    default: bw_item<256, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
   }
 }
 
@@ -760,77 +649,50 @@ __global__ void __launch_bounds__(64 * kBatchWaves, 4)
 // XF / XB, 4 sandwich (XF, multiplier, XB).
 template <int XF, int XB, int L, int KIND>
 __global__ void __launch_bounds__(64 * kBatchWaves, 4)
-    k_batched_level(const PassArgs* passes, const BatchItem* items, int* err) {
+    k_batched_level(const PassArgs* passes, const BatchItem* items) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if (blockIdx.x == 0 && threadIdx.x == 0 && err) err[0] = 0;  // no waits: never set
-  BatchItem bi = items[blockIdx.x];
-  bi.pass = uni(bi.pass);
-  bi.tile = uni(bi.tile);
-  bi.ntile = uni(bi.ntile);
-  const BwArgs a = bw_args(passes[bi.pass]);
-  if constexpr (KIND == 0) bw_contig<L, XF>(a, smem, bi.tile, bi.ntile);
-  else if constexpr (KIND == 1) bw_contig<L, XB>(a, smem, bi.tile, bi.ntile);
-  else if constexpr (KIND == 2) bw_strided<L, XF, XF, false>(a, smem, bi.tile, bi.ntile);
-  else if constexpr (KIND == 3) bw_strided<L, XB, XB, false>(a, smem, bi.tile, bi.ntile);
-  else bw_strided<L, XF, XB, true>(a, smem, bi.tile, bi.ntile);
+  const BatchItem bi = bw_take(items);
+  bw_item<L, XF, XB, KIND>(bw_args(passes[bi.pass]), smem, bi.tile, bi.ntile);
 }
 
 template <int XF, int XB, int L, int KIND>
-hipError_t bw_launch_group(const PassArgs* passes, const BatchItem* items, int n, int* err, int lds,
-                           hipStream_t s) {
-  allow_lds<k_batched_level<XF, XB, L, KIND>>();
-  hipLaunchKernelGGL((k_batched_level<XF, XB, L, KIND>), dim3(n), dim3(64 * kBatchWaves), lds, s,
-                     passes, items, err);
+hipError_t bw_launch_group(const PassArgs* passes, const BatchItem* items, int n, int lds, hipStream_t s) {
+  if constexpr (L == 0) {
+    allow_lds<k_batched_pass<XF, XB, KIND>>();
+    hipLaunchKernelGGL((k_batched_pass<XF, XB, KIND>), dim3(n), dim3(64 * kBatchWaves), lds, s, passes, items);
+  } else {
+    allow_lds<k_batched_level<XF, XB, L, KIND>>();
+    hipLaunchKernelGGL((k_batched_level<XF, XB, L, KIND>), dim3(n), dim3(64 * kBatchWaves), lds, s, passes,
+                       items);
+  }
   return hipGetLastError();
 }
 
 template <int XF, int XB, int L>
-hipError_t bw_launch_kind(const BatchGroup& g, const PassArgs* passes, const BatchItem* it, int* e,
-                          hipStream_t s) {
+hipError_t bw_launch_kind(const BatchGroup& g, const PassArgs* passes, const BatchItem* it, hipStream_t s) {
   switch (g.kind) {
-    case 0: return bw_launch_group<XF, XB, L, 0>(passes, it, g.count, e, g.lds, s);
-    case 1: return bw_launch_group<XF, XB, L, 1>(passes, it, g.count, e, g.lds, s);
-    case 2: return bw_launch_group<XF, XB, L, 2>(passes, it, g.count, e, g.lds, s);
-    case 3: return bw_launch_group<XF, XB, L, 3>(passes, it, g.count, e, g.lds, s);
-    case 4: return bw_launch_group<XF, XB, L, 4>(passes, it, g.count, e, g.lds, s);
+    case 0: return bw_launch_group<XF, XB, L, 0>(passes, it, g.count, g.lds, s);
+    case 1: return bw_launch_group<XF, XB, L, 1>(passes, it, g.count, g.lds, s);
+    case 2: return bw_launch_group<XF, XB, L, 2>(passes, it, g.count, g.lds, s);
+    case 3: return bw_launch_group<XF, XB, L, 3>(passes, it, g.count, g.lds, s);
+    case 4: return bw_launch_group<XF, XB, L, 4>(passes, it, g.count, g.lds, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 template <int XF, int XB>
-hipError_t bw_launch_one(const BatchGroup& g, const PassArgs* passes, const BatchItem* items, int* err,
-                         hipStream_t s) {
+hipError_t bw_launch_one(const BatchGroup& g, const PassArgs* passes, const BatchItem* items, hipStream_t s) {
   if (g.count <= 0) return hipSuccess;
   const BatchItem* it = items + g.first;
   switch (g.L) {
-    case 64: return bw_launch_kind<XF, XB, 64>(g, passes, it, err, s);
-    case 96: return bw_launch_kind<XF, XB, 96>(g, passes, it, err, s);
-    case 128: return bw_launch_kind<XF, XB, 128>(g, passes, it, err, s);
-    case 192: return bw_launch_kind<XF, XB, 192>(g, passes, it, err, s);
-    case 256: return bw_launch_kind<XF, XB, 256>(g, passes, it, err, s);
+    case 0: return bw_launch_kind<XF, XB, 0>(g, passes, it, s);
+    case 64: return bw_launch_kind<XF, XB, 64>(g, passes, it, s);
+    case 96: return bw_launch_kind<XF, XB, 96>(g, passes, it, s);
+    case 128: return bw_launch_kind<XF, XB, 128>(g, passes, it, s);
+    case 192: return bw_launch_kind<XF, XB, 192>(g, passes, it, s);
+    case 256: return bw_launch_kind<XF, XB, 256>(g, passes, it, s);
     default: return hipErrorInvalidValue;
   }
-}
-
-template <int XF, int XB>
-int bw_blocks_per_cu(int lds) {
-  int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batched_wf<XF, XB>, 64 * kBatchWaves, lds) !=
-      hipSuccess) {
-    (void)hipGetLastError();
-    return 1;
-  }
-  return n > 0 ? n : 1;
-}
-
-template <int XF, int XB>
-hipError_t bw_launch(const PassArgs* passes, const BatchItem* items, int nitems, unsigned* counters,
-                     int ncounters, int* err, int grid, int lds, hipStream_t s) {
-  allow_lds<k_batched_wf<XF, XB>>();
-  hipLaunchKernelGGL(k_bw_zero, dim3(1 + ncounters / 256), dim3(256), 0, s, counters, ncounters, err);
-  hipLaunchKernelGGL((k_batched_wf<XF, XB>), dim3(grid), dim3(64 * kBatchWaves), lds, s, passes, items,
-                     nitems, counters, err);
-  return hipGetLastError();
 }
 
 template <int L>
@@ -884,29 +746,11 @@ int batched_wf_group(const PassArgs& a) {
   }
 }
 
-int batched_wf_blocks_per_cu(int xf, int lds) {
-  if (xf == X_DCT2) return bw_blocks_per_cu<X_DCT2, X_DCT3>(lds);
-  if (xf == X_DST2) return bw_blocks_per_cu<X_DST2, X_DST3>(lds);
-  return bw_blocks_per_cu<X_DCT1, X_DCT1>(lds);
-}
-
 hipError_t launch_batched_group(int xf, const PassArgs* passes, const BatchItem* items,
-                                const BatchGroup& g, int* err, hipStream_t s) {
-  if (xf == X_DCT2) return bw_launch_one<X_DCT2, X_DCT3>(g, passes, items, err, s);
-  if (xf == X_DST2) return bw_launch_one<X_DST2, X_DST3>(g, passes, items, err, s);
-  if (xf == X_DCT1) return bw_launch_one<X_DCT1, X_DCT1>(g, passes, items, err, s);
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_batched_wf(int xf, const PassArgs* passes, const BatchItem* items, int nitems,
-                             unsigned* counters, int ncounters, int* err, int grid, int lds,
-                             hipStream_t s) {
-  if (xf == X_DCT2)
-    return bw_launch<X_DCT2, X_DCT3>(passes, items, nitems, counters, ncounters, err, grid, lds, s);
-  if (xf == X_DST2)
-    return bw_launch<X_DST2, X_DST3>(passes, items, nitems, counters, ncounters, err, grid, lds, s);
-  if (xf == X_DCT1)
-    return bw_launch<X_DCT1, X_DCT1>(passes, items, nitems, counters, ncounters, err, grid, lds, s);
+                                const BatchGroup& g, hipStream_t s) {
+  if (xf == X_DCT2) return bw_launch_one<X_DCT2, X_DCT3>(g, passes, items, s);
+  if (xf == X_DST2) return bw_launch_one<X_DST2, X_DST3>(g, passes, items, s);
+  if (xf == X_DCT1) return bw_launch_one<X_DCT1, X_DCT1>(g, passes, items, s);
   return hipErrorInvalidValue;
 }
 

@@ -45,8 +45,8 @@ __host__ __device__ inline bool diff_is_adjoint(int d) {
   return d == D_ADJ_GRAD || d == D_ADJ_CURL || d == D_ADJ_DIV || d == D_ADJ_NABLA;
 }
 
-// Threads per workgroup of the general pencil kernels (and the persistent
-// batched kernel); the wavefront-FFT kernels size their own workgroups.
+// Threads per workgroup of the general pencil kernels (single and batched); the
+// wavefront-FFT kernels size their own workgroups.
 #ifndef HP_GEN_THREADS
 #define HP_GEN_THREADS 256
 #endif
@@ -94,7 +94,6 @@ struct PassArgs {
   int nunk[3];             // unknown counts per logical axis
   int lds_bytes;
   int big;                 // general kernels: 1 = the larger per-thread register budget
-  int prime_table;         // general kernels: the prime stage's factors are in LDS
   // wavefront-FFT kernels of the free-space path (0: general pass)
   int fast;                // FAST_* below
   int un[3];               // physical (undoubled) sizes n_a
@@ -199,7 +198,7 @@ bool fast_tile_ok(int fast, int L, int P, int prec);
 // for all passes: the largest).
 int max_radix(int prec);
 bool general_fits(const PassArgs& a, int prec);
-int general_lds_bytes(PassArgs& a, int P, int prec);  // sets a.prime_table
+int general_lds_bytes(const PassArgs& a, int P, int prec);
 int general_mode(const PassArgs& a, int prec);
 // Launch one pass over `grid_y` independent field groups.
 hipError_t launch_pass(const PassArgs& a, int prec, int grid_y, hipStream_t s);
@@ -240,15 +239,11 @@ hipError_t launch_octant(const double* spec, const int M[3], double scale, void*
 // highest axis wins).
 hipError_t launch_dirichlet_fill(void* out, const int N[3], int ndim, int axes, const void* face[3][2],
                                  int prec, hipStream_t s);
-// Consecutive tiles of one pass of the batched persistent solve.  `dep` is the global
-// index of the pass that must be complete first (-1: none) and `need` its tile
-// count; items are ordered so that every dependency has lower item indices.
+// A work item of a batched plan: consecutive tiles of one pass (one workgroup).
 struct BatchItem {
   int pass;
   int tile;   // first tile of the item
   int ntile;  // consecutive tiles of the pass in the item
-  int dep;    // pass whose tiles must all be done first (-1: none)
-  int need;   // tile count of that pass
 };
 
 // Zero mode of a periodic / Neumann source: per-block partial sums (nb blocks,
@@ -270,41 +265,28 @@ constexpr int kZeroModeMaxComp = 3;
 hipError_t launch_zero_mode_noalloc(const PassArgs* a, const void* const* f, int ncomp,
                                     const int n[3], const int trap[3], const double* W,
                                     double* out, int prec, hipStream_t s);
-// Persistent batched solve: counters[0] is the work-queue head, counters[1 + i]
-// the completed tiles of pass i (zeroed by the launch itself); err[0] is set
-// to 1 if a dependency wait exceeds its spin limit (the item is then skipped).
-hipError_t launch_batched(const PassArgs* passes, const BatchItem* items, int nitems,
-                          unsigned* counters, int ncounters, int* err, int grid, int lds,
-                          int prec, int mode, hipStream_t s);
-// Batched persistent solve on the wavefront kernels (FP32, transform lengths
-// 64, 96, 128, 192, 256; hp_bounded.hip).  Passes carry fast = FAST_R2R_C /
-// FAST_R2R_S / FAST_R2R_SW, the wavefront twiddles and P = 32; xf is the
-// forward type of the batch (DCT-II, DST-II or DCT-I; the backward type is
-// its Table 1 partner).  Tiles: batched_wf_tiles per pass; a strided item
-// should hold a multiple of batched_wf_group tiles (one per group of
-// wavefronts of the workgroup).  LDS: the largest batched_wf_lds of its passes.
+// One launch of a batched solve: items [first, first + count) of one pass level
+// (`level`), one workgroup each with lds bytes of LDS.  Wavefront tile bodies:
+// all of pass kind `kind` (0 / 1 contiguous pass of the forward / backward
+// type, 2 / 3 strided pass of the forward / backward type, 4 sandwich) and of
+// transform length L (0: any of batched_wf_length).
+struct BatchGroup {
+  int first, count, L, kind, lds, level;
+};
+// General passes, any lengths and kinds (mode: the largest general_mode).
+hipError_t launch_batched(const PassArgs* passes, const BatchItem* items, const BatchGroup& g, int prec,
+                          int mode, hipStream_t s);
+// Wavefront tile bodies (FP32, transform lengths 64, 96, 128, 192, 256;
+// hp_bounded.hip).  Passes carry fast = FAST_R2R_C / FAST_R2R_S / FAST_R2R_SW,
+// the wavefront twiddles and P = 32; xf is the forward type of the batch
+// (DCT-II, DST-II or DCT-I; the backward type is its Table 1 partner).
+// Tiles: batched_wf_tiles per pass; a strided item should hold a multiple of
+// batched_wf_group tiles (one per group of wavefronts of the workgroup).
+// LDS: the largest batched_wf_lds of its passes.
 bool batched_wf_length(int L);
 int batched_wf_lds(int fast, int L);
 int batched_wf_tiles(const PassArgs& a);
 int batched_wf_group(const PassArgs& a);
-int batched_wf_blocks_per_cu(int xf, int lds);
-hipError_t launch_batched_wf(int xf, const PassArgs* passes, const BatchItem* items, int nitems,
-                             unsigned* counters, int ncounters, int* err, int grid, int lds,
-                             hipStream_t s);
-// The same tile bodies as one launch per pass level, transform length and
-// pass kind (no queue, no waits): group k runs items [first, first + count),
-// all of one level, one length L and one kind (0 / 1 contiguous pass of the
-// forward / backward type, 2 / 3 strided pass of the forward / backward type,
-// 4 sandwich), one workgroup each with lds bytes of LDS, in group order;
-// err[0] is cleared (there is no wait to fail).
-// One launch of the level form: items [first, first + count) of one pass
-// level (`level`), all of transform length L and pass kind `kind`.
-struct BatchGroup {
-  int first, count, L, kind, lds, level;
-};
-// The launch of one group (its items' err flag: err, may be null).
 hipError_t launch_batched_group(int xf, const PassArgs* passes, const BatchItem* items,
-                                const BatchGroup& g, int* err, hipStream_t s);
-// Resident workgroups per CU of the persistent kernel with `lds` bytes of LDS.
-int batched_blocks_per_cu(int lds, int prec, int mode);
+                                const BatchGroup& g, hipStream_t s);
 }  // namespace hp

@@ -288,7 +288,10 @@ __device__ __attribute__((noinline)) void fft_stage_prime(LTile<T> Z, HP_LDS typ
 // A backward FFT is this one with real and imaginary parts exchanged on both
 // sides, which the loads and stores around it do.
 template <typename T, int MODE>
-__device__ __forceinline__ void fft_lds(LTile<T> Z, HP_LDS typename V2<T>::t* wR, const PassArgs& a) {
+__device__ __forceinline__ void fft_lds(LTile<T> Z, HP_LDS typename V2<T>::t* wR, unsigned char* smem,
+                                        const PassArgs& a) {
+  HP_LDS char* lds0 = (HP_LDS char*)smem;
+  (void)lds0;
   constexpr int ME = Maxe<T, MODE>::v;
   const GC<T> tw = glb<T>(a.tw);
   const int L = a.L;
@@ -315,7 +318,9 @@ __device__ __forceinline__ void fft_lds(LTile<T> Z, HP_LDS typename V2<T>::t* wR
           if (R == 16) { fft_stage<T, 16, ME>(Z, L, Ns, tw); break; }
         }
         if constexpr (MODE == GM_BIG) {
-          if (!a.prime_table) { fft_stage_prime<T, ME, false>(Z, wR, L, R, Ns, tw); break; }
+          // (wR: the LDS after the tiles; no table where that is too short)
+          const int room = (a.lds_bytes - (int)((HP_LDS char*)wR - lds0)) / (int)sizeof(C2<T>);
+          if (room < R) { fft_stage_prime<T, ME, false>(Z, wR, L, R, Ns, tw); break; }
         }
         if constexpr (MODE != GM_SMALL) fft_stage_prime<T, ME, true>(Z, wR, L, R, Ns, tw);
         break;
@@ -711,7 +716,7 @@ __device__ __forceinline__ void oneway(const PassArgs& a, unsigned char* smem, c
   else if (x == X_C2R) load_half<T>(Z, a.in[field], a, t);
   else load_real<T>(Z, a.in[field], x, a, t, has_face_terms(a));
   __syncthreads();
-  fft_lds<T, MODE>(Z, Z.z + (size_t)a.L * Z.S, a);
+  fft_lds<T, MODE>(Z, Z.z + (size_t)a.L * Z.S, smem, a);
   store_out<T>(Z, x, a.out[field], a, t);
 }
 
@@ -751,7 +756,7 @@ __device__ __forceinline__ void sandwich_r2r(const PassArgs& a, unsigned char* s
   HP_LDS typename V2<T>::t* wR = Z.z + (size_t)a.L * Z.S;
   load_real<T>(Z, a.in[field], a.xf, a, t, has_face_terms(a));
   __syncthreads();
-  fft_lds<T, MODE>(Z, wR, a);
+  fft_lds<T, MODE>(Z, wR, smem, a);
   switch (a.xf) {
     case X_DST1: multiply_r2r<T, X_DST1, X_DST1>(Z, a, t); break;
     case X_DST2: multiply_r2r<T, X_DST2, X_DST3>(Z, a, t); break;
@@ -760,7 +765,7 @@ __device__ __forceinline__ void sandwich_r2r(const PassArgs& a, unsigned char* s
     default: multiply_r2r<T, X_DHT, X_DHT>(Z, a, t); break;
   }
   __syncthreads();
-  fft_lds<T, MODE>(Z, wR, a);
+  fft_lds<T, MODE>(Z, wR, smem, a);
   store_out<T>(Z, a.xb, a.out[field], a, t);
 }
 
@@ -788,7 +793,7 @@ __device__ __forceinline__ void sandwich_c2c(const PassArgs& a, unsigned char* s
     if (pair) load_real<T>(dst, src, X_PAIR_F, a, t, false);
     else load_c2c<T>(dst, src, a, t, false);
     __syncthreads();
-    fft_lds<T, MODE>(dst, wR, a);
+    fft_lds<T, MODE>(dst, wR, smem, a);
   };
   // element e of a tile -> column f, bin m (rows first: the multipliers' rows
   // are contiguous along m)
@@ -930,7 +935,7 @@ __device__ __forceinline__ void sandwich_c2c(const PassArgs& a, unsigned char* s
         W.put(z, {v.im, v.re});
       });
       __syncthreads();
-      fft_lds<T, MODE>(W, wR, a);
+      fft_lds<T, MODE>(W, wR, smem, a);
       store_out<T>(W, xb, a.out[a.n_in + d], a, t);
       __syncthreads();
     }
@@ -942,7 +947,7 @@ __device__ __forceinline__ void sandwich_c2c(const PassArgs& a, unsigned char* s
     __syncthreads();
   }
   for (int c = 0; c < nS; ++c) {
-    fft_lds<T, MODE>(tile(c), wR, a);
+    fft_lds<T, MODE>(tile(c), wR, smem, a);
     store_out<T>(tile(c), xb, a.out[fb + c], a, t);
   }
 }
@@ -1053,8 +1058,9 @@ bool general_fits(const PassArgs& a, int prec) {
 
 // LDS bytes of a general pass of tile width P: its FFT tiles (nS coupled
 // fields and a work tile where derivatives couple them) and the table of the
-// largest prime stage (left out, a.prime_table = 0, where it would not fit).
-int general_lds_bytes(PassArgs& a, int P, int prec) {
+// largest prime stage (left out where it would not fit; the kernel sees the
+// room that is left).
+int general_lds_bytes(const PassArgs& a, int P, int prec) {
   const bool cplx = a.xf == X_C2C_F || a.xf == X_C2C_B;
   const int nf = cplx ? P : P / 2;
   int tiles = 1;
@@ -1066,19 +1072,12 @@ int general_lds_bytes(PassArgs& a, int P, int prec) {
   for (int s = 0; s < a.nstage; ++s)
     if (a.radix[s] > max_radix(prec)) table = std::max(table, a.radix[s]);
   const long long cs = prec == 0 ? 8 : 16, data = (long long)tiles * a.L * tile_row(nf) * cs;
-  a.prime_table = table > 0;
-  if (a.big && data + table * cs > 160 * 1024) {
-    a.prime_table = 0;
-    table = 0;
-  }
+  if (a.big && data + table * cs > 160 * 1024) table = 0;
   return (int)std::min<long long>(data + table * cs, 1 << 30);
 }
 
 hipError_t launch_pass(const PassArgs& a, int prec, int grid_y, hipStream_t s) {
-  PassArgs chk = a;
-  if (!general_fits(a, prec) || general_lds_bytes(chk, a.P, prec) > a.lds_bytes ||
-      chk.prime_table != a.prime_table)
-    return hipErrorInvalidValue;
+  if (!general_fits(a, prec) || general_lds_bytes(a, a.P, prec) > a.lds_bytes) return hipErrorInvalidValue;
   const int tiles = ((a.Np + a.P - 1) / a.P) * a.No;
   dim3 grid(tiles, grid_y);
   const int mode = gen_mode(a, prec);
@@ -1087,117 +1086,49 @@ hipError_t launch_pass(const PassArgs& a, int prec, int grid_y, hipStream_t s) {
   return hipGetLastError();
 }
 
-// ------------------------------------------------------- batched persistent
-// Every workgroup pulls items (one tile of one pass of one problem) from a
-// global queue in order, waits until the pass it depends on is complete,
-// runs the tile with the same device code as the one-launch-per-pass path and
-// publishes its completion.  Items are ordered pass by pass, so a workgroup
-// only ever waits for items that running workgroups took earlier.
-__global__ void k_zero_counters(unsigned* c, int n, int* err) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) c[i] = 0u;
-  if (blockIdx.x == 0 && threadIdx.x == 0) err[0] = 0;
-}
-
+// ------------------------------------------------------------ batched passes
+// One pass level of a batched plan (the same pass of every problem, any
+// lengths): one workgroup per item, consecutive tiles of one problem's pass,
+// with the device code of the one-launch-per-pass path.  Launch boundaries
+// order the levels.
 template <typename T, int MODE>
-__global__ void __launch_bounds__(kThreads) k_batched(const PassArgs* passes, const BatchItem* items,
-                                                      int nitems, unsigned* counters, int* err) {
+__global__ void __launch_bounds__(kThreads) k_batched(const PassArgs* passes, const BatchItem* items) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_item, s_ok;
-  // The item index and the wait result are read back with readfirstlane so
-  // that the compiler sees them as uniform: the loop then has one uniform
-  // exit and every barrier is reached by all threads in every iteration.
-  for (;;) {
-    if (threadIdx.x == 0) s_item = (int)atomicAdd(&counters[0], 1u);
-    __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(s_item);
-    if (it >= nitems) break;
-    const BatchItem bi = items[it];
-    if (threadIdx.x == 0) {
-      int ok = 1;
-      if (bi.dep >= 0) {
-        unsigned spins = 0;
-        while (__hip_atomic_load(&counters[1 + bi.dep], __ATOMIC_ACQUIRE,
-                                 __HIP_MEMORY_SCOPE_AGENT) < (unsigned)bi.need) {
-          __builtin_amdgcn_s_sleep(2);
-          // bounded wait: report and skip (also stop at once if another wait failed)
-          if (++spins > (1u << 22) ||
-              __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-            ok = 0;
-            atomicExch(err, 1);
-            break;
-          }
-        }
-      }
-      s_ok = ok;
-    }
-    __syncthreads();
-    const int ok = __builtin_amdgcn_readfirstlane(s_ok);
-    // acquire: the tiles written by the workgroups that completed the pass
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    if (ok) {
-      const PassArgs& a = passes[bi.pass];
-      const int tiles_p = (a.Np + a.P - 1) / a.P;
-      for (int k = 0; k < bi.ntile; ++k) {
-        const int tile = bi.tile + k;
-        Tile t;
-        t.o = tile / tiles_p;
-        t.p0 = (tile - t.o * tiles_p) * a.P;
-        t.np = min(a.P, a.Np - t.p0);
-        if (a.kind == PK_ONEWAY) oneway<T, MODE>(a, smem, t, 0);
-        else sandwich_r2r<T, MODE>(a, smem, t, 0);
-        __syncthreads();  // LDS reuse by the next tile
-      }
-    }
-    // release: this item's stores before its tiles are counted
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    if (threadIdx.x == 0)
-      __hip_atomic_fetch_add(&counters[1 + bi.pass], (unsigned)bi.ntile, __ATOMIC_RELEASE,
-                             __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
+  const BatchItem bi = items[blockIdx.x];
+  const PassArgs& a = passes[__builtin_amdgcn_readfirstlane(bi.pass)];
+  const int tiles_p = (a.Np + a.P - 1) / a.P;
+  const int n = __builtin_amdgcn_readfirstlane(bi.ntile);
+  for (int k = 0; k < n; ++k) {
+    const int tile = bi.tile + k;
+    Tile t;
+    t.o = tile / tiles_p;
+    t.p0 = (tile - t.o * tiles_p) * a.P;
+    t.np = min(a.P, a.Np - t.p0);
+    if (a.kind == PK_ONEWAY) oneway<T, MODE>(a, smem, t, 0);
+    else sandwich_r2r<T, MODE>(a, smem, t, 0);
+    __syncthreads();  // LDS reuse by the next tile
   }
-}
-
-template <typename T>
-static hipError_t batched_occupancy(int* n, int lds, int mode) {
-  if (mode == GM_BIG) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_batched<T, GM_BIG>, kThreads, lds);
-  if (mode == GM_PRIME) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_batched<T, GM_PRIME>, kThreads, lds);
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_batched<T, GM_SMALL>, kThreads, lds);
-}
-
-int batched_blocks_per_cu(int lds, int prec, int mode) {
-  int n = 0;
-  const hipError_t e = prec == 0 ? batched_occupancy<float>(&n, lds, mode) : batched_occupancy<double>(&n, lds, mode);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    return 1;
-  }
-  return n > 0 ? n : 1;
 }
 
 template <typename T, int MODE>
-static void launch_batched_t(const PassArgs* passes, const BatchItem* items, int nitems,
-                             unsigned* counters, int* err, int grid, int lds, hipStream_t s) {
+static void launch_batched_t(const PassArgs* passes, const BatchItem* items, int count, int lds, hipStream_t s) {
   allow_lds<k_batched<T, MODE>>();
-  hipLaunchKernelGGL((k_batched<T, MODE>), dim3(grid), dim3(kThreads), lds, s, passes, items, nitems,
-                     counters, err);
+  hipLaunchKernelGGL((k_batched<T, MODE>), dim3(count), dim3(kThreads), lds, s, passes, items);
 }
 
 template <typename T>
-static void launch_batched_mode(const PassArgs* passes, const BatchItem* items, int nitems, unsigned* counters,
-                                int* err, int grid, int lds, int mode, hipStream_t s) {
-  if (mode == GM_BIG) launch_batched_t<T, GM_BIG>(passes, items, nitems, counters, err, grid, lds, s);
-  else if (mode == GM_PRIME) launch_batched_t<T, GM_PRIME>(passes, items, nitems, counters, err, grid, lds, s);
-  else launch_batched_t<T, GM_SMALL>(passes, items, nitems, counters, err, grid, lds, s);
+static void launch_batched_mode(const PassArgs* passes, const BatchItem* items, int count, int lds, int mode,
+                                hipStream_t s) {
+  if (mode == GM_BIG) launch_batched_t<T, GM_BIG>(passes, items, count, lds, s);
+  else if (mode == GM_PRIME) launch_batched_t<T, GM_PRIME>(passes, items, count, lds, s);
+  else launch_batched_t<T, GM_SMALL>(passes, items, count, lds, s);
 }
 
-hipError_t launch_batched(const PassArgs* passes, const BatchItem* items, int nitems,
-                          unsigned* counters, int ncounters, int* err, int grid, int lds,
-                          int prec, int mode, hipStream_t s) {
-  hipLaunchKernelGGL(k_zero_counters, dim3(1 + ncounters / 256), dim3(256), 0, s, counters,
-                     ncounters, err);
-  if (prec == 0) launch_batched_mode<float>(passes, items, nitems, counters, err, grid, lds, mode, s);
-  else launch_batched_mode<double>(passes, items, nitems, counters, err, grid, lds, mode, s);
+hipError_t launch_batched(const PassArgs* passes, const BatchItem* items, const BatchGroup& g, int prec,
+                          int mode, hipStream_t s) {
+  if (g.count <= 0) return hipSuccess;
+  if (prec == 0) launch_batched_mode<float>(passes, items + g.first, g.count, g.lds, mode, s);
+  else launch_batched_mode<double>(passes, items + g.first, g.count, g.lds, mode, s);
   return hipGetLastError();
 }
 

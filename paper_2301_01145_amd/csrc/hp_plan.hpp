@@ -82,21 +82,20 @@ struct hp_plan_s {
   size_t ws_bytes = 0;
   int alloc_count = 0;
   int fail_alloc_at = -1;
-  // batched persistent-kernel state
+  // batched plans: pass table and work items on the device
   void* batch_probs = nullptr;
   void* batch_items = nullptr;
-  unsigned* batch_counters = nullptr;
-  int batch_nitems = 0, batch_ncounters = 0, batch_grid = 0, batch_lds = 0;
-  int batch_big = 0;  // register budget of the persistent kernel (PassArgs.big)
-  int batch_gen = 0;  // general passes: kernel mode of the persistent launch (general_mode)
-  // kernels of the batched solve: 0 = general passes in one persistent launch
-  // (k_batched); 1 = wavefront tile bodies in one persistent launch
-  // (k_batched_wf, forward type batch_xf); 2 = the wavefront tile bodies as
-  // one launch per pass level (k_batched_level).  batch_mode -1 = the
-  // planner's choice (1 where every pass allows it, else 0); 0, 1, 2 chosen
-  // by the autotuner (1 and 2 fall back to 0 where not allowed)
+  int batch_nitems = 0, batch_lds = 0;
+  int batch_big = 0;  // general passes: register budget of the launches (PassArgs.big)
+  int batch_gen = 0;  // general passes: kernel mode of the launches (general_mode)
+  // kernels of the batched solve: 0 = general passes, one launch per pass
+  // level; 1 = wavefront tile bodies, one launch per pass level (forward type
+  // batch_xf); 2 = wavefront tile bodies, one launch per pass level and
+  // transform length.  batch_mode -1 = the planner's choice (1 where every
+  // pass allows it, else 0); 0, 1, 2 chosen by the autotuner (1 and 2 fall
+  // back to 0 where not allowed)
   int batch_wf = 0, batch_xf = 0, batch_mode = -1;
-  std::vector<hp::BatchGroup> batch_groups;  // mode 2: launches (level, length) in order
+  std::vector<hp::BatchGroup> batch_groups;  // launches in order
   // mode 2 under stream capture: the groups of one level run on forked
   // streams (default priority), joined by events before the next level; fork
   // event and join events per level, created at setup

@@ -10,8 +10,9 @@
 //     and both register budgets;
 //   * wavefront passes: tile widths of 8 and 16 pencils and, for the x and
 //     backward-y passes, both output-tile schemes;
-//   * batched plans: the persistent kernel's tile bodies (wavefront or general
-//     passes) and 1, 2, 4 or 8 tiles per work item.
+//   * batched plans: the tile bodies (wavefront or general passes), the launches
+//     of a level (one, or one per transform length) and 1, 2, 4 or 8 tiles per
+//     work item.
 // A configuration replaces the planner's default only when it is at least 3%
 // faster, and the choices are kept only when the whole solve is faster with
 // them (batched plans: the combination of pass configurations and work-item
@@ -155,8 +156,8 @@ struct Tuner {
       std::vector<int> widths;
       for (int w : {a.P / 2, a.P, a.P * 2})
         if (w >= 1 && std::find(widths.begin(), widths.end(), w) == widths.end()) widths.push_back(w);
-      // a batched plan runs every pass in one kernel whose register budget
-      // and LDS are the largest of its passes: stay within those
+      // a batched plan runs the passes of a level in one kernel whose register
+      // budget and LDS are the largest of its passes: stay within those
       const int big0 = p->batched ? p->batch_big : 0, big1 = p->batched ? p->batch_big : 1;
       for (const auto& o : radix_orders(a.L))
         for (int w : widths)
@@ -324,9 +325,9 @@ struct Tuner {
     std::set<unsigned long long> done;
     for (auto& P : p->probs) HP_TRY_T(tune_list(P, done));
     if (p->batched) {
-      // whole-batch timing decides between the kernels of the persistent
-      // launch (wavefront tile bodies where the batch allows them; the general
-      // passes with default or tuned configurations) and its work-item size
+      // whole-batch timing decides between the kernels of a level (wavefront
+      // tile bodies where the batch allows them; the general passes with
+      // default or tuned configurations) and the work-item size
       const std::map<unsigned long long, Tune> per_pass = p->tuned;
       const int npass = p->tuned_passes;
       const int def_mode = p->batch_wf;
