@@ -183,7 +183,8 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig(const PassArgs
   T* R = (T*)slot;  // the pair's reals: a at R[0..n), b at R[n..2n)
   const int pairs_p = (a.Np + 1) / 2;
   const long long total = (long long)pairs_p * a.No;
-  const long long pr = ((long long)blockIdx.x * kR2RContigWaves + wave) * PPW + qq;
+  const int blk = off_lines(a, sizeof(T), sizeof(T)) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const long long pr = ((long long)blk * kR2RContigWaves + wave) * PPW + qq;
   const bool valid = pr < total;
   const int o = valid ? (int)(pr / pairs_p) : 0;
   const int pa = valid ? 2 * (int)(pr % pairs_p) : 0;
@@ -263,7 +264,7 @@ __global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
   T* tile = (T*)(slots + W * PPW * slot_len(L));
   const int tiles_p = (a.Np + P - 1) / P;
   const int ntiles = tiles_p * a.No;
-  int t = blockIdx.x;
+  int t = off_lines(a, sizeof(T), sizeof(T)) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   if (t >= ntiles) return;  // whole workgroup
   for (int m = threadIdx.x; m < L; m += NT) tw[m] = ((const C2<T>*)a.tw)[m];
   if (a.qtw)

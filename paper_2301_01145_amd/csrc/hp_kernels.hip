@@ -339,11 +339,15 @@ struct Tile {
   int o, p0, np;
 };
 
+template <typename T>
 __device__ __forceinline__ Tile tile_of(const PassArgs& a) {
   const int tiles_p = (a.Np + a.P - 1) / a.P;
+  const int ei = (int)sizeof(T) * (xform_complex_in(a.xf) || a.xf == X_C2R ? 2 : 1);
+  const int eo = (int)sizeof(T) * (xform_complex_in(a.xf) || a.xf == X_R2C ? 2 : 1);
+  const int b = off_lines(a, ei, eo) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   Tile t;
-  t.o = blockIdx.x / tiles_p;
-  t.p0 = (blockIdx.x - t.o * tiles_p) * a.P;
+  t.o = b / tiles_p;
+  t.p0 = (b - t.o * tiles_p) * a.P;
   t.np = min(a.P, a.Np - t.p0);
   return t;
 }
@@ -954,7 +958,17 @@ __device__ __forceinline__ void sandwich_c2c(const PassArgs& a, unsigned char* s
 
 // The pass descriptor where the launch put it (the kernels' only argument).
 // Read as a parameter it is copied to scratch memory once its uses are many.
+// One word of every 64-byte line of it is read at once first: the fields are
+// read where they are needed, and each line's first read would be a miss of
+// the scalar cache of its own in the chain of a workgroup.
 __device__ __forceinline__ const PassArgs& kernel_args() {
+  typedef const volatile __attribute__((address_space(4))) int* cptr;
+  const cptr w = (cptr)__builtin_amdgcn_kernarg_segment_ptr();
+  int x[(sizeof(PassArgs) + 63) / 64];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(x) / sizeof(x[0]); ++i) x[i] = w[16 * i];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(x) / sizeof(x[0]); ++i) asm volatile("" ::"s"(x[i]));
   return *(const PassArgs*)(const __attribute__((address_space(4))) PassArgs*)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
@@ -962,21 +976,21 @@ template <typename T, int MODE>
 __global__ void __launch_bounds__(kThreads) k_oneway(const PassArgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const PassArgs& a = kernel_args();
-  oneway<T, MODE>(a, smem, tile_of(a), blockIdx.y);
+  oneway<T, MODE>(a, smem, tile_of<T>(a), blockIdx.y);
 }
 
 template <typename T, int MODE>
 __global__ void __launch_bounds__(kThreads) k_sandwich_c2c(const PassArgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const PassArgs& a = kernel_args();
-  sandwich_c2c<T, MODE>(a, smem, tile_of(a));
+  sandwich_c2c<T, MODE>(a, smem, tile_of<T>(a));
 }
 
 template <typename T, int MODE>
 __global__ void __launch_bounds__(kThreads) k_sandwich_r2r(const PassArgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const PassArgs& a = kernel_args();
-  sandwich_r2r<T, MODE>(a, smem, tile_of(a), blockIdx.y);
+  sandwich_r2r<T, MODE>(a, smem, tile_of<T>(a), blockIdx.y);
 }
 
 template <auto K>
