@@ -162,12 +162,12 @@ bool choose_radices(PassArgs& a, int prec) {
     for (int i = 0; i < nbig; ++i) rest /= big[i];
   }
   int best[kMaxStages], nbest = -1, sum_best = 0, cur[kMaxStages];
+  const bool cplx = a.xf == X_C2C_F || a.xf == X_C2C_B;
   auto fits = [&](int n) {
-    PassArgs t = a;
-    t.nstage = nbig + n;
-    for (int i = 0; i < nbig; ++i) t.radix[i] = big[i];
-    for (int i = 0; i < n; ++i) t.radix[nbig + i] = cur[i];
-    return general_fits(t, prec);
+    int all[kMaxStages];
+    for (int i = 0; i < nbig; ++i) all[i] = big[i];
+    for (int i = 0; i < n; ++i) all[nbig + i] = cur[i];
+    return stages_fit(a.L, cplx ? a.P : a.P / 2, all, nbig + n, a.big, prec);
   };
   auto search = [&](auto&& self, int r, int limit, int n, int sum) -> void {
     if (r == 1) {
@@ -692,7 +692,6 @@ hp_status setup_problem(hp_plan p, Problem& P) {
                                     M, P.h[u], P.norm * P.h[u] / (double)M, 1, p->prec, p->stream));
       }
     }
-    if (P.nder && P.free_axis < 0) HP_TRY(dev_alloc(p, count_elems(P.nout, P.nd) * es, &P.grad_s));
     // second terms of DIV (d_y psi_y, d_z psi_z) and of the 3D curl, added
     // into the outputs at the end of the solve
     const int ntmp = d.diff == HP_D_DIV ? 2 : (d.diff == HP_D_CURL && P.nd == 3 ? 3 : 0);
@@ -872,7 +871,7 @@ unsigned long long general_key(const PassArgs& a, int prec, int want, int minP, 
                          a.n,      a.nin,     a.nout,    a.Np,      a.No,      a.in_jfast,
                          a.out_jfast, a.in_sj, a.in_sp,  a.in_so,   a.out_sj,  a.out_sp,
                          a.out_so, a.n_in,    a.n_out,   a.diff,    a.mult,    want,
-                         minP,     lds_kind};
+                         minP,     lds_kind,  a.nfan,    a.fan[0].deriv != nullptr, a.fan[0].basis};
   return tune_hash(v, (int)(sizeof(v) / sizeof(v[0])));
 }
 
@@ -914,7 +913,20 @@ hp_status finish_pass(hp_plan p, PassArgs& a, int want, int minP, long long lds_
       return HP_OK;
     }
   }
-  HP_TRY(finish_pass_with(p, a, want, minP, nullptr));
+  // the default's tile, chosen once per signature (every solve builds its passes)
+  auto c = p->tiles.find(key);
+  if (c != p->tiles.end()) {
+    const PassArgs& t = c->second;
+    a.P = t.P;
+    a.big = t.big;
+    a.lds_bytes = t.lds_bytes;
+    a.nstage = t.nstage;
+    for (int s = 0; s < t.nstage; ++s) a.radix[s] = t.radix[s];
+    HP_TRY(twiddles(p, a.L, &a.tw));
+  } else {
+    HP_TRY(finish_pass_with(p, a, want, minP, nullptr));
+    p->tiles[key] = a;
+  }
   a.tune_key = key;
   return HP_OK;
 }
@@ -935,7 +947,7 @@ bool bounded_fast_ok(hp_plan p, const Problem& P, const int* L) {
     ++bounded;
     if (L[a] < 64 || L[a] > 512 || wf_r0(L[a]) <= 0) return false;
     for (int k = FAST_R2R_C; k <= FAST_R2R_SW; ++k) {
-      const int lds = r2r_lds_bytes(k, L[a], P.n[a], p->prec);
+      const int lds = r2r_lds_bytes(k, L[a], P.n[a], 0, p->prec);
       if (lds <= 0 || lds > 160 * 1024) return false;
     }
   }
@@ -944,23 +956,26 @@ bool bounded_fast_ok(hp_plan p, const Problem& P, const int* L) {
 
 // Switch a general bounded pass (same descriptor) to its wavefront kernel.
 hp_status to_fast_r2r(hp_plan p, PassArgs& a) {
-  if (a.fast == FAST_GRAD_PREP || a.fast == FAST_ADD) return HP_OK;
+  if (a.fast == FAST_ADD || a.fast == FAST_FILL) return HP_OK;
   // Hartley passes and the free axis's Green's-row sandwich: general kernels
   if (a.xf == X_DHT || (a.kind == PK_SANDWICH && a.xb == X_DHT)) return HP_OK;
-  if (a.mult == M_GREEN_ROWS || a.mult == M_GREEN_ROWS_ODD || a.xf == X_PAIR_F) return HP_OK;
+  if (a.mult == M_GREEN_ROWS || a.xf == X_PAIR_F) return HP_OK;
   const bool contig = a.kind == PK_ONEWAY && a.in_jfast && a.out_jfast;
   bool faces = false;
   for (int ax = 0; ax < 3; ++ax) faces |= a.face[ax][0] != nullptr || a.face[ax][1] != nullptr;
   if (faces && !contig) return HP_OK;  // boundary terms: contiguous passes only
   const int kind = a.kind == PK_SANDWICH ? FAST_R2R_SW : (contig ? FAST_R2R_C : FAST_R2R_S);
-  const int lds = r2r_lds_bytes(kind, a.L, a.n, p->prec);
+  int nd = 0;
+  for (int i = 0; i < a.nfan; ++i)
+    if (a.fan[i].deriv) nd = std::max(nd, a.fan[i].nd);
+  const int lds = r2r_lds_bytes(kind, a.L, a.n, nd, p->prec);
   if (lds <= 0 || lds > 160 * 1024) return HP_OK;  // stays on the general kernel
   a.fast = kind;
   const void* tw;
   HP_TRY(fast_twiddles(p, a.L, &tw));
   a.tw = tw;
   a.P = r2r_tile(p->prec);
-  a.lds_bytes = r2r_lds_bytes(a.fast, a.L, a.n, p->prec);
+  a.lds_bytes = lds;
   return HP_OK;
 }
 
@@ -1010,6 +1025,46 @@ std::vector<DerivTerm> derivative_terms(const Problem& P) {
   return terms;
 }
 
+// Boundary nodes of a solve (launches of up to kMaxFill arrays, after the
+// transforms and before second terms are added): psi's on REGULAR Dirichlet
+// axes (the face values), and the nodes of the series derivatives that their
+// transforms leave out, all 0: an array differentiated along g has no nodes on
+// the Dirichlet faces of the other axes (psi is 0 there) nor on the faces of a
+// REGULAR Neumann axis g (the normal derivative); NABLA's are psi's.
+void boundary_fill(const Problem& P, std::vector<PassRec>& out) {
+  if (P.d.grid != HP_REGULAR) return;
+  const int dmask = dreg_axes(P.d);
+  PassRec r{PassArgs{}, 1};
+  r.a.fast = FAST_FILL;
+  r.a.Np = r.a.No = 1;
+  r.bytes = 0.0;  // surfaces: not in the byte model
+  r.fill.ndim = P.nd;
+  for (int a = 0; a < 3; ++a) r.fill.N[a] = a < P.nd ? P.nout[a] : 1;
+  auto add = [&](void* dst, int axes, int comp) {
+    if (!axes) return;
+    FillArgs& f = r.fill;
+    f.out[f.nf] = dst;
+    f.axes[f.nf] = axes;
+    for (int a = 0; a < 3; ++a)
+      for (int s = 0; s < 2; ++s)
+        f.face[f.nf][a][s] = comp >= 0 && P.d.inhomogeneous && a < P.nd ? P.face[a][s][comp] : nullptr;
+    if (++f.nf == kMaxFill) {
+      out.push_back(r);
+      f.nf = 0;
+    }
+  };
+  for (int c = 0; c < P.ncomp; ++c) add(P.out[c], dmask, c);
+  for (const DerivTerm& t : derivative_terms(P)) {
+    int axes = dmask;
+    if (t.axis >= 0) {
+      axes &= ~(1 << t.axis);
+      if (axis_bc(P.d, t.axis) == HP_NEUMANN) axes |= 1 << t.axis;
+    }
+    add(t.dst, axes, -1);
+  }
+  if (r.fill.nf > 0) out.push_back(r);
+}
+
 // DIV / 3D CURL: the second terms added into the outputs (elementwise)
 void add_second_terms(const Problem& P, size_t es, std::vector<PassRec>& out) {
   if (P.d.inhomogeneous) return;
@@ -1024,8 +1079,7 @@ void add_second_terms(const Problem& P, size_t es, std::vector<PassRec>& out) {
     a.in[1] = t1;
     long long cnt = 1;
     for (int b = 0; b < P.nd; ++b) cnt *= P.nout[b];
-    a.gp_ext[0] = (int)cnt;
-    a.gp_ext[1] = a.gp_ext[2] = 1;
+    a.n_add = cnt;
     PassRec r{a, 1};
     r.bytes = (double)cnt * (double)es * (t1 ? 4.0 : 3.0);
     out.push_back(r);
@@ -1033,6 +1087,107 @@ void add_second_terms(const Problem& P, size_t es, std::vector<PassRec>& out) {
   if (P.d.diff == HP_D_DIV) add_into(P.der[0], P.dtmp[0], P.dtmp[1]);
   if (P.d.diff == HP_D_CURL && P.nd == 3)
     for (int c = 0; c < 3; ++c) add_into(P.der[c], P.dtmp[c], nullptr);
+}
+
+// ------------------------------------------------- series derivatives (fan)
+// An array of a solve with series derivatives on its way back to space: psi,
+// or a derivative along an axis already done.  Its active view spans len[b]
+// points of axis b from off[b] of the output array.
+struct FanField {
+  void* base;
+  int off[3], len[3];
+};
+
+FanField psi_field(const Problem& P, int comp) {
+  FanField f{P.out[comp], {0, 0, 0}, {1, 1, 1}};
+  const int dmask = dreg_axes(P.d);
+  for (int b = 0; b < P.nd; ++b) { f.off[b] = (dmask >> b) & 1; f.len[b] = P.n[b]; }
+  return f;
+}
+
+void* fan_view(const FanField& f, const long long* ws, size_t es) {
+  long long vo = 0;
+  for (int b = 0; b < 3; ++b) vo += (long long)f.off[b] * ws[b];
+  return (void*)((char*)f.base + vo * (long long)es);
+}
+
+// The derivative along bounded axis g of psi's series (backward type xb): its
+// view in `dst` and the job's derivative fields.  DST-I coefficients give a
+// cosine series on the n + 2 nodes, DCT-I ones a sine series on the n - 2
+// interior nodes, the staggered types each other's on the same points, a
+// Hartley series one with mirrored indices.
+FanField fan_derivative(const Problem& P, int comp, int g, void* dst, double sign, FanJob& q) {
+  FanField f = psi_field(P, comp);
+  f.base = dst;
+  const int bc = axis_bc(P.d, g);
+  const bool dir = bc == HP_DIRICHLET, reg = P.d.grid == HP_REGULAR;
+  q.nd = P.n[g];
+  if (bc == HP_PERIODIC) {
+    q.xd = X_DHT;
+    q.basis = FB_HARTLEY;
+    q.shift = 0;
+    q.scale = sign * 2.0 * M_PI / P.len[g];
+  } else {
+    if (dir && reg) { q.xd = X_DCT1; q.nd = P.n[g] + 2; f.off[g] = 0; }
+    else if (dir) q.xd = X_DCT3;
+    else if (reg) { q.xd = X_DST1; q.nd = P.n[g] - 2; f.off[g] = 1; }
+    else q.xd = X_DST3;
+    f.len[g] = q.nd;
+    q.basis = dir ? FB_SINE : FB_COSINE;
+    q.shift = dir ? -1 : 1;
+    q.scale = sign * (dir ? 1.0 : -1.0) * M_PI / P.len[g];
+  }
+  return f;
+}
+
+// NABLA's second sandwich output: psi's own series times -sum_b w_b^2.
+FanField fan_laplacian(const Problem& P, int comp, int xb, void* dst, double sign, PassArgs& a, FanJob& q) {
+  FanField f = psi_field(P, comp);
+  f.base = dst;
+  q.xd = xb;
+  q.nd = a.n;
+  q.shift = 0;
+  q.basis = FB_LAP;
+  q.scale = sign;
+  for (int b = 0; b < 3; ++b) {
+    const int bc = b < P.nd ? axis_bc(P.d, b) : HP_NEUMANN;
+    a.basis[b] = bc == HP_PERIODIC ? FB_HARTLEY : (bc == HP_DIRICHLET ? FB_SINE : FB_COSINE);
+    a.kc[b] = b < P.nd ? (bc == HP_PERIODIC ? 2.0 : 1.0) * M_PI / P.len[b] : 0.0;
+  }
+  return f;
+}
+
+// The jobs of a backward fan pass along axis c (type xb): every field of the
+// component as it is, and psi's derivative along c into a new field.
+hp_status fan_pass(hp_plan p, const Problem& P, int comp, PassArgs& a, int c, int xb, const DerivTerm* t,
+                   const long long* ws, std::vector<FanField>& fields) {
+  if ((int)fields.size() > kMaxFan) return fail(p, HP_E_UNSUPPORTED, "too many derivative arrays in one pass");
+  a.nfan = (int)fields.size();
+  for (int i = 0; i < a.nfan; ++i) {
+    const FanField& f = fields[i];
+    FanJob& q = a.fan[i];
+    q.in = q.plain = fan_view(f, ws, p->es);
+    q.Np = f.len[a.ax_p];
+    q.No = a.ax_o >= 0 ? f.len[a.ax_o] : 1;
+    q.n = f.len[c];
+    q.xp = xb;
+  }
+  if (t) {
+    FanField f = fan_derivative(P, comp, c, t->dst, t->sign, a.fan[0]);
+    a.fan[0].deriv = fan_view(f, ws, p->es);
+    fields.push_back(f);
+  }
+  return HP_OK;
+}
+
+// Model bytes of a fan pass: every array read once, every output written once.
+double fan_bytes(const PassArgs& a, size_t es) {
+  double b = 0.0;
+  for (int i = 0; i < a.nfan; ++i) {
+    const FanJob& q = a.fan[i];
+    b += (double)q.Np * q.No * (2.0 * q.n + (q.deriv ? q.nd : 0));
+  }
+  return b * (double)es;
 }
 
 hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
@@ -1074,153 +1229,35 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
   auto set_faces = [&](PassArgs& a, int comp) { fill_face_terms(P, comp, a); };
   (void)dreg;
   const int last = nd - 1;
-  // Gradient (homogeneous Dirichlet / Neumann).  The passes of psi are
-  // unchanged.  d/dx_0: the forward pass along axis 0 is done once more, out
-  // of place, so that grad_s holds the source transformed along every axis;
-  // a prep pass writes the coefficients of the derivative series (divided by
-  // the eigenvalue sum) into the output of d/dx_0, and backward passes along
-  // every axis evaluate it, with the transform of the other parity along
-  // axis 0.  d/dx_g, g > 0: psi's own array after the sandwich already holds
-  // the divided coefficients along axes 1.. (axis 0 physical), so the prep
-  // reads it and only the axes 1.. are transformed back.
-  auto grad_forward_x = [&](int comp) -> hp_status {
-    PassArgs a = base();
-    a.kind = PK_ONEWAY;
-    a.xf = xf[0];
-    a.L = L[0]; a.n = P.n[0]; a.nin = a.nout = P.n[0];
-    a.in[0] = nd == 1 ? P.in[comp] : work(comp);
-    a.out[0] = (void*)((char*)P.grad_s + woff * es);
-    a.ax_j = 0;
-    if (nd == 1) {
-      a.in_sj = a.out_sj = 1;
-      a.in_jfast = a.out_jfast = 1;
-    } else {
-      a.in_sj = a.out_sj = ws[0];
-      a.in_sp = a.out_sp = ws[last];
-      a.Np = P.n[last]; a.ax_p = last;
-      if (nd == 3) { a.in_so = a.out_so = ws[1]; a.No = P.n[1]; a.ax_o = 1; }
-    }
-    HP_TRY(finish_pass(p, a, nd == 1 ? 2 : 32, 2, 0, 1));
-    const void* q;
-    HP_TRY(quarter(p, a.n, &q));
-    a.qtw = q;
-    out.push_back({a, 1});
-    return HP_OK;
-  };
-  // derivative g from coefficients `src` (the work-view layout) into `dst`,
-  // times `sign`; `eigen`: the eigenvalue sum still has to be divided out
-  // (source transformed along every axis), else src is psi's array after the
-  // sandwich.  `lap`: NABLA instead, the sum over the axes of the second
-  // derivatives, which keeps every axis's basis (-w_b^2 per eigenfunction),
-  // from the transformed source.
-  auto grad_deriv = [&](int g, const void* src, bool eigen, void* dst, double sign,
-                        bool lap) -> hp_status {
-    const int bcg = axis_bc(d, g);
-    const bool dir = bcg == HP_DIRICHLET, reg = d.grid == HP_REGULAR, per = bcg == HP_PERIODIC;
-    // active view of the derivative output: extent len[b] from off[b]
-    int off[3] = {0, 0, 0}, len[3] = {1, 1, 1};
-    for (int b = 0; b < nd; ++b) { off[b] = (dmask >> b) & 1; len[b] = P.n[b]; }
-    int xd = 0;
-    if (lap) xd = xb[0];
-    else if (per) xd = X_DHT;  // a Hartley series stays one (index mirrored)
-    else if (dir && reg) { xd = X_DCT1; len[g] = P.n[g] + 2; off[g] = 0; }  // n + 2 nodes
-    else if (dir) xd = X_DCT3;
-    else if (reg) { xd = X_DST1; len[g] = P.n[g] - 2; off[g] = 1; }   // interior nodes
-    else xd = X_DST3;
-    {
-      PassArgs a = base();
-      a.fast = FAST_GRAD_PREP;
-      a.ax_j = lap ? -1 : g;
-      a.in[0] = src;
-      a.out[0] = dst;
-      double cnt_in = 1.0, cnt_out = 1.0;
-      for (int b = 0; b < 3; ++b) {
-        a.gp_ext[b] = b < nd ? P.nout[b] : 1;
-        a.gp_off[b] = off[b];
-        a.gp_len[b] = len[b];
-        a.gp_is[b] = a.gp_os[b] = b < nd ? ws[b] : 0;
-        a.nunk[b] = b < nd ? P.n[b] : 1;
-        a.lam[b] = eigen && b < nd ? P.lam[b] : nullptr;
-        const int bb = b < nd ? axis_bc(d, b) : HP_NEUMANN;
-        a.gp_basis[b] = bb == HP_PERIODIC ? 2 : (bb == HP_DIRICHLET ? 0 : 1);
-        a.kc[b] = lap && b < nd ? (bb == HP_PERIODIC ? 2.0 : 1.0) * M_PI / P.len[b] : 0.0;
-        if (b < nd) { cnt_in *= P.n[b]; cnt_out *= P.nout[b]; }
-      }
-      a.gp_eigen = eigen ? 1 : 0;
-      if (lap) {
-        a.diff = D_NABLA;
-        a.gp_shift = 0;
-        a.gp_scale = sign;
-      } else if (per) {
-        a.gp_shift = 0;
-        a.gp_scale = sign * 2.0 * M_PI / P.len[g];
-      } else {
-        a.gp_shift = dir ? -1 : 1;
-        a.gp_scale = sign * (dir ? 1.0 : -1.0) * M_PI / P.len[g];
-      }
-      a.norm = P.norm;
-      PassRec r{a, 1};
-      r.bytes = (cnt_in + cnt_out) * (double)es;
-      out.push_back(r);
-    }
-    long long vo = 0;
-    for (int b = 0; b < nd; ++b) vo += (long long)off[b] * ws[b];
-    void* view = (void*)((char*)dst + vo * (long long)es);
-    // axis 0 is already physical when the coefficients come from psi's array
-    for (int c = last; c >= (eigen ? 0 : 1); --c) {
-      PassArgs a = base();
-      a.kind = PK_ONEWAY;
-      a.xf = (!lap && c == g) ? xd : xb[c];
-      a.L = L[c]; a.n = len[c]; a.nin = a.nout = len[c];
-      a.in[0] = view; a.out[0] = view;
-      a.in_sj = a.out_sj = ws[c];
-      a.ax_j = c;
-      if (nd == 1) {
-        a.in_jfast = a.out_jfast = 1;
-      } else if (c == last) {
-        a.in_sp = a.out_sp = ws[last - 1]; a.Np = len[last - 1]; a.ax_p = last - 1;
-        if (nd == 3) { a.in_so = a.out_so = ws[0]; a.No = len[0]; a.ax_o = 0; }
-        a.in_jfast = a.out_jfast = 1;
-      } else {
-        a.in_sp = a.out_sp = ws[last]; a.Np = len[last]; a.ax_p = last;
-        if (nd == 3) {
-          const int o = c == 0 ? 1 : 0;
-          a.in_so = a.out_so = ws[o]; a.No = len[o]; a.ax_o = o;
-        }
-      }
-      for (int b = 0; b < 3; ++b) a.nunk[b] = b < nd ? len[b] : 0;
-      HP_TRY(finish_pass(p, a, nd == 1 ? 2 : (c == last ? 16 : 32), 2, 0, 1));
-      const void* q;
-      HP_TRY(quarter(p, a.n, &q));
-      a.qtw = q;
-      out.push_back({a, 1});
-    }
-    return HP_OK;
-  };
   const std::vector<DerivTerm> terms = derivative_terms(P);
-  // before the sandwich: the terms along axis 0 and NABLA, from the source
-  // transformed along every axis (one more forward pass along axis 0, out of place)
-  auto pre_terms = [&](int comp) -> hp_status {
-    bool any = false;
-    for (auto& t : terms) any |= t.comp == comp && t.axis <= 0;
-    if (!any) return HP_OK;
-    HP_TRY(grad_forward_x(comp));
-    const void* src = (const void*)((char*)P.grad_s + woff * es);
+  auto term_of = [&](int comp, int axis) -> const DerivTerm* {
     for (auto& t : terms)
-      if (t.comp == comp && t.axis <= 0) HP_TRY(grad_deriv(0, src, true, t.dst, t.sign, t.axis < 0));
-    return HP_OK;
-  };
-  // after the sandwich: the terms along axes 1.., from psi's array (before
-  // the backward passes change it)
-  auto post_terms = [&](int comp) -> hp_status {
-    for (auto& t : terms)
-      if (t.comp == comp && t.axis > 0) HP_TRY(grad_deriv(t.axis, work(comp), false, t.dst, t.sign, false));
-    return HP_OK;
+      if (t.comp == comp && t.axis == axis) return &t;
+    return nullptr;
   };
   // one pass per component (faces differ per component)
   for (int comp = 0; comp < P.ncomp; ++comp) {
+    // the second output of the sandwich: the derivative along axis 0, or NABLA
+    const DerivTerm* t0 = term_of(comp, 0);
+    const DerivTerm* tl = term_of(comp, -1);
+    std::vector<FanField> fields = {psi_field(P, comp)};
+    auto fan_sandwich = [&](PassArgs& a) {
+      if (!t0 && !tl) return;
+      FanJob& q = a.fan[0];
+      a.nfan = 1;
+      q.in = a.in[0];
+      q.plain = a.out[0];
+      q.Np = a.Np; q.No = a.No; q.n = a.n; q.xp = a.xb;
+      fields.push_back(tl ? fan_laplacian(P, comp, a.xb, tl->dst, tl->sign, a, q)
+                          : fan_derivative(P, comp, 0, t0->dst, t0->sign, q));
+      q.deriv = fan_view(fields.back(), ws, es);
+    };
+    auto push = [&](const PassArgs& a) {
+      PassRec r{a, 1};
+      if (a.nfan > 0) r.bytes = fan_bytes(a, es);
+      out.push_back(r);
+    };
     if (nd == 1) {
-      HP_TRY(pre_terms(comp));
       PassArgs a = base();
       a.kind = PK_SANDWICH;
       a.xf = xf[0]; a.xb = xb[0];
@@ -1230,11 +1267,12 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       a.ax_j = 0;
       a.mult = M_EIGEN; a.lam[0] = P.lam[0]; a.norm = P.norm;
       set_faces(a, comp);
+      fan_sandwich(a);
       HP_TRY(finish_pass(p, a, 2, 2, 0, 3));
       const void* q;
       HP_TRY(quarter(p, a.n, &q));
       a.qtw = q;
-      out.push_back({a, 1});
+      push(a);
       continue;
     }
     // P1: forward along the last (contiguous) axis, source + boundary terms
@@ -1277,7 +1315,6 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       out.push_back({a, 1});
       p2 = a;
     }
-    HP_TRY(pre_terms(comp));
     // P3: sandwich along axis 0
     {
       PassArgs a = base();
@@ -1293,14 +1330,40 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       a.mult = M_EIGEN;
       for (int b = 0; b < nd; ++b) a.lam[b] = P.lam[b];
       a.norm = P.norm;
+      fan_sandwich(a);
       HP_TRY(finish_pass(p, a, 32, 2, 0, 3));
       const void* q;
       HP_TRY(quarter(p, a.n, &q));
       a.qtw = q;
-      out.push_back({a, 1});
+      push(a);
     }
-    // after the sandwich: d/dx_g, g > 0, from psi's array (before P4 changes it)
-    HP_TRY(post_terms(comp));
+    // With derivatives: the backward passes along axes 1.. hold every array
+    // so far and, from psi's coefficients along that axis, its derivative.
+    bool derivs = false;
+    for (auto& t : terms) derivs |= t.comp == comp;
+    if (derivs) {
+      for (int c = 1; c <= last; ++c) {
+        PassArgs a = base();
+        a.kind = PK_ONEWAY;
+        a.xf = xb[c];
+        a.L = L[c]; a.n = P.n[c]; a.nin = a.nout = P.n[c];
+        a.in[0] = work(comp); a.out[0] = work(comp);
+        a.in_sj = a.out_sj = ws[c];
+        const int pa = c == last ? last - 1 : last, oa = nd == 3 ? 3 - c - pa : -1;
+        a.in_sp = a.out_sp = ws[pa];
+        a.Np = P.n[pa];
+        a.ax_j = c; a.ax_p = pa;
+        if (nd == 3) { a.in_so = a.out_so = ws[oa]; a.No = P.n[oa]; a.ax_o = oa; }
+        a.in_jfast = a.out_jfast = c == last ? 1 : 0;
+        HP_TRY(fan_pass(p, P, comp, a, c, xb[c], term_of(comp, c), ws, fields));
+        HP_TRY(finish_pass(p, a, c == last ? 16 : 32, 2, 0, 1));
+        const void* q;
+        HP_TRY(quarter(p, a.n, &q));
+        a.qtw = q;
+        push(a);
+      }
+      continue;
+    }
     // P4 (3D): backward along axis 1
     if (nd == 3) {
       PassArgs a = p2;  // same geometry as P2
@@ -1327,6 +1390,7 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       out.push_back({a, 1});
     }
   }
+  boundary_fill(P, out);
   add_second_terms(P, es, out);
   if (bounded_fast_ok(p, P, L))
     for (size_t i = first_pass; i < out.size(); ++i) HP_TRY(to_fast_r2r(p, out[i].a));
@@ -1911,10 +1975,9 @@ hp_status passes_semi(hp_plan p, Problem& P, std::vector<PassRec>& out) {
     return a;
   };
   // pencils along axis j: the tile runs along the last of the other axes
-  // (contiguous unless j is the last axis, whose pencils are contiguous);
-  // extents ext (default: the unknowns)
-  auto geom = [&](PassArgs& a, int j, bool from_input, const int* ext = nullptr) {
-    if (!ext) ext = P.n;
+  // (contiguous unless j is the last axis, whose pencils are contiguous)
+  auto geom = [&](PassArgs& a, int j, bool from_input) {
+    const int* ext = P.n;
     const long long* is = from_input ? fs : ws;
     int others[2], no = 0;
     for (int b = 0; b < nd; ++b)
@@ -1952,143 +2015,83 @@ hp_status passes_semi(hp_plan p, Problem& P, std::vector<PassRec>& out) {
     out.push_back({a, 1});
     return HP_OK;
   };
-  // one real-to-real pass along j, in place on the view at `view` (extents ext)
-  auto oneway_view = [&](void* view, int j, int x, const int* ext) -> hp_status {
-    PassArgs a = base();
-    a.kind = PK_ONEWAY;
-    a.xf = x;
-    a.L = L[j]; a.n = ext[j]; a.nin = a.nout = ext[j];
-    a.in[0] = view;
-    a.out[0] = view;
-    geom(a, j, false, ext);
-    for (int b = 0; b < 3; ++b) a.nunk[b] = b < nd ? ext[b] : 0;
-    HP_TRY(finish_pass(p, a, j == nd - 1 ? 16 : 32, 2, 0, 1));
-    const void* q;
-    HP_TRY(quarter(p, a.n, &q));
-    a.qtw = q;
-    out.push_back({a, 1});
-    return HP_OK;
-  };
-  // the free-axis sandwich on the view at `v`: Green's rows, or the rows of
-  // the kernel's derivative
-  auto sandwich = [&](void* v, bool odd) -> hp_status {
-    PassArgs a = base();
-    a.kind = PK_SANDWICH;
-    a.xf = X_PAIR_F;
-    a.xb = X_PAIR_B;
-    a.L = L[u]; a.n = P.n[u]; a.nin = a.nout = P.n[u];
-    a.in[0] = v;
-    a.out[0] = v;
-    geom(a, u, false);
-    a.mult = odd ? M_GREEN_ROWS_ODD : M_GREEN_ROWS;
-    a.green = odd ? P.green_odd : P.green;
-    for (int b = 0; b < 3; ++b) a.g_s[b] = P.g_s[b];
-    a.diff = D_NONE;
-    HP_TRY(finish_pass(p, a, 16, 2, 0, 5));
-    out.push_back({a, 1});
-    return HP_OK;
-  };
-  // elementwise prep into the whole output array `dst` (zero outside the
-  // active view off / len): along a bounded axis g the series derivative of
-  // psi's coefficients src (the derivative's basis and index shift, times
-  // sign), or with g < 0 a copy of src times sign
-  auto prep = [&](const void* src, const long long* is, void* dst, int g, const int* off, const int* len,
-                  double sign) {
-    PassArgs a = base();
-    a.fast = FAST_GRAD_PREP;
-    a.ax_j = g;
-    a.diff = D_NONE;
-    a.in[0] = src;
-    a.out[0] = dst;
-    double cnt_in = 1.0, cnt_out = 1.0;
-    for (int b = 0; b < 3; ++b) {
-      a.gp_ext[b] = b < nd ? P.nout[b] : 1;
-      a.gp_off[b] = off[b];
-      a.gp_len[b] = len[b];
-      a.gp_is[b] = b < nd ? is[b] : 0;
-      a.gp_os[b] = b < nd ? ws[b] : 0;
-      a.nunk[b] = b < nd ? P.n[b] : 1;
-      a.lam[b] = nullptr;
-      const int bb = b < nd ? axis_bc(d, b) : HP_NEUMANN;
-      a.gp_basis[b] = bb == HP_PERIODIC ? 2 : (bb == HP_DIRICHLET ? 0 : 1);
-      a.kc[b] = 0.0;
-      if (b < nd) { cnt_in *= P.n[b]; cnt_out *= P.nout[b]; }
-    }
-    a.gp_eigen = 0;
-    a.gp_shift = 0;
-    a.gp_scale = sign;
-    if (g >= 0) {
-      const int bcg = axis_bc(d, g);
-      if (bcg == HP_PERIODIC) {
-        a.gp_scale = sign * 2.0 * M_PI / P.len[g];
-      } else {
-        const bool dir = bcg == HP_DIRICHLET;
-        a.gp_shift = dir ? -1 : 1;
-        a.gp_scale = sign * (dir ? 1.0 : -1.0) * M_PI / P.len[g];
-      }
-    }
-    a.norm = P.norm;
-    PassRec r{a, 1};
-    r.bytes = (cnt_in + cnt_out) * (double)es;
-    out.push_back(r);
-  };
-  // Derivatives of homogeneous solves.  Along a bounded axis g: after the
-  // sandwich psi's array holds the bounded coefficients (the free axis
-  // physical); the prep writes the derivative series along g and backward
-  // transforms along the bounded axes (the other parity's along g) evaluate
-  // it.  Along the free axis: the source copied into the output (times the
-  // term's sign), forward bounded transforms, the sandwich with the odd
-  // kernel's rows and the backward transforms.
+  // Derivatives of homogeneous solves: the free-axis sandwich has a second
+  // output for the derivative along the free axis (the rows of the kernel's
+  // derivative), and each backward pass along a bounded axis one for the
+  // derivative along it (fan_pass).
   const std::vector<DerivTerm> terms = derivative_terms(P);
-  auto bounded_term = [&](int comp, int g, void* dst, double sign) -> hp_status {
-    const int bcg = axis_bc(d, g);
-    const bool dir = bcg == HP_DIRICHLET, reg = d.grid == HP_REGULAR;
-    int off[3] = {0, 0, 0}, len[3] = {1, 1, 1};
-    for (int b = 0; b < nd; ++b) { off[b] = (dmask >> b) & 1; len[b] = P.n[b]; }
-    int xd;
-    if (bcg == HP_PERIODIC) xd = X_DHT;
-    else if (dir && reg) { xd = X_DCT1; len[g] = P.n[g] + 2; off[g] = 0; }  // n + 2 nodes
-    else if (dir) xd = X_DCT3;
-    else if (reg) { xd = X_DST1; len[g] = P.n[g] - 2; off[g] = 1; }   // interior nodes
-    else xd = X_DST3;
-    prep(work(comp), ws, dst, g, off, len, sign);
-    long long vo = 0;
-    for (int b = 0; b < nd; ++b) vo += (long long)off[b] * ws[b];
-    void* view = (void*)((char*)dst + vo * (long long)es);
-    for (int c = nd - 1; c >= 0; --c)
-      if (c != u) HP_TRY(oneway_view(view, c, c == g ? xd : xb[c], len));
-    return HP_OK;
-  };
-  auto free_term = [&](int comp, void* dst, double sign) -> hp_status {
-    int off[3] = {0, 0, 0}, len[3] = {1, 1, 1};
-    for (int b = 0; b < nd; ++b) { off[b] = (dmask >> b) & 1; len[b] = P.n[b]; }
-    prep(P.in[comp], fs, dst, -1, off, len, sign);
-    void* view = (void*)((char*)dst + woff * es);
-    for (int j = nd - 1; j >= 0; --j)
-      if (j != u) HP_TRY(oneway_view(view, j, xf[j], P.n));
-    HP_TRY(sandwich(view, true));
-    for (int j = 0; j < nd; ++j)
-      if (j != u) HP_TRY(oneway_view(view, j, xb[j], P.n));
-    return HP_OK;
-  };
   for (int comp = 0; comp < P.ncomp; ++comp) {
+    auto term_of = [&](int axis) -> const DerivTerm* {
+      for (auto& t : terms)
+        if (t.comp == comp && t.axis == axis) return &t;
+      return nullptr;
+    };
+    bool derivs = false;
+    for (auto& t : terms) derivs |= t.comp == comp;
+    std::vector<FanField> fields = {psi_field(P, comp)};
     bool first = true;
     for (int j = nd - 1; j >= 0; --j) {
       if (j == u) continue;
       HP_TRY(oneway(comp, j, xf[j], first));
       first = false;
     }
-    HP_TRY(sandwich(work(comp), false));
-    // bounded-axis terms from psi's array before the backward passes change it
-    for (const DerivTerm& t : terms)
-      if (t.comp == comp && t.axis != u) HP_TRY(bounded_term(comp, t.axis, t.dst, t.sign));
+    {
+      PassArgs a = base();
+      a.kind = PK_SANDWICH;
+      a.xf = X_PAIR_F;
+      a.xb = X_PAIR_B;
+      a.L = L[u]; a.n = P.n[u]; a.nin = a.nout = P.n[u];
+      a.in[0] = work(comp);
+      a.out[0] = work(comp);
+      geom(a, u, false);
+      a.mult = M_GREEN_ROWS;
+      a.green = P.green;
+      for (int b = 0; b < 3; ++b) a.g_s[b] = P.g_s[b];
+      a.diff = D_NONE;
+      if (const DerivTerm* t = term_of(u)) {
+        FanJob& q = a.fan[0];
+        a.nfan = 1;
+        q.in = a.in[0];
+        q.plain = a.out[0];
+        q.Np = a.Np; q.No = a.No; q.n = q.nd = a.n;
+        q.xp = q.xd = X_PAIR_B;
+        q.basis = FB_ODD;
+        q.scale = t->sign;
+        q.green_odd = P.green_odd;
+        FanField f = psi_field(P, comp);
+        f.base = t->dst;
+        q.deriv = fan_view(f, ws, es);
+        fields.push_back(f);
+      }
+      HP_TRY(finish_pass(p, a, 16, 2, 0, 5));
+      PassRec r{a, 1};
+      if (a.nfan > 0) r.bytes = fan_bytes(a, es);
+      out.push_back(r);
+    }
     for (int j = 0; j < nd; ++j) {
       if (j == u) continue;
-      HP_TRY(oneway(comp, j, xb[j], false));
+      if (!derivs) {
+        HP_TRY(oneway(comp, j, xb[j], false));
+        continue;
+      }
+      PassArgs a = base();
+      a.kind = PK_ONEWAY;
+      a.xf = xb[j];
+      a.L = L[j]; a.n = P.n[j]; a.nin = a.nout = P.n[j];
+      a.in[0] = work(comp);
+      a.out[0] = work(comp);
+      geom(a, j, false);
+      HP_TRY(fan_pass(p, P, comp, a, j, xb[j], term_of(j), ws, fields));
+      HP_TRY(finish_pass(p, a, j == nd - 1 ? 16 : 32, 2, 0, 1));
+      const void* q;
+      HP_TRY(quarter(p, a.n, &q));
+      a.qtw = q;
+      PassRec r{a, 1};
+      r.bytes = fan_bytes(a, es);
+      out.push_back(r);
     }
-    for (const DerivTerm& t : terms)
-      if (t.comp == comp && t.axis == u) HP_TRY(free_term(comp, t.dst, t.sign));
   }
+  boundary_fill(P, out);
   add_second_terms(P, es, out);
   // the passes along Dirichlet / Neumann axes on the wavefront kernels where
   // their lengths allow (the free axis and Hartley axes stay general)
@@ -2149,7 +2152,7 @@ double model_bytes(hp_plan p, const std::vector<PassRec>& ps) {
 const char* pass_name(const PassArgs& a) {
   static const char* fast_names[] = {"",       "r2c_z",      "fwd_y",       "sandwich_x", "inv_y",
                                      "c2r_z",  "r2r_contig", "r2r_strided", "r2r_sandwich",
-                                     "grad_prep", "add", "small2d"};
+                                     "add", "small2d", "boundary_fill"};
   constexpr int nfast = (int)(sizeof(fast_names) / sizeof(fast_names[0]));
   if (a.fast > 0 && a.fast < nfast) return fast_names[a.fast];
   if (a.fast) return "wavefront";
@@ -2173,6 +2176,13 @@ hp_status next_event(hp_plan p, hipEvent_t* e) {
   return HP_OK;
 }
 
+hipError_t launch_one(hp_plan p, const PassRec& r) {
+  return r.a.fast == FAST_FILL    ? launch_boundary_fill(r.fill, p->prec, p->stream)
+         : r.a.fast >= FAST_R2R_C ? launch_bounded(r.a, p->prec, p->stream)
+         : r.a.fast               ? launch_fast(r.a, p->prec, r.grid_y, p->stream)
+                                  : launch_pass(r.a, p->prec, r.grid_y, p->stream);
+}
+
 hp_status run_passes(hp_plan p, const std::vector<PassRec>& ps) {
   std::vector<PassEvents> evs;
   if (p->timing) {
@@ -2189,9 +2199,7 @@ hp_status run_passes(hp_plan p, const std::vector<PassRec>& ps) {
       HP_TRY(next_event(p, &e1));
       HP_HIP(p, hipEventRecord(e0, p->stream));
     }
-    hipError_t e = r.a.fast >= FAST_R2R_C ? launch_bounded(r.a, p->prec, p->stream)
-                   : r.a.fast               ? launch_fast(r.a, p->prec, r.grid_y, p->stream)
-                                            : launch_pass(r.a, p->prec, r.grid_y, p->stream);
+    const hipError_t e = launch_one(p, r);
     if (e != hipSuccess) return fail(p, HP_E_DEVICE, std::string("pass launch: ") + hipGetErrorString(e));
     if (rec) {
       HP_HIP(p, hipEventRecord(e1, p->stream));
@@ -2362,9 +2370,7 @@ void plan_free(hp_plan p, void* ptr) {
 hp_status plan_outputs(hp_plan p, Problem& P) { return ensure_outputs(p, P); }
 hp_status plan_fast_twiddles(hp_plan p, int L, const void** out) { return fast_twiddles(p, L, out); }
 hp_status launch_rec(hp_plan p, const PassRec& r) {
-  hipError_t e = r.a.fast >= FAST_R2R_C ? launch_bounded(r.a, p->prec, p->stream)
-                 : r.a.fast               ? launch_fast(r.a, p->prec, r.grid_y, p->stream)
-                                          : launch_pass(r.a, p->prec, r.grid_y, p->stream);
+  const hipError_t e = launch_one(p, r);
   if (e != hipSuccess) return fail(p, HP_E_DEVICE, std::string("pass launch: ") + hipGetErrorString(e));
   return HP_OK;
 }
@@ -2474,20 +2480,6 @@ hp_status hp_solve(hp_plan plan) {
   std::vector<PassRec> ps;
   HP_TRY(build_passes(plan, P, false, ps));
   HP_TRY(run_passes(plan, ps));
-  if (dreg_axes(P.d)) {
-    for (int c = 0; c < P.ncomp; ++c) {
-      const void* faces[3][2] = {};
-      for (int a = 0; a < P.nd; ++a)
-        for (int s = 0; s < 2; ++s) faces[a][s] = P.d.inhomogeneous ? P.face[a][s][c] : nullptr;
-      int N[3] = {1, 1, 1};
-      for (int a = 0; a < P.nd; ++a) N[3 - P.nd + a] = P.nout[a];
-      // the fill kernel indexes logical axes; pass dims in logical order
-      int Nl[3] = {P.nout[0], P.nd > 1 ? P.nout[1] : 1, P.nd > 2 ? P.nout[2] : 1};
-      (void)N;
-      HP_HIP(plan, launch_dirichlet_fill(P.out[c], Nl, P.nd, dreg_axes(P.d), faces, plan->prec,
-                                         plan->stream));
-    }
-  }
   if (P.d.inhomogeneous && P.nder > 0) HP_TRY(fd_derivatives(plan, P));
   plan->solved = true;
   return HP_OK;

@@ -364,6 +364,268 @@ __global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
   }
 }
 
+// ------------------------------------------------------- fan passes (FanJob)
+// The passes of solves with series derivatives: a pencil pair is read once and
+// transformed for the plain output and the derivative along the pencil.  One
+// launch holds every array of a pass (job = blockIdx.y): the gradient of a 3D
+// Dirichlet solve is 5 launches where one launch per array, with elementwise
+// passes for the coefficients, was 16 (128^3 FP32 with its gradient: 85 us, was
+// 168).
+namespace {
+
+// The backward (forward) type as a compile-time constant.
+template <class F>
+__device__ __forceinline__ void with_backward(int x, F&& f) {
+  switch (x) {
+    case X_DST1: f(std::integral_constant<int, X_DST1>{}); break;
+    case X_DST3: f(std::integral_constant<int, X_DST3>{}); break;
+    case X_DCT1: f(std::integral_constant<int, X_DCT1>{}); break;
+    default: f(std::integral_constant<int, X_DCT3>{}); break;
+  }
+}
+template <class F>
+__device__ __forceinline__ void with_forward(int x, F&& f) {
+  switch (x) {
+    case X_DST1: f(std::integral_constant<int, X_DST1>{}); break;
+    case X_DST2: f(std::integral_constant<int, X_DST2>{}); break;
+    case X_DCT1: f(std::integral_constant<int, X_DCT1>{}); break;
+    default: f(std::integral_constant<int, X_DCT2>{}); break;
+  }
+}
+// Backward type of the derivative of a series with backward type x.
+__host__ __device__ constexpr int r2r_other_parity(int x) {
+  return x == X_DST1 ? X_DCT1 : (x == X_DCT1 ? X_DST1 : (x == X_DST3 ? X_DCT3 : X_DST3));
+}
+
+__device__ __forceinline__ double fan_kappa(const FanJob& q, int k) {
+  return q.scale * (double)(q.basis == FB_SINE ? k + 1 : k);
+}
+
+}  // namespace
+
+template <typename T, int L>
+__global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const PassArgs) {
+  constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
+  constexpr int NT = 64 * kR2RContigWaves;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const PassArgs& a = kernel_args();
+  const FanJob& job = a.fan[blockIdx.y];
+  const int n = job.n;
+  C2<T>* tw = (C2<T>*)smem;
+  C2<T>* q = tw + L;
+  C2<T>* slots = q + a.n;
+  for (int m = threadIdx.x; m < L; m += NT) tw[m] = ((const C2<T>*)a.tw)[m];
+  if (a.qtw)
+    for (int m = threadIdx.x; m < a.n; m += NT) q[m] = ((const C2<T>*)a.qtw)[m];
+  __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int qq = lane / G, g = lane % G;
+  C2<T>* slot = slots + (wave * PPW + qq) * slot_len(L);
+  T* R = (T*)slot;  // the pair's reals, pencil b after pencil a
+  const int pairs_p = (job.Np + 1) / 2;
+  const long long total = (long long)pairs_p * job.No;
+  const int blk = off_lines(a, sizeof(T), sizeof(T)) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const long long pr = ((long long)blk * kR2RContigWaves + wave) * PPW + qq;
+  const bool valid = pr < total;
+  const int o = valid ? (int)(pr / pairs_p) : 0;
+  const int pa = valid ? 2 * (int)(pr % pairs_p) : 0;
+  const bool vb = valid && pa + 1 < job.Np;
+  const T* in = (const T*)job.in;
+  const long long ib = (long long)o * a.in_so + (long long)pa * a.in_sp;
+  constexpr int NJ = (L / 2 + 1 + G - 1) / G;
+  T va[NJ], vbv[NJ];
+  const long long ibb = ib + (vb ? a.in_sp : 0);
+#pragma unroll
+  for (int r = 0; r < NJ; ++r) {
+    const long long jo = (long long)min(g + G * r, n - 1) * a.in_sj;
+    va[r] = valid ? in[ib + jo] : (T)0;
+    vbv[r] = vb ? in[ibb + jo] : (T)0;
+  }
+  const long long ob = (long long)o * a.out_so + (long long)pa * a.out_sp;
+  auto run = [&](auto XC, int cnt, void* dst) __attribute__((always_inline)) {
+    constexpr int X = decltype(XC)::value;
+    T* out = (T*)dst;
+    C2<T> v[R0];
+    r2r_fft<T, L>(v, X, cnt, slot, g, tw, q, [&](int s, int w) { return R[w * cnt + s]; });
+#pragma unroll
+    for (int i = 0; i < R0; ++i) {
+      T oa, obv;
+      const int k = r2r_extract<T>(X, g + G * i, cnt, v[i], q, oa, obv);
+      if (k < 0) continue;
+      if (valid) st_stream(&out[ob + (long long)k * a.out_sj], oa);
+      if (vb) st_stream(&out[ob + a.out_sp + (long long)k * a.out_sj], obv);
+    }
+    wave_sync();  // the slot is filled again
+  };
+  if (job.deriv) {
+    const int nd = job.nd;
+    // places that no coefficient reaches: the first and the last at most
+    if (g == 0) R[0] = R[nd - 1] = R[nd] = R[2 * nd - 1] = (T)0;
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < NJ; ++r) {
+      const int j = g + G * r, s = j - job.shift;
+      if (j < n && s >= 0 && s < nd) {
+        const T m = (T)fan_kappa(job, j);
+        R[s] = m * va[r];
+        R[nd + s] = m * vbv[r];
+      }
+    }
+    wave_sync();
+    with_backward(job.xd, [&](auto XC) __attribute__((always_inline)) { run(XC, nd, job.deriv); });
+  }
+#pragma unroll
+  for (int r = 0; r < NJ; ++r) {
+    const int j = g + G * r;
+    if (j < n) {
+      R[j] = va[r];
+      R[n + j] = vbv[r];
+    }
+  }
+  wave_sync();
+  with_backward(job.xp, [&](auto XC) __attribute__((always_inline)) { run(XC, n, job.plain); });
+}
+
+// Strided fan pass and sandwich: the tile of the plain transform and a second
+// tile for the derivative, both transformed in place (kb_strided).
+template <typename T, int L, int P, int W, bool SW>
+__global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
+  constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
+  constexpr int NT = 64 * W, TS = P + 1;
+  constexpr int MAXN = L / 2 + 1;
+  constexpr int PER = (MAXN * P + NT - 1) / NT;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const PassArgs& a = kernel_args();
+  const FanJob& job = a.fan[blockIdx.y];
+  const int n = job.n, nd = job.nd;
+  C2<T>* tw = (C2<T>*)smem;
+  C2<T>* q = tw + L;
+  C2<T>* slots = q + a.n;
+  T* tile = (T*)(slots + W * PPW * slot_len(L));
+  T* dtile = tile + n * TS;
+  const int tiles_p = (job.Np + P - 1) / P;
+  const int t = off_lines(a, sizeof(T), sizeof(T)) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  if (t >= tiles_p * job.No) return;  // whole workgroup
+  for (int m = threadIdx.x; m < L; m += NT) tw[m] = ((const C2<T>*)a.tw)[m];
+  if (a.qtw)
+    for (int m = threadIdx.x; m < a.n; m += NT) q[m] = ((const C2<T>*)a.qtw)[m];
+  const int o = t / tiles_p, p0 = (t % tiles_p) * P;
+  const int np = min(P, job.Np - p0);
+  {
+    // the whole tile's loads in flight at once (kb_strided)
+    const T* in = (const T*)job.in;
+    const long long ib = (long long)o * a.in_so + (long long)p0 * a.in_sp;
+    T pre[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      const int e = threadIdx.x + r * NT;
+      const int j = e / P, c = e - (e / P) * P;
+      pre[r] = in[ib + (long long)min(j, n - 1) * a.in_sj + (long long)min(c, np - 1) * a.in_sp];
+    }
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      const int e = threadIdx.x + r * NT;
+      const int j = e / P, c = e - (e / P) * P;
+      if (j < n) tile[j * TS + c] = c < np ? pre[r] : (T)0;
+    }
+  }
+  __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int qq = lane / G, g = lane % G;
+  C2<T>* slot = slots + (wave * PPW + qq) * slot_len(L);
+  static_assert(P / 2 == W * PPW, "one pair per wavefront lane group");
+  const int f = wave * PPW + qq;  // pair: columns 2f, 2f + 1
+  T* ca = tile + 2 * f;
+  T* da = dtile + 2 * f;
+  // transform the pair's columns `col` in place (cnt points)
+  auto back = [&](auto XC, T* col, int cnt) __attribute__((always_inline)) {
+    constexpr int X = decltype(XC)::value;
+    C2<T> v[R0];
+    r2r_fft<T, L>(v, X, cnt, slot, g, tw, q, [&](int s, int w) { return col[s * TS + w]; });
+#pragma unroll
+    for (int i = 0; i < R0; ++i) {
+      T oa, obv;
+      const int k = r2r_extract<T>(X, g + G * i, cnt, v[i], q, oa, obv);
+      if (k < 0) continue;
+      col[k * TS] = oa;
+      col[k * TS + 1] = obv;
+    }
+    wave_sync();  // the slot is used again
+  };
+  // a derivative coefficient into its place
+  auto place = [&](int k, T sa, T sb) {
+    const int s = job.basis == FB_LAP ? k : k - job.shift;
+    if (s >= 0 && s < nd) {
+      da[s * TS] = sa;
+      da[s * TS + 1] = sb;
+    }
+  };
+  if (job.deriv) {
+    if (g == 0) da[0] = da[1] = da[(nd - 1) * TS] = da[(nd - 1) * TS + 1] = (T)0;
+    wave_sync();
+  }
+  if constexpr (SW) {
+    const int pa = min(p0 + 2 * f, job.Np - 1), pb = min(p0 + 2 * f + 1, job.Np - 1);
+    const double ra = eigen_rest(a, pa, o), rb = eigen_rest(a, pb, o);
+    const bool lap = job.basis == FB_LAP;
+    auto w2 = [&](int ax, int k) {
+      if (ax < 0) return 0.0;
+      const double w = a.kc[ax] * (double)(a.basis[ax] == FB_SINE ? k + 1 : (a.basis[ax] == FB_COSINE ? k : signed_index(k, a.nunk[ax])));
+      return w * w;
+    };
+    const double la = lap ? w2(a.ax_p, pa) + w2(a.ax_o, o) : 0.0, lb = lap ? w2(a.ax_p, pb) + w2(a.ax_o, o) : 0.0;
+    with_forward(a.xf, [&](auto XC) {
+      constexpr int XF = decltype(XC)::value;
+      constexpr int XB = r2r_partner(XF);
+      {
+        C2<T> v[R0];
+        r2r_fft<T, L>(v, XF, n, slot, g, tw, q, [&](int s, int w) { return ca[s * TS + w]; });
+#pragma unroll
+        for (int i = 0; i < R0; ++i) {
+          T sa, sb;
+          const int k = r2r_extract<T>(XF, g + G * i, n, v[i], q, sa, sb);
+          if (k < 0) continue;
+          const double lam = a.lam[a.ax_j][k];
+          const double ma = lam + ra == 0.0 ? 0.0 : a.norm / (lam + ra);
+          const double mb = lam + rb == 0.0 ? 0.0 : a.norm / (lam + rb);
+          // (the plain value with the multiplier of a solve without derivatives)
+          ca[k * TS] = sa * eigen_mult<T>(a, k, ra);
+          ca[k * TS + 1] = sb * eigen_mult<T>(a, k, rb);
+          const double wj = lap ? w2(a.ax_j, k) : 0.0;
+          const double fa = lap ? -job.scale * (wj + la) : fan_kappa(job, k);
+          const double fb = lap ? -job.scale * (wj + lb) : fa;
+          place(k, sa * (T)(ma * fa), sb * (T)(mb * fb));
+        }
+        wave_sync();
+      }
+      if (lap) back(std::integral_constant<int, XB>{}, da, nd);
+      else back(std::integral_constant<int, r2r_other_parity(XB)>{}, da, nd);
+      back(std::integral_constant<int, XB>{}, ca, n);
+    });
+  } else {
+    if (job.deriv) {
+      for (int k = g; k < n; k += G) {
+        const T m = (T)fan_kappa(job, k);
+        place(k, m * ca[k * TS], m * ca[k * TS + 1]);
+      }
+      wave_sync();
+      with_backward(job.xd, [&](auto XC) __attribute__((always_inline)) { back(XC, da, nd); });
+    }
+    with_backward(job.xp, [&](auto XC) __attribute__((always_inline)) { back(XC, ca, n); });
+  }
+  __syncthreads();
+  const long long ob = (long long)o * a.out_so + (long long)p0 * a.out_sp;
+  auto store = [&](const T* src, int cnt, void* dst) {
+    T* out = (T*)dst;
+    for (int e = threadIdx.x; e < cnt * P; e += NT) {
+      const int j = e / P, c = e - (e / P) * P;
+      if (c < np) st_stream(&out[ob + (long long)j * a.out_sj + (long long)c * a.out_sp], src[j * TS + c]);
+    }
+  };
+  if (job.deriv) store(dtile, nd, job.deriv);
+  store(tile, n, job.plain);
+}
+
 // ------------------------------------------ batched solve
 // A pass level of a batched plan (one pass of every problem) is one launch, one
 // workgroup of kBatchWaves wavefronts per work item (consecutive tiles of one
@@ -763,7 +1025,9 @@ int r2r_tile(int prec) { return prec == 0 ? 32 : 16; }
 // for short transforms).
 constexpr int r2r_waves(int P, int ppw) { return (P / 2) / ppw; }
 
-int r2r_lds_bytes(int fast, int L, int n, int prec) {
+// n: rows of the tile (and quarter twists), nd: rows of the derivative's tile
+// of a fan pass (0: none).
+int r2r_lds_bytes(int fast, int L, int n, int nd, int prec) {
   const int cs = prec == 0 ? 8 : 16, es = cs / 2;
   const int R0 = wf_r0(L);
   if (R0 <= 0 || (R0 % 3 == 0 && prec != 0)) return -1;  // 3 x 2^k: FP32 only
@@ -773,16 +1037,59 @@ int r2r_lds_bytes(int fast, int L, int n, int prec) {
   const int P = r2r_tile(prec);
   // one pencil pair per lane group: the tile's pairs must fill whole wavefronts
   if ((P / 2) % ppw != 0) return -1;
-  return (L + n + r2r_waves(P, ppw) * ppw * SL) * cs + n * (P + 1) * es;
+  return (L + n + r2r_waves(P, ppw) * ppw * SL) * cs + (n + nd) * (P + 1) * es;
 }
 
 namespace {
+
+template <typename T, int L>
+hipError_t launch_fan_L(const PassArgs& a, hipStream_t s) {
+  constexpr int PPW = WF<L>::PPW;
+  constexpr int P = sizeof(T) == 4 ? 32 : 16;
+  constexpr int W = r2r_waves(P, PPW);
+  if (a.nfan > kMaxFan || a.P != P) return hipErrorInvalidValue;
+  long long blocks = 0;
+  int rows = 0, drows = 0;
+  for (int i = 0; i < a.nfan; ++i) {
+    const FanJob& q = a.fan[i];
+    if (!q.in || !q.plain || q.n < 1 || q.n > L / 2 + 1 || q.Np < 1 || q.No < 1) return hipErrorInvalidValue;
+    if (q.deriv && (q.nd < 1 || q.nd > L / 2 + 1 || q.basis == FB_HARTLEY || q.basis == FB_ODD))
+      return hipErrorInvalidValue;
+    // quarter twists (staggered types) are those of n points
+    if ((q.xp == X_DST3 || q.xp == X_DCT3) && q.n != a.n) return hipErrorInvalidValue;
+    const long long per = (long long)kR2RContigWaves * PPW;
+    blocks = std::max(blocks, a.fast == FAST_R2R_C ? ((long long)((q.Np + 1) / 2) * q.No + per - 1) / per
+                                                   : (long long)((q.Np + P - 1) / P) * q.No);
+    rows = std::max(rows, q.n);
+    if (q.deriv) drows = std::max(drows, q.nd);
+  }
+  if (r2r_lds_bytes(a.fast, L, std::max(rows, a.n), drows, sizeof(T) == 8) > a.lds_bytes || a.lds_bytes > 160 * 1024)
+    return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks, a.nfan);
+  if (a.fast == FAST_R2R_C) {
+    allow_lds<kb_contig_fan<T, L>>();
+    hipLaunchKernelGGL((kb_contig_fan<T, L>), grid, dim3(64 * kR2RContigWaves), a.lds_bytes, s, a);
+    return hipGetLastError();
+  }
+  if constexpr (W < 1 || (P / 2) % PPW != 0) {
+    return hipErrorInvalidValue;
+  } else if (a.fast == FAST_R2R_SW) {
+    if (a.xb != r2r_partner(a.xf) || a.nfan != 1 || !a.fan[0].deriv) return hipErrorInvalidValue;
+    allow_lds<kb_strided_fan<T, L, P, W, true>>();
+    hipLaunchKernelGGL((kb_strided_fan<T, L, P, W, true>), grid, dim3(64 * W), a.lds_bytes, s, a);
+  } else {
+    allow_lds<kb_strided_fan<T, L, P, W, false>>();
+    hipLaunchKernelGGL((kb_strided_fan<T, L, P, W, false>), grid, dim3(64 * W), a.lds_bytes, s, a);
+  }
+  return hipGetLastError();
+}
 
 template <typename T, int L>
 hipError_t launch_bounded_L(const PassArgs& a, hipStream_t s) {
   constexpr int PPW = WF<L>::PPW;
   const int lds = a.lds_bytes;
   if (a.n < 1 || a.n > L / 2 + 1) return hipErrorInvalidValue;  // rows per pencil of every Table 1 type
+  if (a.nfan > 0) return launch_fan_L<T, L>(a, s);
   if (a.fast == FAST_R2R_C) {
     const long long pairs = (long long)((a.Np + 1) / 2) * a.No;
     const long long per_block = (long long)kR2RContigWaves * PPW;
@@ -850,80 +1157,11 @@ hipError_t launch_bounded_T(const PassArgs& a, hipStream_t s) {
   }
 }
 
-// Coefficients of the derivative along ax_j of a Dirichlet / Neumann solve.
-// The source holds the forward-transformed right-hand side (every axis; with
-// gp_eigen, dividing by the eigenvalue sum gives the coefficients u of psi)
-// or already the coefficients u (axis 0 physical); d/dx of
-// the sine (cosine) series is the cosine (sine) series with coefficients
-// +-(pi kappa / L) u, one index over.  Written so that the backward transform
-// along ax_j of the other type (DST-I -> DCT-I on the n + 2 nodes, DST-III ->
-// DCT-III, DCT-III -> DST-III, DCT-I -> DST-I on the n - 2 interior nodes)
-// and the usual backward transforms along the other axes evaluate it.
-// One thread per output element; consecutive threads take consecutive
-// elements of the last logical axis.
-template <typename T>
-__global__ void __launch_bounds__(256) k_grad_prep(PassArgs a) {
-  const long long total = (long long)a.gp_ext[0] * a.gp_ext[1] * a.gp_ext[2];
-  const T* src = (const T*)a.in[0];
-  T* dst = (T*)a.out[0];
-  const long long step = (long long)gridDim.x * blockDim.x;
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += step) {
-    long long r = e;
-    int i[3];
-    i[2] = (int)(r % a.gp_ext[2]);
-    r /= a.gp_ext[2];
-    i[1] = (int)(r % a.gp_ext[1]);
-    i[0] = (int)(r / a.gp_ext[1]);
-    bool ok = true;
-    long long so = 0, dof = 0;
-    double lam = 0.0, w2 = 0.0, kap = 0.0;
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      dof += (long long)i[b] * a.gp_os[b];
-      const int sb = i[b] - a.gp_off[b];
-      const int basis = a.gp_basis[b];
-      int k = sb;
-      if (b == a.ax_j) k = basis == 2 ? (sb == 0 ? 0 : a.nunk[b] - sb) : sb + a.gp_shift;
-      ok = ok && sb >= 0 && sb < a.gp_len[b] && k >= 0 && k < a.nunk[b];
-      if (ok) {
-        so += (long long)k * a.gp_is[b];
-        if (a.lam[b]) lam += a.lam[b][k];
-        // wavenumber index of coefficient k: k + 1 (sine), k (cosine), signed k (Hartley)
-        const double kk = basis == 2 ? (double)signed_index(k, a.nunk[b]) : (double)(k + (basis == 0 ? 1 : 0));
-        if (b == a.ax_j) kap = basis == 2 ? -(double)signed_index(sb, a.nunk[b]) : kk;
-        const double w = a.kc[b] * kk;  // NABLA: the wavenumber of axis b
-        w2 += w * w;
-      }
-    }
-    T v = (T)0;
-    if (ok) {
-      // gradient: +-(pi kappa / L) one index over (Hartley: -(2 pi k~ / L)
-      // from the mirrored index); NABLA (diff = D_NABLA): -sum_b w_b^2 on the
-      // same index
-      // (ax_j < 0 otherwise: a plain copy times gp_scale)
-      double m = a.diff == D_NABLA ? -a.gp_scale * w2 : (a.ax_j < 0 ? a.gp_scale : a.gp_scale * kap);
-      if (a.gp_eigen) m = lam == 0.0 ? 0.0 : m * a.norm / lam;
-      v = (T)m * src[so];
-    }
-    dst[dof] = v;
-  }
-}
-
-template <typename T>
-hipError_t launch_grad_prep(const PassArgs& a, hipStream_t s) {
-  const long long total = (long long)a.gp_ext[0] * a.gp_ext[1] * a.gp_ext[2];
-  if (total <= 0) return hipSuccess;
-  const long long blocks = (total + 255) / 256;
-  const int grid = (int)(blocks < 8192 ? blocks : 8192);
-  hipLaunchKernelGGL(k_grad_prep<T>, dim3(grid), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-// out[0][i] += in[0][i] (+ in[1][i]), i < gp_ext[0]: the second terms of the
+// out[0][i] += in[0][i] (+ in[1][i]), i < n_add: the second terms of the
 // Dirichlet / Neumann divergence and curl.
 template <typename T>
 __global__ void __launch_bounds__(256) k_add(PassArgs a) {
-  const long long total = a.gp_ext[0];
+  const long long total = a.n_add;
   T* dst = (T*)a.out[0];
   const T* x = (const T*)a.in[0];
   const T* y = (const T*)a.in[1];
@@ -937,7 +1175,7 @@ __global__ void __launch_bounds__(256) k_add(PassArgs a) {
 
 template <typename T>
 hipError_t launch_add(const PassArgs& a, hipStream_t s) {
-  const long long total = a.gp_ext[0];
+  const long long total = a.n_add;
   if (total <= 0) return hipSuccess;
   const long long blocks = (total + 255) / 256;
   const int grid = (int)(blocks < 8192 ? blocks : 8192);
@@ -1009,8 +1247,6 @@ hipError_t launch_fd_deriv(const FdArgs& a, int prec, hipStream_t s) {
 }
 
 hipError_t launch_bounded(const PassArgs& a, int prec, hipStream_t s) {
-  if (a.fast == FAST_GRAD_PREP)
-    return prec == 0 ? launch_grad_prep<float>(a, s) : launch_grad_prep<double>(a, s);
   if (a.fast == FAST_ADD) return prec == 0 ? launch_add<float>(a, s) : launch_add<double>(a, s);
   if (a.fast == FAST_SMALL2D) return launch_small2d(a, prec, s);
   if (prec == 0) return launch_bounded_T<float>(a, s);

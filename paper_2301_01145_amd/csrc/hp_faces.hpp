@@ -1,4 +1,5 @@
-// Boundary terms of the inhomogeneous FD2 solves (Section 2.4.2): the
+// What the real-to-real kernels share beside the FFTs: the pass descriptor and
+// the boundary terms of the inhomogeneous FD2 solves (Section 2.4.2), the
 // weighted face values added to the source at the unknowns next to a face.
 #pragma once
 
@@ -6,6 +7,22 @@
 #include "hp_internal.hpp"
 
 namespace hp {
+
+// The pass descriptor where the launch put it (the kernels' only argument).
+// Read as a parameter it is copied to scratch memory once its uses are many.
+// One word of every 64-byte line of it is read at once first: the fields are
+// read where they are needed, and each line's first read would be a miss of
+// the scalar cache of its own in the chain of a workgroup.
+__device__ __forceinline__ const PassArgs& kernel_args() {
+  typedef const volatile __attribute__((address_space(4))) int* cptr;
+  const cptr w = (cptr)__builtin_amdgcn_kernarg_segment_ptr();
+  int x[(sizeof(PassArgs) + 63) / 64];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(x) / sizeof(x[0]); ++i) x[i] = w[16 * i];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(x) / sizeof(x[0]); ++i) asm volatile("" ::"s"(x[i]));
+  return *(const PassArgs*)(const __attribute__((address_space(4))) PassArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+}
 
 // Boundary terms of inhomogeneous FD2 problems (added to the source value of
 // an unknown next to a face).

@@ -32,11 +32,10 @@ enum MultKind : int { M_NONE = 0, M_EIGEN = 1, M_GREEN = 2,
                       // semi-unbounded free axis: one real-even row of the
                       // Helmholtz Green's spectrum per bounded mode of the
                       // pencil (green[m g_s[ax_j] + p g_s[ax_p] + o g_s[ax_o]],
-                      // m <= L / 2), paired real pencils
-                      M_GREEN_ROWS = 3,
-                      // the same for the free-axis derivative: rows b of the
-                      // odd kernel's spectrum i b(m) (b real, odd in m)
-                      M_GREEN_ROWS_ODD = 4 };
+                      // m <= L / 2), paired real pencils; the free-axis
+                      // derivative (FB_ODD): rows b of the odd kernel's spectrum
+                      // i b(m) (b real, odd in m)
+                      M_GREEN_ROWS = 3 };
 // Derivative coupling inside the sandwich pass (D_ADJ_*: the transposes used
 // by the adjoint solve).
 enum DiffKind : int { D_NONE = 0, D_GRAD = 1, D_CURL = 2, D_ADJ_GRAD = 3, D_ADJ_CURL = 4,
@@ -56,6 +55,30 @@ constexpr int kThreads = HP_GEN_THREADS;
 constexpr int kMaxLenThreads = 256;
 constexpr int kMaxStages = 8;
 constexpr int kMaxFields = 6;
+
+// One job of a fan pass: the pencils of one array read once and transformed
+// for up to two outputs, the plain transform and the derivative along the
+// pencil.  The input holds n coefficients per pencil (a sandwich: its forward
+// transform); element s (0 <= s < nd) of the derivative series is
+// scale * kappa(s + shift) times coefficient s + shift (0 outside [0, n)),
+// kappa the wavenumber index of the input's basis (sine k + 1, cosine k); a
+// Hartley series takes coefficient -s (mod n) times -scale * (signed s).
+// FB_LAP (sandwich): every coefficient times -scale * sum_b w_b^2 instead;
+// FB_ODD (free-axis sandwich): the rows of the kernel's derivative
+// (green_odd) times scale.
+enum FanBasis : int { FB_SINE = 0, FB_COSINE = 1, FB_HARTLEY = 2, FB_LAP = 3, FB_ODD = 4 };
+struct FanJob {
+  const void* in;
+  void* plain;        // may be the input array; null: none
+  void* deriv;        // another array; null: none
+  int Np, No;         // pencils along the tile / outer axis
+  int n, xp;          // plain transform: points and type
+  int nd, xd;         // derivative transform
+  int shift, basis;
+  double scale;
+  const void* green_odd;
+};
+constexpr int kMaxFan = 3;
 
 struct PassArgs {
   int kind;          // PassKind
@@ -108,21 +131,13 @@ struct PassArgs {
   // signature of the pass geometry (host planner): passes with equal keys
   // share the configuration chosen by the autotuner
   unsigned long long tune_key;
-  // FAST_GRAD_PREP (series derivative along ax_j): output element i (logical
-  // axes, extents gp_ext, strides gp_os) is active where s = i - gp_off lies
-  // in [0, gp_len) on every axis.  gp_basis[b] names axis b's series: 0 sine
-  // (index k carries wavenumber k + 1), 1 cosine (k), 2 Hartley (signed k,
-  // Nyquist 0).  Along ax_j a sine / cosine source is read at src = s +
-  // gp_shift and scaled by gp_scale times src's wavenumber; a Hartley source
-  // at -s (mod nunk), scaled by -gp_scale times s's signed wavenumber.  Other
-  // axes read src = s (strides gp_is, extents nunk).  With gp_eigen the value
-  // is divided by sum_b lam[b][src_b] / norm (0 where that sum is 0).
-  // ax_j < 0 without D_NABLA: a copy, src = s on every axis, times gp_scale.
-  // Elements that are not active, or whose source lies outside, are 0.
-  int gp_ext[3], gp_off[3], gp_len[3];
-  int gp_shift, gp_basis[3], gp_eigen;
-  double gp_scale;
-  long long gp_is[3], gp_os[3];
+  // Fan passes (nfan > 0: the passes of real-to-real solves with series
+  // derivatives): blockIdx.y = job, see FanJob; in / out / n / nin / nout /
+  // Np / No above are those of job 0, strides and length common.
+  int nfan;
+  FanJob fan[kMaxFan];
+  int basis[3];        // FD_LAP: series of each axis (FanBasis), wavenumbers kc
+  long long n_add;     // FAST_ADD: elements
 };
 
 // Whether the rows of a pass start off the 128-byte cache lines on either side
@@ -148,14 +163,14 @@ enum FastKind : int { FAST_NONE = 0, FAST_R2C = 1, FAST_FWD_Y = 2, FAST_SANDWICH
                       FAST_INV_Y = 4, FAST_C2R = 5,
                       // bounded real-to-real passes (hp_bounded.hip)
                       FAST_R2R_C = 6, FAST_R2R_S = 7, FAST_R2R_SW = 8,
-                      // elementwise: spectral derivative coefficients (hp_bounded.hip)
-                      FAST_GRAD_PREP = 9,
-                      // elementwise: out[0] += in[0] (+ in[1]) over gp_ext[0] elements
-                      FAST_ADD = 10,
+                      // elementwise: out[0] += in[0] (+ in[1]) over n_add elements
+                      FAST_ADD = 9,
                       // the whole 2D periodic solve in one workgroup (hp_small.hip):
                       // lengths gM[0] x gM[1], twiddles of the x FFT in tw and of
                       // the y FFT in qtw, n_in inputs, n_out outputs
-                      FAST_SMALL2D = 11 };
+                      FAST_SMALL2D = 10,
+                      // boundary nodes of the outputs (PassRec.fill; hp_kernels.hip)
+                      FAST_FILL = 11 };
 // Derivative completion in the backward y pass of the free-space path.
 enum InvYMode : int { IY_PLAIN = 0, IY_CURL5 = 1, IY_GRAD2 = 2 };
 
@@ -201,7 +216,7 @@ hipError_t launch_fd_deriv(const FdArgs& a, int prec, hipStream_t s);
 int small2d_lds_bytes(int L0, int L1, int prec, int nbuf);
 hipError_t launch_small2d(const PassArgs& a, int prec, hipStream_t s);
 int r2r_tile(int prec);
-int r2r_lds_bytes(int fast, int L, int n, int prec);
+int r2r_lds_bytes(int fast, int L, int n, int nd, int prec);
 // Dynamic LDS bytes of a wavefront-FFT pass; 0 if the pass is not available.
 int fast_lds_bytes(int fast, int L, int P, int K2, int prec, int dbl, int pad);
 int fast_emit_dbl(int fast, int prec);
@@ -216,6 +231,7 @@ bool fast_tile_ok(int fast, int L, int P, int prec);
 // P pencils, and the kernel mode the pass needs (batched plans run one mode
 // for all passes: the largest).
 int max_radix(int prec);
+bool stages_fit(int L, long long nf, const int* radix, int nstage, int big, int prec);
 bool general_fits(const PassArgs& a, int prec);
 int general_lds_bytes(const PassArgs& a, int P, int prec);
 int general_mode(const PassArgs& a, int prec);
@@ -253,11 +269,17 @@ hipError_t launch_semi_green(void* out, const double* lam1, int n1, const double
                              int M, double h, double scale, int odd, int prec, hipStream_t s);
 hipError_t launch_octant(const double* spec, const int M[3], double scale, void* out,
                          int prec, hipStream_t s);
-// Write the boundary nodes of the REGULAR Dirichlet axes (bit a of `axes`)
-// of an output [N0][N1][N2] from face arrays (node with several faces:
-// highest axis wins).
-hipError_t launch_dirichlet_fill(void* out, const int N[3], int ndim, int axes, const void* face[3][2],
-                                 int prec, hipStream_t s);
+// Boundary nodes of up to kMaxFill outputs [N0][N1][N2] in one launch: field
+// f's nodes on the end faces of the axes in its mask `axes` take its face
+// values (null: 0; a node with several faces: the highest axis in the mask).
+constexpr int kMaxFill = 6;
+struct FillArgs {
+  int nf, ndim, N[3];
+  void* out[kMaxFill];
+  int axes[kMaxFill];
+  const void* face[kMaxFill][3][2];
+};
+hipError_t launch_boundary_fill(const FillArgs& a, int prec, hipStream_t s);
 // A work item of a batched plan: consecutive tiles of one pass (one workgroup).
 struct BatchItem {
   int pass;

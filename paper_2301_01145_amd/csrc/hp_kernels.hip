@@ -340,15 +340,15 @@ struct Tile {
 };
 
 template <typename T>
-__device__ __forceinline__ Tile tile_of(const PassArgs& a) {
-  const int tiles_p = (a.Np + a.P - 1) / a.P;
+__device__ __forceinline__ Tile tile_of(const PassArgs& a, int Np) {
+  const int tiles_p = (Np + a.P - 1) / a.P;
   const int ei = (int)sizeof(T) * (xform_complex_in(a.xf) || a.xf == X_C2R ? 2 : 1);
   const int eo = (int)sizeof(T) * (xform_complex_in(a.xf) || a.xf == X_R2C ? 2 : 1);
   const int b = off_lines(a, ei, eo) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   Tile t;
   t.o = b / tiles_p;
   t.p0 = (b - t.o * tiles_p) * a.P;
-  t.np = min(a.P, a.Np - t.p0);
+  t.np = min(a.P, Np - t.p0);
   return t;
 }
 
@@ -390,8 +390,8 @@ __device__ __forceinline__ void zero_rows(LTile<T> Z, int m0, int m1) {
 //           (DST-III: x reversed), for the backward FFT (parts exchanged)
 //   others  x_s (rows beyond the input zeroed by extend_zeros)
 template <typename T, int XC>
-__device__ __forceinline__ void extend(LTile<T> Z, int f, int s, C2<T> v, const PassArgs& a) {
-  const int L = a.L, n = a.n;
+__device__ __forceinline__ void extend(LTile<T> Z, int f, int s, C2<T> v, const PassArgs& a, int n) {
+  const int L = a.L;
   auto put = [&](int m, C2<T> z) { Z.put(m * Z.S + f, z); };
   if constexpr (XC == X_DST1) {
     put(s + 1, v);
@@ -416,12 +416,12 @@ __device__ __forceinline__ void extend(LTile<T> Z, int f, int s, C2<T> v, const 
 
 // The rows of the FFT input that no element reaches.
 template <typename T, int XC>
-__device__ __forceinline__ void extend_zeros(LTile<T> Z, const PassArgs& a, int cnt) {
+__device__ __forceinline__ void extend_zeros(LTile<T> Z, const PassArgs& a, int n, int cnt) {
   if constexpr (XC == X_DST1) {
     zero_rows<T>(Z, 0, 1);
-    zero_rows<T>(Z, a.n + 1, a.n + 2);
+    zero_rows<T>(Z, n + 1, n + 2);
   } else if constexpr (XC == X_DCT3 || XC == X_DST3) {
-    zero_rows<T>(Z, a.n, a.n + 1);
+    zero_rows<T>(Z, n, n + 1);
   } else if constexpr (XC == X_R2C || XC == X_PAIR_F || XC == X_DHT) {
     zero_rows<T>(Z, cnt, a.L);
   }
@@ -447,8 +447,9 @@ __device__ __forceinline__ bool beside_face(const PassArgs& a, int j, int p, int
 // Real pencils, two per column, with boundary terms when present (first
 // passes only: forward transforms).
 template <typename T, int XC>
-__device__ __forceinline__ void load_real_x(LTile<T> Z, const void* src, const PassArgs& a, const Tile& t, bool faces) {
-  const int cnt = a.nin, jfast = a.in_jfast;
+__device__ __forceinline__ void load_real_x(LTile<T> Z, const void* src, const PassArgs& a, const Tile& t, int n,
+                                            int cnt, bool faces) {
+  const int jfast = a.in_jfast;
   const int total = cnt << Z.lg;
   const unsigned mc = div_magic(cnt);
   const HP_GLB T* in = (const HP_GLB T*)src + (long long)t.o * a.in_so + (long long)t.p0 * a.in_sp;
@@ -480,10 +481,10 @@ __device__ __forceinline__ void load_real_x(LTile<T> Z, const void* src, const P
     for (int u = 0; u < kLoadBatch; ++u) {
       if (e0 + u * kThreads >= total) continue;
       const int p = 2 * ff[u];
-      extend<T, XC>(Z, ff[u], jj[u], {p < t.np ? v[u].re : (T)0, p + 1 < t.np ? v[u].im : (T)0}, a);
+      extend<T, XC>(Z, ff[u], jj[u], {p < t.np ? v[u].re : (T)0, p + 1 < t.np ? v[u].im : (T)0}, a, n);
     }
   }
-  extend_zeros<T, XC>(Z, a, cnt);
+  extend_zeros<T, XC>(Z, a, n, cnt);
   if (faces) {
     // boundary terms: the elements next to a face are read back from their
     // (first) place in the FFT input and extended again
@@ -497,21 +498,93 @@ __device__ __forceinline__ void load_real_x(LTile<T> Z, const void* src, const P
       if (XC == X_DST2 && (j & 1)) v = {-v.re, -v.im};
       v.re = (T)((double)v.re + face_terms<T>(a, j, t.p0 + p, t.o));
       if (p + 1 < t.np) v.im = (T)((double)v.im + face_terms<T>(a, j, t.p0 + p + 1, t.o));
-      extend<T, XC>(Z, f, j, v, a);
+      extend<T, XC>(Z, f, j, v, a, n);
     }
   }
 }
 
 template <typename T>
-__device__ __forceinline__ void load_real(LTile<T> Z, const void* src, int x, const PassArgs& a, const Tile& t, bool faces) {
+__device__ __forceinline__ void load_real(LTile<T> Z, const void* src, int x, const PassArgs& a, const Tile& t, int n,
+                                          int cnt, bool faces) {
   switch (x) {
-    case X_DST1: load_real_x<T, X_DST1>(Z, src, a, t, faces); break;
-    case X_DST2: load_real_x<T, X_DST2>(Z, src, a, t, faces); break;
-    case X_DST3: load_real_x<T, X_DST3>(Z, src, a, t, faces); break;
-    case X_DCT1: load_real_x<T, X_DCT1>(Z, src, a, t, faces); break;
-    case X_DCT2: load_real_x<T, X_DCT2>(Z, src, a, t, faces); break;
-    case X_DCT3: load_real_x<T, X_DCT3>(Z, src, a, t, faces); break;
-    default: load_real_x<T, X_R2C>(Z, src, a, t, faces); break;  // R2C, paired, Hartley: as they are
+    case X_DST1: load_real_x<T, X_DST1>(Z, src, a, t, n, cnt, faces); break;
+    case X_DST2: load_real_x<T, X_DST2>(Z, src, a, t, n, cnt, faces); break;
+    case X_DST3: load_real_x<T, X_DST3>(Z, src, a, t, n, cnt, faces); break;
+    case X_DCT1: load_real_x<T, X_DCT1>(Z, src, a, t, n, cnt, faces); break;
+    case X_DCT2: load_real_x<T, X_DCT2>(Z, src, a, t, n, cnt, faces); break;
+    case X_DCT3: load_real_x<T, X_DCT3>(Z, src, a, t, n, cnt, faces); break;
+    default: load_real_x<T, X_R2C>(Z, src, a, t, n, cnt, faces); break;  // R2C, paired, Hartley: as they are
+  }
+}
+
+// ------------------------------------------------ series derivatives (FanJob)
+// Wavenumber factor of coefficient k of the input for its place in the
+// derivative series, and that place.
+__device__ __forceinline__ double fan_factor(const FanJob& q, int k) {
+  if (q.basis == FB_HARTLEY) {
+    const int s = k == 0 ? 0 : q.n - k;
+    return -q.scale * (double)(2 * s < q.n ? s : (2 * s == q.n ? 0 : s - q.n));
+  }
+  return q.scale * (double)(q.basis == FB_SINE ? k + 1 : k);
+}
+__device__ __forceinline__ int fan_place(const FanJob& q, int k) {
+  if (q.basis == FB_HARTLEY) return k == 0 ? 0 : q.n - k;
+  return q.basis == FB_LAP ? k : k - q.shift;
+}
+
+// Extends coefficient k (value v, the factor applied) of the input into the
+// derivative's FFT input; the thread of the first (last) coefficient also
+// writes the places beside it that no coefficient reaches.
+template <typename T, int XD>
+__device__ __forceinline__ void extend_derivative(LTile<T> Z, int f, int k, C2<T> v, const FanJob& q,
+                                                  const PassArgs& a) {
+  const int s = fan_place(q, k);
+  if (s >= 0 && s < q.nd) extend<T, XD>(Z, f, s, v, a, q.nd);
+  if (q.basis == FB_SINE || q.basis == FB_COSINE) {
+    const C2<T> zero = {(T)0, (T)0};
+    if (k == 0 && q.shift < 0) extend<T, XD>(Z, f, 0, zero, a, q.nd);
+    if (k == q.n - 1 && s + 1 < q.nd) extend<T, XD>(Z, f, s + 1, zero, a, q.nd);
+  }
+}
+
+// The coefficients of a pencil tile times their factors, as the FFT input of
+// the derivative's transform.
+template <typename T, int XD>
+__device__ __forceinline__ void load_derivative_x(LTile<T> Z, const FanJob& q, const PassArgs& a, const Tile& t) {
+  const int cnt = q.n, jfast = a.in_jfast;
+  const int total = cnt << Z.lg;
+  const unsigned mc = div_magic(cnt);
+  const HP_GLB T* in = (const HP_GLB T*)q.in + (long long)t.o * a.in_so + (long long)t.p0 * a.in_sp;
+  for (int e0 = threadIdx.x; e0 < total; e0 += kLoadBatch * kThreads) {
+    C2<T> v[kLoadBatch];
+    int ff[kLoadBatch], jj[kLoadBatch];
+#pragma unroll
+    for (int u = 0; u < kLoadBatch; ++u) {
+      tile_fj(min(e0 + u * kThreads, total - 1), Z.lg, cnt, mc, jfast, ff[u], jj[u]);
+      const HP_GLB T* row = in + (long long)jj[u] * a.in_sj;
+      v[u].re = row[(long long)min(2 * ff[u], t.np - 1) * a.in_sp];
+      v[u].im = row[(long long)min(2 * ff[u] + 1, t.np - 1) * a.in_sp];
+    }
+#pragma unroll
+    for (int u = 0; u < kLoadBatch; ++u) {
+      if (e0 + u * kThreads >= total) continue;
+      const int p = 2 * ff[u];
+      const T m = (T)fan_factor(q, jj[u]);
+      extend_derivative<T, XD>(Z, ff[u], jj[u], {p < t.np ? m * v[u].re : (T)0, p + 1 < t.np ? m * v[u].im : (T)0}, q,
+                               a);
+    }
+  }
+  extend_zeros<T, XD>(Z, a, q.nd, q.nd);
+}
+
+template <typename T>
+__device__ __forceinline__ void load_derivative(LTile<T> Z, const FanJob& q, const PassArgs& a, const Tile& t) {
+  switch (q.xd) {
+    case X_DST1: load_derivative_x<T, X_DST1>(Z, q, a, t); break;
+    case X_DST3: load_derivative_x<T, X_DST3>(Z, q, a, t); break;
+    case X_DCT1: load_derivative_x<T, X_DCT1>(Z, q, a, t); break;
+    case X_DCT3: load_derivative_x<T, X_DCT3>(Z, q, a, t); break;
+    default: load_derivative_x<T, X_DHT>(Z, q, a, t); break;
   }
 }
 
@@ -575,14 +648,14 @@ __device__ __forceinline__ void load_half(LTile<T> Z, const void* src, const Pas
 // ---------------------------------------------------------------- storing
 // Output k of the two pencils of column f from the transformed tile.
 template <typename T, int XC>
-__device__ __forceinline__ C2<T> real_out(LTile<T> Z, const PassArgs& a, int f, int k) {
+__device__ __forceinline__ C2<T> real_out(LTile<T> Z, const PassArgs& a, int n, int f, int k) {
   if constexpr (XC == X_DST1) {
     const C2<T> v = Z.get((k + 1) * Z.S + f);
     return {-v.im, v.re};
   } else if constexpr (XC == X_DCT1) {
     return Z.get(k * Z.S + f);
   } else if constexpr (XC == X_DCT2 || XC == X_DST2) {
-    const int kk = XC == X_DST2 ? a.n - 1 - k : k;
+    const int kk = XC == X_DST2 ? n - 1 - k : k;
     return cmul(Z.get(kk * Z.S + f), ldc<T>(glb<T>(a.qtw), kk));
   } else if constexpr (XC == X_DHT) {
     // Z = X_a + i X_b with X_a, X_b Hermitian; H = Re X - Im X per pencil
@@ -596,8 +669,9 @@ __device__ __forceinline__ C2<T> real_out(LTile<T> Z, const PassArgs& a, int f, 
 }
 
 template <typename T, int XC>
-__device__ __forceinline__ void store_real_x(LTile<T> Z, void* dst, const PassArgs& a, const Tile& t) {
-  const int cnt = a.nout, jfast = a.out_jfast;
+__device__ __forceinline__ void store_real_x(LTile<T> Z, void* dst, const PassArgs& a, const Tile& t, int n,
+                                             int cnt) {
+  const int jfast = a.out_jfast;
   const int total = cnt << Z.lg;
   const unsigned mc = div_magic(cnt);
   HP_GLB T* out = (HP_GLB T*)dst + (long long)t.o * a.out_so + (long long)t.p0 * a.out_sp;
@@ -606,7 +680,7 @@ __device__ __forceinline__ void store_real_x(LTile<T> Z, void* dst, const PassAr
     int f, k;
     tile_fj(e, Z.lg, cnt, mc, jfast, f, k);
     if (2 * f >= t.np) continue;
-    const C2<T> v = real_out<T, XC>(Z, a, f, k);
+    const C2<T> v = real_out<T, XC>(Z, a, n, f, k);
     HP_GLB T* row = out + (long long)k * a.out_sj;
     if (pairs) {
       typename V2<T>::u w;
@@ -657,18 +731,26 @@ __device__ __forceinline__ void store_half(LTile<T> Z, void* dst, const PassArgs
 }
 
 template <typename T>
+__device__ __forceinline__ void store_real(LTile<T> Z, int x, void* dst, const PassArgs& a, const Tile& t, int n,
+                                           int cnt) {
+  switch (x) {
+    case X_DST1: store_real_x<T, X_DST1>(Z, dst, a, t, n, cnt); break;
+    case X_DST2: store_real_x<T, X_DST2>(Z, dst, a, t, n, cnt); break;
+    case X_DST3: store_real_x<T, X_DST3>(Z, dst, a, t, n, cnt); break;
+    case X_DCT1: store_real_x<T, X_DCT1>(Z, dst, a, t, n, cnt); break;
+    case X_DCT2: store_real_x<T, X_DCT2>(Z, dst, a, t, n, cnt); break;
+    case X_DHT: store_real_x<T, X_DHT>(Z, dst, a, t, n, cnt); break;
+    default: store_real_x<T, X_DCT3>(Z, dst, a, t, n, cnt); break;  // DCT-III, C2R, paired backward
+  }
+}
+
+template <typename T>
 __device__ __forceinline__ void store_out(LTile<T> Z, int x, void* dst, const PassArgs& a, const Tile& t) {
   switch (x) {
     case X_C2C_F: store_c2c<T>(Z, dst, a, t, false); break;
     case X_C2C_B: store_c2c<T>(Z, dst, a, t, true); break;
     case X_R2C: store_half<T>(Z, dst, a, t); break;
-    case X_DST1: store_real_x<T, X_DST1>(Z, dst, a, t); break;
-    case X_DST2: store_real_x<T, X_DST2>(Z, dst, a, t); break;
-    case X_DST3: store_real_x<T, X_DST3>(Z, dst, a, t); break;
-    case X_DCT1: store_real_x<T, X_DCT1>(Z, dst, a, t); break;
-    case X_DCT2: store_real_x<T, X_DCT2>(Z, dst, a, t); break;
-    case X_DHT: store_real_x<T, X_DHT>(Z, dst, a, t); break;
-    default: store_real_x<T, X_DCT3>(Z, dst, a, t); break;  // DCT-III, C2R, paired backward
+    default: store_real<T>(Z, x, dst, a, t, a.n, a.nout); break;
   }
 }
 
@@ -678,14 +760,16 @@ struct KIdx {
   int k0, k1, k2;
 };
 
+__device__ __forceinline__ double eigen_multiplier(const PassArgs& a, const KIdx& k) {
+  double lam = ((const HP_GLB double*)a.lam[0])[k.k0];
+  if (a.lam[1]) lam += ((const HP_GLB double*)a.lam[1])[k.k1];
+  if (a.lam[2]) lam += ((const HP_GLB double*)a.lam[2])[k.k2];
+  return lam == 0.0 ? 0.0 : a.norm / lam;
+}
+
 template <typename T>
 __device__ __forceinline__ T multiplier(const PassArgs& a, const KIdx& k) {
-  if (a.mult == M_EIGEN) {
-    double lam = ((const HP_GLB double*)a.lam[0])[k.k0];
-    if (a.lam[1]) lam += ((const HP_GLB double*)a.lam[1])[k.k1];
-    if (a.lam[2]) lam += ((const HP_GLB double*)a.lam[2])[k.k2];
-    return lam == 0.0 ? (T)0 : (T)(a.norm / lam);
-  }
+  if (a.mult == M_EIGEN) return (T)eigen_multiplier(a, k);
   if (a.mult == M_GREEN) {
     const int i0 = min(k.k0, a.gM[0] - k.k0);
     const int i1 = min(k.k1, a.gM[1] - k.k1);
@@ -718,7 +802,7 @@ __device__ __forceinline__ void oneway(const PassArgs& a, unsigned char* smem, c
   const LTile<T> Z = lds_tile<T>(smem, nf, a.L, 0);
   if (cplx) load_c2c<T>(Z, a.in[field], a, t, x == X_C2C_B);
   else if (x == X_C2R) load_half<T>(Z, a.in[field], a, t);
-  else load_real<T>(Z, a.in[field], x, a, t, has_face_terms(a));
+  else load_real<T>(Z, a.in[field], x, a, t, a.n, a.nin, has_face_terms(a));
   __syncthreads();
   fft_lds<T, MODE>(Z, Z.z + (size_t)a.L * Z.S, smem, a);
   store_out<T>(Z, x, a.out[field], a, t);
@@ -739,17 +823,17 @@ __device__ __forceinline__ void multiply_r2r(LTile<T> Z, const PassArgs& a, cons
   };
   for (int e = threadIdx.x; e < total; e += kThreads) {
     const int m = e >> Z.lg, f = e - (m << Z.lg);
-    const C2<T> v = scaled(real_out<T, XF>(Z, a, f, m), m, f);
+    const C2<T> v = scaled(real_out<T, XF>(Z, a, a.n, f, m), m, f);
     if constexpr (XF == X_DHT) {
       const int mm = m == 0 ? 0 : a.L - m;
       if (mm != m) {
-        const C2<T> w = scaled(real_out<T, XF>(Z, a, f, mm), mm, f);
-        extend<T, XB>(Z, f, mm, w, a);
+        const C2<T> w = scaled(real_out<T, XF>(Z, a, a.n, f, mm), mm, f);
+        extend<T, XB>(Z, f, mm, w, a, a.n);
       }
     }
-    extend<T, XB>(Z, f, m, v, a);
+    extend<T, XB>(Z, f, m, v, a, a.n);
   }
-  extend_zeros<T, XB>(Z, a, a.n);
+  extend_zeros<T, XB>(Z, a, a.n, a.n);
 }
 
 // Real-to-real sandwich (Dirichlet / Neumann / Hartley): forward R2R, multiply
@@ -758,7 +842,7 @@ template <typename T, int MODE>
 __device__ __forceinline__ void sandwich_r2r(const PassArgs& a, unsigned char* smem, const Tile& t, int field) {
   const LTile<T> Z = lds_tile<T>(smem, a.P / 2, a.L, 0);
   HP_LDS typename V2<T>::t* wR = Z.z + (size_t)a.L * Z.S;
-  load_real<T>(Z, a.in[field], a.xf, a, t, has_face_terms(a));
+  load_real<T>(Z, a.in[field], a.xf, a, t, a.n, a.nin, has_face_terms(a));
   __syncthreads();
   fft_lds<T, MODE>(Z, wR, smem, a);
   switch (a.xf) {
@@ -771,6 +855,175 @@ __device__ __forceinline__ void sandwich_r2r(const PassArgs& a, unsigned char* s
   __syncthreads();
   fft_lds<T, MODE>(Z, wR, smem, a);
   store_out<T>(Z, a.xb, a.out[field], a, t);
+}
+
+// Green's rows of a semi-unbounded plan's free axis.  Paired real pencils 2f,
+// 2f + 1 of the tile belong to different bounded modes, so they take different
+// real-even rows G_a, G_b.  The FFT Z of a + ib holds the Hermitian spectra
+// X_a = (Z_m + conj Z_-m) / 2 and X_b = (Z_m - conj Z_-m) / 2i; G_a X_a + i G_b X_b
+// recombines to Z'_m = A Z_m + B conj Z_-m with A = (G_a + G_b) / 2,
+// B = (G_a - G_b) / 2, the same A, B at -m.  One thread per bin pair (m, L - m).
+// ODD: also the rows of the kernel's derivative into D (bins i b_a, i b_b, b odd
+// in m): Z'_m = i (A Z_m + B conj Z_-m) and Z'_-m = -i (A Z_-m + B conj Z_m),
+// A, B from b_a, b_b at m.  Both with parts exchanged for the backward FFT.
+template <typename T, bool ODD>
+__device__ __forceinline__ void multiply_rows(LTile<T> S, LTile<T> D, const PassArgs& a, const Tile& t,
+                                              const FanJob* q) {
+  const int L = a.L, half = L / 2;
+  const unsigned mh = div_magic(half + 1);
+  auto row = [&](const void* g, int p, int m) -> T {
+    p = min(p, a.Np - 1);
+    const long long sj = a.ax_j == 0 ? a.g_s[0] : (a.ax_j == 1 ? a.g_s[1] : a.g_s[2]);
+    const long long sp = a.ax_p == 0 ? a.g_s[0] : (a.ax_p == 1 ? a.g_s[1] : a.g_s[2]);
+    long long off = (long long)m * sj + (long long)p * sp;
+    if (a.ax_o >= 0) off += (long long)t.o * (a.ax_o == 0 ? a.g_s[0] : (a.ax_o == 1 ? a.g_s[1] : a.g_s[2]));
+    return ((const HP_GLB T*)g)[off];
+  };
+  for (int e = threadIdx.x; e < ((half + 1) << S.lg); e += kThreads) {
+    const int f = div_by(e, half + 1, mh);
+    const int m = e - f * (half + 1);
+    const int mm = m == 0 ? 0 : L - m;
+    const int im = m * S.S + f, imm = mm * S.S + f;
+    const C2<T> zm = S.get(im), zmm = S.get(imm);
+    if constexpr (ODD) {
+      const T sc = (T)q->scale;
+      const T ga = sc * row(q->green_odd, t.p0 + 2 * f, m), gb = sc * row(q->green_odd, t.p0 + 2 * f + 1, m);
+      const T A = (T)0.5 * (ga + gb), B = (T)0.5 * (ga - gb);
+      const C2<T> ym = cadd(cscale(zm, A), cscale(cconj(zmm), B));    // times i, exchanged
+      const C2<T> ymm = cadd(cscale(zmm, A), cscale(cconj(zm), B));  // times -i, exchanged
+      D.put(im, {ym.re, -ym.im});
+      if (mm != m) D.put(imm, {-ymm.re, ymm.im});
+    }
+    const T ga = row(a.green, t.p0 + 2 * f, m), gb = row(a.green, t.p0 + 2 * f + 1, m);
+    const T A = (T)0.5 * (ga + gb), B = (T)0.5 * (ga - gb);
+    const C2<T> ym = cadd(cscale(zm, A), cscale(cconj(zmm), B));
+    const C2<T> ymm = cadd(cscale(zmm, A), cscale(cconj(zm), B));
+    S.put(im, {ym.im, ym.re});
+    if (mm != m) S.put(imm, {ymm.im, ymm.re});
+  }
+}
+
+// ------------------------------------------------------------- fan passes
+// One-way fan pass: the derivative first, then the plain transform, which may
+// replace the input in place (its tile is this workgroup's alone).
+template <typename T, int MODE>
+__device__ __forceinline__ void oneway_fan(const PassArgs& a, unsigned char* smem, const Tile& t, const FanJob& q) {
+  const LTile<T> Z = lds_tile<T>(smem, a.P / 2, a.L, 0);
+  HP_LDS typename V2<T>::t* wR = Z.z + (size_t)a.L * Z.S;
+  if (q.deriv) {
+    load_derivative<T>(Z, q, a, t);
+    __syncthreads();
+    fft_lds<T, MODE>(Z, wR, smem, a);
+    store_real<T>(Z, q.xd, q.deriv, a, t, q.nd, q.nd);
+    __syncthreads();
+  }
+  load_real<T>(Z, q.in, q.xp, a, t, q.n, q.n, false);
+  __syncthreads();
+  fft_lds<T, MODE>(Z, wR, smem, a);
+  store_real<T>(Z, q.xp, q.plain, a, t, q.n, q.n);
+}
+
+// multiply_r2r for both outputs: the multiplied spectrum into Z (plain) and,
+// times the derivative's factors, into D.  XD: the derivative's transform
+// (the Laplacian's is XB).
+template <typename T, int XF, int XB, int XD>
+__device__ __forceinline__ void multiply_r2r_fan(LTile<T> Z, LTile<T> D, const PassArgs& a, const Tile& t,
+                                                 const FanJob& q) {
+  const int rows = XF == X_DHT ? a.n / 2 + 1 : a.n;
+  const int total = rows << Z.lg;
+  auto axis_w2 = [&](int b, int k) {
+    const int bs = b == 0 ? a.basis[0] : (b == 1 ? a.basis[1] : a.basis[2]);
+    const int n = b == 0 ? a.nunk[0] : (b == 1 ? a.nunk[1] : a.nunk[2]);
+    const double kc = b == 0 ? a.kc[0] : (b == 1 ? a.kc[1] : a.kc[2]);
+    const int kk = bs == FB_HARTLEY ? (2 * k < n ? k : (2 * k == n ? 0 : k - n)) : (bs == FB_SINE ? k + 1 : k);
+    const double w = kc * (double)kk;
+    return w * w;
+  };
+  // plain and derivative value of bin m of column f from the spectra s
+  auto both = [&](C2<T> s, int m, int f, C2<T>& d) {
+    const KIdx ka = spectral_index(a, m, t.p0 + 2 * f, t.o), kb = spectral_index(a, m, t.p0 + 2 * f + 1, t.o);
+    const double ma = eigen_multiplier(a, ka), mb = eigen_multiplier(a, kb);
+    double fa, fb;
+    if (q.basis == FB_LAP) {
+      fa = -q.scale * (axis_w2(0, ka.k0) + axis_w2(1, ka.k1) + axis_w2(2, ka.k2));
+      fb = -q.scale * (axis_w2(0, kb.k0) + axis_w2(1, kb.k1) + axis_w2(2, kb.k2));
+    } else {
+      fa = fb = fan_factor(q, m);
+    }
+    d = {s.re * (T)(ma * fa), s.im * (T)(mb * fb)};
+    return C2<T>{s.re * (T)ma, s.im * (T)mb};
+  };
+  for (int e = threadIdx.x; e < total; e += kThreads) {
+    const int m = e >> Z.lg, f = e - (m << Z.lg);
+    C2<T> d;
+    const C2<T> v = both(real_out<T, XF>(Z, a, a.n, f, m), m, f, d);
+    if constexpr (XF == X_DHT) {
+      const int mm = m == 0 ? 0 : a.L - m;
+      if (mm != m) {
+        C2<T> dm;
+        const C2<T> w = both(real_out<T, XF>(Z, a, a.n, f, mm), mm, f, dm);
+        extend<T, XB>(Z, f, mm, w, a, a.n);
+        extend_derivative<T, XD>(D, f, mm, dm, q, a);
+      }
+    }
+    extend<T, XB>(Z, f, m, v, a, a.n);
+    extend_derivative<T, XD>(D, f, m, d, q, a);
+  }
+  extend_zeros<T, XB>(Z, a, a.n, a.n);
+  extend_zeros<T, XD>(D, a, q.nd, q.nd);
+}
+
+// Real-to-real fan sandwich: forward, multiplier, and two backward transforms.
+template <typename T, int MODE>
+__device__ __forceinline__ void sandwich_r2r_fan(const PassArgs& a, unsigned char* smem, const Tile& t,
+                                                 const FanJob& q) {
+  const LTile<T> Z = lds_tile<T>(smem, a.P / 2, a.L, 0), D = lds_tile<T>(smem, a.P / 2, a.L, 1);
+  HP_LDS typename V2<T>::t* wR = D.z + (size_t)a.L * Z.S;
+  load_real<T>(Z, q.in, a.xf, a, t, a.n, a.n, has_face_terms(a));
+  __syncthreads();
+  fft_lds<T, MODE>(Z, wR, smem, a);
+  const bool lap = q.basis == FB_LAP;
+  switch (a.xf) {
+    case X_DST1:
+      if (lap) multiply_r2r_fan<T, X_DST1, X_DST1, X_DST1>(Z, D, a, t, q);
+      else multiply_r2r_fan<T, X_DST1, X_DST1, X_DCT1>(Z, D, a, t, q);
+      break;
+    case X_DST2:
+      if (lap) multiply_r2r_fan<T, X_DST2, X_DST3, X_DST3>(Z, D, a, t, q);
+      else multiply_r2r_fan<T, X_DST2, X_DST3, X_DCT3>(Z, D, a, t, q);
+      break;
+    case X_DCT1:
+      if (lap) multiply_r2r_fan<T, X_DCT1, X_DCT1, X_DCT1>(Z, D, a, t, q);
+      else multiply_r2r_fan<T, X_DCT1, X_DCT1, X_DST1>(Z, D, a, t, q);
+      break;
+    case X_DCT2:
+      if (lap) multiply_r2r_fan<T, X_DCT2, X_DCT3, X_DCT3>(Z, D, a, t, q);
+      else multiply_r2r_fan<T, X_DCT2, X_DCT3, X_DST3>(Z, D, a, t, q);
+      break;
+    default: multiply_r2r_fan<T, X_DHT, X_DHT, X_DHT>(Z, D, a, t, q); break;
+  }
+  __syncthreads();
+  fft_lds<T, MODE>(D, wR, smem, a);
+  fft_lds<T, MODE>(Z, wR, smem, a);
+  store_real<T>(D, q.xd, q.deriv, a, t, q.nd, q.nd);
+  store_real<T>(Z, a.xb, q.plain, a, t, a.n, a.n);
+}
+
+// Free-axis fan sandwich (Green's rows): psi and its free-axis derivative.
+template <typename T, int MODE>
+__device__ __forceinline__ void sandwich_rows_fan(const PassArgs& a, unsigned char* smem, const Tile& t,
+                                                  const FanJob& q) {
+  const LTile<T> Z = lds_tile<T>(smem, a.P / 2, a.L, 0), D = lds_tile<T>(smem, a.P / 2, a.L, 1);
+  HP_LDS typename V2<T>::t* wR = D.z + (size_t)a.L * Z.S;
+  load_real<T>(Z, q.in, X_PAIR_F, a, t, a.n, a.nin, false);
+  __syncthreads();
+  fft_lds<T, MODE>(Z, wR, smem, a);
+  multiply_rows<T, true>(Z, D, a, t, &q);
+  __syncthreads();
+  fft_lds<T, MODE>(D, wR, smem, a);
+  fft_lds<T, MODE>(Z, wR, smem, a);
+  store_real<T>(D, X_PAIR_B, q.deriv, a, t, a.n, a.nout);
+  store_real<T>(Z, X_PAIR_B, q.plain, a, t, a.n, a.nout);
 }
 
 // Complex sandwich (periodic after R2C, unbounded, 1D periodic pairs):
@@ -794,7 +1047,7 @@ __device__ __forceinline__ void sandwich_c2c(const PassArgs& a, unsigned char* s
   auto tile = [&](int c) { return LTile<T>{S.z + (size_t)c * tileC, S.S, S.lg}; };
 
   auto load_into = [&](LTile<T> dst, const void* src) {
-    if (pair) load_real<T>(dst, src, X_PAIR_F, a, t, false);
+    if (pair) load_real<T>(dst, src, X_PAIR_F, a, t, a.n, a.nin, false);
     else load_c2c<T>(dst, src, a, t, false);
     __syncthreads();
     fft_lds<T, MODE>(dst, wR, smem, a);
@@ -867,41 +1120,8 @@ __device__ __forceinline__ void sandwich_c2c(const PassArgs& a, unsigned char* s
   // The multiplied spectra S keep their parts in place while derivative
   // outputs still read them, and are exchanged for the backward FFT otherwise.
   const bool derivs = a.diff == D_GRAD || a.diff == D_CURL || a.diff == D_DIV || a.diff == D_NABLA;
-  if (a.mult == M_GREEN_ROWS || a.mult == M_GREEN_ROWS_ODD) {
-    // Paired real pencils 2f, 2f + 1 of the tile belong to different bounded
-    // modes, so they take different real-even Green's rows G_a, G_b.  The FFT
-    // Z of a + ib holds the Hermitian spectra X_a = (Z_m + conj Z_-m) / 2 and
-    // X_b = (Z_m - conj Z_-m) / 2i; G_a X_a + i G_b X_b recombines to
-    // Z'_m = A Z_m + B conj Z_-m with A = (G_a + G_b) / 2, B = (G_a - G_b) / 2,
-    // the same A, B at -m.  One thread per bin pair (m, L - m).  Odd rows
-    // (bins i b_a, i b_b, b odd in m): Z'_m = i (A Z_m + B conj Z_-m) and
-    // Z'_-m = -i (A Z_-m + B conj Z_m), A, B from b_a, b_b at m.
-    const int half = L / 2;
-    const unsigned mh = div_magic(half + 1);
-    const bool odd = a.mult == M_GREEN_ROWS_ODD;
-    auto row = [&](int p, int m) -> T {
-      p = min(p, a.Np - 1);
-      long long off = (long long)m * a.g_s[a.ax_j] + (long long)p * a.g_s[a.ax_p];
-      if (a.ax_o >= 0) off += (long long)t.o * a.g_s[a.ax_o];
-      return ((const HP_GLB T*)a.green)[off];
-    };
-    for (int e = threadIdx.x; e < ((half + 1) << S.lg); e += kThreads) {
-      const int f = div_by(e, half + 1, mh);
-      const int m = e - f * (half + 1);
-      const int mm = m == 0 ? 0 : L - m;
-      const T ga = row(t.p0 + 2 * f, m), gb = row(t.p0 + 2 * f + 1, m);
-      const T A = (T)0.5 * (ga + gb), B = (T)0.5 * (ga - gb);
-      const int im = m * S.S + f, imm = mm * S.S + f;
-      const C2<T> zm = S.get(im), zmm = S.get(imm);
-      C2<T> ym = cadd(cscale(zm, A), cscale(cconj(zmm), B));
-      C2<T> ymm = cadd(cscale(zmm, A), cscale(cconj(zm), B));
-      if (odd) {
-        ym = cmuli(ym);
-        ymm = cscale(cmuli(ymm), (T)-1);
-      }
-      S.put(im, {ym.im, ym.re});
-      if (mm != m) S.put(imm, {ymm.im, ymm.re});
-    }
+  if (a.mult == M_GREEN_ROWS) {
+    multiply_rows<T, false>(S, S, a, t, nullptr);
   } else {
     // multiply by the spectral multiplier
     each([&](int z, const KIdx& k) {
@@ -956,41 +1176,38 @@ __device__ __forceinline__ void sandwich_c2c(const PassArgs& a, unsigned char* s
   }
 }
 
-// The pass descriptor where the launch put it (the kernels' only argument).
-// Read as a parameter it is copied to scratch memory once its uses are many.
-// One word of every 64-byte line of it is read at once first: the fields are
-// read where they are needed, and each line's first read would be a miss of
-// the scalar cache of its own in the chain of a workgroup.
-__device__ __forceinline__ const PassArgs& kernel_args() {
-  typedef const volatile __attribute__((address_space(4))) int* cptr;
-  const cptr w = (cptr)__builtin_amdgcn_kernarg_segment_ptr();
-  int x[(sizeof(PassArgs) + 63) / 64];
-#pragma unroll
-  for (unsigned i = 0; i < sizeof(x) / sizeof(x[0]); ++i) x[i] = w[16 * i];
-#pragma unroll
-  for (unsigned i = 0; i < sizeof(x) / sizeof(x[0]); ++i) asm volatile("" ::"s"(x[i]));
-  return *(const PassArgs*)(const __attribute__((address_space(4))) PassArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-}
-
 template <typename T, int MODE>
 __global__ void __launch_bounds__(kThreads) k_oneway(const PassArgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const PassArgs& a = kernel_args();
-  oneway<T, MODE>(a, smem, tile_of<T>(a), blockIdx.y);
+  oneway<T, MODE>(a, smem, tile_of<T>(a, a.Np), blockIdx.y);
 }
 
 template <typename T, int MODE>
 __global__ void __launch_bounds__(kThreads) k_sandwich_c2c(const PassArgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const PassArgs& a = kernel_args();
-  sandwich_c2c<T, MODE>(a, smem, tile_of<T>(a));
+  sandwich_c2c<T, MODE>(a, smem, tile_of<T>(a, a.Np));
 }
 
 template <typename T, int MODE>
 __global__ void __launch_bounds__(kThreads) k_sandwich_r2r(const PassArgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const PassArgs& a = kernel_args();
-  sandwich_r2r<T, MODE>(a, smem, tile_of<T>(a), blockIdx.y);
+  sandwich_r2r<T, MODE>(a, smem, tile_of<T>(a, a.Np), blockIdx.y);
+}
+
+// KIND: 0 one-way, 1 real-to-real sandwich, 2 free-axis sandwich.
+template <typename T, int MODE, int KIND>
+__global__ void __launch_bounds__(kThreads) k_fan(const PassArgs) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const PassArgs& a = kernel_args();
+  const FanJob& q = a.fan[blockIdx.y];
+  const Tile t = tile_of<T>(a, q.Np);
+  if (t.o >= q.No) return;  // fewer tiles than the largest job: whole workgroup
+  if constexpr (KIND == 0) oneway_fan<T, MODE>(a, smem, t, q);
+  else if constexpr (KIND == 1) sandwich_r2r_fan<T, MODE>(a, smem, t, q);
+  else sandwich_rows_fan<T, MODE>(a, smem, t, q);
 }
 
 template <auto K>
@@ -1011,9 +1228,19 @@ static void allow_lds() {
   }
 }
 
+template <typename T, int MODE, int KIND>
+static void launch_fan(const PassArgs& a, dim3 grid, hipStream_t s) {
+  allow_lds<k_fan<T, MODE, KIND>>();
+  hipLaunchKernelGGL((k_fan<T, MODE, KIND>), grid, dim3(kThreads), a.lds_bytes, s, a);
+}
+
 template <typename T, int MODE>
 static void launch_t(const PassArgs& a, dim3 grid, hipStream_t s) {
-  if (a.kind == PK_ONEWAY) {
+  if (a.nfan > 0) {
+    if (a.kind == PK_ONEWAY) launch_fan<T, MODE, 0>(a, grid, s);
+    else if (a.mult == M_GREEN_ROWS) launch_fan<T, MODE, 2>(a, grid, s);
+    else launch_fan<T, MODE, 1>(a, grid, s);
+  } else if (a.kind == PK_ONEWAY) {
     allow_lds<k_oneway<T, MODE>>();
     hipLaunchKernelGGL((k_oneway<T, MODE>), grid, dim3(kThreads), a.lds_bytes, s, a);
   } else if (a.xf == X_C2C_F || a.xf == X_PAIR_F) {
@@ -1044,20 +1271,17 @@ static void launch_mode(const PassArgs& a, int mode, dim3 grid, hipStream_t s) {
   else launch_t<T, GM_SMALL>(a, grid, s);
 }
 
-// Every stage of the pass has room for its butterflies in the threads'
-// registers, and the tile (with the prime stage's table) in LDS.
-bool general_fits(const PassArgs& a, int prec) {
-  const int maxe = (a.big ? 32 : 16) / (prec == 0 ? 1 : 2);
-  const bool cplx = a.xf == X_C2C_F || a.xf == X_C2C_B;
-  const long long nf = cplx ? a.P : a.P / 2;
-  if (nf < 1 || (nf & (nf - 1)) || a.L < 1 || a.L > 8192 || a.nin > a.L + 1 || a.nout > a.L + 1) return false;
+// Every stage has room for its butterflies in the threads' registers (nf
+// transforms of length L in a tile), and the radices make up L.
+bool stages_fit(int L, long long nf, const int* radix, int nstage, int big, int prec) {
+  const int maxe = (big ? 32 : 16) / (prec == 0 ? 1 : 2);
   long long prod = 1;
-  for (int s = 0; s < a.nstage; ++s) {
-    const int R = a.radix[s];
+  for (int s = 0; s < nstage; ++s) {
+    const int R = radix[s];
     if (R < 2) return false;
     prod *= R;
-    if (a.L % prod != 0) return false;
-    const long long nbl = a.L / R;
+    if (L % prod != 0) return false;
+    const long long nbl = L / R;
     if (R <= max_radix(prec)) {
       if (nf * nbl > (long long)(prec == 0 ? stage_slots<float>(R, maxe) : stage_slots<double>(R, maxe)) * kThreads)
         return false;
@@ -1067,7 +1291,14 @@ bool general_fits(const PassArgs& a, int prec) {
       if (nf * nbl * nb > (long long)std::max(2, maxe * 3 / 16) * kThreads) return false;
     }
   }
-  return prod == a.L;
+  return prod == L;
+}
+
+bool general_fits(const PassArgs& a, int prec) {
+  const bool cplx = a.xf == X_C2C_F || a.xf == X_C2C_B;
+  const long long nf = cplx ? a.P : a.P / 2;
+  if (nf < 1 || (nf & (nf - 1)) || a.L < 1 || a.L > 8192 || a.nin > a.L + 1 || a.nout > a.L + 1) return false;
+  return stages_fit(a.L, nf, a.radix, a.nstage, a.big, prec);
 }
 
 // LDS bytes of a general pass of tile width P: its FFT tiles (nS coupled
@@ -1082,6 +1313,7 @@ int general_lds_bytes(const PassArgs& a, int P, int prec) {
     const int nS = diff_is_adjoint(a.diff) ? a.n_out : a.n_in;
     tiles = a.diff == D_NONE ? nS : nS + 1;
   }
+  if (a.nfan > 0) tiles = a.kind == PK_SANDWICH ? 2 : 1;
   int table = 0;
   for (int s = 0; s < a.nstage; ++s)
     if (a.radix[s] > max_radix(prec)) table = std::max(table, a.radix[s]);
@@ -1092,7 +1324,19 @@ int general_lds_bytes(const PassArgs& a, int P, int prec) {
 
 hipError_t launch_pass(const PassArgs& a, int prec, int grid_y, hipStream_t s) {
   if (!general_fits(a, prec) || general_lds_bytes(a, a.P, prec) > a.lds_bytes) return hipErrorInvalidValue;
-  const int tiles = ((a.Np + a.P - 1) / a.P) * a.No;
+  int tiles = ((a.Np + a.P - 1) / a.P) * a.No;
+  if (a.nfan > 0) {
+    // jobs fit the pass: sizes within the FFT input, a sandwich one job with
+    // both outputs
+    if (a.nfan > kMaxFan || (a.kind == PK_SANDWICH && (a.nfan != 1 || !a.fan[0].deriv))) return hipErrorInvalidValue;
+    for (int i = 0; i < a.nfan; ++i) {
+      const FanJob& q = a.fan[i];
+      if (!q.in || !q.plain || q.n < 1 || q.n > a.L || (q.deriv && (q.nd < 0 || q.nd > a.L)) || q.Np < 1 || q.No < 1)
+        return hipErrorInvalidValue;
+      tiles = std::max(tiles, ((q.Np + a.P - 1) / a.P) * q.No);
+    }
+    grid_y = a.nfan;
+  }
   dim3 grid(tiles, grid_y);
   const int mode = gen_mode(a, prec);
   if (prec == 0) launch_mode<float>(a, mode, grid, s);
@@ -1539,53 +1783,44 @@ hipError_t launch_semi_green(void* out, const double* lam1, int n1, const double
   return hipGetLastError();
 }
 
-struct FacePtrs {
-  const void* f[3][2];
-};
-
-// Boundary nodes of the REGULAR Dirichlet axes (bit a of `axes`) of an
-// output [N0][N1][N2]: block row blockIdx.y = 2 a + side walks face (a, side)
-// only, one thread per node, the node's other two coordinates row-major (the
-// face array's own index).  A node on several such faces is written once, by
+// Boundary nodes of the fields of a solve (FillArgs): block row blockIdx.y =
+// 2 a + side walks face (a, side) of field blockIdx.z only, one thread per
+// node, the node's other two coordinates row-major (the face array's own
+// index).  A node on several faces of the field's mask is written once, by
 // the face of its highest axis.  32-bit node indices within a face: the
 // launch refuses faces of 2^30 nodes or more.
 template <typename T>
-__global__ void k_dirichlet_fill(T* out, int N0, int N1, int N2, int ndim, int axes, FacePtrs fp) {
-  const int N[3] = {N0, N1, N2};
+__global__ void k_boundary_fill(const FillArgs p) {
+  const int fld = blockIdx.z, axes = p.axes[fld];
+  const int N[3] = {p.N[0], p.N[1], p.N[2]};
   const int a = blockIdx.y >> 1, side = blockIdx.y & 1;
-  if (a >= ndim || !((axes >> a) & 1)) return;
+  if (a >= p.ndim || !((axes >> a) & 1)) return;
   const int o0 = a == 0 ? 1 : 0, o1 = a == 2 ? 1 : 2;  // the other axes, in order
   const int n1 = N[o1], fsize = N[o0] * N[o1];
-  const T* g = (const T*)fp.f[a][side];
-  const long long st[3] = {(long long)N1 * N2, (long long)N2, 1LL};
+  const T* g = (const T*)p.face[fld][a][side];
+  T* out = (T*)p.out[fld];
+  const long long st[3] = {(long long)N[1] * N[2], (long long)N[2], 1LL};
   for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < fsize; j += gridDim.x * blockDim.x) {
     int c[3];
     c[a] = side ? N[a] - 1 : 0;
     c[o0] = j / n1;
     c[o1] = j - c[o0] * n1;
     bool own = true;
-    for (int b = a + 1; b < ndim; ++b)
+    for (int b = a + 1; b < p.ndim; ++b)
       if (((axes >> b) & 1) && (c[b] == 0 || c[b] == N[b] - 1)) own = false;
     if (!own) continue;
     out[c[0] * st[0] + c[1] * st[1] + c[2] * st[2]] = g ? g[j] : (T)0;
   }
 }
 
-hipError_t launch_dirichlet_fill(void* out, const int N[3], int ndim, int axes, const void* face[3][2],
-                                 int prec, hipStream_t s) {
-  FacePtrs fp;
-  for (int a = 0; a < 3; ++a)
-    for (int b = 0; b < 2; ++b) fp.f[a][b] = face[a][b];
+hipError_t launch_boundary_fill(const FillArgs& a, int prec, hipStream_t s) {
+  if (a.nf < 1 || a.nf > kMaxFill) return hipErrorInvalidValue;
   long long fmax = 1;
-  for (int a = 0; a < 3; ++a) fmax = std::max(fmax, (long long)N[0] * N[1] * N[2] / std::max(N[a], 1));
+  for (int b = 0; b < 3; ++b) fmax = std::max(fmax, (long long)a.N[0] * a.N[1] * a.N[2] / std::max(a.N[b], 1));
   if (fmax >= (1LL << 30)) return hipErrorInvalidValue;
-  const int bx = (int)std::min<long long>((fmax + 255) / 256, 1024);
-  if (prec == 0)
-    hipLaunchKernelGGL(k_dirichlet_fill<float>, dim3(bx, 6), dim3(256), 0, s, (float*)out, N[0],
-                       N[1], N[2], ndim, axes, fp);
-  else
-    hipLaunchKernelGGL(k_dirichlet_fill<double>, dim3(bx, 6), dim3(256), 0, s, (double*)out, N[0],
-                       N[1], N[2], ndim, axes, fp);
+  const dim3 grid((unsigned)std::min<long long>((fmax + 255) / 256, 1024), 6, (unsigned)a.nf);
+  if (prec == 0) hipLaunchKernelGGL(k_boundary_fill<float>, grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(k_boundary_fill<double>, grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -24,6 +24,7 @@ struct PassRec {
   PassArgs a;
   int grid_y;
   double bytes = -1.0;  // algorithmic bytes when set by the planner
+  FillArgs fill{};      // FAST_FILL
 };
 
 struct Problem {
@@ -42,7 +43,6 @@ struct Problem {
   void* own_in[kMaxFields] = {};
   void* own_out[3] = {};
   void* own_der[3] = {};
-  void* grad_s = nullptr;  // Dirichlet / Neumann gradient: transformed source
   void* dtmp[3] = {};      // Dirichlet / Neumann DIV / CURL: second derivative terms
   void* own_face[3][2][3] = {};
   std::vector<void*> a1, b2, c2, c1;  // unbounded / periodic workspaces
@@ -105,6 +105,7 @@ struct hp_plan_s {
   std::vector<hp::PassRec> batch_passes;
   int batch_tiles = 0;  // tiles per work item (0: the default)
   double* zm_partial = nullptr;  // per-block partial sums of the zero-mode query
+  std::map<unsigned long long, hp::PassArgs> tiles;  // default tiles of the general passes by signature
   // autotuning (hp_autotune): chosen configurations by pass signature, the
   // number of signatures that left the default, and the summed per-pass
   // times of the default and chosen configurations measured while tuning
