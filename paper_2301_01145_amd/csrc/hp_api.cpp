@@ -1682,6 +1682,29 @@ bool fast_unbounded_ok(hp_plan p, const Problem& P) {
   return true;
 }
 
+// Whether a wavefront pass stores its output of `bytes` streaming
+// (nontemporal).  Stored through the caches instead, the output is still in
+// the 256 MB Infinity Cache when the next pass reads it, which pays from about
+// the size of the eight L2s up to that of the cache (kernel traces, producer +
+// consumer in us, streaming against through the caches):
+//   R2C -> y pass:      25 MB 24.6, 23.8; 135 MB 120.2, 96.8; 8 MB 15.9, 17.5;
+//                       404 MB 352.6, 376.7
+//   y -> x pass:        25 MB 34.1, 33.7; 135 MB 162.1, 139.7; 17 MB 24.5, 25.1;
+//                       406 MB even.  Periodic plans only: the x pass of a
+//                       free-space plan keeps its Green's rows in the caches
+//                       (135 MB 124.0, 135.1)
+//   x -> y pass back:   42 MB 44.0, 40.5; 168 MB 159.4, 139.8; 8 MB 16.6, 18.1;
+//                       338 MB 292.1, 302.6
+//   y back -> C2R pass: 51 MB 49.5, 42.2; 113 MB 89.9, 80.5; 9 MB 21.3, 20.1;
+//                       390 MB 299.2, 324.5
+// The fields that the C2R pass writes leave the solve and stay streaming (no
+// reader; cached they displace the next solve's input: R2C 82 -> 89 us).
+bool stream_out(int kind, bool periodic, double bytes) {
+  constexpr double kMiB = 1024.0 * 1024.0;
+  if (kind == FAST_C2R || (kind == FAST_FWD_Y && !periodic)) return true;
+  return bytes < (kind == FAST_INV_Y ? 8 : 20) * kMiB || bytes > 256 * kMiB;
+}
+
 // Free-space passes, or (periodic) the same five passes on undoubled
 // pencils with the Table 1 eigenvalue multiplier in place of the Green's
 // function.
@@ -1761,6 +1784,7 @@ hp_status passes_unbounded_fast(hp_plan p, Problem& P, bool adjoint, std::vector
     for (int f = 0; f < n_src; ++f) { r.a.in[f] = src[f]; r.a.out[f] = P.a1[f]; }
     r.grid_y = n_src;
     r.bytes = n_live * ((double)n0 * n1 * n2 * es + (double)n0 * K2 * n1 * cs);
+    r.a.stream = stream_out(FAST_R2C, periodic, n_live * (double)n0 * K2 * n1 * cs);
   }
   // P2 - P4 per kz slab (one slab covering all K2 planes unless HP_SLAB set)
   for (const auto& slab : P.slabs) {
@@ -1774,6 +1798,7 @@ hp_status passes_unbounded_fast(hp_plan p, Problem& P, bool adjoint, std::vector
       for (int f = 0; f < n_src; ++f) { r.a.in[f] = src[f] ? P.a1[f] : nullptr; r.a.out[f] = P.b2[f]; }
       r.grid_y = n_src;
       r.bytes = n_live * ((double)n0 * kc * n1 * cs + (double)kc * M1 * n0 * cs);
+      r.a.stream = stream_out(FAST_FWD_Y, periodic, n_live * (double)kc * M1 * n0 * cs);
     }
     // P3: sandwich along x into C2
     HP_TRY(base(FAST_SANDWICH, M0));
@@ -1799,6 +1824,7 @@ hp_status passes_unbounded_fast(hp_plan p, Problem& P, bool adjoint, std::vector
                      ? nc : 1;
       const double oct = periodic ? 0.0 : (double)(M0 / 2 + 1) * (M1 / 2 + 1) * kc * es;
       r.bytes = (n_live + n_mid) * (double)kc * M1 * n0 * cs + oct;
+      a.stream = stream_out(FAST_SANDWICH, periodic, n_mid * (double)kc * M1 * n0 * cs);
     }
     // P4: backward C2C along y (with derivative completion) into C1 (= A1 buffers)
     HP_TRY(base(FAST_INV_Y, M1));
@@ -1811,6 +1837,7 @@ hp_status passes_unbounded_fast(hp_plan p, Problem& P, bool adjoint, std::vector
       for (int f = 0; f < n_dst; ++f) r.a.out[f] = P.c1.empty() ? P.a1[f] : P.c1[f];
       r.grid_y = iy_mode == IY_PLAIN ? n_mid : (iy_mode == IY_CURL5 ? 2 : 1);
       r.bytes = n_mid * (double)kc * n0 * M1 * cs + n_dst * (double)n1 * n0 * kc * cs;
+      r.a.stream = stream_out(FAST_INV_Y, periodic, n_dst * (double)n1 * n0 * K2 * cs);
     }
   }
   // P5: C2R along z into the destination arrays
@@ -1820,6 +1847,7 @@ hp_status passes_unbounded_fast(hp_plan p, Problem& P, bool adjoint, std::vector
     for (int f = 0; f < n_dst; ++f) { r.a.in[f] = P.c1.empty() ? P.a1[f] : P.c1[f]; r.a.out[f] = dst[f]; }
     r.grid_y = n_dst;
     r.bytes = n_dst * ((double)n1 * n0 * K2 * cs + (double)n0 * n1 * n2 * es);
+    r.a.stream = stream_out(FAST_C2R, periodic, 0.0);
   }
   return HP_OK;
 }

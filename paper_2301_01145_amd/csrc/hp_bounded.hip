@@ -369,8 +369,10 @@ __global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
 // transformed for the plain output and the derivative along the pencil.  One
 // launch holds every array of a pass (job = blockIdx.y): the gradient of a 3D
 // Dirichlet solve is 5 launches where one launch per array, with elementwise
-// passes for the coefficients, was 16 (128^3 FP32 with its gradient: 85 us, was
-// 168).
+// passes for the coefficients, was 16 (128^3 FP32 with its gradient: 81 us, was
+// 168).  Rows off the cache lines are stored through the caches, where the parts
+// of a line merge (127 points a row: 81 us, 85 streaming); aligned ones stream
+// (256^3: 457 us, 462 through the caches).
 namespace {
 
 // The backward (forward) type as a compile-time constant.
@@ -391,6 +393,12 @@ __device__ __forceinline__ void with_forward(int x, F&& f) {
     case X_DCT1: f(std::integral_constant<int, X_DCT1>{}); break;
     default: f(std::integral_constant<int, X_DCT2>{}); break;
   }
+}
+// The stores of a fan pass, through the caches or streaming.
+template <class F>
+__device__ __forceinline__ void fan_stores(bool cached, F&& f) {
+  if (cached) f(std::false_type{});
+  else f(std::true_type{});
 }
 // Backward type of the derivative of a series with backward type x.
 __host__ __device__ constexpr int r2r_other_parity(int x) {
@@ -424,7 +432,8 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const Pass
   T* R = (T*)slot;  // the pair's reals, pencil b after pencil a
   const int pairs_p = (job.Np + 1) / 2;
   const long long total = (long long)pairs_p * job.No;
-  const int blk = off_lines(a, sizeof(T), sizeof(T)) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const bool cached = off_lines(a, sizeof(T), sizeof(T));
+  const int blk = cached ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const long long pr = ((long long)blk * kR2RContigWaves + wave) * PPW + qq;
   const bool valid = pr < total;
   const int o = valid ? (int)(pr / pairs_p) : 0;
@@ -447,14 +456,16 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const Pass
     T* out = (T*)dst;
     C2<T> v[R0];
     r2r_fft<T, L>(v, X, cnt, slot, g, tw, q, [&](int s, int w) { return R[w * cnt + s]; });
+    fan_stores(cached, [&](auto ST) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < R0; ++i) {
-      T oa, obv;
-      const int k = r2r_extract<T>(X, g + G * i, cnt, v[i], q, oa, obv);
-      if (k < 0) continue;
-      if (valid) st_stream(&out[ob + (long long)k * a.out_sj], oa);
-      if (vb) st_stream(&out[ob + a.out_sp + (long long)k * a.out_sj], obv);
-    }
+      for (int i = 0; i < R0; ++i) {
+        T oa, obv;
+        const int k = r2r_extract<T>(X, g + G * i, cnt, v[i], q, oa, obv);
+        if (k < 0) continue;
+        if (valid) st_out<decltype(ST)::value>(&out[ob + (long long)k * a.out_sj], oa);
+        if (vb) st_out<decltype(ST)::value>(&out[ob + a.out_sp + (long long)k * a.out_sj], obv);
+      }
+    });
     wave_sync();  // the slot is filled again
   };
   if (job.deriv) {
@@ -504,7 +515,8 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
   T* tile = (T*)(slots + W * PPW * slot_len(L));
   T* dtile = tile + n * TS;
   const int tiles_p = (job.Np + P - 1) / P;
-  const int t = off_lines(a, sizeof(T), sizeof(T)) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const bool cached = off_lines(a, sizeof(T), sizeof(T));
+  const int t = cached ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   if (t >= tiles_p * job.No) return;  // whole workgroup
   for (int m = threadIdx.x; m < L; m += NT) tw[m] = ((const C2<T>*)a.tw)[m];
   if (a.qtw)
@@ -617,10 +629,12 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
   const long long ob = (long long)o * a.out_so + (long long)p0 * a.out_sp;
   auto store = [&](const T* src, int cnt, void* dst) {
     T* out = (T*)dst;
-    for (int e = threadIdx.x; e < cnt * P; e += NT) {
-      const int j = e / P, c = e - (e / P) * P;
-      if (c < np) st_stream(&out[ob + (long long)j * a.out_sj + (long long)c * a.out_sp], src[j * TS + c]);
-    }
+    fan_stores(cached, [&](auto ST) __attribute__((always_inline)) {
+      for (int e = threadIdx.x; e < cnt * P; e += NT) {
+        const int j = e / P, c = e - (e / P) * P;
+        if (c < np) st_out<decltype(ST)::value>(&out[ob + (long long)j * a.out_sj + (long long)c * a.out_sp], src[j * TS + c]);
+      }
+    });
   };
   if (job.deriv) store(dtile, nd, job.deriv);
   store(tile, n, job.plain);
@@ -640,7 +654,9 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
 //     group of W wavefronts).
 // LDS: twiddles [L] | quarter twists [L/2 + 1] | exchange slots | S tiles.
 // Four wavefronts per workgroup keep the exchange slots small enough for
-// three or four workgroups per CU at every length.
+// three or four workgroups per CU at every length.  Stores go through the
+// caches, never slower than streaming (64 problems of 64^3: 267 us, 279; 64 of
+// 128^3, beyond the caches: 1918, 1917).
 constexpr int kBatchWaves = 4;
 
 namespace {
@@ -769,8 +785,8 @@ __device__ __forceinline__ void bw_contig(const BwArgs& a, unsigned char* smem, 
       T oa, obv;
       const int kk = r2r_extract<T>(X, g + G * i, n, v[i], q, oa, obv);
       if (kk < 0) continue;
-      if (valid) st_stream(&a.out[ob + (long long)kk * a.out_sj], oa);
-      if (vb) st_stream(&a.out[ob + a.out_sp + (long long)kk * a.out_sj], obv);
+      if (valid) a.out[ob + (long long)kk * a.out_sj] = oa;
+      if (vb) a.out[ob + a.out_sp + (long long)kk * a.out_sj] = obv;
     }
     wave_sync();  // the slot is reused by the next pair
   }
@@ -858,7 +874,7 @@ __device__ __forceinline__ void bw_strided(const BwArgs& a, unsigned char* smem,
     const long long ob = (long long)o * a.out_so + (long long)p0 * a.out_sp;
     for (int e = ts; e < n * P; e += NTS) {
       const int j = e / P, c = e - (e / P) * P;
-      if (c < np) st_stream(&a.out[ob + (long long)j * a.out_sj + (long long)c * a.out_sp], tile_s[j * TS + c]);
+      if (c < np) a.out[ob + (long long)j * a.out_sj + (long long)c * a.out_sp] = tile_s[j * TS + c];
     }
     __syncthreads();  // the tiles are reloaded by the next step
   }

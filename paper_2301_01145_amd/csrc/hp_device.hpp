@@ -45,6 +45,12 @@ template <typename T>
 __device__ __forceinline__ void st_stream(T* p, T v) {
   __builtin_nontemporal_store(v, p);
 }
+// Global store, streaming (STREAM) or through the caches.
+template <bool STREAM, typename T>
+__device__ __forceinline__ void st_out(T* p, const T& v) {
+  if constexpr (STREAM) st_stream(p, v);
+  else *p = v;
+}
 // Streaming (nontemporal) global loads: data read once per pass.
 template <typename T>
 __device__ __forceinline__ C2<T> ld_stream(const C2<T>* p) {

@@ -23,6 +23,17 @@ namespace hp {
 
 constexpr int kC2RThreads = 256;  // workgroup of the C2R pass
 
+// The stores of a pass: streaming, or through the caches where the next pass
+// finds its input there (a.stream, set by the planner).  One uniform branch
+// around whole store rounds; ALWAYS: no branch, the pass always streams.  (The
+// backward y pass takes the choice as a template argument: with the branch it
+// took 397 us at 256^3 instead of 393.)
+template <bool ALWAYS = false, typename F>
+__device__ __forceinline__ void with_stream(const PassArgs& a, F&& f) {
+  if (ALWAYS || a.stream) f(std::true_type{});
+  else f(std::false_type{});
+}
+
 template <typename T, int L>
 __device__ __forceinline__ void load_tw(C2<T>* tw_s, const void* tw) {
   const C2<T>* src = (const C2<T>*)tw;
@@ -98,12 +109,15 @@ __global__ void __launch_bounds__((R2CShape<L, P>::NT)) kf_r2c(const PassArgs a)
   const long long obase = (long long)x * K2 * n1 + y0;
   // a compile-time count: every LDS read of the thread is issued before the
   // first store waits for one (a run-time loop reads, waits and stores in turn)
+  with_stream(a, [&](auto ST) __attribute__((always_inline)) {
 #pragma unroll
-  for (int r = 0; r < (K2 * P + NT - 1) / NT; ++r) {
-    const int e = threadIdx.x + r * NT;
-    const int k = e / P, c = e - (e / P) * P;
-    if (e < K2 * P && y0 + c < n1) st_stream(&out[obase + (long long)k * n1 + c], tile[k * TS + c]);
-  }
+    for (int r = 0; r < (K2 * P + NT - 1) / NT; ++r) {
+      const int e = threadIdx.x + r * NT;
+      const int k = e / P, c = e - (e / P) * P;
+      if (e < K2 * P && y0 + c < n1)
+        st_out<decltype(ST)::value>(&out[obase + (long long)k * n1 + c], tile[k * TS + c]);
+    }
+  });
   (void)n0;
 }
 
@@ -153,12 +167,15 @@ __global__ void __launch_bounds__(64 * (P / WF<L>::PPW)) kf_fwd_y(const PassArgs
   __syncthreads();
   const long long obase = (long long)kzl * L * n0 + x0;
   static_assert((L * P) % NT == 0, "whole rounds of the tile store");
+  with_stream<PAD>(a, [&](auto ST) __attribute__((always_inline)) {
 #pragma unroll
-  for (int r = 0; r < L * P / NT; ++r) {
-    const int e = threadIdx.x + r * NT;
-    const int ky = e / P, c = e - (e / P) * P;
-    if (x0 + c < n0) st_stream(&out[obase + (long long)ky * n0 + c], tile[padrow(ky) * TS + c]);
-  }
+    for (int r = 0; r < L * P / NT; ++r) {
+      const int e = threadIdx.x + r * NT;
+      const int ky = e / P, c = e - (e / P) * P;
+      if (x0 + c < n0)
+        st_out<decltype(ST)::value>(&out[obase + (long long)ky * n0 + c], tile[padrow(ky) * TS + c]);
+    }
+  });
 }
 
 // --------------------------------------------------------- P3: sandwich (x)
@@ -339,12 +356,14 @@ __global__ void __launch_bounds__(64 * (P / WF<L>::PPW),
       // compile-time count (all LDS reads before the stores); offsets within
       // the kz slab, NX * M1 <= 2^20
       static_assert((NX * P) % NT == 0, "whole rounds of the tile store");
+      with_stream(a, [&](auto ST) __attribute__((always_inline)) {
 #pragma unroll
-      for (int r = 0; r < NX * P / NT; ++r) {
-        const int e = threadIdx.x + r * NT;
-        const int x = e / P, c = e - (e / P) * P;
-        st_stream(&d[x * M1 + c], tile[row(x) * TS + c]);
-      }
+        for (int r = 0; r < NX * P / NT; ++r) {
+          const int e = threadIdx.x + r * NT;
+          const int x = e / P, c = e - (e / P) * P;
+          st_out<decltype(ST)::value>(&d[x * M1 + c], tile[row(x) * TS + c]);
+        }
+      });
       if (DBL) tb ^= 1;
       else __syncthreads();
     };
@@ -506,7 +525,7 @@ __global__ void __launch_bounds__(64 * (P / WF<L>::PPW),
 // psi_z, A, B give psi and u = curl psi (u_x = d_y psi_z - d_z psi_y,
 // u_y = d_z psi_x + A, u_z = B - d_y psi_x); in gradient mode psi, d_x psi give
 // psi and grad psi.  At most two spectra are live per lane.
-template <typename T, int L, int P, bool DBL, bool PAD>
+template <typename T, int L, int P, bool DBL, bool PAD, bool STREAM>
 __global__ void __launch_bounds__(64 * (P / WF<L>::PPW)) kf_inv_y(const PassArgs a) {
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
   constexpr int NIN = PAD ? R0 / 2 : R0;  // elements per lane stored (y < n1)
@@ -560,7 +579,7 @@ __global__ void __launch_bounds__(64 * (P / WF<L>::PPW)) kf_inv_y(const PassArgs
     for (int r = 0; r < NY * P / NT; ++r) {
       const int e = threadIdx.x + r * NT;
       const int y = e / P, c = e - (e / P) * P;
-      if (c < nvalid) st_stream(&d[(long long)y * a.c1_sy + c], tile[row(y) * TS + c]);
+      if (c < nvalid) st_out<STREAM>(&d[(long long)y * a.c1_sy + c], tile[row(y) * TS + c]);
     }
     if (DBL) tb ^= 1;
     else __syncthreads();
@@ -776,13 +795,21 @@ static hipError_t launch_LP(const PassArgs& a0, int grid_y, hipStream_t s) {
       constexpr int NT = 64 * (P / WF<L>::PPW);
       dim3 grid(((a.kz_count + P - 1) / P) * n0, grid_y);
       if (a.P > 64) return hipErrorInvalidValue;
+      auto go = [&](auto kern) {
+        allow_lds<decltype(kern)::value>();
+        hipLaunchKernelGGL(decltype(kern)::value, grid, dim3(NT), lds, s, a);
+      };
+#define HP_IY(DBL, STREAM)                                               \
+  go(std::integral_constant<decltype(&kf_inv_y<T, L, P, DBL, PAD, STREAM>), \
+                            &kf_inv_y<T, L, P, DBL, PAD, STREAM>>{})
       if (a.emit_dbl) {  // double-buffered output tiles
-        allow_lds<kf_inv_y<T, L, P, true, PAD>>();
-        hipLaunchKernelGGL((kf_inv_y<T, L, P, true, PAD>), grid, dim3(NT), lds, s, a);
+        if (a.stream) HP_IY(true, true);
+        else HP_IY(true, false);
       } else {
-        allow_lds<kf_inv_y<T, L, P, false, PAD>>();
-        hipLaunchKernelGGL((kf_inv_y<T, L, P, false, PAD>), grid, dim3(NT), lds, s, a);
+        if (a.stream) HP_IY(false, true);
+        else HP_IY(false, false);
       }
+#undef HP_IY
     } break;
     default:
       return hipErrorInvalidValue;

@@ -127,6 +127,7 @@ struct PassArgs {
   int c1_ld;               // row length (kz) of C1: K2 rounded up to 16
   long long c1_sx, c1_sy;  // C1 strides (elements) of x and y
   int ngrp;                // x pass: output groups per tile (set at launch)
+  int stream;              // 1: streaming (nontemporal) stores
   int pad;                 // 1: doubled free-space pencils (physical half), 0: periodic
   // signature of the pass geometry (host planner): passes with equal keys
   // share the configuration chosen by the autotuner
