@@ -933,9 +933,11 @@ hp_status finish_pass(hp_plan p, PassArgs& a, int want, int minP, long long lds_
 
 // --------------------------------------------------------- pass lists
 // Wavefront-FFT kernels for the bounded passes (hp_bounded.hip): 2D / 3D
-// single plans whose every Dirichlet / Neumann transform length is a power of
-// two in [64, 512], or 96 or 192 (the Hartley passes of periodic axes stay on
-// the general kernels).
+// single plans whose every Dirichlet / Neumann axis has a wavefront FFT: on
+// REGULAR grids a transform length that is a power of two in [64, 512], or 96 or
+// 192; on STAGGERED ones, whose FFT has the axis's own length, 32 to 256 points,
+// or 48, 96 or 192 (the Hartley passes of periodic axes stay on the general
+// kernels).
 bool bounded_fast_ok(hp_plan p, const Problem& P, const int* L) {
   if (std::getenv("HP_GENERIC") || p->batched || P.nd < 2) return false;
   int bounded = 0;
@@ -945,9 +947,12 @@ bool bounded_fast_ok(hp_plan p, const Problem& P, const int* L) {
     // (to_fast_r2r)
     if (axis_bc(P.d, a) == HP_PERIODIC || axis_bc(P.d, a) == HP_UNBOUNDED) continue;
     ++bounded;
-    if (L[a] < 64 || L[a] > 512 || wf_r0(L[a]) <= 0) return false;
+    // the FFT length: the staggered types' own (half the extension L)
+    const bool half = P.d.grid == HP_STAGGERED;
+    const int len = half ? P.n[a] : L[a];
+    if (len < (half ? 32 : 64) || len > (half ? 256 : 512) || wf_r0(len) <= 0) return false;
     for (int k = FAST_R2R_C; k <= FAST_R2R_SW; ++k) {
-      const int lds = r2r_lds_bytes(k, L[a], P.n[a], 0, p->prec);
+      const int lds = r2r_lds_bytes(k, len, P.n[a], 0, p->prec);
       if (lds <= 0 || lds > 160 * 1024) return false;
     }
   }
@@ -968,13 +973,15 @@ hp_status to_fast_r2r(hp_plan p, PassArgs& a) {
   int nd = 0;
   for (int i = 0; i < a.nfan; ++i)
     if (a.fan[i].deriv) nd = std::max(nd, a.fan[i].nd);
-  const int lds = r2r_lds_bytes(kind, a.L, a.n, nd, p->prec);
+  const int len = wf_length(a);
+  const int lds = r2r_lds_bytes(kind, len, a.n, nd, p->prec);
   if (lds <= 0 || lds > 160 * 1024) return HP_OK;  // stays on the general kernel
   a.fast = kind;
+  a.L = len;
   const void* tw;
   HP_TRY(fast_twiddles(p, a.L, &tw));
   a.tw = tw;
-  a.P = r2r_tile(p->prec);
+  a.P = r2r_tile(a.L, p->prec);
   a.lds_bytes = lds;
   return HP_OK;
 }

@@ -3,15 +3,16 @@
 // in place in the problem's output array); the passes of all problems at one
 // place in their lists form a level, whose work items (one item =
 // consecutive tiles of one pass) are independent and run in one launch.
-// Where every pass of every problem has a wavefront FFT (FP32, lengths 64,
-// 96, 128, 192, 256) the launches run the wavefront tile bodies
-// (k_batched_pass); otherwise the general pass code (k_batched).
+// Where every pass of every problem has a wavefront FFT (FP32, staggered axes
+// of 32, 48, 64, 96 or 128 points or, REGULAR Neumann, FFT lengths 64, 96, 128,
+// 192, 256) the launches run the wavefront tile bodies (k_batched_pass);
+// otherwise the general pass code (k_batched).
 //
 // A single persistent launch with per-pass completion counters, the other way
 // to order the levels, was always slower: the agent-scope release and acquire
 // between dependent items write back and invalidate the L2 caches of all XCDs
 // once per item, a launch boundary once per level (64 Neumann problems of 32
-// to 128 cells per axis: 2430 us persistent, 484 us in launches; one
+// to 128 cells per axis: 2430 us persistent, 420 us in launches; one
 // 128^3 problem 656 and 63 us; two of 32^3 101 and 26 us).
 #include <algorithm>
 #include <cstdlib>
@@ -58,7 +59,7 @@ int wf_family(hp_plan p, const std::vector<std::vector<PassRec>>& lists) {
   for (auto& l : lists)
     for (auto& r : l) {
       const PassArgs& a = r.a;
-      if (a.fast != FAST_NONE || !batched_wf_length(a.L) || a.n > a.L / 2 + 1) return 0;
+      if (a.fast != FAST_NONE || !batched_wf_length(wf_length(a), wf_half(a)) || a.n > a.L / 2 + 1) return 0;
       if (a.kind == PK_SANDWICH ? (a.xf != xf || a.xb != xb) : (a.xf != xf && a.xf != xb)) return 0;
       for (int ax = 0; ax < 3; ++ax)
         if (a.face[ax][0] || a.face[ax][1]) return 0;
@@ -66,16 +67,17 @@ int wf_family(hp_plan p, const std::vector<std::vector<PassRec>>& lists) {
   return xf;
 }
 
-// The pass on the wavefront tile bodies of k_batched_wf (same descriptor).
+// The pass on the wavefront tile bodies of k_batched_pass (same descriptor).
 hp_status to_wf(hp_plan p, PassArgs& a) {
   const bool contig = a.kind == PK_ONEWAY && a.in_jfast && a.out_jfast;
   a.fast = a.kind == PK_SANDWICH ? FAST_R2R_SW : (contig ? FAST_R2R_C : FAST_R2R_S);
+  a.L = wf_length(a);
   const void* tw;
   hp_status s = plan_fast_twiddles(p, a.L, &tw);
   if (s != HP_OK) return s;
   a.tw = tw;
   a.P = 32;
-  a.lds_bytes = batched_wf_lds(a.fast, a.L);
+  a.lds_bytes = batched_wf_lds(a);
   return HP_OK;
 }
 

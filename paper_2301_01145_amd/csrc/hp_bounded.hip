@@ -1,18 +1,15 @@
 // Bounded (Dirichlet / Neumann) passes with one FFT per wavefront, for
-// transform lengths L = 64 .. 1024 (powers of two), 96 and 192
-// (hp_wavefft.hpp).
+// FFT lengths L = 32 .. 512 (powers of two), 48, 96 and 192 (hp_wavefft.hpp).
 //
 // The real-to-real transforms of Table 1 (DST-I/II/III, DCT-I/II/III) run as
-// one complex FFT of length L on a pair of real pencils packed as a + ib,
-// after extending each pencil to the symmetry of its transform:
+// one complex FFT of length L on a pair of real pencils packed as a + ib.  The
+// regular types extend each pencil to its symmetry:
 //   DST-I   L = 2(n+1): [0, x_0..x_{n-1}, 0, -x_{n-1}..-x_0]
 //   DCT-I   L = 2(n-1): [x_0..x_{n-1}, x_{n-2}..x_1]
-//   DCT-II  L = 2n:     [x_0..x_{n-1}, x_{n-1}..x_0] (DST-II: (-1)^j x_j)
-//   DCT-III L = 2n:     e^{+i pi j / 2n} (a_j + i b_j) below n, 0 at n, the
-//                       conjugate twist above (inverse FFT; DST-III reversed)
-// Every output of these transforms is read from a single FFT bin (with the
-// quarter-wave twist e^{-i pi k / 2n} for DCT-II / DST-II), and lane g holds
-// bins g + G i, so the outputs stay in the lanes that computed them.
+// and every output is read from a single FFT bin.  The staggered types reorder
+// it instead (r2r_build), L = n; types II take an output from the bins k and
+// n - k (mirror_bin).  Lane g holds bins g + G i, so the outputs stay in the
+// lanes that computed them.
 //
 // Passes (the pencil descriptors are those of the general path, in place in
 // the output array): contiguous one-way passes load the pencil pair straight
@@ -32,8 +29,24 @@ namespace {
 
 __device__ __forceinline__ bool r2r_inverse_fft(int x) { return x == X_DCT3 || x == X_DST3; }
 
-// FFT input z[m] of the pair (a, b) for transform x of n points (length L);
-// get(s, w) is element s of pencil a (w = 0) or b (w = 1).
+// Rows of a pencil that an FFT of length L transforms at most: the staggered
+// types (H) use an FFT of their own length, the regular ones one of 2 (n + 1)
+// or 2 (n - 1).
+template <int L, bool H>
+constexpr int kMaxRows = H ? L : L / 2 + 1;
+
+// FFT input z[m] of the pair (a, b) for transform x of n points (FFT length
+// L); get(s, w) is element s of pencil a (w = 0) or b (w = 1).
+//
+// The staggered types use an FFT of n points, half the symmetric extension
+// (Makhoul's reordering; n even): type II transforms v[m] = x[2m], v[n-1-m] =
+// x[2m+1] and takes the real part of q[k] V[k] afterwards (r2r_extract); type
+// III starts from conj(q[k]) (c[k] - i c[n-k]) and puts the reals back in
+// order.  The sine forms alternate signs and reverse the coefficients.  Against
+// the extension: 128^3 FP32 Dirichlet 50.2 -> 44.1 us, FP64 77.6 -> 59.4, 256^3
+// FP32 224 -> 184, 192^3 (FFT 384: general kernels) 201 -> 112; batches of eight
+// 128^3 251 -> 188, of 32 96^3 582 -> 437, of 64 64^3 267 -> 205.  A first and
+// last pass of 128^3 is bound by its launch and one memory latency either way.
 template <typename T, class Get>
 __device__ __forceinline__ C2<T> r2r_build(int x, int m, int n, int L, const C2<T>* q, Get get) {
   switch (x) {
@@ -47,31 +60,47 @@ __device__ __forceinline__ C2<T> r2r_build(int x, int m, int n, int L, const C2<
     }
     case X_DCT2:
     case X_DST2: {
-      const int s = m < n ? m : L - 1 - m;
+      const bool even = 2 * m < n;
+      const int s = even ? 2 * m : 2 * (n - m) - 1;
       C2<T> z = {get(s, 0), get(s, 1)};
-      if (x == X_DST2 && (s & 1)) z = {-z.re, -z.im};
+      if (x == X_DST2 && !even) z = {-z.re, -z.im};
       return z;
     }
     case X_DCT3:
     case X_DST3: {
-      if (m == n) return {(T)0, (T)0};
-      const int s = m < n ? m : L - m;
-      const int src = x == X_DST3 ? n - 1 - s : s;
-      const C2<T> v = {get(src, 0), get(src, 1)};
-      C2<T> w = q[s];  // e^{-i pi s / 2n}
-      if (m < n) w.im = -w.im;
-      return cmul(v, w);
+      const int s = x == X_DST3 ? n - 1 - m : m;
+      const int sm = m == 0 ? s : (x == X_DST3 ? m - 1 : n - m);
+      const C2<T> u = {get(s, 0), get(s, 1)};
+      C2<T> um = {get(sm, 0), get(sm, 1)};
+      if (m == 0) um = {(T)0, (T)0};
+      const C2<T> d = {u.re + um.im, u.im - um.re}, w = q[m];
+      return cmul_fixed(d, cconj(w));
     }
     default:
       return {(T)0, (T)0};
   }
 }
 
-// Output index carried by FFT bin m of transform x (-1: none) and the two
-// real outputs (pencils a and b).
-template <typename T>
-__device__ __forceinline__ int r2r_extract(int x, int m, int n, C2<T> z, const C2<T>* q, T& oa,
-                                           T& ob) {
+// The bin n - k (0 for k = 0) of every bin k = g + G i that a lane holds:
+// element R0 - 1 - i of lane G - g, lane 0's own ones in reverse.  (Types II
+// separate the two pencils with it; one lane exchange per component instead
+// of a second LDS exchange.)
+template <typename T, int L>
+__device__ __forceinline__ C2<T> mirror_bin(const C2<T> (&v)[WF<L>::R0], int i, int g) {
+  constexpr int R0 = WF<L>::R0, G = WF<L>::G;
+  const int from = ((int)(threadIdx.x & 63) & ~(G - 1)) + ((G - g) & (G - 1));
+  const C2<T> o = v[(R0 - i) % R0];
+  const C2<T> w = {__shfl(v[R0 - 1 - i].re, from, 64), __shfl(v[R0 - 1 - i].im, from, 64)};
+  return g == 0 ? o : w;
+}
+
+// Output index carried by bin i of the lane (m = g + G i) of transform x (-1:
+// none) and the two real outputs (pencils a and b).
+template <typename T, int L>
+__device__ __forceinline__ int r2r_extract(int x, int i, int g, int n, const C2<T> (&v)[WF<L>::R0], const C2<T>* q,
+                                           T& oa, T& ob) {
+  const int m = g + WF<L>::G * i;
+  const C2<T> z = v[i];
   switch (x) {
     case X_DST1:
       if (m < 1 || m > n) return -1;
@@ -79,22 +108,24 @@ __device__ __forceinline__ int r2r_extract(int x, int m, int n, C2<T> z, const C
       ob = z.re;
       return m - 1;
     case X_DCT1:
-    case X_DCT3:
       if (m >= n) return -1;
       oa = z.re;
       ob = z.im;
       return m;
-    case X_DST3:
-      if (m >= n) return -1;
-      oa = (m & 1) ? -z.re : z.re;
-      ob = (m & 1) ? -z.im : z.im;
-      return m;
+    case X_DCT3:
+    case X_DST3: {
+      const bool even = 2 * m < n;
+      const T sg = (x == X_DST3 && !even) ? (T)-1 : (T)1;
+      oa = sg * z.re;
+      ob = sg * z.im;
+      return even ? 2 * m : 2 * (n - m) - 1;
+    }
     case X_DCT2:
     case X_DST2: {
-      if (m >= n) return -1;
-      const C2<T> v = cmul(z, q[m]);
-      oa = v.re;
-      ob = v.im;
+      const C2<T> c = cconj(mirror_bin<T, L>(v, i, g)), w = q[m];
+      const C2<T> s = cadd(z, c), d = csub(z, c);
+      oa = fma(s.re, w.re, -rounded(s.im * w.im));
+      ob = fma(d.re, w.im, rounded(d.im * w.re));
       return x == X_DST2 ? n - 1 - m : m;
     }
     default:
@@ -118,21 +149,25 @@ __device__ __forceinline__ void r2r_fft(C2<T> (&v)[WF<L>::R0], int x, int n, C2<
 #pragma unroll
   for (int i = 0; i < R0; ++i) v[i] = r2r_build<T>(x, g + G * i, n, L, q, get);
   wave_sync();  // the FFT overwrites the slot the inputs may have come from
-  if (r2r_inverse_fft(x)) wave_fft<T, L, true>(v, slot, 1, g, tw);
-  else wave_fft<T, L, false>(v, slot, 1, g, tw);
+  if (r2r_inverse_fft(x)) wave_fft<T, L, true, false, false, true, true>(v, slot, 1, g, tw);
+  else wave_fft<T, L, false, false, false, true, true>(v, slot, 1, g, tw);
 }
 
 // Runs f with the transform type as a compile-time constant: one branch per
-// FFT (uniform per wavefront) instead of a switch per element.
-template <class F>
+// FFT (uniform per wavefront) instead of a switch per element.  H: one of the
+// staggered types, else one of the regular ones (a kernel holds one family).
+template <bool H, class F>
 __device__ __forceinline__ void with_xform(int x, F&& f) {
-  switch (x) {
-    case X_DST1: f(std::integral_constant<int, X_DST1>{}); break;
-    case X_DST2: f(std::integral_constant<int, X_DST2>{}); break;
-    case X_DST3: f(std::integral_constant<int, X_DST3>{}); break;
-    case X_DCT1: f(std::integral_constant<int, X_DCT1>{}); break;
-    case X_DCT2: f(std::integral_constant<int, X_DCT2>{}); break;
-    default: f(std::integral_constant<int, X_DCT3>{}); break;
+  if constexpr (H) {
+    switch (x) {
+      case X_DST2: f(std::integral_constant<int, X_DST2>{}); break;
+      case X_DST3: f(std::integral_constant<int, X_DST3>{}); break;
+      case X_DCT2: f(std::integral_constant<int, X_DCT2>{}); break;
+      default: f(std::integral_constant<int, X_DCT3>{}); break;
+    }
+  } else {
+    if (x == X_DST1) f(std::integral_constant<int, X_DST1>{});
+    else f(std::integral_constant<int, X_DCT1>{});
   }
 }
 
@@ -164,12 +199,12 @@ constexpr int kR2RContigWaves = 4;
 
 // ----------------------------------------------- contiguous one-way pass
 // Pairs (p, p+1) of pencils at one o; the pencil axis is unit stride.
-template <typename T, int L>
+template <typename T, int L, bool H>
 __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig(const PassArgs a) {
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
   constexpr int NT = 64 * kR2RContigWaves;
   extern __shared__ __align__(16) unsigned char smem[];
-  const int n = a.n;
+  const int n = H ? L : a.n;
   C2<T>* tw = (C2<T>*)smem;
   C2<T>* q = tw + L;
   C2<T>* slots = q + n;
@@ -192,9 +227,9 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig(const PassArgs
   const bool faces = has_faces(a);
   const T* in = (const T*)a.in[0];
   const long long ib = (long long)o * a.in_so + (long long)pa * a.in_sp;
-  // every load of the pair is issued before the first is used (n <= L/2 + 1,
+  // every load of the pair is issued before the first is used (n <= kMaxRows,
   // checked at launch): one memory latency per pass, not one per row
-  constexpr int NJ = (L / 2 + 1 + G - 1) / G;
+  constexpr int NJ = (kMaxRows<L, H> + G - 1) / G;
   T va[NJ], vbv[NJ];
   // (unconditional loads from clamped addresses: pencil pa + 1 only where it
   // exists, rows below n; the conditions apply where the values are kept)
@@ -224,14 +259,14 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig(const PassArgs
   wave_sync();
   T* out = (T*)a.out[0];
   const long long ob = (long long)o * a.out_so + (long long)pa * a.out_sp;
-  with_xform(a.xf, [&](auto XF) {
+  with_xform<H>(a.xf, [&](auto XF) {
     constexpr int X = decltype(XF)::value;
     C2<T> v[R0];
     r2r_fft<T, L>(v, X, n, slot, g, tw, q, [&](int s, int w) { return R[w * n + s]; });
 #pragma unroll
     for (int i = 0; i < R0; ++i) {
       T oa, obv;
-      const int k = r2r_extract<T>(X, g + G * i, n, v[i], q, oa, obv);
+      const int k = r2r_extract<T, L>(X, i, g, n, v, q, oa, obv);
       if (k < 0) continue;
       if (valid) st_stream(&out[ob + (long long)k * a.out_sj], oa);
       if (vb) st_stream(&out[ob + a.out_sp + (long long)k * a.out_sj], obv);
@@ -250,14 +285,14 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig(const PassArgs
 // FFTs and writes it to LDS after the current tile has been stored.  Chosen
 // when there are many more tiles than resident workgroups.
 // (Boundary terms enter in the contiguous first pass only.)
-template <typename T, int L, int P, int W, bool SW, bool PERS>
+template <typename T, int L, bool H, int P, int W, bool SW, bool PERS>
 __global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
   constexpr int NT = 64 * W, TS = P + 1;
-  constexpr int MAXN = L / 2 + 1;             // rows of a tile (n <= L/2 + 1)
+  constexpr int MAXN = kMaxRows<L, H>;           // rows of a tile at most
   constexpr int PER = (MAXN * P + NT - 1) / NT;  // tile elements per thread
   extern __shared__ __align__(16) unsigned char smem[];
-  const int n = a.n;
+  const int n = H ? L : a.n;
   C2<T>* tw = (C2<T>*)smem;
   C2<T>* q = tw + L;
   C2<T>* slots = q + n;
@@ -318,7 +353,7 @@ __global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
       auto get = [&](int s, int w) { return ca[s * TS + w]; };
       // the sandwich's backward type is the Table 1 partner of its forward
       // type (checked at launch)
-      with_xform(a.xf, [&](auto XF) {
+      with_xform<H>(a.xf, [&](auto XF) {
         constexpr int XFc = decltype(XF)::value;
         constexpr int XO = SW ? r2r_partner(XFc) : XFc;
         C2<T> v[R0];
@@ -330,7 +365,7 @@ __global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
 #pragma unroll
           for (int i = 0; i < R0; ++i) {
             T sa, sb;
-            const int k = r2r_extract<T>(XFc, g + G * i, n, v[i], q, sa, sb);
+            const int k = r2r_extract<T, L>(XFc, i, g, n, v, q, sa, sb);
             if (k < 0) continue;
             ca[k * TS] = sa * eigen_mult<T>(a, k, ra);
             ca[k * TS + 1] = sb * eigen_mult<T>(a, k, rb);
@@ -342,7 +377,7 @@ __global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
 #pragma unroll
         for (int i = 0; i < R0; ++i) {
           T oa, obv;
-          const int k = r2r_extract<T>(XO, g + G * i, n, v[i], q, oa, obv);
+          const int k = r2r_extract<T, L>(XO, i, g, n, v, q, oa, obv);
           if (k < 0) continue;
           ca[k * TS] = oa;
           ca[k * TS + 1] = obv;
@@ -376,22 +411,24 @@ __global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
 namespace {
 
 // The backward (forward) type as a compile-time constant.
-template <class F>
+template <bool H, class F>
 __device__ __forceinline__ void with_backward(int x, F&& f) {
-  switch (x) {
-    case X_DST1: f(std::integral_constant<int, X_DST1>{}); break;
-    case X_DST3: f(std::integral_constant<int, X_DST3>{}); break;
-    case X_DCT1: f(std::integral_constant<int, X_DCT1>{}); break;
-    default: f(std::integral_constant<int, X_DCT3>{}); break;
+  if constexpr (H) {
+    if (x == X_DST3) f(std::integral_constant<int, X_DST3>{});
+    else f(std::integral_constant<int, X_DCT3>{});
+  } else {
+    if (x == X_DST1) f(std::integral_constant<int, X_DST1>{});
+    else f(std::integral_constant<int, X_DCT1>{});
   }
 }
-template <class F>
+template <bool H, class F>
 __device__ __forceinline__ void with_forward(int x, F&& f) {
-  switch (x) {
-    case X_DST1: f(std::integral_constant<int, X_DST1>{}); break;
-    case X_DST2: f(std::integral_constant<int, X_DST2>{}); break;
-    case X_DCT1: f(std::integral_constant<int, X_DCT1>{}); break;
-    default: f(std::integral_constant<int, X_DCT2>{}); break;
+  if constexpr (H) {
+    if (x == X_DST2) f(std::integral_constant<int, X_DST2>{});
+    else f(std::integral_constant<int, X_DCT2>{});
+  } else {
+    if (x == X_DST1) f(std::integral_constant<int, X_DST1>{});
+    else f(std::integral_constant<int, X_DCT1>{});
   }
 }
 // The stores of a fan pass, through the caches or streaming.
@@ -411,14 +448,14 @@ __device__ __forceinline__ double fan_kappa(const FanJob& q, int k) {
 
 }  // namespace
 
-template <typename T, int L>
+template <typename T, int L, bool H>
 __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const PassArgs) {
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
   constexpr int NT = 64 * kR2RContigWaves;
   extern __shared__ __align__(16) unsigned char smem[];
   const PassArgs& a = kernel_args();
   const FanJob& job = a.fan[blockIdx.y];
-  const int n = job.n;
+  const int n = H ? L : job.n;
   C2<T>* tw = (C2<T>*)smem;
   C2<T>* q = tw + L;
   C2<T>* slots = q + a.n;
@@ -441,7 +478,7 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const Pass
   const bool vb = valid && pa + 1 < job.Np;
   const T* in = (const T*)job.in;
   const long long ib = (long long)o * a.in_so + (long long)pa * a.in_sp;
-  constexpr int NJ = (L / 2 + 1 + G - 1) / G;
+  constexpr int NJ = (kMaxRows<L, H> + G - 1) / G;
   T va[NJ], vbv[NJ];
   const long long ibb = ib + (vb ? a.in_sp : 0);
 #pragma unroll
@@ -460,7 +497,7 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const Pass
 #pragma unroll
       for (int i = 0; i < R0; ++i) {
         T oa, obv;
-        const int k = r2r_extract<T>(X, g + G * i, cnt, v[i], q, oa, obv);
+        const int k = r2r_extract<T, L>(X, i, g, cnt, v, q, oa, obv);
         if (k < 0) continue;
         if (valid) st_out<decltype(ST)::value>(&out[ob + (long long)k * a.out_sj], oa);
         if (vb) st_out<decltype(ST)::value>(&out[ob + a.out_sp + (long long)k * a.out_sj], obv);
@@ -469,7 +506,7 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const Pass
     wave_sync();  // the slot is filled again
   };
   if (job.deriv) {
-    const int nd = job.nd;
+    const int nd = H ? L : job.nd;
     // places that no coefficient reaches: the first and the last at most
     if (g == 0) R[0] = R[nd - 1] = R[nd] = R[2 * nd - 1] = (T)0;
     wave_sync();
@@ -483,7 +520,7 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const Pass
       }
     }
     wave_sync();
-    with_backward(job.xd, [&](auto XC) __attribute__((always_inline)) { run(XC, nd, job.deriv); });
+    with_backward<H>(job.xd, [&](auto XC) __attribute__((always_inline)) { run(XC, nd, job.deriv); });
   }
 #pragma unroll
   for (int r = 0; r < NJ; ++r) {
@@ -494,21 +531,21 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const Pass
     }
   }
   wave_sync();
-  with_backward(job.xp, [&](auto XC) __attribute__((always_inline)) { run(XC, n, job.plain); });
+  with_backward<H>(job.xp, [&](auto XC) __attribute__((always_inline)) { run(XC, n, job.plain); });
 }
 
 // Strided fan pass and sandwich: the tile of the plain transform and a second
 // tile for the derivative, both transformed in place (kb_strided).
-template <typename T, int L, int P, int W, bool SW>
+template <typename T, int L, bool H, int P, int W, bool SW>
 __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
   constexpr int NT = 64 * W, TS = P + 1;
-  constexpr int MAXN = L / 2 + 1;
+  constexpr int MAXN = kMaxRows<L, H>;
   constexpr int PER = (MAXN * P + NT - 1) / NT;
   extern __shared__ __align__(16) unsigned char smem[];
   const PassArgs& a = kernel_args();
   const FanJob& job = a.fan[blockIdx.y];
-  const int n = job.n, nd = job.nd;
+  const int n = H ? L : job.n, nd = H ? L : job.nd;
   C2<T>* tw = (C2<T>*)smem;
   C2<T>* q = tw + L;
   C2<T>* slots = q + a.n;
@@ -557,7 +594,7 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
 #pragma unroll
     for (int i = 0; i < R0; ++i) {
       T oa, obv;
-      const int k = r2r_extract<T>(X, g + G * i, cnt, v[i], q, oa, obv);
+      const int k = r2r_extract<T, L>(X, i, g, cnt, v, q, oa, obv);
       if (k < 0) continue;
       col[k * TS] = oa;
       col[k * TS + 1] = obv;
@@ -586,7 +623,7 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
       return w * w;
     };
     const double la = lap ? w2(a.ax_p, pa) + w2(a.ax_o, o) : 0.0, lb = lap ? w2(a.ax_p, pb) + w2(a.ax_o, o) : 0.0;
-    with_forward(a.xf, [&](auto XC) {
+    with_forward<H>(a.xf, [&](auto XC) {
       constexpr int XF = decltype(XC)::value;
       constexpr int XB = r2r_partner(XF);
       {
@@ -595,7 +632,7 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
 #pragma unroll
         for (int i = 0; i < R0; ++i) {
           T sa, sb;
-          const int k = r2r_extract<T>(XF, g + G * i, n, v[i], q, sa, sb);
+          const int k = r2r_extract<T, L>(XF, i, g, n, v, q, sa, sb);
           if (k < 0) continue;
           const double lam = a.lam[a.ax_j][k];
           const double ma = lam + ra == 0.0 ? 0.0 : a.norm / (lam + ra);
@@ -621,9 +658,9 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
         place(k, m * ca[k * TS], m * ca[k * TS + 1]);
       }
       wave_sync();
-      with_backward(job.xd, [&](auto XC) __attribute__((always_inline)) { back(XC, da, nd); });
+      with_backward<H>(job.xd, [&](auto XC) __attribute__((always_inline)) { back(XC, da, nd); });
     }
-    with_backward(job.xp, [&](auto XC) __attribute__((always_inline)) { back(XC, ca, n); });
+    with_backward<H>(job.xp, [&](auto XC) __attribute__((always_inline)) { back(XC, ca, n); });
   }
   __syncthreads();
   const long long ob = (long long)o * a.out_so + (long long)p0 * a.out_sp;
@@ -652,7 +689,7 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
 //     kBatchWaves) wavefronts, each lane group taking P / (2 W PPW) pairs in
 //     turn; the workgroup holds S = kBatchWaves / W tiles at once (one per
 //     group of W wavefronts).
-// LDS: twiddles [L] | quarter twists [L/2 + 1] | exchange slots | S tiles.
+// LDS: twiddles [L] | quarter twists [MAXN] | exchange slots | S tiles.
 // Four wavefronts per workgroup keep the exchange slots small enough for
 // three or four workgroups per CU at every length.  Stores go through the
 // caches, never slower than streaming (64 problems of 64^3: 267 us, 279; 64 of
@@ -661,25 +698,23 @@ constexpr int kBatchWaves = 4;
 
 namespace {
 
-template <int L>
+template <int L, bool H>
 struct BW {
   static constexpr int PPW = WF<L>::PPW;
   static constexpr int P = 32;  // FP32 pencils per strided tile (128-byte runs)
   static constexpr int W = (P / 2) / PPW < kBatchWaves ? (P / 2) / PPW : kBatchWaves;
   static constexpr int PPL = (P / 2) / (W * PPW);  // pairs per lane group
   static constexpr int S = kBatchWaves / W;
-  static constexpr int MAXN = L / 2 + 1;
+  static constexpr int MAXN = kMaxRows<L, H>;
   static constexpr int TS = P + 1;
   static_assert(W >= 1 && kBatchWaves % W == 0 && PPL * W * PPW == P / 2, "batched strided tile");
 };
 
-// The fields of a pass that the tile bodies read, as wavefront-uniform
-// values.  The pass table is read with vector loads (the kernel also writes
-// global memory, so the compiler cannot use scalar loads for it); passing
-// each field through readfirstlane lets it live in scalar registers instead
-// of vector registers for the whole item.
+// The fields of a pass that the tile bodies read.  The pass table and the work
+// list are read through the constant address space: they do not change while
+// the launch runs, so the reads are scalar loads into scalar registers.
 struct BwArgs {
-  int L, fast, xf, n, Np, No;
+  int L, n, Np, No;
   long long in_sj, in_sp, in_so, out_sj, out_sp, out_so;
   const float* in;
   float* out;
@@ -691,38 +726,30 @@ struct BwArgs {
   double norm;
 };
 
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ long long uni(long long v) {
-  const unsigned lo = (unsigned)uni((int)(v & 0xffffffffLL)), hi = (unsigned)uni((int)(v >> 32));
-  return (long long)(((unsigned long long)hi << 32) | lo);
-}
-template <typename P>
-__device__ __forceinline__ P* uni(P* p) { return (P*)uni((long long)p); }
-__device__ __forceinline__ double uni(double d) { return __longlong_as_double(uni(__double_as_longlong(d))); }
+using ConstPass = const __attribute__((address_space(4))) PassArgs;
+using ConstItem = const __attribute__((address_space(4))) BatchItem;
 
-__device__ __forceinline__ BwArgs bw_args(const PassArgs& a) {
+__device__ __forceinline__ BwArgs bw_args(ConstPass* a) {
   BwArgs b;
-  b.L = uni(a.L);
-  b.fast = uni(a.fast);
-  b.xf = uni(a.xf);
-  b.n = uni(a.n);
-  b.Np = uni(a.Np);
-  b.No = uni(a.No);
-  b.in_sj = uni(a.in_sj);
-  b.in_sp = uni(a.in_sp);
-  b.in_so = uni(a.in_so);
-  b.out_sj = uni(a.out_sj);
-  b.out_sp = uni(a.out_sp);
-  b.out_so = uni(a.out_so);
-  b.in = uni((const float*)a.in[0]);
-  b.out = uni((float*)a.out[0]);
-  b.tw = uni((const C2<float>*)a.tw);
-  b.qtw = uni((const C2<float>*)a.qtw);
-  const int aj = uni(a.ax_j), ap = uni(a.ax_p), ao = uni(a.ax_o);
-  b.lam_j = aj >= 0 ? uni(a.lam[aj]) : nullptr;
-  b.lam_p = ap >= 0 ? uni(a.lam[ap]) : nullptr;
-  b.lam_o = ao >= 0 ? uni(a.lam[ao]) : nullptr;
-  b.norm = uni(a.norm);
+  b.L = a->L;
+  b.n = a->n;
+  b.Np = a->Np;
+  b.No = a->No;
+  b.in_sj = a->in_sj;
+  b.in_sp = a->in_sp;
+  b.in_so = a->in_so;
+  b.out_sj = a->out_sj;
+  b.out_sp = a->out_sp;
+  b.out_so = a->out_so;
+  b.in = (const float*)a->in[0];
+  b.out = (float*)a->out[0];
+  b.tw = (const C2<float>*)a->tw;
+  b.qtw = (const C2<float>*)a->qtw;
+  const int aj = a->ax_j, ap = a->ax_p, ao = a->ax_o;
+  b.lam_j = aj >= 0 ? a->lam[aj] : nullptr;
+  b.lam_p = ap >= 0 ? a->lam[ap] : nullptr;
+  b.lam_o = ao >= 0 ? a->lam[ao] : nullptr;
+  b.norm = a->norm;
   return b;
 }
 
@@ -737,53 +764,56 @@ __device__ __forceinline__ void bw_tables(const BwArgs& a, C2<float>* tw, C2<flo
 
 template <int L, int X>
 __device__ __forceinline__ void bw_contig(const BwArgs& a, unsigned char* smem, int tile, int ntile) {
+  constexpr bool H = r2r_half(X);
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
   using T = float;
-  const int n = a.n;
+  const int n = H ? L : a.n;
   C2<T>* tw = (C2<T>*)smem;
   C2<T>* q = tw + L;
-  C2<T>* slots = q + BW<L>::MAXN;
+  C2<T>* slots = q + BW<L, H>::MAXN;
   const int tid = threadIdx.x;
-  bw_tables<L>(a, tw, q, tid);
-  __syncthreads();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int qq = lane / G, g = lane % G;
   C2<T>* slot = slots + (wave * PPW + qq) * slot_len(L);
   T* R = (T*)slot;
-  const int pairs_p = (a.Np + 1) / 2;
-  const long long total = (long long)pairs_p * a.No;
+  // (every axis has at most 256 points: 32 bits count the pairs)
+  const unsigned pairs_p = (a.Np + 1) / 2, total = pairs_p * a.No;
   for (int k = 0; k < ntile; ++k) {
-    const long long pr = ((long long)(tile + k) * kBatchWaves + wave) * PPW + qq;
+    const unsigned pr = ((tile + k) * kBatchWaves + wave) * PPW + qq;
     const bool valid = pr < total;
     const int o = valid ? (int)(pr / pairs_p) : 0;
     const int pa = valid ? 2 * (int)(pr % pairs_p) : 0;
     const bool vb = valid && pa + 1 < a.Np;
     const long long ib = (long long)o * a.in_so + (long long)pa * a.in_sp;
-    // every load of the pair in flight at once (compile-time trip count)
-    constexpr int NJ = (BW<L>::MAXN + G - 1) / G;
+    // every load of the pair in flight at once (compile-time trip count,
+    // addresses clamped to the array), the tables' loads behind them
+    constexpr int NJ = (BW<L, H>::MAXN + G - 1) / G;
     T va[NJ], vbv[NJ];
+    const long long ibb = ib + (vb ? a.in_sp : 0);
 #pragma unroll
     for (int r = 0; r < NJ; ++r) {
-      const int j = g + r * G;
-      va[r] = (valid && j < n) ? a.in[ib + (long long)j * a.in_sj] : (T)0;
-      vbv[r] = (vb && j < n) ? a.in[ib + a.in_sp + (long long)j * a.in_sj] : (T)0;
+      const long long jo = (long long)min(g + r * G, n - 1) * a.in_sj;
+      va[r] = a.in[ib + jo];
+      vbv[r] = a.in[ibb + jo];
     }
+    if (k == 0) bw_tables<L>(a, tw, q, tid);
 #pragma unroll
     for (int r = 0; r < NJ; ++r) {
       const int j = g + r * G;
       if (j < n) {
-        R[j] = va[r];
-        R[n + j] = vbv[r];
+        R[j] = valid ? va[r] : (T)0;
+        R[n + j] = vb ? vbv[r] : (T)0;
       }
     }
-    wave_sync();
+    if (k == 0) __syncthreads();
+    else wave_sync();
     const long long ob = (long long)o * a.out_so + (long long)pa * a.out_sp;
     C2<T> v[R0];
     r2r_fft<T, L>(v, X, n, slot, g, tw, q, [&](int s, int w) { return R[w * n + s]; });
 #pragma unroll
     for (int i = 0; i < R0; ++i) {
       T oa, obv;
-      const int kk = r2r_extract<T>(X, g + G * i, n, v[i], q, oa, obv);
+      const int kk = r2r_extract<T, L>(X, i, g, n, v, q, oa, obv);
       if (kk < 0) continue;
       if (valid) a.out[ob + (long long)kk * a.out_sj] = oa;
       if (vb) a.out[ob + a.out_sp + (long long)kk * a.out_sj] = obv;
@@ -794,17 +824,17 @@ __device__ __forceinline__ void bw_contig(const BwArgs& a, unsigned char* smem, 
 
 template <int L, int XF, int XO, bool SW>
 __device__ __forceinline__ void bw_strided(const BwArgs& a, unsigned char* smem, int tile, int ntile) {
+  constexpr bool H = r2r_half(XF);
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
-  constexpr int P = BW<L>::P, W = BW<L>::W, S = BW<L>::S, TS = BW<L>::TS, PPL = BW<L>::PPL;
-  constexpr int MAXN = BW<L>::MAXN, NTS = 64 * W;
+  constexpr int P = BW<L, H>::P, W = BW<L, H>::W, S = BW<L, H>::S, TS = BW<L, H>::TS, PPL = BW<L, H>::PPL;
+  constexpr int MAXN = BW<L, H>::MAXN, NTS = 64 * W;
   using T = float;
-  const int n = a.n;
+  const int n = H ? L : a.n;
   C2<T>* tw = (C2<T>*)smem;
   C2<T>* q = tw + L;
   C2<T>* slots = q + MAXN;
   T* tiles = (T*)(slots + kBatchWaves * PPW * slot_len(L));
   const int tid = threadIdx.x;
-  bw_tables<L>(a, tw, q, tid);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int sub = wave / W, wv = wave - sub * W;  // tile group and wavefront in it
   const int ts = tid - sub * NTS;                  // thread in the group
@@ -818,22 +848,25 @@ __device__ __forceinline__ void bw_strided(const BwArgs& a, unsigned char* smem,
     const int o = active ? t / tiles_p : 0, p0 = active ? (t % tiles_p) * P : 0;
     const int np = active ? min(P, a.Np - p0) : 0;
     const long long ib = (long long)o * a.in_so + (long long)p0 * a.in_sp;
-    // eight loads in flight per thread before their LDS stores: one load at a
-    // time waits out the memory latency once per element (a register copy of
-    // the whole tile spilled)
-    constexpr int U = 8;
+    // a batch of loads in flight per thread before their LDS stores: one load at
+    // a time waits out the memory latency once per element.  The staggered types
+    // (tiles of exactly [L][P]) take the whole tile at once, the others, whose
+    // FFT needs twice the registers, eight rows (a whole tile spilled).
+    // Addresses are clamped to the array; np = 0: the group's tile is idle.
+    constexpr int U = H ? MAXN * P / NTS : 8;
     for (int e0 = ts; e0 < n * P; e0 += U * NTS) {
       T v8[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int e = e0 + u * NTS;
-        const int j = e / P, c = e % P;
-        v8[u] = (j < n && c < np) ? a.in[ib + (long long)j * a.in_sj + (long long)c * a.in_sp] : (T)0;
+        const int j = min(e / P, n - 1), c = max(min(e % P, np - 1), 0);
+        v8[u] = a.in[ib + (long long)j * a.in_sj + (long long)c * a.in_sp];
       }
+      if (base == 0 && e0 == ts) bw_tables<L>(a, tw, q, tid);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int e = e0 + u * NTS;
-        if (e < n * P) tile_s[(e / P) * TS + e % P] = v8[u];
+        if (e < n * P) tile_s[(e / P) * TS + e % P] = e % P < np ? v8[u] : (T)0;
       }
     }
     __syncthreads();
@@ -851,7 +884,7 @@ __device__ __forceinline__ void bw_strided(const BwArgs& a, unsigned char* smem,
 #pragma unroll
         for (int i = 0; i < R0; ++i) {
           T sa, sb;
-          const int k = r2r_extract<T>(XF, g + G * i, n, v[i], q, sa, sb);
+          const int k = r2r_extract<T, L>(XF, i, g, n, v, q, sa, sb);
           if (k < 0) continue;
           const double la = a.lam_j[k] + ra, lb = a.lam_j[k] + rb;
           ca[k * TS] = la == 0.0 ? (T)0 : sa * ((T)a.norm / (T)la);
@@ -863,7 +896,7 @@ __device__ __forceinline__ void bw_strided(const BwArgs& a, unsigned char* smem,
 #pragma unroll
       for (int i = 0; i < R0; ++i) {
         T oa, obv;
-        const int k = r2r_extract<T>(XO, g + G * i, n, v[i], q, oa, obv);
+        const int k = r2r_extract<T, L>(XO, i, g, n, v, q, oa, obv);
         if (k < 0) continue;
         ca[k * TS] = oa;
         ca[k * TS + 1] = obv;
@@ -892,11 +925,12 @@ __device__ __forceinline__ void bw_item(const BwArgs& a, unsigned char* smem, in
 }
 
 __device__ __forceinline__ BatchItem bw_take(const BatchItem* items) {
-  BatchItem bi = items[blockIdx.x];
-  bi.pass = uni(bi.pass);
-  bi.tile = uni(bi.tile);
-  bi.ntile = uni(bi.ntile);
-  return bi;
+  ConstItem* it = (ConstItem*)items + blockIdx.x;
+  BatchItem b;
+  b.pass = it->pass;
+  b.tile = it->tile;
+  b.ntile = it->ntile;
+  return b;
 }
 
 // One pass level of the batch, every transform length in one launch: the
@@ -908,13 +942,23 @@ __global__ void __launch_bounds__(64 * kBatchWaves, 4)
     k_batched_pass(const PassArgs* passes, const BatchItem* items) {
   extern __shared__ __align__(16) unsigned char smem[];
   const BatchItem bi = bw_take(items);
-  const BwArgs a = bw_args(passes[bi.pass]);
-  switch (a.L) {
-    case 64: bw_item<64, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
-    case 96: bw_item<96, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
-    case 128: bw_item<128, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
-    case 192: bw_item<192, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
-    default: bw_item<256, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+  const BwArgs a = bw_args((ConstPass*)passes + bi.pass);
+  if constexpr (r2r_half(XF)) {
+    switch (a.L) {
+      case 32: bw_item<32, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+      case 48: bw_item<48, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+      case 64: bw_item<64, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+      case 96: bw_item<96, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+      default: bw_item<128, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+    }
+  } else {
+    switch (a.L) {
+      case 64: bw_item<64, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+      case 96: bw_item<96, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+      case 128: bw_item<128, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+      case 192: bw_item<192, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+      default: bw_item<256, XF, XB, KIND>(a, smem, bi.tile, bi.ntile); break;
+    }
   }
 }
 
@@ -931,7 +975,7 @@ __global__ void __launch_bounds__(64 * kBatchWaves, 4)
     k_batched_level(const PassArgs* passes, const BatchItem* items) {
   extern __shared__ __align__(16) unsigned char smem[];
   const BatchItem bi = bw_take(items);
-  bw_item<L, XF, XB, KIND>(bw_args(passes[bi.pass]), smem, bi.tile, bi.ntile);
+  bw_item<L, XF, XB, KIND>(bw_args((ConstPass*)passes + bi.pass), smem, bi.tile, bi.ntile);
 }
 
 template <int XF, int XB, int L, int KIND>
@@ -968,61 +1012,82 @@ hipError_t bw_launch_one(const BatchGroup& g, const PassArgs* passes, const Batc
     case 64: return bw_launch_kind<XF, XB, 64>(g, passes, it, s);
     case 96: return bw_launch_kind<XF, XB, 96>(g, passes, it, s);
     case 128: return bw_launch_kind<XF, XB, 128>(g, passes, it, s);
-    case 192: return bw_launch_kind<XF, XB, 192>(g, passes, it, s);
-    case 256: return bw_launch_kind<XF, XB, 256>(g, passes, it, s);
-    default: return hipErrorInvalidValue;
+    default: break;
   }
+  if constexpr (r2r_half(XF)) {
+    if (g.L == 32) return bw_launch_kind<XF, XB, 32>(g, passes, it, s);
+    if (g.L == 48) return bw_launch_kind<XF, XB, 48>(g, passes, it, s);
+  } else {
+    if (g.L == 192) return bw_launch_kind<XF, XB, 192>(g, passes, it, s);
+    if (g.L == 256) return bw_launch_kind<XF, XB, 256>(g, passes, it, s);
+  }
+  return hipErrorInvalidValue;
 }
 
-template <int L>
-int bw_lds_L(int fast) {
-  using B = BW<L>;
-  const int base = (L + B::MAXN + kBatchWaves * B::PPW * slot_len(L)) * 8;
-  return fast == FAST_R2R_C ? base : base + B::S * B::MAXN * B::TS * 4;
+// f(L, H) as compile-time constants for the lengths of batched_wf_length;
+// false: no such length.
+template <class F>
+bool with_batch_length(int L, bool half, F&& f) {
+  auto go = [&](auto Lc, auto Hc) {
+    f(Lc, Hc);
+    return true;
+  };
+  using std::integral_constant;
+  if (half) {
+    switch (L) {
+      case 32: return go(integral_constant<int, 32>{}, std::true_type{});
+      case 48: return go(integral_constant<int, 48>{}, std::true_type{});
+      case 64: return go(integral_constant<int, 64>{}, std::true_type{});
+      case 96: return go(integral_constant<int, 96>{}, std::true_type{});
+      case 128: return go(integral_constant<int, 128>{}, std::true_type{});
+      default: return false;
+    }
+  }
+  switch (L) {
+    case 64: return go(integral_constant<int, 64>{}, std::false_type{});
+    case 96: return go(integral_constant<int, 96>{}, std::false_type{});
+    case 128: return go(integral_constant<int, 128>{}, std::false_type{});
+    case 192: return go(integral_constant<int, 192>{}, std::false_type{});
+    case 256: return go(integral_constant<int, 256>{}, std::false_type{});
+    default: return false;
+  }
 }
 
 }  // namespace
 
-bool batched_wf_length(int L) { return L == 64 || L == 96 || L == 128 || L == 192 || L == 256; }
+bool batched_wf_length(int L, bool half) {
+  return with_batch_length(L, half, [](auto, auto) {});
+}
 
-int batched_wf_lds(int fast, int L) {
-  switch (L) {
-    case 64: return bw_lds_L<64>(fast);
-    case 96: return bw_lds_L<96>(fast);
-    case 128: return bw_lds_L<128>(fast);
-    case 192: return bw_lds_L<192>(fast);
-    case 256: return bw_lds_L<256>(fast);
-    default: return -1;
-  }
+int batched_wf_lds(const PassArgs& a) {
+  int lds = -1;
+  with_batch_length(a.L, r2r_half(a.xf), [&](auto Lc, auto Hc) {
+    constexpr int L = decltype(Lc)::value;
+    using B = BW<L, decltype(Hc)::value>;
+    lds = (L + B::MAXN + kBatchWaves * B::PPW * slot_len(L)) * 8;
+    if (a.fast != FAST_R2R_C) lds += B::S * B::MAXN * B::TS * 4;
+  });
+  return lds;
 }
 
 int batched_wf_tiles(const PassArgs& a) {
-  int ppw = 0, P = 32;
-  switch (a.L) {
-    case 64: ppw = WF<64>::PPW; break;
-    case 96: ppw = WF<96>::PPW; break;
-    case 128: ppw = WF<128>::PPW; break;
-    case 192: ppw = WF<192>::PPW; break;
-    case 256: ppw = WF<256>::PPW; break;
-    default: return 0;
-  }
-  if (a.fast == FAST_R2R_C) {
+  if (a.fast != FAST_R2R_C) return ((a.Np + 31) / 32) * a.No;
+  int tiles = 0;
+  with_batch_length(a.L, r2r_half(a.xf), [&](auto Lc, auto) {
     const long long pairs = (long long)((a.Np + 1) / 2) * a.No;
-    const long long per = (long long)kBatchWaves * ppw;
-    return (int)((pairs + per - 1) / per);
-  }
-  return ((a.Np + P - 1) / P) * a.No;
+    const long long per = (long long)kBatchWaves * WF<decltype(Lc)::value>::PPW;
+    tiles = (int)((pairs + per - 1) / per);
+  });
+  return tiles;
 }
 
 int batched_wf_group(const PassArgs& a) {
   if (a.fast == FAST_R2R_C) return 1;
-  switch (a.L) {
-    case 64: return BW<64>::S;
-    case 96: return BW<96>::S;
-    case 128: return BW<128>::S;
-    case 192: return BW<192>::S;
-    default: return BW<256>::S;
-  }
+  int s = 1;
+  with_batch_length(a.L, r2r_half(a.xf), [&](auto Lc, auto Hc) {
+    s = BW<decltype(Lc)::value, decltype(Hc)::value>::S;
+  });
+  return s;
 }
 
 hipError_t launch_batched_group(int xf, const PassArgs* passes, const BatchItem* items,
@@ -1034,8 +1099,10 @@ hipError_t launch_batched_group(int xf, const PassArgs* passes, const BatchItem*
 }
 
 // ---------------------------------------------------------------- launch
-// Pencils per tile of the strided passes: runs of 128 bytes.
-int r2r_tile(int prec) { return prec == 0 ? 32 : 16; }
+// Pencils per tile of the strided passes: runs of 128 bytes (FP64 at length 32:
+// 256, the 16 pairs that one wavefront transforms).
+static constexpr int r2r_tile_of(int L, bool f32) { return f32 || L == 32 ? 32 : 16; }
+int r2r_tile(int L, int prec) { return r2r_tile_of(L, prec == 0); }
 
 // Wavefronts per strided workgroup: one per pair (PPW pairs per wavefront
 // for short transforms).
@@ -1050,7 +1117,7 @@ int r2r_lds_bytes(int fast, int L, int n, int nd, int prec) {
   const int ppw = 64 / (L / R0);
   const int SL = slot_len(L);
   if (fast == FAST_R2R_C) return (L + n + kR2RContigWaves * ppw * SL) * cs;
-  const int P = r2r_tile(prec);
+  const int P = r2r_tile(L, prec);
   // one pencil pair per lane group: the tile's pairs must fill whole wavefronts
   if ((P / 2) % ppw != 0) return -1;
   return (L + n + r2r_waves(P, ppw) * ppw * SL) * cs + (n + nd) * (P + 1) * es;
@@ -1058,21 +1125,22 @@ int r2r_lds_bytes(int fast, int L, int n, int nd, int prec) {
 
 namespace {
 
-template <typename T, int L>
+template <typename T, int L, bool H>
 hipError_t launch_fan_L(const PassArgs& a, hipStream_t s) {
   constexpr int PPW = WF<L>::PPW;
-  constexpr int P = sizeof(T) == 4 ? 32 : 16;
+  constexpr int P = r2r_tile_of(L, sizeof(T) == 4);
   constexpr int W = r2r_waves(P, PPW);
   if (a.nfan > kMaxFan || a.P != P) return hipErrorInvalidValue;
   long long blocks = 0;
   int rows = 0, drows = 0;
   for (int i = 0; i < a.nfan; ++i) {
     const FanJob& q = a.fan[i];
-    if (!q.in || !q.plain || q.n < 1 || q.n > L / 2 + 1 || q.Np < 1 || q.No < 1) return hipErrorInvalidValue;
-    if (q.deriv && (q.nd < 1 || q.nd > L / 2 + 1 || q.basis == FB_HARTLEY || q.basis == FB_ODD))
+    if (!q.in || !q.plain || q.n < 1 || q.n > kMaxRows<L, H> || q.Np < 1 || q.No < 1) return hipErrorInvalidValue;
+    if (q.deriv && (q.nd < 1 || q.nd > kMaxRows<L, H> || q.basis == FB_HARTLEY || q.basis == FB_ODD))
       return hipErrorInvalidValue;
-    // quarter twists (staggered types) are those of n points
-    if ((q.xp == X_DST3 || q.xp == X_DCT3) && q.n != a.n) return hipErrorInvalidValue;
+    // one family of types per kernel; the staggered ones have L points
+    if (r2r_half(q.xp) != H || (q.deriv && r2r_half(q.xd) != H)) return hipErrorInvalidValue;
+    if (H && (q.n != L || a.n != L || (q.deriv && q.nd != L))) return hipErrorInvalidValue;
     const long long per = (long long)kR2RContigWaves * PPW;
     blocks = std::max(blocks, a.fast == FAST_R2R_C ? ((long long)((q.Np + 1) / 2) * q.No + per - 1) / per
                                                    : (long long)((q.Np + P - 1) / P) * q.No);
@@ -1083,38 +1151,39 @@ hipError_t launch_fan_L(const PassArgs& a, hipStream_t s) {
     return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks, a.nfan);
   if (a.fast == FAST_R2R_C) {
-    allow_lds<kb_contig_fan<T, L>>();
-    hipLaunchKernelGGL((kb_contig_fan<T, L>), grid, dim3(64 * kR2RContigWaves), a.lds_bytes, s, a);
+    allow_lds<kb_contig_fan<T, L, H>>();
+    hipLaunchKernelGGL((kb_contig_fan<T, L, H>), grid, dim3(64 * kR2RContigWaves), a.lds_bytes, s, a);
     return hipGetLastError();
   }
   if constexpr (W < 1 || (P / 2) % PPW != 0) {
     return hipErrorInvalidValue;
   } else if (a.fast == FAST_R2R_SW) {
     if (a.xb != r2r_partner(a.xf) || a.nfan != 1 || !a.fan[0].deriv) return hipErrorInvalidValue;
-    allow_lds<kb_strided_fan<T, L, P, W, true>>();
-    hipLaunchKernelGGL((kb_strided_fan<T, L, P, W, true>), grid, dim3(64 * W), a.lds_bytes, s, a);
+    allow_lds<kb_strided_fan<T, L, H, P, W, true>>();
+    hipLaunchKernelGGL((kb_strided_fan<T, L, H, P, W, true>), grid, dim3(64 * W), a.lds_bytes, s, a);
   } else {
-    allow_lds<kb_strided_fan<T, L, P, W, false>>();
-    hipLaunchKernelGGL((kb_strided_fan<T, L, P, W, false>), grid, dim3(64 * W), a.lds_bytes, s, a);
+    allow_lds<kb_strided_fan<T, L, H, P, W, false>>();
+    hipLaunchKernelGGL((kb_strided_fan<T, L, H, P, W, false>), grid, dim3(64 * W), a.lds_bytes, s, a);
   }
   return hipGetLastError();
 }
 
-template <typename T, int L>
+template <typename T, int L, bool H>
 hipError_t launch_bounded_L(const PassArgs& a, hipStream_t s) {
   constexpr int PPW = WF<L>::PPW;
   const int lds = a.lds_bytes;
-  if (a.n < 1 || a.n > L / 2 + 1) return hipErrorInvalidValue;  // rows per pencil of every Table 1 type
-  if (a.nfan > 0) return launch_fan_L<T, L>(a, s);
+  // rows per pencil of every Table 1 type
+  if (H ? a.n != L : (a.n < 1 || a.n > L / 2 + 1)) return hipErrorInvalidValue;
+  if (a.nfan > 0) return launch_fan_L<T, L, H>(a, s);
   if (a.fast == FAST_R2R_C) {
     const long long pairs = (long long)((a.Np + 1) / 2) * a.No;
     const long long per_block = (long long)kR2RContigWaves * PPW;
-    allow_lds<kb_contig<T, L>>();
-    hipLaunchKernelGGL((kb_contig<T, L>), dim3((unsigned)((pairs + per_block - 1) / per_block)),
+    allow_lds<kb_contig<T, L, H>>();
+    hipLaunchKernelGGL((kb_contig<T, L, H>), dim3((unsigned)((pairs + per_block - 1) / per_block)),
                        dim3(64 * kR2RContigWaves), lds, s, a);
     return hipGetLastError();
   }
-  constexpr int P = sizeof(T) == 4 ? 32 : 16;
+  constexpr int P = r2r_tile_of(L, sizeof(T) == 4);
   constexpr int W = r2r_waves(P, PPW);
   if (a.P != P) return hipErrorInvalidValue;
   if constexpr (W < 1 || (P / 2) % PPW != 0) {
@@ -1128,26 +1197,26 @@ hipError_t launch_bounded_L(const PassArgs& a, hipStream_t s) {
     if (a.fast == FAST_R2R_SW) {
       if (a.xb != r2r_partner(a.xf)) return hipErrorInvalidValue;
       if constexpr (kPers) {
-        allow_lds<kb_strided<T, L, P, W, true, true>>();
-        const int nb = persistent_grid<kb_strided<T, L, P, W, true, true>>(64 * W, lds, ntiles);
+        allow_lds<kb_strided<T, L, H, P, W, true, true>>();
+        const int nb = persistent_grid<kb_strided<T, L, H, P, W, true, true>>(64 * W, lds, ntiles);
         if (ntiles > 4 * nb && !std::getenv("HP_R2R_NOPERS")) {
-          hipLaunchKernelGGL((kb_strided<T, L, P, W, true, true>), dim3(nb), dim3(64 * W), lds, s, a);
+          hipLaunchKernelGGL((kb_strided<T, L, H, P, W, true, true>), dim3(nb), dim3(64 * W), lds, s, a);
           return hipGetLastError();
         }
       }
-      allow_lds<kb_strided<T, L, P, W, true, false>>();
-      hipLaunchKernelGGL((kb_strided<T, L, P, W, true, false>), grid, dim3(64 * W), lds, s, a);
+      allow_lds<kb_strided<T, L, H, P, W, true, false>>();
+      hipLaunchKernelGGL((kb_strided<T, L, H, P, W, true, false>), grid, dim3(64 * W), lds, s, a);
     } else {
       if constexpr (kPers) {
-        allow_lds<kb_strided<T, L, P, W, false, true>>();
-        const int nb = persistent_grid<kb_strided<T, L, P, W, false, true>>(64 * W, lds, ntiles);
+        allow_lds<kb_strided<T, L, H, P, W, false, true>>();
+        const int nb = persistent_grid<kb_strided<T, L, H, P, W, false, true>>(64 * W, lds, ntiles);
         if (ntiles > 4 * nb) {
-          hipLaunchKernelGGL((kb_strided<T, L, P, W, false, true>), dim3(nb), dim3(64 * W), lds, s, a);
+          hipLaunchKernelGGL((kb_strided<T, L, H, P, W, false, true>), dim3(nb), dim3(64 * W), lds, s, a);
           return hipGetLastError();
         }
       }
-      allow_lds<kb_strided<T, L, P, W, false, false>>();
-      hipLaunchKernelGGL((kb_strided<T, L, P, W, false, false>), grid, dim3(64 * W), lds, s, a);
+      allow_lds<kb_strided<T, L, H, P, W, false, false>>();
+      hipLaunchKernelGGL((kb_strided<T, L, H, P, W, false, false>), grid, dim3(64 * W), lds, s, a);
     }
     return hipGetLastError();
   }
@@ -1155,20 +1224,32 @@ hipError_t launch_bounded_L(const PassArgs& a, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_bounded_T(const PassArgs& a, hipStream_t s) {
+  // 3 x 2^k lengths: FP32 only (radix-12 first stage; FP64 stays on the
+  // general kernels, see r2r_lds_bytes)
+  if constexpr (sizeof(T) == 4) {
+    if (wf_half(a)) {
+      if (a.L == 48) return launch_bounded_L<T, 48, true>(a, s);
+      if (a.L == 96) return launch_bounded_L<T, 96, true>(a, s);
+      if (a.L == 192) return launch_bounded_L<T, 192, true>(a, s);
+    } else {
+      if (a.L == 96) return launch_bounded_L<T, 96, false>(a, s);
+      if (a.L == 192) return launch_bounded_L<T, 192, false>(a, s);
+    }
+  }
+  if (wf_half(a)) {
+    switch (a.L) {
+      case 32: return launch_bounded_L<T, 32, true>(a, s);
+      case 64: return launch_bounded_L<T, 64, true>(a, s);
+      case 128: return launch_bounded_L<T, 128, true>(a, s);
+      case 256: return launch_bounded_L<T, 256, true>(a, s);
+      default: return hipErrorInvalidValue;
+    }
+  }
   switch (a.L) {
-    case 64: return launch_bounded_L<T, 64>(a, s);
-    // 3 x 2^k lengths: FP32 only (radix-12 first stage; FP64 stays on the
-    // general kernels, see r2r_lds_bytes)
-    case 96:
-      if constexpr (sizeof(T) == 4) return launch_bounded_L<T, 96>(a, s);
-      else return hipErrorInvalidValue;
-    case 192:
-      if constexpr (sizeof(T) == 4) return launch_bounded_L<T, 192>(a, s);
-      else return hipErrorInvalidValue;
-    case 128: return launch_bounded_L<T, 128>(a, s);
-    case 256: return launch_bounded_L<T, 256>(a, s);
-    case 512: return launch_bounded_L<T, 512>(a, s);
-    case 1024: return launch_bounded_L<T, 1024>(a, s);
+    case 64: return launch_bounded_L<T, 64, false>(a, s);
+    case 128: return launch_bounded_L<T, 128, false>(a, s);
+    case 256: return launch_bounded_L<T, 256, false>(a, s);
+    case 512: return launch_bounded_L<T, 512, false>(a, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -18,6 +18,20 @@ template <typename T>
 __device__ __forceinline__ C2<T> cmul(C2<T> a, C2<T> b) {
   return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
+// A value that is rounded here: no fused multiply-add takes the product that
+// made it.  Left to the compiler, which of two products of a sum is fused
+// depends on the kernel around it; kernels that owe each other the same bits
+// use this (no instruction of its own).
+template <typename T>
+__device__ __forceinline__ T rounded(T x) {
+  asm("" : "+v"(x));
+  return x;
+}
+// cmul with one order of roundings everywhere.
+template <typename T>
+__device__ __forceinline__ C2<T> cmul_fixed(C2<T> a, C2<T> b) {
+  return {fma(a.re, b.re, -rounded(a.im * b.im)), fma(a.re, b.im, rounded(a.im * b.re))};
+}
 template <typename T>
 __device__ __forceinline__ C2<T> cscale(C2<T> a, T s) { return {a.re * s, a.im * s}; }
 template <typename T>
@@ -89,7 +103,8 @@ __device__ __forceinline__ void dft4v(C2<T>* v) {
 
 // HALF: v[4..7] are known to be zero (zero-padded input), the first
 // butterfly layer reduces to copies.
-template <typename T, bool INV, bool HALF = false>
+// FIX: the 45 degree products rounded on their own (`rounded`).
+template <typename T, bool INV, bool HALF = false, bool FIX = false>
 __device__ __forceinline__ void dft8(C2<T>* v) {
   const T r = (T)0.70710678118654752440084436210485;
   C2<T> a0, a1, a2, a3, b0, b1, b2, b3;
@@ -106,6 +121,10 @@ __device__ __forceinline__ void dft8(C2<T>* v) {
   } else {
     b1 = {(b1.re + b1.im) * r, (b1.im - b1.re) * r};
     b3 = {(b3.im - b3.re) * r, (-b3.re - b3.im) * r};
+  }
+  if constexpr (FIX) {
+    b1 = {rounded(b1.re), rounded(b1.im)};
+    b3 = {rounded(b3.re), rounded(b3.im)};
   }
   b2 = rot<T, INV>(b2);
   dft4<T, INV>(a0, a1, a2, a3);

@@ -176,12 +176,23 @@ enum FastKind : int { FAST_NONE = 0, FAST_R2C = 1, FAST_FWD_Y = 2, FAST_SANDWICH
 enum InvYMode : int { IY_PLAIN = 0, IY_CURL5 = 1, IY_GRAD2 = 2 };
 
 // Elements per lane of the wavefront FFT of length L (0: no such FFT):
-// powers of two 64 .. 1024 (8, 16 from 1024) and 48, 96, 192 (12).
+// powers of two 32 .. 1024 (8, 16 from 1024) and 48, 96, 192 (12).
 __host__ __device__ constexpr int wf_r0(int L) {
   return (L == 48 || L == 96 || L == 192) ? 12
-         : (L >= 64 && L <= 1024 && (L & (L - 1)) == 0) ? (L >= 1024 ? 16 : 8)
+         : (L >= 32 && L <= 1024 && (L & (L - 1)) == 0) ? (L >= 1024 ? 16 : 8)
                                                          : 0;
 }
+
+// The staggered real-to-real types: on the wavefront kernels their FFT has the
+// n points of the transform (PassArgs.L = n), not the 2 n of the symmetric
+// extension that the general kernels transform.  Half the butterflies and LDS
+// traffic per pencil.
+__host__ __device__ constexpr bool r2r_half(int x) {
+  return x == X_DCT2 || x == X_DST2 || x == X_DCT3 || x == X_DST3;
+}
+inline bool wf_half(const PassArgs& a) { return r2r_half(a.nfan > 0 ? a.fan[0].xp : a.xf); }
+// FFT length of a general real-to-real pass on the wavefront kernels.
+inline int wf_length(const PassArgs& a) { return wf_half(a) ? a.n : a.L; }
 
 // Launch one wavefront-FFT pass (power-of-two L in [64, 1024]).
 hipError_t launch_fast(const PassArgs& a, int prec, int grid_y, hipStream_t s);
@@ -216,7 +227,7 @@ hipError_t launch_fd_deriv(const FdArgs& a, int prec, hipStream_t s);
 // spectral buffers (-1: no kernel for these lengths) and the launch
 int small2d_lds_bytes(int L0, int L1, int prec, int nbuf);
 hipError_t launch_small2d(const PassArgs& a, int prec, hipStream_t s);
-int r2r_tile(int prec);
+int r2r_tile(int L, int prec);
 int r2r_lds_bytes(int fast, int L, int n, int nd, int prec);
 // Dynamic LDS bytes of a wavefront-FFT pass; 0 if the pass is not available.
 int fast_lds_bytes(int fast, int L, int P, int K2, int prec, int dbl, int pad);
@@ -325,8 +336,8 @@ hipError_t launch_batched(const PassArgs* passes, const BatchItem* items, const 
 // Tiles: batched_wf_tiles per pass; a strided item should hold a multiple of
 // batched_wf_group tiles (one per group of wavefronts of the workgroup).
 // LDS: the largest batched_wf_lds of its passes.
-bool batched_wf_length(int L);
-int batched_wf_lds(int fast, int L);
+bool batched_wf_length(int L, bool half);
+int batched_wf_lds(const PassArgs& a);
 int batched_wf_tiles(const PassArgs& a);
 int batched_wf_group(const PassArgs& a);
 hipError_t launch_batched_group(int xf, const PassArgs* passes, const BatchItem* items,

@@ -1,4 +1,4 @@
-// Wavefront-level FFT of length L = 64 .. 1024 (powers of two) and
+// Wavefront-level FFT of length L = 32 .. 1024 (powers of two) and
 // L = 48, 96, 192 (3 times a power of two) (gfx950).
 //
 // A pencil of length L is held by G = L / R0 lanes, R0 elements per lane:
@@ -69,8 +69,11 @@ __device__ __forceinline__ int padrun(int a, int t) {
 // barrier, so their LDS latency overlaps it (read at the multiply, each pair
 // of them costs a wait of its own); it holds NB (R - 1) more complex values in
 // registers across the exchange.
+// FIX: one order of roundings whatever the kernel around (`rounded`): the
+// bounded passes owe each other the same bits, since psi of a solve with
+// derivatives comes from other kernels than psi alone.
 template <typename T, int L, int R, int NS, bool LAST, bool INV, typename PR, typename PW,
-          bool TWPRE = true>
+          bool TWPRE = true, bool FIX = false>
 __device__ __forceinline__ void wstage(C2<T> (&x)[WF<L>::R0], C2<T>* buf, int bs, int g,
                                        const C2<T>* twS) {
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, NB = R0 / R;
@@ -99,9 +102,11 @@ __device__ __forceinline__ void wstage(C2<T> (&x)[WF<L>::R0], C2<T>* buf, int bs
     for (int t = 1; t < R; ++t) {
       C2<T> tw1 = TWPRE ? w[b * (R - 1) + t - 1] : twS[(t - 1) * NS + k];
       if (INV) tw1.im = -tw1.im;
-      v[b * R + t] = cmul(v[b * R + t], tw1);
+      if constexpr (FIX) v[b * R + t] = cmul_fixed(v[b * R + t], tw1);
+      else v[b * R + t] = cmul(v[b * R + t], tw1);
     }
-    dftN<T, R, INV>(&v[b * R]);
+    if constexpr (FIX && R == 8) dft8<T, INV, false, true>(&v[b * R]);
+    else dftN<T, R, INV>(&v[b * R]);
     if constexpr (LAST) {
 #pragma unroll
       for (int t = 0; t < R; ++t) x[b + t * NB] = v[b * R + t];
@@ -127,7 +132,8 @@ __device__ __forceinline__ void wstage(C2<T> (&x)[WF<L>::R0], C2<T>* buf, int bs
 // In-place FFT of the pencil held as x[i] = x[g + G i]; on return x[i] = X[g + G i].
 // HALF: x[i] is zero for i >= R0 / 2 (zero-padded input).  tw is the
 // per-stage twiddle table (stage 1 at 0, stage 2 at 7 R0).
-template <typename T, int L, bool INV, bool HALF = false, bool SMALL = false, bool TWPRE = true>
+template <typename T, int L, bool INV, bool HALF = false, bool SMALL = false, bool TWPRE = true,
+          bool FIX = false>
 __device__ __forceinline__ void wave_fft(C2<T> (&x)[WF<L>::R0], C2<T>* buf, int bs, int g,
                                          const C2<T>* tw) {
   // SMALL: both exchanges in the first layout (a shorter slot, 2x conflicts
@@ -135,6 +141,7 @@ __device__ __forceinline__ void wave_fft(C2<T> (&x)[WF<L>::R0], C2<T>* buf, int 
   using PB = typename std::conditional<SMALL, PadA, PadB<L>>::type;
   constexpr int R0 = WF<L>::R0, G = WF<L>::G;
   if constexpr (HALF) dftN_half<T, R0, INV>(x);
+  else if constexpr (FIX && R0 == 8) dft8<T, INV, false, true>(x);
   else dftN<T, R0, INV>(x);
   wave_sync();
   if constexpr (R0 % 16 == 0 || 16 % R0 == 0) {
@@ -148,16 +155,16 @@ __device__ __forceinline__ void wave_fft(C2<T> (&x)[WF<L>::R0], C2<T>* buf, int 
   }
   wave_sync();
   if constexpr (G <= 8 && R0 % G == 0) {
-    // one more stage, of radix G (R0 = 8, G = 8; R0 = 12, G = 4)
-    wstage<T, L, G, R0, true, INV, PadA, PadA, TWPRE>(x, buf, bs, g, tw);
+    // one more stage, of radix G (R0 = 8, G = 4 or 8; R0 = 12, G = 4)
+    wstage<T, L, G, R0, true, INV, PadA, PadA, TWPRE, FIX>(x, buf, bs, g, tw);
   } else if constexpr (R0 % 3 == 0) {
     // R0 = 12: a radix-4 stage, then radix G / 4 (2 or 4)
-    wstage<T, L, 4, R0, false, INV, PadA, PadA, TWPRE>(x, buf, bs, g, tw);
-    wstage<T, L, G / 4, 4 * R0, true, INV, PadA, PadA, TWPRE>(x, buf, bs, g, tw + 3 * R0);
+    wstage<T, L, 4, R0, false, INV, PadA, PadA, TWPRE, FIX>(x, buf, bs, g, tw);
+    wstage<T, L, G / 4, 4 * R0, true, INV, PadA, PadA, TWPRE, FIX>(x, buf, bs, g, tw + 3 * R0);
   } else {
     static_assert((R0 & (R0 - 1)) == 0, "three stages: power-of-two lengths only");
-    wstage<T, L, 8, R0, false, INV, PadA, PB, TWPRE>(x, buf, bs, g, tw);
-    wstage<T, L, G / 8, 8 * R0, true, INV, PB, PB, TWPRE>(x, buf, bs, g, tw + 7 * R0);
+    wstage<T, L, 8, R0, false, INV, PadA, PB, TWPRE, FIX>(x, buf, bs, g, tw);
+    wstage<T, L, G / 8, 8 * R0, true, INV, PB, PB, TWPRE, FIX>(x, buf, bs, g, tw + 7 * R0);
   }
 }
 

@@ -1,0 +1,68 @@
+"""Staggered transforms on the wavefront kernels, whose FFT has the transform's
+own length: the smallest and largest lengths of the rule, the 3 x 2^k ones, one
+beyond it on either side (general kernels), pencil counts that leave a pair or
+a tile unfilled, and batches of them, against the oracle; psi has the same bits
+with and without derivatives.  Tolerances: those of the parity tests."""
+import numpy as np
+import pytest
+
+from gpu_util import TOL, rel_l2, rel_max, to_dev
+
+pytestmark = pytest.mark.gpu
+
+LO = [0.0, -0.5, 1.0]
+HI = [1.0, 1.3, 2.5]
+
+CASES = [
+    (["dirichlet"] * 2, [32, 48]), (["neumann"] * 2, [48, 32]), (["neumann", "dirichlet"], [256, 64]),
+    (["dirichlet", "neumann"], [192, 256]), (["neumann"] * 2, [16, 64]), (["dirichlet"] * 2, [512, 32]),
+    (["neumann"] * 3, [32, 96, 48]), (["dirichlet"] * 3, [64, 32, 128]),
+    (["periodic", "neumann", "dirichlet"], [37, 48, 32]), (["dirichlet", "periodic", "neumann"], [64, 3, 96]),
+    (["neumann", "dirichlet", "periodic"], [32, 64, 35]),
+]
+
+
+@pytest.mark.parametrize("bc,nc", CASES)
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_half_length_types(bc, nc, prec):
+    import oracle
+    import torch
+    from paper_2301_01145_amd import Solver
+    print(f"half {bc} {nc} {prec}", flush=True)
+    nd = len(nc)
+    dtype = torch.float32 if prec == "f32" else torch.float64
+    f = np.random.default_rng(17).normal(size=nc).astype(np.float32 if prec == "f32" else np.float64)
+    l2, mx = TOL[prec]
+    psis = []
+    for diff in ("none", "grad"):
+        ref, rd = oracle.solve(bc, "staggered", nc, LO[:nd], HI[:nd], f.astype(np.float64), operator="fd2", diff=diff)
+        s = Solver(bc, "staggered", nc, LO[:nd], HI[:nd], kernel="fd2", diff=diff, dtype=dtype)
+        psi, der = s.solve(to_dev(f, dtype, torch))
+        torch.cuda.synchronize()
+        psis.append(psi[0].double().cpu().numpy())
+        for g, r in [(psis[-1], ref)] + [(d.double().cpu().numpy(), r) for d, r in zip(der, rd)]:
+            assert g.shape == r.shape and np.all(np.isfinite(g))
+            assert rel_l2(g, r) <= l2 and rel_max(g, r) <= mx, (diff, rel_l2(g, r), rel_max(g, r))
+        s.close()
+    if "periodic" not in bc:
+        assert np.array_equal(psis[0], psis[1])
+
+
+@pytest.mark.parametrize("bc", ["dirichlet", "neumann"])
+def test_batches_of_every_length(bc):
+    import oracle
+    import torch
+    from paper_2301_01145_amd.batched import BatchedSolver
+    sizes = [[32, 32, 32], [48, 32, 96], [128, 64, 48], [96, 128, 32], [64, 48, 64], [32, 128, 32]]
+    rng = np.random.default_rng(23)
+    fs = [rng.normal(size=nc).astype(np.float32) for nc in sizes]
+    b = BatchedSolver(bc, "staggered", [{"nc": nc} for nc in sizes], kernel="fd2")
+    psi = b.bind([to_dev(f, torch.float32, torch) for f in fs])
+    b.run()
+    torch.cuda.synchronize()
+    l2, mx = TOL["f32"]
+    for nc, f, g in zip(sizes, fs, psi):
+        nd = len(nc)
+        ref, _ = oracle.solve(bc, "staggered", nc, [0.0] * nd, [1.0] * nd, f.astype(np.float64), operator="fd2")
+        g = g.double().cpu().numpy()
+        assert rel_l2(g, ref) <= l2 and rel_max(g, ref) <= mx, (nc, rel_l2(g, ref), rel_max(g, ref))
