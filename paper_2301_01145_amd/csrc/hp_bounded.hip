@@ -7,8 +7,9 @@
 //   DST-I   L = 2(n+1): [0, x_0..x_{n-1}, 0, -x_{n-1}..-x_0]
 //   DCT-I   L = 2(n-1): [x_0..x_{n-1}, x_{n-2}..x_1]
 // and every output is read from a single FFT bin.  The staggered types reorder
-// it instead (r2r_build), L = n; types II take an output from the bins k and
-// n - k (mirror_bin).  Lane g holds bins g + G i, so the outputs stay in the
+// it instead (r2r_build), L = n; types II, and the Hartley transform of a
+// periodic axis of a mixed plan, take an output from the bins k and n - k
+// (mirror_bin).  Lane g holds bins g + G i, so the outputs stay in the
 // lanes that computed them.
 //
 // Passes (the pencil descriptors are those of the general path, in place in
@@ -76,6 +77,7 @@ __device__ __forceinline__ C2<T> r2r_build(int x, int m, int n, int L, const C2<
       const C2<T> d = {u.re + um.im, u.im - um.re}, w = q[m];
       return cmul_fixed(d, cconj(w));
     }
+    case X_DHT: return {get(m, 0), get(m, 1)};
     default:
       return {(T)0, (T)0};
   }
@@ -128,6 +130,13 @@ __device__ __forceinline__ int r2r_extract(int x, int i, int g, int n, const C2<
       ob = fma(d.re, w.im, rounded(d.im * w.re));
       return x == X_DST2 ? n - 1 - m : m;
     }
+    case X_DHT: {  // Re - Im of either pencil's bin, from the bins k and n - k
+      const C2<T> c = mirror_bin<T, L>(v, i, g);
+      const T h = (T)0.5;
+      oa = h * ((z.re + c.re) - (z.im - c.im));
+      ob = h * ((z.im + c.im) + (z.re - c.re));
+      return m;
+    }
     default:
       return -1;
   }
@@ -155,7 +164,7 @@ __device__ __forceinline__ void r2r_fft(C2<T> (&v)[WF<L>::R0], int x, int n, C2<
 
 // Runs f with the transform type as a compile-time constant: one branch per
 // FFT (uniform per wavefront) instead of a switch per element.  H: one of the
-// staggered types, else one of the regular ones (a kernel holds one family).
+// types of r2r_half, else one of the regular ones (a kernel holds one family).
 template <bool H, class F>
 __device__ __forceinline__ void with_xform(int x, F&& f) {
   if constexpr (H) {
@@ -163,6 +172,7 @@ __device__ __forceinline__ void with_xform(int x, F&& f) {
       case X_DST2: f(std::integral_constant<int, X_DST2>{}); break;
       case X_DST3: f(std::integral_constant<int, X_DST3>{}); break;
       case X_DCT2: f(std::integral_constant<int, X_DCT2>{}); break;
+      case X_DHT: f(std::integral_constant<int, X_DHT>{}); break;
       default: f(std::integral_constant<int, X_DCT3>{}); break;
     }
   } else {

@@ -183,12 +183,12 @@ __host__ __device__ constexpr int wf_r0(int L) {
                                                          : 0;
 }
 
-// The staggered real-to-real types: on the wavefront kernels their FFT has the
-// n points of the transform (PassArgs.L = n), not the 2 n of the symmetric
-// extension that the general kernels transform.  Half the butterflies and LDS
-// traffic per pencil.
+// The real-to-real types whose FFT on the wavefront kernels has the n points of
+// the transform (PassArgs.L = n): the staggered ones, not the 2 n of the
+// symmetric extension that the general kernels transform (half the butterflies
+// and LDS traffic per pencil), and the Hartley transform.
 __host__ __device__ constexpr bool r2r_half(int x) {
-  return x == X_DCT2 || x == X_DST2 || x == X_DCT3 || x == X_DST3;
+  return x == X_DCT2 || x == X_DST2 || x == X_DCT3 || x == X_DST3 || x == X_DHT;
 }
 inline bool wf_half(const PassArgs& a) { return r2r_half(a.nfan > 0 ? a.fan[0].xp : a.xf); }
 // FFT length of a general real-to-real pass on the wavefront kernels.

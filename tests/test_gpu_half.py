@@ -19,6 +19,11 @@ CASES = [
     (["neumann"] * 3, [32, 96, 48]), (["dirichlet"] * 3, [64, 32, 128]),
     (["periodic", "neumann", "dirichlet"], [37, 48, 32]), (["dirichlet", "periodic", "neumann"], [64, 3, 96]),
     (["neumann", "dirichlet", "periodic"], [32, 64, 35]),
+    # Hartley transforms on either side of 64 points, along every axis
+    (["periodic", "neumann", "dirichlet"], [64, 48, 32]), (["dirichlet", "periodic", "neumann"], [32, 96, 64]),
+    (["neumann", "dirichlet", "periodic"], [64, 32, 128]), (["periodic", "dirichlet", "periodic"], [48, 32, 192]),
+    (["unbounded", "periodic", "periodic"], [24, 64, 96]), (["periodic", "unbounded"], [256, 33]),
+    (["periodic", "neumann"], [512, 64]),
 ]
 
 
