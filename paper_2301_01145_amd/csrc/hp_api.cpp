@@ -894,8 +894,32 @@ hp_status finish_pass_with(hp_plan p, PassArgs& a, int want, int minP, const Tun
       return HP_E_UNSUPPORTED;  // does not fit: caller takes the default
     return HP_OK;
   }
-  if (!choose_tile(a, p->prec, want, minP))
-    return fail(p, HP_E_UNSUPPORTED, "pass of length " + std::to_string(a.L) + " does not fit in LDS");
+  // A pass with derivatives takes the stages of the same pass without them, so
+  // that psi has the same bits in both; a sandwich, which then holds a second
+  // tile, narrows its tile instead (radices that fit a tile fit a narrower one)
+  PassArgs plain = a;
+  plain.nfan = 0;
+  bool ok = choose_tile(plain, p->prec, want, minP);
+  if (ok) {
+    a.P = plain.P;
+    a.big = plain.big;
+    a.nstage = plain.nstage;
+    for (int s = 0; s < a.nstage; ++s) a.radix[s] = plain.radix[s];
+    const int budget = plain.lds_bytes <= 64 * 1024 ? 64 * 1024 : 160 * 1024;
+    a.lds_bytes = general_lds_bytes(a, a.P, p->prec);
+    while (a.lds_bytes > budget && a.P / 2 >= minP) {
+      a.P >>= 1;
+      a.lds_bytes = general_lds_bytes(a, a.P, p->prec);
+    }
+    // two tiles of a long prime length beside its table (FP64 primes above
+    // 3413): the larger register budget's kernel runs without the table
+    if (a.lds_bytes > 160 * 1024 && !a.big) {
+      a.big = 1;
+      a.lds_bytes = general_lds_bytes(a, a.P, p->prec);
+    }
+    ok = general_fits(a, p->prec) && a.lds_bytes <= 160 * 1024;
+  }
+  if (!ok) return fail(p, HP_E_UNSUPPORTED, "pass of length " + std::to_string(a.L) + " does not fit in LDS");
   return HP_OK;
 }
 
