@@ -202,7 +202,8 @@ bool choose_radices(PassArgs& a, int prec) {
 // short of workgroups the tile is narrowed (kFillTiles): a pass of fewer tiles
 // than CUs takes as long as one tile does (FP64 periodic 2D of about 200 x 250
 // points, 16 and 5 tiles: 151 -> 38 us together with the stages above).
-constexpr int kFillTiles = 256;  // one workgroup per CU
+constexpr int kCUs = 256;
+constexpr int kFillTiles = kCUs;  // one workgroup per CU
 constexpr int kNarrowest = 4;    // pencils a tile is narrowed to
 
 bool choose_tile(PassArgs& a, int prec, int want, int minP) {
@@ -985,11 +986,12 @@ bool bounded_fast_ok(hp_plan p, const Problem& P, const int* L) {
 // Switch a general bounded pass (same descriptor) to its wavefront kernel.
 hp_status to_fast_r2r(hp_plan p, PassArgs& a) {
   if (a.fast == FAST_ADD || a.fast == FAST_FILL) return HP_OK;
-  // the free axis's Green's-row sandwich, Hartley passes with derivatives and of
-  // lengths without a wavefront FFT: general kernels; Hartley passes of 32 and 48
-  // points too (a free and two periodic axes, FP32: 32^3 29.4 us general, 27.4; 48^3
-  // 31.8, 33.4; but 64^3 35.7, 31.0; 128^3 75.1, 56.8; 256^3 308, 221)
-  if (a.xf == X_DHT && (a.nfan > 0 || a.n < 64 || a.n > 256 || wf_r0(a.n) <= 0)) return HP_OK;
+  // the free axis's Green's-row sandwich and Hartley passes of lengths without a
+  // wavefront FFT: general kernels; Hartley passes of 32 and 48 points too (a free
+  // and two periodic axes, FP32: 32^3 29.4 us general, 27.4; 48^3 31.8, 33.4; but
+  // 64^3 35.7, 31.0; 128^3 75.1, 56.8; 256^3 308, 221).  The line is the same with
+  // and without derivatives, as psi has the same bits in both.
+  if (a.xf == X_DHT && (a.n < 64 || a.n > 256 || wf_r0(a.n) <= 0)) return HP_OK;
   if (a.mult == M_GREEN_ROWS || a.xf == X_PAIR_F) return HP_OK;
   const bool contig = a.kind == PK_ONEWAY && a.in_jfast && a.out_jfast;
   bool faces = false;
@@ -997,17 +999,31 @@ hp_status to_fast_r2r(hp_plan p, PassArgs& a) {
   if (faces && !contig) return HP_OK;  // boundary terms: contiguous passes only
   const int kind = a.kind == PK_SANDWICH ? FAST_R2R_SW : (contig ? FAST_R2R_C : FAST_R2R_S);
   int nd = 0;
-  for (int i = 0; i < a.nfan; ++i)
+  long long tiles = 0;
+  const int len = wf_length(a), P = r2r_tile(len, p->prec);
+  for (int i = 0; i < a.nfan; ++i) {
     if (a.fan[i].deriv) nd = std::max(nd, a.fan[i].nd);
-  const int len = wf_length(a);
-  const int lds = r2r_lds_bytes(kind, len, a.n, nd, p->prec);
+    tiles = std::max(tiles, (long long)((a.fan[i].Np + P - 1) / P) * a.fan[i].No * a.nfan);
+  }
+  int lds = r2r_lds_bytes(kind, len, std::max(a.n, nd), 0, p->prec);
+  a.emit_dbl = 0;
+  if (a.nfan > 0 && kind != FAST_R2R_C) {
+    // a second tile for the derivative where that costs no workgroup its place:
+    // one tile holds no more workgroups, or all are resident with two
+    const int both = r2r_lds_bytes(kind, len, std::max(a.n, nd), nd, p->prec);
+    if (both <= 0) return HP_OK;
+    if (!fan_one_tile(kind, len, wf_half(a), p->prec) || tiles <= (long long)kCUs * (160 * 1024 / both)) {
+      a.emit_dbl = 1;
+      lds = both;
+    }
+  }
   if (lds <= 0 || lds > 160 * 1024) return HP_OK;  // stays on the general kernel
   a.fast = kind;
   a.L = len;
   const void* tw;
   HP_TRY(fast_twiddles(p, a.L, &tw));
   a.tw = tw;
-  a.P = r2r_tile(a.L, p->prec);
+  a.P = P;
   a.lds_bytes = lds;
   return HP_OK;
 }
@@ -1213,6 +1229,23 @@ hp_status fan_pass(hp_plan p, const Problem& P, int comp, PassArgs& a, int c, in
   return HP_OK;
 }
 
+// Whether a fan pass on the wavefront kernels streams its outputs (rows off the
+// cache lines are stored through the caches in any case): the last pass of a
+// solve, whose outputs no pass reads, and outputs too small or too large to be
+// found in the Infinity Cache (gradients, whole solves in us, through the caches
+// against streaming; MiB of a pass's two arrays: FP32 128^3, 16 MiB 68.3, 66.8; 192 x
+// 128 x 128, 24 MiB 85.6, 88.0; 192 x 128 x 160, 30 MiB 166, 175; 256^3, 128 MiB 330, 337;
+// FP64 256^3, 256 MiB 631, 619).
+void fan_stream(PassArgs& a, bool last, size_t es) {
+  constexpr double kMiB = 1024.0 * 1024.0;
+  double out = 0.0;
+  for (int i = 0; i < a.nfan; ++i) {
+    const FanJob& q = a.fan[i];
+    out += (double)q.Np * q.No * (q.n + (q.deriv ? q.nd : 0)) * (double)es;
+  }
+  a.stream = last || out < 20 * kMiB || out > 256 * kMiB;
+}
+
 // Model bytes of a fan pass: every array read once, every output written once.
 double fan_bytes(const PassArgs& a, size_t es) {
   double b = 0.0;
@@ -1284,6 +1317,7 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       fields.push_back(tl ? fan_laplacian(P, comp, a.xb, tl->dst, tl->sign, a, q)
                           : fan_derivative(P, comp, 0, t0->dst, t0->sign, q));
       q.deriv = fan_view(fields.back(), ws, es);
+      fan_stream(a, nd == 1, es);
     };
     auto push = [&](const PassArgs& a) {
       PassRec r{a, 1};
@@ -1389,6 +1423,7 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
         if (nd == 3) { a.in_so = a.out_so = ws[oa]; a.No = P.n[oa]; a.ax_o = oa; }
         a.in_jfast = a.out_jfast = c == last ? 1 : 0;
         HP_TRY(fan_pass(p, P, comp, a, c, xb[c], term_of(comp, c), ws, fields));
+        fan_stream(a, c == last, es);
         HP_TRY(finish_pass(p, a, c == last ? 16 : 32, 2, 0, 1));
         const void* q;
         HP_TRY(quarter(p, a.n, &q));
@@ -2143,6 +2178,7 @@ hp_status passes_semi(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       a.out[0] = work(comp);
       geom(a, j, false);
       HP_TRY(fan_pass(p, P, comp, a, j, xb[j], term_of(j), ws, fields));
+      fan_stream(a, j == (u == nd - 1 ? nd - 2 : nd - 1), es);
       HP_TRY(finish_pass(p, a, j == nd - 1 ? 16 : 32, 2, 0, 1));
       const void* q;
       HP_TRY(quarter(p, a.n, &q));

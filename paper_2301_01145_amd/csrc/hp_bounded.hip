@@ -96,50 +96,57 @@ __device__ __forceinline__ C2<T> mirror_bin(const C2<T> (&v)[WF<L>::R0], int i, 
   return g == 0 ? o : w;
 }
 
-// Output index carried by bin i of the lane (m = g + G i) of transform x (-1:
-// none) and the two real outputs (pencils a and b).
+// Output index carried by bin i of the lane (m = g + G i) of transform x (-1: none).
+template <int L>
+__device__ __forceinline__ int r2r_index(int x, int i, int g, int n) {
+  const int m = g + WF<L>::G * i;
+  switch (x) {
+    case X_DST1: return m < 1 || m > n ? -1 : m - 1;
+    case X_DCT1: return m < n ? m : -1;
+    case X_DCT3:
+    case X_DST3: return 2 * m < n ? 2 * m : 2 * (n - m) - 1;
+    case X_DST2: return n - 1 - m;
+    default: return m;  // DCT-II, Hartley
+  }
+}
+
+// That index and the two real outputs (pencils a and b).
 template <typename T, int L>
 __device__ __forceinline__ int r2r_extract(int x, int i, int g, int n, const C2<T> (&v)[WF<L>::R0], const C2<T>* q,
                                            T& oa, T& ob) {
   const int m = g + WF<L>::G * i;
   const C2<T> z = v[i];
+  const int k = r2r_index<L>(x, i, g, n);
   switch (x) {
     case X_DST1:
-      if (m < 1 || m > n) return -1;
       oa = -z.im;
       ob = z.re;
-      return m - 1;
+      break;
     case X_DCT1:
-      if (m >= n) return -1;
       oa = z.re;
       ob = z.im;
-      return m;
+      break;
     case X_DCT3:
     case X_DST3: {
-      const bool even = 2 * m < n;
-      const T sg = (x == X_DST3 && !even) ? (T)-1 : (T)1;
+      const T sg = (x == X_DST3 && 2 * m >= n) ? (T)-1 : (T)1;
       oa = sg * z.re;
       ob = sg * z.im;
-      return even ? 2 * m : 2 * (n - m) - 1;
-    }
+    } break;
     case X_DCT2:
     case X_DST2: {
       const C2<T> c = cconj(mirror_bin<T, L>(v, i, g)), w = q[m];
       const C2<T> s = cadd(z, c), d = csub(z, c);
       oa = fma(s.re, w.re, -rounded(s.im * w.im));
       ob = fma(d.re, w.im, rounded(d.im * w.re));
-      return x == X_DST2 ? n - 1 - m : m;
-    }
-    case X_DHT: {  // Re - Im of either pencil's bin, from the bins k and n - k
+    } break;
+    default: {  // Hartley: Re - Im of either pencil's bin, from the bins k and n - k
       const C2<T> c = mirror_bin<T, L>(v, i, g);
       const T h = (T)0.5;
       oa = h * ((z.re + c.re) - (z.im - c.im));
       ob = h * ((z.im + c.im) + (z.re - c.re));
-      return m;
-    }
-    default:
-      return -1;
+    } break;
   }
+  return k;
 }
 
 __device__ __forceinline__ bool has_faces(const PassArgs& a) {
@@ -416,14 +423,22 @@ __global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
 // Dirichlet solve is 5 launches where one launch per array, with elementwise
 // passes for the coefficients, was 16 (128^3 FP32 with its gradient: 81 us, was
 // 168).  Rows off the cache lines are stored through the caches, where the parts
-// of a line merge (127 points a row: 81 us, 85 streaming); aligned ones stream
-// (256^3: 457 us, 462 through the caches).
+// of a line merge (127 points a row: 81 us, 85 streaming); aligned ones as the
+// planner says (fan_stream).
 namespace {
 
+// Families of types: a kernel holds one (the instances of several need more
+// registers than any of theirs alone).
+enum Family : int { FAM_REGULAR = 0, FAM_STAGGERED = 1, FAM_HARTLEY = 2 };
+__host__ __device__ constexpr int family(int x) {
+  return x == X_DHT ? FAM_HARTLEY : (r2r_half(x) ? FAM_STAGGERED : FAM_REGULAR);
+}
 // The backward (forward) type as a compile-time constant.
-template <bool H, class F>
+template <int FAM, class F>
 __device__ __forceinline__ void with_backward(int x, F&& f) {
-  if constexpr (H) {
+  if constexpr (FAM == FAM_HARTLEY) {
+    f(std::integral_constant<int, X_DHT>{});
+  } else if constexpr (FAM == FAM_STAGGERED) {
     if (x == X_DST3) f(std::integral_constant<int, X_DST3>{});
     else f(std::integral_constant<int, X_DCT3>{});
   } else {
@@ -431,9 +446,11 @@ __device__ __forceinline__ void with_backward(int x, F&& f) {
     else f(std::integral_constant<int, X_DCT1>{});
   }
 }
-template <bool H, class F>
+template <int FAM, class F>
 __device__ __forceinline__ void with_forward(int x, F&& f) {
-  if constexpr (H) {
+  if constexpr (FAM == FAM_HARTLEY) {
+    f(std::integral_constant<int, X_DHT>{});
+  } else if constexpr (FAM == FAM_STAGGERED) {
     if (x == X_DST2) f(std::integral_constant<int, X_DST2>{});
     else f(std::integral_constant<int, X_DCT2>{});
   } else {
@@ -449,17 +466,14 @@ __device__ __forceinline__ void fan_stores(bool cached, F&& f) {
 }
 // Backward type of the derivative of a series with backward type x.
 __host__ __device__ constexpr int r2r_other_parity(int x) {
-  return x == X_DST1 ? X_DCT1 : (x == X_DCT1 ? X_DST1 : (x == X_DST3 ? X_DCT3 : X_DST3));
-}
-
-__device__ __forceinline__ double fan_kappa(const FanJob& q, int k) {
-  return q.scale * (double)(q.basis == FB_SINE ? k + 1 : k);
+  return x == X_DST1 ? X_DCT1 : (x == X_DCT1 ? X_DST1 : (x == X_DST3 ? X_DCT3 : (x == X_DCT3 ? X_DST3 : x)));
 }
 
 }  // namespace
 
-template <typename T, int L, bool H>
+template <typename T, int L, int FAM>
 __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const PassArgs) {
+  constexpr bool H = FAM != FAM_REGULAR;
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
   constexpr int NT = 64 * kR2RContigWaves;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -479,8 +493,8 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const Pass
   T* R = (T*)slot;  // the pair's reals, pencil b after pencil a
   const int pairs_p = (job.Np + 1) / 2;
   const long long total = (long long)pairs_p * job.No;
-  const bool cached = off_lines(a, sizeof(T), sizeof(T));
-  const int blk = cached ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const bool off = off_lines(a, sizeof(T), sizeof(T)), cached = off || !a.stream;
+  const int blk = off ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const long long pr = ((long long)blk * kR2RContigWaves + wave) * PPW + qq;
   const bool valid = pr < total;
   const int o = valid ? (int)(pr / pairs_p) : 0;
@@ -522,15 +536,15 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const Pass
     wave_sync();
 #pragma unroll
     for (int r = 0; r < NJ; ++r) {
-      const int j = g + G * r, s = j - job.shift;
+      const int j = g + G * r, s = fan_place<FAM == FAM_HARTLEY>(job, j);
       if (j < n && s >= 0 && s < nd) {
-        const T m = (T)fan_kappa(job, j);
+        const T m = (T)fan_factor<FAM == FAM_HARTLEY>(job, j);
         R[s] = m * va[r];
         R[nd + s] = m * vbv[r];
       }
     }
     wave_sync();
-    with_backward<H>(job.xd, [&](auto XC) __attribute__((always_inline)) { run(XC, nd, job.deriv); });
+    with_backward<FAM>(job.xd, [&](auto XC) __attribute__((always_inline)) { run(XC, nd, job.deriv); });
   }
 #pragma unroll
   for (int r = 0; r < NJ; ++r) {
@@ -541,13 +555,20 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const Pass
     }
   }
   wave_sync();
-  with_backward<H>(job.xp, [&](auto XC) __attribute__((always_inline)) { run(XC, n, job.plain); });
+  with_backward<FAM>(job.xp, [&](auto XC) __attribute__((always_inline)) { run(XC, n, job.plain); });
 }
 
-// Strided fan pass and sandwich: the tile of the plain transform and a second
-// tile for the derivative, both transformed in place (kb_strided).
-template <typename T, int L, bool H, int P, int W, bool SW>
+// Strided fan pass and sandwich (kb_strided).  TWO: a tile for either transform;
+// otherwise both run in one tile, one after the other, the input of a one-way
+// pass or the spectrum of a sandwich waiting in registers for the second one.
+// One tile lets more workgroups share a CU (four instead of two at 128 points:
+// FP64 128^3, a sandwich 37.8 -> 24.3 us, a one-way pass of two arrays 38.1 ->
+// 26.8), and costs two barriers and a store phase where every workgroup is
+// resident anyway (64^3: 9.1 -> 9.5): the planner's rule is to_fast_r2r's
+// (PassArgs.emit_dbl: two tiles).
+template <typename T, int L, int FAM, int P, int W, bool SW, bool TWO>
 __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
+  constexpr bool H = FAM != FAM_REGULAR;
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
   constexpr int NT = 64 * W, TS = P + 1;
   constexpr int MAXN = kMaxRows<L, H>;
@@ -560,21 +581,21 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
   C2<T>* q = tw + L;
   C2<T>* slots = q + a.n;
   T* tile = (T*)(slots + W * PPW * slot_len(L));
-  T* dtile = tile + n * TS;
+  T* dtile = TWO ? tile + n * TS : tile;
   const int tiles_p = (job.Np + P - 1) / P;
-  const bool cached = off_lines(a, sizeof(T), sizeof(T));
-  const int t = cached ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const bool off = off_lines(a, sizeof(T), sizeof(T)), cached = off || !a.stream;
+  const int t = off ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   if (t >= tiles_p * job.No) return;  // whole workgroup
   for (int m = threadIdx.x; m < L; m += NT) tw[m] = ((const C2<T>*)a.tw)[m];
   if (a.qtw)
     for (int m = threadIdx.x; m < a.n; m += NT) q[m] = ((const C2<T>*)a.qtw)[m];
   const int o = t / tiles_p, p0 = (t % tiles_p) * P;
   const int np = min(P, job.Np - p0);
+  // the whole tile's loads in flight at once (kb_strided); pencils beyond np are 0
+  T pre[PER];
   {
-    // the whole tile's loads in flight at once (kb_strided)
     const T* in = (const T*)job.in;
     const long long ib = (long long)o * a.in_so + (long long)p0 * a.in_sp;
-    T pre[PER];
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
       const int e = threadIdx.x + r * NT;
@@ -582,13 +603,8 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
       pre[r] = in[ib + (long long)min(j, n - 1) * a.in_sj + (long long)min(c, np - 1) * a.in_sp];
     }
 #pragma unroll
-    for (int r = 0; r < PER; ++r) {
-      const int e = threadIdx.x + r * NT;
-      const int j = e / P, c = e - (e / P) * P;
-      if (j < n) tile[j * TS + c] = c < np ? pre[r] : (T)0;
-    }
+    for (int r = 0; r < PER; ++r) pre[r] = (int)(threadIdx.x + r * NT) % P < np ? pre[r] : (T)0;
   }
-  __syncthreads();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int qq = lane / G, g = lane % G;
   C2<T>* slot = slots + (wave * PPW + qq) * slot_len(L);
@@ -611,34 +627,57 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
     }
     wave_sync();  // the slot is used again
   };
-  // a derivative coefficient into its place
-  auto place = [&](int k, T sa, T sb) {
-    const int s = job.basis == FB_LAP ? k : k - job.shift;
-    if (s >= 0 && s < nd) {
-      da[s * TS] = sa;
-      da[s * TS + 1] = sb;
+  const long long ob = (long long)o * a.out_so + (long long)p0 * a.out_sp;
+  auto store = [&](const T* src, int cnt, void* dst) {
+    T* out = (T*)dst;
+    fan_stores(cached, [&](auto ST) __attribute__((always_inline)) {
+      for (int e = threadIdx.x; e < cnt * P; e += NT) {
+        const int j = e / P, c = e - (e / P) * P;
+        if (c < np) st_out<decltype(ST)::value>(&out[ob + (long long)j * a.out_sj + (long long)c * a.out_sp], src[j * TS + c]);
+      }
+    });
+  };
+  auto put_plain = [&] {
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+      const int e = threadIdx.x + r * NT;
+      const int j = e / P, c = e - (e / P) * P;
+      if (j < n) tile[j * TS + c] = pre[r];
     }
   };
-  if (job.deriv) {
+  // places that no coefficient reaches: the first and the last at most
+  auto zero_ends = [&] {
     if (g == 0) da[0] = da[1] = da[(nd - 1) * TS] = da[(nd - 1) * TS + 1] = (T)0;
     wave_sync();
-  }
+  };
+  // a derivative coefficient into its place
+  const bool lap = SW && job.basis == FB_LAP;
+  auto place = [&](int k, T va, T vb) {
+    const int s = lap ? k : fan_place<FAM == FAM_HARTLEY>(job, k);
+    if (s >= 0 && s < nd) {
+      da[s * TS] = va;
+      da[s * TS + 1] = vb;
+    }
+  };
   if constexpr (SW) {
+    put_plain();
+    __syncthreads();
     const int pa = min(p0 + 2 * f, job.Np - 1), pb = min(p0 + 2 * f + 1, job.Np - 1);
     const double ra = eigen_rest(a, pa, o), rb = eigen_rest(a, pb, o);
-    const bool lap = job.basis == FB_LAP;
     auto w2 = [&](int ax, int k) {
       if (ax < 0) return 0.0;
       const double w = a.kc[ax] * (double)(a.basis[ax] == FB_SINE ? k + 1 : (a.basis[ax] == FB_COSINE ? k : signed_index(k, a.nunk[ax])));
       return w * w;
     };
     const double la = lap ? w2(a.ax_p, pa) + w2(a.ax_o, o) : 0.0, lb = lap ? w2(a.ax_p, pb) + w2(a.ax_o, o) : 0.0;
-    with_forward<H>(a.xf, [&](auto XC) {
+    with_forward<FAM>(a.xf, [&](auto XC) __attribute__((always_inline)) {
       constexpr int XF = decltype(XC)::value;
       constexpr int XB = r2r_partner(XF);
+      T wa[TWO ? 1 : R0], wb[TWO ? 1 : R0];  // the derivative's coefficients
       {
         C2<T> v[R0];
         r2r_fft<T, L>(v, XF, n, slot, g, tw, q, [&](int s, int w) { return ca[s * TS + w]; });
+        if constexpr (TWO) zero_ends();
 #pragma unroll
         for (int i = 0; i < R0; ++i) {
           T sa, sb;
@@ -651,40 +690,77 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
           ca[k * TS] = sa * eigen_mult<T>(a, k, ra);
           ca[k * TS + 1] = sb * eigen_mult<T>(a, k, rb);
           const double wj = lap ? w2(a.ax_j, k) : 0.0;
-          const double fa = lap ? -job.scale * (wj + la) : fan_kappa(job, k);
+          const double fa = lap ? -job.scale * (wj + la) : fan_factor<FAM == FAM_HARTLEY>(job, k);
           const double fb = lap ? -job.scale * (wj + lb) : fa;
-          place(k, sa * (T)(ma * fa), sb * (T)(mb * fb));
+          const T va = sa * (T)(ma * fa), vb = sb * (T)(mb * fb);
+          if constexpr (TWO) {
+            place(k, va, vb);
+          } else {
+            wa[i] = va;
+            wb[i] = vb;
+          }
+        }
+        wave_sync();
+      }
+      back(std::integral_constant<int, XB>{}, ca, n);
+      if constexpr (!TWO) {
+        __syncthreads();
+        store(tile, n, job.plain);
+        __syncthreads();
+        zero_ends();
+#pragma unroll
+        for (int i = 0; i < R0; ++i) {
+          const int k = r2r_index<L>(XF, i, g, n);
+          if (k >= 0) place(k, wa[i], wb[i]);
         }
         wave_sync();
       }
       if (lap) back(std::integral_constant<int, XB>{}, da, nd);
       else back(std::integral_constant<int, r2r_other_parity(XB)>{}, da, nd);
-      back(std::integral_constant<int, XB>{}, ca, n);
     });
+    __syncthreads();
+    if constexpr (TWO) store(tile, n, job.plain);
+    store(dtile, nd, job.deriv);
   } else {
-    if (job.deriv) {
-      for (int k = g; k < n; k += G) {
-        const T m = (T)fan_kappa(job, k);
-        place(k, m * ca[k * TS], m * ca[k * TS + 1]);
+    if constexpr (TWO) {
+      put_plain();
+      __syncthreads();
+      if (job.deriv) {
+        zero_ends();
+        for (int k = g; k < n; k += G) {
+          const T m = (T)fan_factor<FAM == FAM_HARTLEY>(job, k);
+          place(k, m * ca[k * TS], m * ca[k * TS + 1]);
+        }
+        wave_sync();
+        with_backward<FAM>(job.xd, [&](auto XC) __attribute__((always_inline)) { back(XC, da, nd); });
       }
-      wave_sync();
-      with_backward<H>(job.xd, [&](auto XC) __attribute__((always_inline)) { back(XC, da, nd); });
+    } else {
+      if (job.deriv) {
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+          const int e = threadIdx.x + r * NT;
+          const int k = e / P, c = e - (e / P) * P;
+          if (k >= n) continue;
+          const int s = fan_place<FAM == FAM_HARTLEY>(job, k);
+          if (s >= 0 && s < nd) tile[s * TS + c] = (T)fan_factor<FAM == FAM_HARTLEY>(job, k) * pre[r];
+          // the places beside the first and the last coefficient's
+          if (FAM != FAM_HARTLEY && k == 0 && s > 0) tile[c] = (T)0;
+          if (FAM != FAM_HARTLEY && k == n - 1 && s + 1 < nd) tile[(s + 1) * TS + c] = (T)0;
+        }
+        __syncthreads();
+        with_backward<FAM>(job.xd, [&](auto XC) __attribute__((always_inline)) { back(XC, ca, nd); });
+        __syncthreads();
+        store(tile, nd, job.deriv);
+        __syncthreads();
+      }
+      put_plain();
+      __syncthreads();
     }
-    with_backward<H>(job.xp, [&](auto XC) __attribute__((always_inline)) { back(XC, ca, n); });
+    with_backward<FAM>(job.xp, [&](auto XC) __attribute__((always_inline)) { back(XC, ca, n); });
+    __syncthreads();
+    if (TWO && job.deriv) store(dtile, nd, job.deriv);
+    store(tile, n, job.plain);
   }
-  __syncthreads();
-  const long long ob = (long long)o * a.out_so + (long long)p0 * a.out_sp;
-  auto store = [&](const T* src, int cnt, void* dst) {
-    T* out = (T*)dst;
-    fan_stores(cached, [&](auto ST) __attribute__((always_inline)) {
-      for (int e = threadIdx.x; e < cnt * P; e += NT) {
-        const int j = e / P, c = e - (e / P) * P;
-        if (c < np) st_out<decltype(ST)::value>(&out[ob + (long long)j * a.out_sj + (long long)c * a.out_sp], src[j * TS + c]);
-      }
-    });
-  };
-  if (job.deriv) store(dtile, nd, job.deriv);
-  store(tile, n, job.plain);
 }
 
 // ------------------------------------------ batched solve
@@ -1118,25 +1194,36 @@ int r2r_tile(int L, int prec) { return r2r_tile_of(L, prec == 0); }
 // for short transforms).
 constexpr int r2r_waves(int P, int ppw) { return (P / 2) / ppw; }
 
-// n: rows of the tile (and quarter twists), nd: rows of the derivative's tile
-// of a fan pass (0: none).
+// LDS bytes of a strided pass with `rows` tile rows (n quarter twists); -1: a
+// tile's pairs do not fill whole wavefronts (one pair per lane group).
+static constexpr int r2r_strided_lds(int L, int n, int rows, int prec) {
+  const int cs = prec == 0 ? 8 : 16, es = cs / 2, P = r2r_tile_of(L, prec == 0), ppw = 64 / (L / wf_r0(L));
+  if ((P / 2) % ppw != 0) return -1;
+  return (L + n + r2r_waves(P, ppw) * ppw * slot_len(L)) * cs + rows * (P + 1) * es;
+}
+// n: rows of the tile (and quarter twists), nd: rows of a second tile (0: none).
 int r2r_lds_bytes(int fast, int L, int n, int nd, int prec) {
-  const int cs = prec == 0 ? 8 : 16, es = cs / 2;
   const int R0 = wf_r0(L);
   if (R0 <= 0 || (R0 % 3 == 0 && prec != 0)) return -1;  // 3 x 2^k: FP32 only
-  const int ppw = 64 / (L / R0);
-  const int SL = slot_len(L);
-  if (fast == FAST_R2R_C) return (L + n + kR2RContigWaves * ppw * SL) * cs;
-  const int P = r2r_tile(L, prec);
-  // one pencil pair per lane group: the tile's pairs must fill whole wavefronts
-  if ((P / 2) % ppw != 0) return -1;
-  return (L + n + r2r_waves(P, ppw) * ppw * SL) * cs + (n + nd) * (P + 1) * es;
+  if (fast == FAST_R2R_C) return (L + n + kR2RContigWaves * (64 / (L / R0)) * slot_len(L)) * (prec == 0 ? 8 : 16);
+  return r2r_strided_lds(L, n, n + nd, prec);
+}
+// Whether one tile instead of two (n rows each) lets a fan pass of FFT length L
+// have more workgroups on a CU.
+static constexpr bool r2r_one_tile(int L, int n, int prec) {
+  const int one = r2r_strided_lds(L, n, n, prec), two = r2r_strided_lds(L, n, 2 * n, prec);
+  return one > 0 && (160 * 1024) / one > (160 * 1024) / two;
+}
+bool fan_one_tile(int fast, int L, bool half, int prec) {
+  if (wf_r0(L) <= 0 || fast == FAST_R2R_C || (fast == FAST_R2R_SW && wf_r0(L) % 3 == 0)) return false;
+  return r2r_one_tile(L, half ? L : L / 2, prec);
 }
 
 namespace {
 
-template <typename T, int L, bool H>
+template <typename T, int L, int FAM>
 hipError_t launch_fan_L(const PassArgs& a, hipStream_t s) {
+  constexpr bool H = FAM != FAM_REGULAR;
   constexpr int PPW = WF<L>::PPW;
   constexpr int P = r2r_tile_of(L, sizeof(T) == 4);
   constexpr int W = r2r_waves(P, PPW);
@@ -1146,10 +1233,10 @@ hipError_t launch_fan_L(const PassArgs& a, hipStream_t s) {
   for (int i = 0; i < a.nfan; ++i) {
     const FanJob& q = a.fan[i];
     if (!q.in || !q.plain || q.n < 1 || q.n > kMaxRows<L, H> || q.Np < 1 || q.No < 1) return hipErrorInvalidValue;
-    if (q.deriv && (q.nd < 1 || q.nd > kMaxRows<L, H> || q.basis == FB_HARTLEY || q.basis == FB_ODD))
-      return hipErrorInvalidValue;
-    // one family of types per kernel; the staggered ones have L points
-    if (r2r_half(q.xp) != H || (q.deriv && r2r_half(q.xd) != H)) return hipErrorInvalidValue;
+    if (q.deriv && (q.nd < 1 || q.nd > kMaxRows<L, H> || q.basis == FB_ODD)) return hipErrorInvalidValue;
+    // one family of types per kernel; all but the regular ones have L points
+    if (family(q.xp) != FAM || (q.deriv && family(q.xd) != FAM)) return hipErrorInvalidValue;
+    if (q.deriv && q.basis != FB_LAP && (q.basis == FB_HARTLEY) != (FAM == FAM_HARTLEY)) return hipErrorInvalidValue;
     if (H && (q.n != L || a.n != L || (q.deriv && q.nd != L))) return hipErrorInvalidValue;
     const long long per = (long long)kR2RContigWaves * PPW;
     blocks = std::max(blocks, a.fast == FAST_R2R_C ? ((long long)((q.Np + 1) / 2) * q.No + per - 1) / per
@@ -1157,23 +1244,38 @@ hipError_t launch_fan_L(const PassArgs& a, hipStream_t s) {
     rows = std::max(rows, q.n);
     if (q.deriv) drows = std::max(drows, q.nd);
   }
-  if (r2r_lds_bytes(a.fast, L, std::max(rows, a.n), drows, sizeof(T) == 8) > a.lds_bytes || a.lds_bytes > 160 * 1024)
+  const bool two = a.emit_dbl != 0;
+  rows = std::max(rows, a.n);
+  if (r2r_lds_bytes(a.fast, L, two ? rows : std::max(rows, drows), two ? drows : 0, sizeof(T) == 8) > a.lds_bytes ||
+      a.lds_bytes > 160 * 1024)
     return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks, a.nfan);
   if (a.fast == FAST_R2R_C) {
-    allow_lds<kb_contig_fan<T, L, H>>();
-    hipLaunchKernelGGL((kb_contig_fan<T, L, H>), grid, dim3(64 * kR2RContigWaves), a.lds_bytes, s, a);
+    allow_lds<kb_contig_fan<T, L, FAM>>();
+    hipLaunchKernelGGL((kb_contig_fan<T, L, FAM>), grid, dim3(64 * kR2RContigWaves), a.lds_bytes, s, a);
     return hipGetLastError();
   }
   if constexpr (W < 1 || (P / 2) % PPW != 0) {
     return hipErrorInvalidValue;
-  } else if (a.fast == FAST_R2R_SW) {
-    if (a.xb != r2r_partner(a.xf) || a.nfan != 1 || !a.fan[0].deriv) return hipErrorInvalidValue;
-    allow_lds<kb_strided_fan<T, L, H, P, W, true>>();
-    hipLaunchKernelGGL((kb_strided_fan<T, L, H, P, W, true>), grid, dim3(64 * W), a.lds_bytes, s, a);
   } else {
-    allow_lds<kb_strided_fan<T, L, H, P, W, false>>();
-    hipLaunchKernelGGL((kb_strided_fan<T, L, H, P, W, false>), grid, dim3(64 * W), a.lds_bytes, s, a);
+    const bool sw = a.fast == FAST_R2R_SW;
+    if (sw && (a.xb != r2r_partner(a.xf) || a.nfan != 1 || !a.fan[0].deriv)) return hipErrorInvalidValue;
+    auto go = [&](auto S, auto B) {
+      constexpr bool SW = decltype(S)::value, TWO = decltype(B)::value;
+      allow_lds<kb_strided_fan<T, L, FAM, P, W, SW, TWO>>();
+      hipLaunchKernelGGL((kb_strided_fan<T, L, FAM, P, W, SW, TWO>), grid, dim3(64 * W), a.lds_bytes, s, a);
+    };
+    // (one-tile instances where r2r_one_tile can ask for them)
+    constexpr bool kOne = r2r_one_tile(L, H ? L : L / 2, sizeof(T) == 8);
+    if constexpr (kOne) {
+      if (!two && !sw) { go(std::false_type{}, std::false_type{}); return hipGetLastError(); }
+      if constexpr (WF<L>::R0 % 3 != 0) {
+        if (!two) { go(std::true_type{}, std::false_type{}); return hipGetLastError(); }
+      }
+    }
+    if (!two) return hipErrorInvalidValue;
+    if (sw) go(std::true_type{}, std::true_type{});
+    else go(std::false_type{}, std::true_type{});
   }
   return hipGetLastError();
 }
@@ -1184,7 +1286,12 @@ hipError_t launch_bounded_L(const PassArgs& a, hipStream_t s) {
   const int lds = a.lds_bytes;
   // rows per pencil of every Table 1 type
   if (H ? a.n != L : (a.n < 1 || a.n > L / 2 + 1)) return hipErrorInvalidValue;
-  if (a.nfan > 0) return launch_fan_L<T, L, H>(a, s);
+  if (a.nfan > 0) {
+    if constexpr (H && L >= 64) {  // (shorter Hartley passes stay general)
+      if (a.fan[0].xp == X_DHT) return launch_fan_L<T, L, FAM_HARTLEY>(a, s);
+    }
+    return launch_fan_L<T, L, H ? FAM_STAGGERED : FAM_REGULAR>(a, s);
+  }
   if (a.fast == FAST_R2R_C) {
     const long long pairs = (long long)((a.Np + 1) / 2) * a.No;
     const long long per_block = (long long)kR2RContigWaves * PPW;

@@ -1,6 +1,7 @@
-// What the real-to-real kernels share beside the FFTs: the pass descriptor and
-// the boundary terms of the inhomogeneous FD2 solves (Section 2.4.2), the
-// weighted face values added to the source at the unknowns next to a face.
+// What the real-to-real kernels share beside the FFTs: the pass descriptor, the
+// boundary terms of the inhomogeneous FD2 solves (Section 2.4.2), the weighted
+// face values added to the source at the unknowns next to a face, and the
+// coefficients of the series derivatives.
 #pragma once
 
 #include "hp_device.hpp"
@@ -53,6 +54,23 @@ __device__ __forceinline__ double face_terms(const PassArgs& a, int j, int p, in
     }
   }
   return add;
+}
+
+// Series derivatives (FanJob): the factor of coefficient k of the input for its
+// place in the derivative series, and that place (a Laplacian's coefficients
+// stay in theirs, its factors are the caller's).  HARTLEY: a Hartley series.
+template <bool HARTLEY>
+__device__ __forceinline__ double fan_factor(const FanJob& q, int k) {
+  if constexpr (HARTLEY) {
+    const int s = k == 0 ? 0 : q.n - k;
+    return -q.scale * (double)(2 * s < q.n ? s : (2 * s == q.n ? 0 : s - q.n));
+  }
+  return q.scale * (double)(q.basis == FB_SINE ? k + 1 : k);
+}
+template <bool HARTLEY>
+__device__ __forceinline__ int fan_place(const FanJob& q, int k) {
+  if constexpr (HARTLEY) return k == 0 ? 0 : q.n - k;
+  return k - q.shift;
 }
 
 }  // namespace hp

@@ -229,6 +229,9 @@ int small2d_lds_bytes(int L0, int L1, int prec, int nbuf);
 hipError_t launch_small2d(const PassArgs& a, int prec, hipStream_t s);
 int r2r_tile(int L, int prec);
 int r2r_lds_bytes(int fast, int L, int n, int nd, int prec);
+// Fan passes: whether there is a one-tile form that leaves room for more
+// workgroups (half: FFT of the transform's own length).
+bool fan_one_tile(int fast, int L, bool half, int prec);
 // Dynamic LDS bytes of a wavefront-FFT pass; 0 if the pass is not available.
 int fast_lds_bytes(int fast, int L, int P, int K2, int prec, int dbl, int pad);
 int fast_emit_dbl(int fast, int prec);

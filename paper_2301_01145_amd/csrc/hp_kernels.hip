@@ -518,27 +518,13 @@ __device__ __forceinline__ void load_real(LTile<T> Z, const void* src, int x, co
 }
 
 // ------------------------------------------------ series derivatives (FanJob)
-// Wavenumber factor of coefficient k of the input for its place in the
-// derivative series, and that place.
-__device__ __forceinline__ double fan_factor(const FanJob& q, int k) {
-  if (q.basis == FB_HARTLEY) {
-    const int s = k == 0 ? 0 : q.n - k;
-    return -q.scale * (double)(2 * s < q.n ? s : (2 * s == q.n ? 0 : s - q.n));
-  }
-  return q.scale * (double)(q.basis == FB_SINE ? k + 1 : k);
-}
-__device__ __forceinline__ int fan_place(const FanJob& q, int k) {
-  if (q.basis == FB_HARTLEY) return k == 0 ? 0 : q.n - k;
-  return q.basis == FB_LAP ? k : k - q.shift;
-}
-
 // Extends coefficient k (value v, the factor applied) of the input into the
 // derivative's FFT input; the thread of the first (last) coefficient also
 // writes the places beside it that no coefficient reaches.
 template <typename T, int XD>
 __device__ __forceinline__ void extend_derivative(LTile<T> Z, int f, int k, C2<T> v, const FanJob& q,
                                                   const PassArgs& a) {
-  const int s = fan_place(q, k);
+  const int s = q.basis == FB_HARTLEY ? fan_place<true>(q, k) : fan_place<false>(q, k);
   if (s >= 0 && s < q.nd) extend<T, XD>(Z, f, s, v, a, q.nd);
   if (q.basis == FB_SINE || q.basis == FB_COSINE) {
     const C2<T> zero = {(T)0, (T)0};
@@ -569,7 +555,7 @@ __device__ __forceinline__ void load_derivative_x(LTile<T> Z, const FanJob& q, c
     for (int u = 0; u < kLoadBatch; ++u) {
       if (e0 + u * kThreads >= total) continue;
       const int p = 2 * ff[u];
-      const T m = (T)fan_factor(q, jj[u]);
+      const T m = (T)(q.basis == FB_HARTLEY ? fan_factor<true>(q, jj[u]) : fan_factor<false>(q, jj[u]));
       extend_derivative<T, XD>(Z, ff[u], jj[u], {p < t.np ? m * v[u].re : (T)0, p + 1 < t.np ? m * v[u].im : (T)0}, q,
                                a);
     }
@@ -948,7 +934,7 @@ __device__ __forceinline__ void multiply_r2r_fan(LTile<T> Z, LTile<T> D, const P
       fa = -q.scale * (axis_w2(0, ka.k0) + axis_w2(1, ka.k1) + axis_w2(2, ka.k2));
       fb = -q.scale * (axis_w2(0, kb.k0) + axis_w2(1, kb.k1) + axis_w2(2, kb.k2));
     } else {
-      fa = fb = fan_factor(q, m);
+      fa = fb = XF == X_DHT ? fan_factor<true>(q, m) : fan_factor<false>(q, m);
     }
     d = {s.re * (T)(ma * fa), s.im * (T)(mb * fb)};
     return C2<T>{s.re * (T)ma, s.im * (T)mb};
