@@ -1751,26 +1751,36 @@ bool fast_unbounded_ok(hp_plan p, const Problem& P) {
 }
 
 // Whether a wavefront pass stores its output of `bytes` streaming
-// (nontemporal).  Stored through the caches instead, the output is still in
-// the 256 MB Infinity Cache when the next pass reads it, which pays from about
-// the size of the eight L2s up to that of the cache (kernel traces, producer +
-// consumer in us, streaming against through the caches):
-//   R2C -> y pass:      25 MB 24.6, 23.8; 135 MB 120.2, 96.8; 8 MB 15.9, 17.5;
-//                       404 MB 352.6, 376.7
-//   y -> x pass:        25 MB 34.1, 33.7; 135 MB 162.1, 139.7; 17 MB 24.5, 25.1;
-//                       406 MB even.  Periodic plans only: the x pass of a
-//                       free-space plan keeps its Green's rows in the caches
-//                       (135 MB 124.0, 135.1)
-//   x -> y pass back:   42 MB 44.0, 40.5; 168 MB 159.4, 139.8; 8 MB 16.6, 18.1;
-//                       338 MB 292.1, 302.6
-//   y back -> C2R pass: 51 MB 49.5, 42.2; 113 MB 89.9, 80.5; 9 MB 21.3, 20.1;
-//                       390 MB 299.2, 324.5
+// (nontemporal).  Stored through the caches instead, the output may still be in
+// the 256 MB Infinity Cache when the next pass reads it.  The lines are the
+// crossovers of whole solves with one pass switched (us streaming, through the
+// caches; output of that pass):
+//   R2C:     12 MB 65.6, 67.1; 24 MB 84.7, 83.3; 129 MB 394, 379; 193 MB 813, 798;
+//            385 MB 1582, 1600
+//   y:       16 MB 53.8, 52.2; 48 MB 145, 138; 97 MB 257, 254 and 321, 327; 129 MB 297,
+//            301; 193 MB 587, 604.  Periodic plans only: the x pass of a free-space
+//            plan keeps its Green's rows in the caches (even at every size)
+//   x:       8 MB 33.9, 37.3; 32 MB 66.1, 62.7; 81 MB 115, 109; 129 MB 185, 194 and 199,
+//            204; 161 MB 207, 212; periodic plans 40 MB 84.1, 82.3; 65 MB 154, 160;
+//            81 MB 137, 144
+//   y back:  8 MB 33.9, 36.3; 12 MB 48.9, 47.9; 49 MB 89.5, 82.3; 130 MB 172, 154; 193 MB
+//            388, 379; 258 MB 288, 296
 // The fields that the C2R pass writes leave the solve and stay streaming (no
 // reader; cached they displace the next solve's input: R2C 82 -> 89 us).
 bool stream_out(int kind, bool periodic, double bytes) {
   constexpr double kMiB = 1024.0 * 1024.0;
-  if (kind == FAST_C2R || (kind == FAST_FWD_Y && !periodic)) return true;
-  return bytes < (kind == FAST_INV_Y ? 8 : 20) * kMiB || bytes > 256 * kMiB;
+  double lo = 20, hi = 256;
+  switch (kind) {
+    case FAST_R2C: break;
+    case FAST_FWD_Y:
+      if (!periodic) return true;
+      hi = 110;
+      break;
+    case FAST_SANDWICH: hi = periodic ? 60 : 100; break;
+    case FAST_INV_Y: lo = 10; break;
+    default: return true;
+  }
+  return bytes < lo * kMiB || bytes > hi * kMiB;
 }
 
 // Free-space passes, or (periodic) the same five passes on undoubled

@@ -25,9 +25,11 @@ constexpr int kC2RThreads = 256;  // workgroup of the C2R pass
 
 // The stores of a pass: streaming, or through the caches where the next pass
 // finds its input there (a.stream, set by the planner).  One uniform branch
-// around whole store rounds; ALWAYS: no branch, the pass always streams.  (The
-// backward y pass takes the choice as a template argument: with the branch it
-// took 397 us at 256^3 instead of 393.)
+// around whole store rounds; ALWAYS: no branch, the pass always streams.  (The x
+// and backward y passes take the choice as a template argument: with the branch
+// the backward y pass took 397 us at 256^3 instead of 393, the x pass of the
+// periodic curl 178 instead of 172 and that of the FP64 divergence at 64^3 36
+// instead of 28: 298 registers instead of 254, one resident wavefront per SIMD.)
 template <bool ALWAYS = false, typename F>
 __device__ __forceinline__ void with_stream(const PassArgs& a, F&& f) {
   if (ALWAYS || a.stream) f(std::true_type{});
@@ -196,8 +198,11 @@ __global__ void __launch_bounds__(64 * (P / WF<L>::PPW)) kf_fwd_y(const PassArgs
 // output groups; the XCD-contiguous numbering keeps such tiles behind one L2.
 // EXT: the divergence and the Laplacian (D_DIV, D_NABLA and their
 // transposes) in instances of their own; the other instances keep the code
-// of psi, the gradient and the curl only.
-template <typename T, int L, int P, bool ADJ, bool DBL, bool PAD, bool EXT>
+// of psi, the gradient and the curl only.  They always stream below 256 points;
+// from there they branch (with_stream), where that takes no wavefront from a CU in
+// FP64 and the compiler's other schedule is the faster one (128^3 divergence, x
+// pass: FP64 240 us without the branch, 227 with; FP32 111, 102).
+template <typename T, int L, int P, bool ADJ, bool DBL, bool PAD, bool EXT, bool STREAM>
 __global__ void __launch_bounds__(64 * (P / WF<L>::PPW),
                                   (sizeof(T) == 4 && P == 8 && L == 512 && !ADJ && !EXT) ? 4 : 1)
     kf_sandwich(const PassArgs a) {
@@ -356,14 +361,16 @@ __global__ void __launch_bounds__(64 * (P / WF<L>::PPW),
       // compile-time count (all LDS reads before the stores); offsets within
       // the kz slab, NX * M1 <= 2^20
       static_assert((NX * P) % NT == 0, "whole rounds of the tile store");
-      with_stream(a, [&](auto ST) __attribute__((always_inline)) {
+      auto put = [&](auto ST) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < NX * P / NT; ++r) {
           const int e = threadIdx.x + r * NT;
           const int x = e / P, c = e - (e / P) * P;
           st_out<decltype(ST)::value>(&d[x * M1 + c], tile[row(x) * TS + c]);
         }
-      });
+      };
+      if constexpr (EXT && L >= 256) with_stream(a, put);
+      else put(std::integral_constant<bool, STREAM>{});
       if (DBL) tb ^= 1;
       else __syncthreads();
     };
@@ -773,21 +780,22 @@ static hipError_t launch_LP(const PassArgs& a0, int grid_y, hipStream_t s) {
         const int nb = persistent_grid<decltype(kern)::value>(NT, lds, ntiles);
         hipLaunchKernelGGL(decltype(kern)::value, dim3(nb), dim3(NT), lds, s, a);
       };
-#define HP_SW(ADJ, DBL, EXT) \
-  go(std::integral_constant<decltype(&kf_sandwich<T, L, P, ADJ, DBL, PAD, EXT>), \
-                            &kf_sandwich<T, L, P, ADJ, DBL, PAD, EXT>>{})
-#define HP_SW2(DBL, EXT) \
-  do {                   \
-    if (adj) HP_SW(true, DBL, EXT); \
-    else HP_SW(false, DBL, EXT);    \
+#define HP_SW(ADJ, DBL, EXT, STREAM) \
+  go(std::integral_constant<decltype(&kf_sandwich<T, L, P, ADJ, DBL, PAD, EXT, STREAM>), \
+                            &kf_sandwich<T, L, P, ADJ, DBL, PAD, EXT, STREAM>>{})
+// (the configurations that only the autotuner picks always stream)
+#define HP_SW2(DBL)                                               \
+  do {                                                            \
+    constexpr bool kPlan = P == 8 && DBL == (sizeof(T) == 8);     \
+    if (ext && adj) HP_SW(true, DBL, true, true);                 \
+    else if (ext) HP_SW(false, DBL, true, true);                  \
+    else if (adj && (a.stream || !kPlan)) HP_SW(true, DBL, false, true); \
+    else if (adj) HP_SW(true, DBL, false, !kPlan);                \
+    else if (a.stream || !kPlan) HP_SW(false, DBL, false, true);  \
+    else HP_SW(false, DBL, false, !kPlan);                        \
   } while (0)
-      if (a.emit_dbl) {  // double-buffered output tiles
-        if (ext) HP_SW2(true, true);
-        else HP_SW2(true, false);
-      } else {
-        if (ext) HP_SW2(false, true);
-        else HP_SW2(false, false);
-      }
+      if (a.emit_dbl) HP_SW2(true);  // double-buffered output tiles
+      else HP_SW2(false);
 #undef HP_SW2
 #undef HP_SW
     } break;

@@ -8,7 +8,9 @@ beside other conditions) of the wavefront kernels' lengths, which run there with
 and without a derivative, and next to them, along every axis.  Outputs of the
 latter against the oracle too, with the tolerances of the parity tests.  Passes of
 more workgroups than are resident at once, whose two transforms share one tile,
-against the general kernels as well."""
+against the general kernels as well.  Periodic and free-space plans of the
+wavefront kernels, whose passes store streaming or through the caches by their
+size: plans with and without a gradient on either side of those lines."""
 import numpy as np
 import pytest
 
@@ -132,3 +134,22 @@ def test_one_tile(bc, grid, prec, nc, monkeypatch):
         for g, r in zip(*out):
             assert np.all(np.isfinite(g))
             assert rel_l2(g, r) <= l2 and rel_max(g, r) <= mx, (diff, rel_l2(g, r), rel_max(g, r))
+
+
+@pytest.mark.parametrize("bc", ["unbounded", "periodic"])
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("nc", [[32, 32, 64], [64, 64, 64], [64, 64, 128], [64, 128, 128], [128, 128, 128]])
+def test_periodic_and_free_space(bc, prec, nc):
+    import torch
+    from paper_2301_01145_amd import Solver
+    dtype = torch.float32 if prec == "f32" else torch.float64
+    out = []
+    for diff in ("none", "grad"):
+        s = Solver(bc, "staggered", nc, diff=diff, dtype=dtype)
+        f = to_dev(np.random.default_rng(3).normal(size=s.in_shape).astype(np.float32), dtype, torch)
+        psi, _ = s.solve(f)
+        torch.cuda.synchronize()
+        out.append(psi[0].cpu().numpy())
+        s.close()
+    assert np.all(np.isfinite(out[0]))
+    assert np.array_equal(out[0], out[1])
