@@ -214,12 +214,55 @@ __device__ __forceinline__ double eigen_rest(const PassArgs& a, int p, int o) {
 
 constexpr int kR2RContigWaves = 4;
 
+// Boundary terms of the elements j = g + G r of pencil (p, o), added in the order
+// of face_terms.  One face after the other for all of them, so that its loads are
+// in flight together; element by element each waited for its own (64^3 staggered
+// with values on every face 33.6 us, 31.3; 128^3 51.0, 47.7).
+template <int NJ, int G, typename T>
+__device__ __forceinline__ void add_faces(const PassArgs& a, T (&v)[NJ], int g, int p, int o, int n, bool live) {
+  double add[NJ];
+#pragma unroll
+  for (int r = 0; r < NJ; ++r) add[r] = 0.0;
+#pragma unroll
+  for (int ax = 0; ax < 3; ++ax) {
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      const T* f = (const T*)a.face[ax][side];
+      if (!f) continue;
+      const int edge = side == 0 ? 0 : a.nunk[ax] - 1;
+      // the whole pencil lies beside the face, or one of its elements
+      const bool along = ax != a.ax_j;
+      if (along && (ax == a.ax_p ? p : o) != edge) continue;
+      const int b0 = ax == 0 ? 1 : 0, b1 = ax == 2 ? 1 : 2;  // the face's axes, ascending
+      auto at = [&](int b, int j) {
+        return (long long)((a.ax_j == b ? j : (a.ax_p == b ? p : o)) + ((a.face_off >> b) & 1));
+      };
+      T w[NJ];
+#pragma unroll
+      for (int r = 0; r < NJ; ++r) {
+        const int j = min(g + G * r, n - 1);
+        long long off = 0;
+        if (a.nunk[b0] > 0) off += at(b0, j) * a.face_s[ax][0];
+        if (a.nunk[b1] > 0) off += at(b1, j) * a.face_s[ax][a.nunk[b0] > 0 ? 1 : 0];
+        w[r] = (T)0;
+        if (live && (along || j == edge)) w[r] = f[off];
+      }
+#pragma unroll
+      for (int r = 0; r < NJ; ++r) add[r] += a.face_w[ax][side] * (double)w[r];
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < NJ; ++r)
+    if (live) v[r] = (T)((double)v[r] + add[r]);
+}
+
 // ----------------------------------------------- contiguous one-way pass
-// Pairs (p, p+1) of pencils at one o; the pencil axis is unit stride.
-template <typename T, int L, bool H>
-__global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig(const PassArgs a) {
+// Pairs (p, p+1) of pencils at one o; the pencil axis is unit stride.  CW
+// wavefronts a workgroup (launch_bounded_L).
+template <typename T, int L, bool H, int CW>
+__global__ void __launch_bounds__(64 * CW) kb_contig(const PassArgs a) {
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
-  constexpr int NT = 64 * kR2RContigWaves;
+  constexpr int NT = 64 * CW;
   extern __shared__ __align__(16) unsigned char smem[];
   const int n = H ? L : a.n;
   C2<T>* tw = (C2<T>*)smem;
@@ -236,7 +279,7 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig(const PassArgs
   const int pairs_p = (a.Np + 1) / 2;
   const long long total = (long long)pairs_p * a.No;
   const int blk = off_lines(a, sizeof(T), sizeof(T)) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  const long long pr = ((long long)blk * kR2RContigWaves + wave) * PPW + qq;
+  const long long pr = ((long long)blk * CW + wave) * PPW + qq;
   const bool valid = pr < total;
   const int o = valid ? (int)(pr / pairs_p) : 0;
   const int pa = valid ? 2 * (int)(pr % pairs_p) : 0;
@@ -258,12 +301,8 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig(const PassArgs
     vbv[r] = in[ibb + jo];
   }
   if (faces) {
-#pragma unroll
-    for (int r = 0; r < NJ; ++r) {
-      const int j = g + G * r;
-      if (j < n && valid) va[r] = (T)((double)va[r] + face_terms<T>(a, j, pa, o));
-      if (j < n && vb) vbv[r] = (T)((double)vbv[r] + face_terms<T>(a, j, pa + 1, o));
-    }
+    add_faces<NJ, G>(a, va, g, pa, o, n, valid);
+    add_faces<NJ, G>(a, vbv, g, pa + 1, o, n, vb);
   }
 #pragma unroll
   for (int r = 0; r < NJ; ++r) {
@@ -297,15 +336,21 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig(const PassArgs
 // wavefront pairs transform columns (2f, 2f+1) in place in it, and it is
 // stored as runs of P.  SW: sandwich (forward, multiplier, backward).
 //
+// Four wavefronts at least load and store the tile, the first W transform it (one
+// pair per lane group): the staggered types need half the lanes per pencil that
+// their extension took, and with these alone the tile's accesses were a longer
+// chain per thread (FP32 32^3 27.3 us, 23.9; 48^3 35.9, 30.6; 64^3 27.8, 25.8).
+//
 // PERS (persistent): a workgroup walks tiles blockIdx-strided; every thread
 // loads its share of the next tile into registers before the current tile's
 // FFTs and writes it to LDS after the current tile has been stored.  Chosen
 // when there are many more tiles than resident workgroups.
 // (Boundary terms enter in the contiguous first pass only.)
+__host__ __device__ constexpr int strided_threads(int W) { return 64 * (W < 4 ? 4 : W); }
 template <typename T, int L, bool H, int P, int W, bool SW, bool PERS>
-__global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
+__global__ void __launch_bounds__(strided_threads(W)) kb_strided(const PassArgs a) {
   constexpr int R0 = WF<L>::R0, G = WF<L>::G, PPW = WF<L>::PPW;
-  constexpr int NT = 64 * W, TS = P + 1;
+  constexpr int NT = strided_threads(W), TS = P + 1;
   constexpr int MAXN = kMaxRows<L, H>;           // rows of a tile at most
   constexpr int PER = (MAXN * P + NT - 1) / NT;  // tile elements per thread
   extern __shared__ __align__(16) unsigned char smem[];
@@ -364,7 +409,7 @@ __global__ void __launch_bounds__(64 * W) kb_strided(const PassArgs a) {
     int g = g_lane;
     if constexpr (PERS) asm volatile("" : "+v"(g));
     static_assert(P / 2 == W * PPW, "one pair per wavefront lane group");
-    {
+    if (wave < W) {
       const int f = wave * PPW + qq;  // pair: columns 2f, 2f + 1
       T* ca = tile + 2 * f;
       auto get = [&](int s, int w) { return ca[s * TS + w]; };
@@ -1293,11 +1338,22 @@ hipError_t launch_bounded_L(const PassArgs& a, hipStream_t s) {
     return launch_fan_L<T, L, H ? FAM_STAGGERED : FAM_REGULAR>(a, s);
   }
   if (a.fast == FAST_R2R_C) {
-    const long long pairs = (long long)((a.Np + 1) / 2) * a.No;
-    const long long per_block = (long long)kR2RContigWaves * PPW;
-    allow_lds<kb_contig<T, L, H>>();
-    hipLaunchKernelGGL((kb_contig<T, L, H>), dim3((unsigned)((pairs + per_block - 1) / per_block)),
-                       dim3(64 * kR2RContigWaves), lds, s, a);
+    const long long waves = ((long long)((a.Np + 1) / 2) * a.No + PPW - 1) / PPW;
+    auto go = [&](auto C) {
+      constexpr int CW = decltype(C)::value;
+      allow_lds<kb_contig<T, L, H, CW>>();
+      hipLaunchKernelGGL((kb_contig<T, L, H, CW>), dim3((unsigned)((waves + CW - 1) / CW)), dim3(64 * CW), lds, s, a);
+    };
+    // short staggered pencils (8 or 16 pairs a wavefront): a wavefront a workgroup
+    // where that leaves no CU two of them (FP32 32^3 23.9 -> 22.1 us, 128 x 64 x 32 28.0 ->
+    // 27.2; but 128 x 128 x 64, 1024 wavefronts, 33.1 -> 34.8)
+    if constexpr (H && L <= 64) {
+      if (waves <= 256) {
+        go(std::integral_constant<int, 1>{});
+        return hipGetLastError();
+      }
+    }
+    go(std::integral_constant<int, kR2RContigWaves>{});
     return hipGetLastError();
   }
   constexpr int P = r2r_tile_of(L, sizeof(T) == 4);
@@ -1315,25 +1371,25 @@ hipError_t launch_bounded_L(const PassArgs& a, hipStream_t s) {
       if (a.xb != r2r_partner(a.xf)) return hipErrorInvalidValue;
       if constexpr (kPers) {
         allow_lds<kb_strided<T, L, H, P, W, true, true>>();
-        const int nb = persistent_grid<kb_strided<T, L, H, P, W, true, true>>(64 * W, lds, ntiles);
+        const int nb = persistent_grid<kb_strided<T, L, H, P, W, true, true>>(strided_threads(W), lds, ntiles);
         if (ntiles > 4 * nb && !std::getenv("HP_R2R_NOPERS")) {
-          hipLaunchKernelGGL((kb_strided<T, L, H, P, W, true, true>), dim3(nb), dim3(64 * W), lds, s, a);
+          hipLaunchKernelGGL((kb_strided<T, L, H, P, W, true, true>), dim3(nb), dim3(strided_threads(W)), lds, s, a);
           return hipGetLastError();
         }
       }
       allow_lds<kb_strided<T, L, H, P, W, true, false>>();
-      hipLaunchKernelGGL((kb_strided<T, L, H, P, W, true, false>), grid, dim3(64 * W), lds, s, a);
+      hipLaunchKernelGGL((kb_strided<T, L, H, P, W, true, false>), grid, dim3(strided_threads(W)), lds, s, a);
     } else {
       if constexpr (kPers) {
         allow_lds<kb_strided<T, L, H, P, W, false, true>>();
-        const int nb = persistent_grid<kb_strided<T, L, H, P, W, false, true>>(64 * W, lds, ntiles);
+        const int nb = persistent_grid<kb_strided<T, L, H, P, W, false, true>>(strided_threads(W), lds, ntiles);
         if (ntiles > 4 * nb) {
-          hipLaunchKernelGGL((kb_strided<T, L, H, P, W, false, true>), dim3(nb), dim3(64 * W), lds, s, a);
+          hipLaunchKernelGGL((kb_strided<T, L, H, P, W, false, true>), dim3(nb), dim3(strided_threads(W)), lds, s, a);
           return hipGetLastError();
         }
       }
       allow_lds<kb_strided<T, L, H, P, W, false, false>>();
-      hipLaunchKernelGGL((kb_strided<T, L, H, P, W, false, false>), grid, dim3(64 * W), lds, s, a);
+      hipLaunchKernelGGL((kb_strided<T, L, H, P, W, false, false>), grid, dim3(strided_threads(W)), lds, s, a);
     }
     return hipGetLastError();
   }
