@@ -202,7 +202,6 @@ bool choose_radices(PassArgs& a, int prec) {
 // short of workgroups the tile is narrowed (kFillTiles): a pass of fewer tiles
 // than CUs takes as long as one tile does (FP64 periodic 2D of about 200 x 250
 // points, 16 and 5 tiles: 151 -> 38 us together with the stages above).
-constexpr int kCUs = 256;
 constexpr int kFillTiles = kCUs;  // one workgroup per CU
 constexpr int kNarrowest = 4;    // pencils a tile is narrowed to
 

@@ -50,6 +50,7 @@ __host__ __device__ inline bool diff_is_adjoint(int d) {
 #define HP_GEN_THREADS 256
 #endif
 constexpr int kThreads = HP_GEN_THREADS;
+constexpr int kCUs = 256;
 // Longest transform of the general path: 32 (FP32) or 16 (FP64) elements per
 // thread of a 256-thread workgroup.
 constexpr int kMaxLenThreads = 256;
@@ -137,7 +138,8 @@ struct PassArgs {
   // Np / No above are those of job 0, strides and length common.
   int nfan;
   FanJob fan[kMaxFan];
-  int basis[3];        // FD_LAP: series of each axis (FanBasis), wavenumbers kc
+  int basis[3];        // FB_LAP: series of each axis (FanBasis), wavenumbers kc
+  int tight;           // general kernels, coupled fields: LDS rows without a pad element
   long long n_add;     // FAST_ADD: elements
 };
 

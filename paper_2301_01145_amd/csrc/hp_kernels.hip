@@ -93,13 +93,13 @@ struct LTile {
     z[i] = v;
   }
 };
-__host__ __device__ constexpr int tile_row(int nf) { return nf > 1 ? nf + 1 : 1; }
+__host__ __device__ constexpr int tile_row(int nf, bool pad) { return nf > 1 && pad ? nf + 1 : nf; }
 
 template <typename T>
-__device__ __forceinline__ LTile<T> lds_tile(unsigned char* smem, int nf, int L, int index) {
+__device__ __forceinline__ LTile<T> lds_tile(unsigned char* smem, int nf, int L, int index, bool pad = true) {
   LTile<T> z;
   z.lg = 31 - __builtin_clz((unsigned)nf);
-  z.S = tile_row(nf);
+  z.S = tile_row(nf, pad);
   z.z = (HP_LDS typename V2<T>::t*)smem + (size_t)index * L * z.S;
   return z;
 }
@@ -1024,10 +1024,11 @@ __device__ __forceinline__ void sandwich_c2c(const PassArgs& a, unsigned char* s
   const int nS = adj ? a.n_out : a.n_in;
   // independent fields (no derivative coupling) take their field from blockIdx.y
   const int fb = (a.diff == D_NONE) ? (int)blockIdx.y : 0;
-  const LTile<T> S = lds_tile<T>(smem, nf, L, 0);
-  const LTile<T> W = lds_tile<T>(smem, nf, L, a.diff == D_NONE ? 0 : nS);
+  const int tiles = a.diff == D_NONE ? nS : nS + 1;
+  const LTile<T> S = lds_tile<T>(smem, nf, L, 0, !a.tight);
+  const LTile<T> W = lds_tile<T>(smem, nf, L, a.diff == D_NONE ? 0 : nS, !a.tight);
   const int tileC = L * S.S;  // LDS elements of a tile
-  HP_LDS typename V2<T>::t* wR = S.z + (size_t)(a.diff == D_NONE ? nS : nS + 1) * tileC;
+  HP_LDS typename V2<T>::t* wR = S.z + (size_t)tiles * tileC;
   const int total = L << S.lg;
   const unsigned mL = div_magic(L);
   auto tile = [&](int c) { return LTile<T>{S.z + (size_t)c * tileC, S.S, S.lg}; };
@@ -1287,28 +1288,50 @@ bool general_fits(const PassArgs& a, int prec) {
   return stages_fit(a.L, nf, a.radix, a.nstage, a.big, prec);
 }
 
-// LDS bytes of a general pass of tile width P: its FFT tiles (nS coupled
-// fields and a work tile where derivatives couple them) and the table of the
+// Tiles of a pass: nS coupled fields and a work tile where derivatives couple
+// them, a fan sandwich's two outputs.
+static int pass_tiles(const PassArgs& a) {
+  if (a.nfan > 0) return a.kind == PK_SANDWICH ? 2 : 1;
+  if (a.kind != PK_SANDWICH || !(a.xf == X_C2C_F || a.xf == X_C2C_B || a.xf == X_PAIR_F)) return 1;
+  const int nS = diff_is_adjoint(a.diff) ? a.n_out : a.n_in;
+  return a.diff == D_NONE ? nS : nS + 1;
+}
+
+// Whether the rows of the tiles of coupled fields leave the pad out: where no more
+// than four workgroups share a CU with it, more do without, and the pass has more
+// tiles than are resident.  Free-space curl of 150 x 80 x 100 cells, FP64 937 -> 657 us
+// (four tiles of 300 x 2, two workgroups and four), FP32 454 -> 402, 100 x 60 x 80 FP32
+// 255 -> 214.  Otherwise the bank conflicts cost more: seven and eight workgroups
+// 127 -> 134 us (20 x 100 x 100 FP32), every tile resident anyway 127 -> 129 (periodic
+// gradient 150 x 80 x 100 FP64), rows of 256 bytes, a turn of the banks each, whose
+// accesses along m are served one lane at a time, 146 -> 156 (20 x 100 x 100 FP64).
+static bool pass_tight(const PassArgs& a, int P, int prec) {
+  const bool cplx = a.xf == X_C2C_F || a.xf == X_C2C_B;
+  const int nf = cplx ? P : P / 2, tiles = pass_tiles(a), cs = prec == 0 ? 8 : 16;
+  if (a.nfan > 0 || tiles < 2 || nf < 2 || nf * cs >= 256) return false;
+  const long long lds = 160 * 1024, row = (long long)tiles * a.L * cs;
+  const long long with = lds / (row * (nf + 1));
+  return with <= 4 && lds / (row * nf) > with && (long long)((a.Np + P - 1) / P) * a.No > with * kCUs;
+}
+
+// LDS bytes of a general pass of tile width P: its FFT tiles and the table of the
 // largest prime stage (left out where it would not fit; the kernel sees the
 // room that is left).
 int general_lds_bytes(const PassArgs& a, int P, int prec) {
   const bool cplx = a.xf == X_C2C_F || a.xf == X_C2C_B;
   const int nf = cplx ? P : P / 2;
-  int tiles = 1;
-  if (a.kind == PK_SANDWICH && (cplx || a.xf == X_PAIR_F)) {
-    const int nS = diff_is_adjoint(a.diff) ? a.n_out : a.n_in;
-    tiles = a.diff == D_NONE ? nS : nS + 1;
-  }
-  if (a.nfan > 0) tiles = a.kind == PK_SANDWICH ? 2 : 1;
   int table = 0;
   for (int s = 0; s < a.nstage; ++s)
     if (a.radix[s] > max_radix(prec)) table = std::max(table, a.radix[s]);
-  const long long cs = prec == 0 ? 8 : 16, data = (long long)tiles * a.L * tile_row(nf) * cs;
+  const long long cs = prec == 0 ? 8 : 16;
+  const long long data = (long long)pass_tiles(a) * a.L * tile_row(nf, !pass_tight(a, P, prec)) * cs;
   if (a.big && data + table * cs > 160 * 1024) table = 0;
   return (int)std::min<long long>(data + table * cs, 1 << 30);
 }
 
-hipError_t launch_pass(const PassArgs& a, int prec, int grid_y, hipStream_t s) {
+hipError_t launch_pass(const PassArgs& pass, int prec, int grid_y, hipStream_t s) {
+  PassArgs a = pass;
+  a.tight = pass_tight(a, a.P, prec);
   if (!general_fits(a, prec) || general_lds_bytes(a, a.P, prec) > a.lds_bytes) return hipErrorInvalidValue;
   int tiles = ((a.Np + a.P - 1) / a.P) * a.No;
   if (a.nfan > 0) {
