@@ -1325,6 +1325,17 @@ hipError_t launch_fan_L(const PassArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Workgroups of a persistent strided pass; HP_PERSIST=<n>, n > 0, caps them, which
+// makes passes of few tiles persistent too (a pass of more than four tiles per
+// workgroup is).
+template <auto K>
+int strided_grid(int nt, int lds, int ntiles) {
+  const int nb = persistent_grid<K>(nt, lds, ntiles);
+  const char* e = std::getenv("HP_PERSIST");
+  const int cap = e ? std::atoi(e) : 0;
+  return cap > 0 ? std::min(nb, cap) : nb;
+}
+
 template <typename T, int L, bool H>
 hipError_t launch_bounded_L(const PassArgs& a, hipStream_t s) {
   constexpr int PPW = WF<L>::PPW;
@@ -1371,7 +1382,7 @@ hipError_t launch_bounded_L(const PassArgs& a, hipStream_t s) {
       if (a.xb != r2r_partner(a.xf)) return hipErrorInvalidValue;
       if constexpr (kPers) {
         allow_lds<kb_strided<T, L, H, P, W, true, true>>();
-        const int nb = persistent_grid<kb_strided<T, L, H, P, W, true, true>>(strided_threads(W), lds, ntiles);
+        const int nb = strided_grid<kb_strided<T, L, H, P, W, true, true>>(strided_threads(W), lds, ntiles);
         if (ntiles > 4 * nb && !std::getenv("HP_R2R_NOPERS")) {
           hipLaunchKernelGGL((kb_strided<T, L, H, P, W, true, true>), dim3(nb), dim3(strided_threads(W)), lds, s, a);
           return hipGetLastError();
@@ -1382,7 +1393,7 @@ hipError_t launch_bounded_L(const PassArgs& a, hipStream_t s) {
     } else {
       if constexpr (kPers) {
         allow_lds<kb_strided<T, L, H, P, W, false, true>>();
-        const int nb = persistent_grid<kb_strided<T, L, H, P, W, false, true>>(strided_threads(W), lds, ntiles);
+        const int nb = strided_grid<kb_strided<T, L, H, P, W, false, true>>(strided_threads(W), lds, ntiles);
         if (ntiles > 4 * nb) {
           hipLaunchKernelGGL((kb_strided<T, L, H, P, W, false, true>), dim3(nb), dim3(strided_threads(W)), lds, s, a);
           return hipGetLastError();
