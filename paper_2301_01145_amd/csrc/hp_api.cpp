@@ -928,8 +928,7 @@ hp_status finish_pass(hp_plan p, PassArgs& a, int want, int minP, long long lds_
   (void)lds_per_P_fixed;
   const unsigned long long key = general_key(a, p->prec, want, minP, lds_kind);
   auto it = p->tuned.find(key);
-  if (it != p->tuned.end() && it->second.fast == FAST_NONE &&
-      radix_ok(a.L, it->second.radix, it->second.nstage)) {
+  if (it != p->tuned.end() && it->second.fast == FAST_NONE) {
     PassArgs t = a;
     if (finish_pass_with(p, t, want, minP, &it->second) == HP_OK) {
       a = t;
@@ -2479,17 +2478,6 @@ hp_status launch_rec(hp_plan p, const PassRec& r) {
   const hipError_t e = launch_one(p, r);
   if (e != hipSuccess) return fail(p, HP_E_DEVICE, std::string("pass launch: ") + hipGetErrorString(e));
   return HP_OK;
-}
-// A radix order the general kernels run: radices 2, 3, 4, 5, 8 whose product is L.
-bool radix_ok(int L, const int* radix, int nstage) {
-  if (nstage < 1 || nstage > kMaxStages) return false;
-  long long prod = 1;
-  for (int s = 0; s < nstage; ++s) {
-    const int r = radix[s];
-    if (r != 2 && r != 3 && r != 4 && r != 5 && r != 8) return false;
-    prod *= r;
-  }
-  return prod == L;
 }
 hp_status passes_for(hp_plan p, Problem& P, bool adjoint, std::vector<PassRec>& out) {
   return build_passes(p, P, adjoint, out);

@@ -129,7 +129,6 @@ hp_status plan_fail(hp_plan p, hp_status s, const std::string& msg);
 hp_status plan_alloc(hp_plan p, size_t bytes, void** out);
 void plan_free(hp_plan p, void* ptr);
 hp_status launch_rec(hp_plan p, const PassRec& r);
-bool radix_ok(int L, const int* radix, int nstage);
 hp_status plan_outputs(hp_plan p, Problem& P);
 hp_status plan_fast_twiddles(hp_plan p, int L, const void** out);
 hp_status passes_for(hp_plan p, Problem& P, bool adjoint, std::vector<PassRec>& out);

@@ -3,11 +3,9 @@
 // Every pass of a plan carries a signature of its geometry (PassArgs.tune_key).
 // For each distinct signature the tuner times, on the plan's stream, the
 // configurations the kernels are built for:
-//   * general kernels: every radix order of the transform length over the
-//     radices 2, 3, 4, 5 and 8 (the power-of-two part split into 8s, at most
-//     three 4s and at most one 2; each split in descending and ascending
-//     order), tile widths of half, one and two times the planner's default,
-//     and both register budgets;
+//   * general kernels: the planner's stages and other splits of the transform
+//     length over the register radices (radix_orders), tile widths of half, one
+//     and two times the planner's default, and both register budgets;
 //   * wavefront passes: tile widths of 8 and 16 pencils and, for the x and
 //     backward-y passes, both output-tile schemes;
 //   * batched plans: the tile bodies (wavefront or general passes), the launches
@@ -33,6 +31,7 @@
 #include <vector>
 
 #include "hp_plan.hpp"
+#include "hp_radix.hpp"
 
 #define HP_TRY_T(expr)                  \
   do {                                  \
@@ -47,34 +46,6 @@ size_t elems(const int* n, int nd) {
   size_t c = 1;
   for (int a = 0; a < nd; ++a) c *= (size_t)n[a];
   return c;
-}
-
-// Radix orders of L = 2^a 3^b 5^c that the general kernels run (none for
-// lengths with a larger prime factor: those keep the planner's order).
-std::vector<std::vector<int>> radix_orders(int L) {
-  int a = 0, b = 0, c = 0, r = L;
-  while (r % 2 == 0) { r /= 2; ++a; }
-  while (r % 3 == 0) { r /= 3; ++b; }
-  while (r % 5 == 0) { r /= 5; ++c; }
-  std::vector<std::vector<int>> out;
-  if (r != 1) return out;
-  for (int n8 = a / 3; n8 >= 0; --n8) {
-    for (int n4 = 0; n4 <= 3; ++n4) {
-      const int n2 = a - 3 * n8 - 2 * n4;
-      if (n2 < 0 || n2 > 1) continue;
-      std::vector<int> m;
-      m.insert(m.end(), n8, 8);
-      m.insert(m.end(), n4, 4);
-      m.insert(m.end(), n2, 2);
-      m.insert(m.end(), b, 3);
-      m.insert(m.end(), c, 5);
-      if (m.empty() || (int)m.size() > kMaxStages) continue;
-      const std::vector<int> asc(m.rbegin(), m.rend());
-      for (const auto& o : {m, asc})
-        if (std::find(out.begin(), out.end(), o) == out.end()) out.push_back(o);
-    }
-  }
-  return out;
 }
 
 struct Tuner {
@@ -159,7 +130,8 @@ struct Tuner {
       // a batched plan runs the passes of a level in one kernel whose register
       // budget and LDS are the largest of its passes: stay within those
       const int big0 = p->batched ? p->batch_big : 0, big1 = p->batched ? p->batch_big : 1;
-      for (const auto& o : radix_orders(a.L))
+      const std::vector<int> own(a.radix, a.radix + a.nstage);
+      for (const auto& o : radix_orders(a.L, max_radix(p->prec), kMaxStages, own))
         for (int w : widths)
           for (int big = big0; big <= big1; ++big) {
             Tune t;
