@@ -866,12 +866,12 @@ unsigned long long tune_hash(const long long* v, int n) {
 
 // Signature of a general pass from the fields its builder sets before the
 // tile is chosen.
-unsigned long long general_key(const PassArgs& a, int prec, int want, int minP, int lds_kind) {
+unsigned long long general_key(const PassArgs& a, int prec, int want, int minP) {
   const long long v[] = {0,        prec,      a.kind,    a.xf,      a.xb,      a.L,
                          a.n,      a.nin,     a.nout,    a.Np,      a.No,      a.in_jfast,
                          a.out_jfast, a.in_sj, a.in_sp,  a.in_so,   a.out_sj,  a.out_sp,
                          a.out_so, a.n_in,    a.n_out,   a.diff,    a.mult,    want,
-                         minP,     lds_kind,  a.nfan,    a.fan[0].deriv != nullptr, a.fan[0].basis};
+                         minP,     a.nfan,    a.fan[0].deriv != nullptr, a.fan[0].basis};
   return tune_hash(v, (int)(sizeof(v) / sizeof(v[0])));
 }
 
@@ -923,10 +923,8 @@ hp_status finish_pass_with(hp_plan p, PassArgs& a, int want, int minP, const Tun
   return HP_OK;
 }
 
-hp_status finish_pass(hp_plan p, PassArgs& a, int want, int minP, long long lds_per_P_fixed,
-                      int lds_kind) {
-  (void)lds_per_P_fixed;
-  const unsigned long long key = general_key(a, p->prec, want, minP, lds_kind);
+hp_status finish_pass(hp_plan p, PassArgs& a, int want, int minP) {
+  const unsigned long long key = general_key(a, p->prec, want, minP);
   auto it = p->tuned.find(key);
   if (it != p->tuned.end() && it->second.fast == FAST_NONE) {
     PassArgs t = a;
@@ -1333,7 +1331,7 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       a.mult = M_EIGEN; a.lam[0] = P.lam[0]; a.norm = P.norm;
       set_faces(a, comp);
       fan_sandwich(a);
-      HP_TRY(finish_pass(p, a, 2, 2, 0, 3));
+      HP_TRY(finish_pass(p, a, 2, 2));
       const void* q;
       HP_TRY(quarter(p, a.n, &q));
       a.qtw = q;
@@ -1354,7 +1352,7 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       if (nd == 3) { a.in_so = fs[0]; a.out_so = ws[0]; a.No = P.n[0]; a.ax_o = 0; }
       a.in_jfast = a.out_jfast = 1;
       set_faces(a, comp);
-      HP_TRY(finish_pass(p, a, 16, 2, 0, 1));
+      HP_TRY(finish_pass(p, a, 16, 2));
       const void* q;
       HP_TRY(quarter(p, a.n, &q));
       a.qtw = q;
@@ -1373,7 +1371,7 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       a.in_so = a.out_so = ws[0];
       a.Np = P.n[2]; a.No = P.n[0];
       a.ax_j = 1; a.ax_p = 2; a.ax_o = 0;
-      HP_TRY(finish_pass(p, a, 32, 2, 0, 1));
+      HP_TRY(finish_pass(p, a, 32, 2));
       const void* q;
       HP_TRY(quarter(p, a.n, &q));
       a.qtw = q;
@@ -1396,7 +1394,7 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       for (int b = 0; b < nd; ++b) a.lam[b] = P.lam[b];
       a.norm = P.norm;
       fan_sandwich(a);
-      HP_TRY(finish_pass(p, a, 32, 2, 0, 3));
+      HP_TRY(finish_pass(p, a, 32, 2));
       const void* q;
       HP_TRY(quarter(p, a.n, &q));
       a.qtw = q;
@@ -1422,7 +1420,7 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
         a.in_jfast = a.out_jfast = c == last ? 1 : 0;
         HP_TRY(fan_pass(p, P, comp, a, c, xb[c], term_of(comp, c), ws, fields));
         fan_stream(a, c == last, es);
-        HP_TRY(finish_pass(p, a, c == last ? 16 : 32, 2, 0, 1));
+        HP_TRY(finish_pass(p, a, c == last ? 16 : 32, 2));
         const void* q;
         HP_TRY(quarter(p, a.n, &q));
         a.qtw = q;
@@ -1449,7 +1447,7 @@ hp_status passes_bounded(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       a.ax_j = last; a.ax_p = last - 1;
       if (nd == 3) { a.in_so = a.out_so = ws[0]; a.No = P.n[0]; a.ax_o = 0; }
       a.in_jfast = a.out_jfast = 1;
-      HP_TRY(finish_pass(p, a, 16, 2, 0, 1));
+      HP_TRY(finish_pass(p, a, 16, 2));
       const void* q;
       HP_TRY(quarter(p, a.n, &q));
       a.qtw = q;
@@ -1495,7 +1493,7 @@ hp_status passes_periodic(hp_plan p, Problem& P, std::vector<PassRec>& out) {
     a.in_sj = a.out_sj = 1;
     a.in_jfast = a.out_jfast = 1;
     a.ax_j = 0;
-    HP_TRY(finish_pass(p, a, 2, 2, 0, 5));
+    HP_TRY(finish_pass(p, a, 2, 2));
     out.push_back({a, coupled ? 1 : nin});
     return HP_OK;
   }
@@ -1550,7 +1548,7 @@ hp_status passes_periodic(hp_plan p, Problem& P, std::vector<PassRec>& out) {
     a.Np = P.n[last - 1];
     if (nd == 3) { a.in_so = fs[0]; a.out_so = ss[0]; a.No = P.n[0]; }
     a.in_jfast = a.out_jfast = 1;
-    HP_TRY(finish_pass(p, a, 16, 2, 0, 1));
+    HP_TRY(finish_pass(p, a, 16, 2));
     out.push_back({a, nin});
   }
   // P2 (3D): forward C2C along axis 1, in place
@@ -1565,7 +1563,7 @@ hp_status passes_periodic(hp_plan p, Problem& P, std::vector<PassRec>& out) {
     a.in_sp = a.out_sp = ss[2];
     a.in_so = a.out_so = ss[0];
     a.Np = K; a.No = P.n[0];
-    HP_TRY(finish_pass(p, a, 16, 1, 0, 0));
+    HP_TRY(finish_pass(p, a, 16, 1));
     p2 = a;
     out.push_back({a, nin});
   }
@@ -1582,7 +1580,7 @@ hp_status passes_periodic(hp_plan p, Problem& P, std::vector<PassRec>& out) {
     a.Np = K;
     a.ax_j = 0; a.ax_p = last;
     if (nd == 3) { a.in_so = a.out_so = ss[1]; a.No = P.n[1]; a.ax_o = 1; }
-    HP_TRY(finish_pass(p, a, 16, 1, 0, 4));
+    HP_TRY(finish_pass(p, a, 16, 1));
     out.push_back({a, coupled ? 1 : nin});
   }
   // P4 (3D): backward C2C along axis 1 on every output field
@@ -1604,7 +1602,7 @@ hp_status passes_periodic(hp_plan p, Problem& P, std::vector<PassRec>& out) {
     a.Np = P.n[last - 1];
     if (nd == 3) { a.in_so = ss[0]; a.out_so = fs[0]; a.No = P.n[0]; }
     a.in_jfast = a.out_jfast = 1;
-    HP_TRY(finish_pass(p, a, 16, 2, 0, 2));
+    HP_TRY(finish_pass(p, a, 16, 2));
     out.push_back({a, nfo});
   }
   return HP_OK;
@@ -1652,7 +1650,7 @@ hp_status passes_unbounded(hp_plan p, Problem& P, bool adjoint, std::vector<Pass
     a.out_sj = n1; a.out_sp = 1; a.out_so = (long long)K2 * n1;
     a.Np = n1; a.No = n0;
     a.in_jfast = 1; a.out_jfast = 0;
-    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 2, 0, 1));
+    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 2));
     out.push_back({a, n_src});
   }
   // P2: C2C along y (pruned input y < n1 of M1), transposing to [kz][ky][x]
@@ -1666,7 +1664,7 @@ hp_status passes_unbounded(hp_plan p, Problem& P, bool adjoint, std::vector<Pass
     a.out_sj = n0; a.out_sp = 1; a.out_so = (long long)M1 * n0;
     a.Np = n0; a.No = K2;
     a.in_jfast = 1; a.out_jfast = 0;
-    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 1, 0, 0));
+    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 1));
     out.push_back({a, n_src});
   }
   // P3: sandwich along x: forward (x < n0 of M0), Ghat, derivative, backward (x < n0)
@@ -1692,7 +1690,7 @@ hp_status passes_unbounded(hp_plan p, Problem& P, bool adjoint, std::vector<Pass
     const bool coupled = a.diff != D_NONE;
     a.n_in = coupled ? n_src : 1;
     a.n_out = coupled ? n_dst : 1;
-    HP_TRY(finish_pass(p, a, 16, 1, 0, 4));
+    HP_TRY(finish_pass(p, a, 16, 1));
     out.push_back({a, coupled ? 1 : nc});
   }
   // P4: backward C2C along y, keep y < n1, in place in B2
@@ -1707,7 +1705,7 @@ hp_status passes_unbounded(hp_plan p, Problem& P, bool adjoint, std::vector<Pass
     a.in_so = a.out_so = (long long)M1 * n0;
     a.Np = n0; a.No = K2;
     a.in_jfast = a.out_jfast = 0;
-    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 1, 0, 0));
+    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 1));
     out.push_back({a, n_dst});
   }
   // P5: C2R along z, keep z < n2, into the destination arrays [x][y][z]
@@ -1721,7 +1719,7 @@ hp_status passes_unbounded(hp_plan p, Problem& P, bool adjoint, std::vector<Pass
     a.out_sj = 1; a.out_sp = (long long)n1 * n2; a.out_so = n2;
     a.Np = n0; a.No = n1;
     a.in_jfast = 0; a.out_jfast = 1;
-    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 2, 0, 2));
+    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 2));
     out.push_back({a, n_dst});
   }
   return HP_OK;
@@ -1978,7 +1976,7 @@ hp_status passes_unbounded_low(hp_plan p, Problem& P, bool adjoint, std::vector<
     for (int f = 0; f < n_dst; ++f) a.out[f] = dst[f];
     a.in_sj = a.out_sj = 1;
     a.in_jfast = a.out_jfast = 1;
-    HP_TRY(finish_pass(p, a, 2, 2, 0, 5));
+    HP_TRY(finish_pass(p, a, 2, 2));
     out.push_back({a, coupled ? 1 : nc});
     return HP_OK;
   }
@@ -1997,7 +1995,7 @@ hp_status passes_unbounded_low(hp_plan p, Problem& P, bool adjoint, std::vector<
     a.out_sj = n0; a.out_sp = 1;
     a.Np = n0;
     a.in_jfast = 1; a.out_jfast = 0;
-    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 2, 0, 1));
+    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 2));
     out.push_back({a, n_src});
   }
   // P2: sandwich along x on the half spectrum ky < K1
@@ -2014,7 +2012,7 @@ hp_status passes_unbounded_low(hp_plan p, Problem& P, bool adjoint, std::vector<
     a.in_sp = a.out_sp = n0;
     a.Np = K1;
     a.in_jfast = a.out_jfast = 1;
-    HP_TRY(finish_pass(p, a, 16, 1, 0, 4));
+    HP_TRY(finish_pass(p, a, 16, 1));
     out.push_back({a, coupled ? 1 : nc});
   }
   // P3: C2R along y, keep y < n1, into the destination arrays [x][y]
@@ -2031,7 +2029,7 @@ hp_status passes_unbounded_low(hp_plan p, Problem& P, bool adjoint, std::vector<
     a.out_sj = 1; a.out_sp = n1;
     a.Np = n0;
     a.in_jfast = 0; a.out_jfast = 1;
-    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 2, 0, 2));
+    HP_TRY(finish_pass(p, a, p->prec == 0 ? 32 : 16, 2));
     out.push_back({a, n_dst});
   }
   return HP_OK;
@@ -2112,7 +2110,7 @@ hp_status passes_semi(hp_plan p, Problem& P, std::vector<PassRec>& out) {
     a.out[0] = work(comp);
     geom(a, j, first);
     if (first) fill_face_terms(P, comp, a);
-    HP_TRY(finish_pass(p, a, j == nd - 1 ? 16 : 32, 2, 0, 1));
+    HP_TRY(finish_pass(p, a, j == nd - 1 ? 16 : 32, 2));
     const void* q;
     HP_TRY(quarter(p, a.n, &q));
     a.qtw = q;
@@ -2167,7 +2165,7 @@ hp_status passes_semi(hp_plan p, Problem& P, std::vector<PassRec>& out) {
         q.deriv = fan_view(f, ws, es);
         fields.push_back(f);
       }
-      HP_TRY(finish_pass(p, a, 16, 2, 0, 5));
+      HP_TRY(finish_pass(p, a, 16, 2));
       PassRec r{a, 1};
       if (a.nfan > 0) r.bytes = fan_bytes(a, es);
       out.push_back(r);
@@ -2187,7 +2185,7 @@ hp_status passes_semi(hp_plan p, Problem& P, std::vector<PassRec>& out) {
       geom(a, j, false);
       HP_TRY(fan_pass(p, P, comp, a, j, xb[j], term_of(j), ws, fields));
       fan_stream(a, j == (u == nd - 1 ? nd - 2 : nd - 1), es);
-      HP_TRY(finish_pass(p, a, j == nd - 1 ? 16 : 32, 2, 0, 1));
+      HP_TRY(finish_pass(p, a, j == nd - 1 ? 16 : 32, 2));
       const void* q;
       HP_TRY(quarter(p, a.n, &q));
       a.qtw = q;

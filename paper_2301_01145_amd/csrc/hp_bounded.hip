@@ -278,7 +278,7 @@ __global__ void __launch_bounds__(64 * CW) kb_contig(const PassArgs a) {
   T* R = (T*)slot;  // the pair's reals: a at R[0..n), b at R[n..2n)
   const int pairs_p = (a.Np + 1) / 2;
   const long long total = (long long)pairs_p * a.No;
-  const int blk = off_lines(a, sizeof(T), sizeof(T)) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int blk = off_lines(a, sizeof(T), sizeof(T)) ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const long long pr = ((long long)blk * CW + wave) * PPW + qq;
   const bool valid = pr < total;
   const int o = valid ? (int)(pr / pairs_p) : 0;
@@ -361,7 +361,7 @@ __global__ void __launch_bounds__(strided_threads(W)) kb_strided(const PassArgs 
   T* tile = (T*)(slots + W * PPW * slot_len(L));
   const int tiles_p = (a.Np + P - 1) / P;
   const int ntiles = tiles_p * a.No;
-  int t = off_lines(a, sizeof(T), sizeof(T)) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  int t = off_lines(a, sizeof(T), sizeof(T)) ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   if (t >= ntiles) return;  // whole workgroup
   for (int m = threadIdx.x; m < L; m += NT) tw[m] = ((const C2<T>*)a.tw)[m];
   if (a.qtw)
@@ -539,7 +539,7 @@ __global__ void __launch_bounds__(64 * kR2RContigWaves) kb_contig_fan(const Pass
   const int pairs_p = (job.Np + 1) / 2;
   const long long total = (long long)pairs_p * job.No;
   const bool off = off_lines(a, sizeof(T), sizeof(T)), cached = off || !a.stream;
-  const int blk = off ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int blk = off ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const long long pr = ((long long)blk * kR2RContigWaves + wave) * PPW + qq;
   const bool valid = pr < total;
   const int o = valid ? (int)(pr / pairs_p) : 0;
@@ -629,7 +629,7 @@ __global__ void __launch_bounds__(64 * W) kb_strided_fan(const PassArgs) {
   T* dtile = TWO ? tile + n * TS : tile;
   const int tiles_p = (job.Np + P - 1) / P;
   const bool off = off_lines(a, sizeof(T), sizeof(T)), cached = off || !a.stream;
-  const int t = off ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int t = off ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   if (t >= tiles_p * job.No) return;  // whole workgroup
   for (int m = threadIdx.x; m < L; m += NT) tw[m] = ((const C2<T>*)a.tw)[m];
   if (a.qtw)

@@ -146,7 +146,7 @@ struct PassArgs {
 // Whether the rows of a pass start off the 128-byte cache lines on either side
 // (ei, eo: bytes of a stored element).  The tiles of such a pass share lines
 // with their neighbours; neighbouring tiles are then run on one XCD (workgroups
-// are dealt to the 8 XCDs in turn), so that the shared lines merge in one L2:
+// are dealt to the 8 XCDs in turn; xcd_block), so that the shared lines merge in one L2:
 // FP64 y pass of 121 x 97 x 81 points 16.4 -> 11.8 us.  Aligned rows keep the
 // plain order, which spreads a power-of-two grid over the memory channels
 // (FP32 128^3 y pass 8.5 us, 10.7 in XCD order).
@@ -155,13 +155,6 @@ __host__ __device__ inline bool off_lines(const PassArgs& a, int ei, int eo) {
   const long long o = a.out_jfast ? a.out_sp | a.out_so : a.out_sj | a.out_so;
   return ((i * ei) & 127) != 0 || ((o * eo) & 127) != 0;
 }
-// Tile of workgroup `bid` of `nb`, the tiles of one XCD contiguous: a bijection
-// on [0, nb).
-__host__ __device__ inline int xcd_tile(int bid, int nb) {
-  const int xcd = bid & 7, per = nb >> 3, rem = nb & 7;
-  return xcd * per + (xcd < rem ? xcd : rem) + (bid >> 3);
-}
-
 enum FastKind : int { FAST_NONE = 0, FAST_R2C = 1, FAST_FWD_Y = 2, FAST_SANDWICH = 3,
                       FAST_INV_Y = 4, FAST_C2R = 5,
                       // bounded real-to-real passes (hp_bounded.hip)

@@ -33,6 +33,7 @@
 #include "hp_faces.hpp"
 #include "hp_gendft.hpp"
 #include "hp_internal.hpp"
+#include "hp_wavefft.hpp"
 
 namespace hp {
 
@@ -344,7 +345,7 @@ __device__ __forceinline__ Tile tile_of(const PassArgs& a, int Np) {
   const int tiles_p = (Np + a.P - 1) / a.P;
   const int ei = (int)sizeof(T) * (xform_complex_in(a.xf) || a.xf == X_C2R ? 2 : 1);
   const int eo = (int)sizeof(T) * (xform_complex_in(a.xf) || a.xf == X_R2C ? 2 : 1);
-  const int b = off_lines(a, ei, eo) ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int b = off_lines(a, ei, eo) ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   Tile t;
   t.o = b / tiles_p;
   t.p0 = (b - t.o * tiles_p) * a.P;
@@ -1197,24 +1198,6 @@ __global__ void __launch_bounds__(kThreads) k_fan(const PassArgs) {
   else sandwich_rows_fan<T, MODE>(a, smem, t, q);
 }
 
-template <auto K>
-static void allow_lds() {
-  static bool done = false;  // one flag per kernel instantiation
-  if (!done) {
-    // ask for the whole 160 KB minus the kernel's static LDS; a refusal is
-    // not an error here (the launch itself reports a size that does not fit),
-    // so clear it instead of leaving it for the next hipGetLastError
-    hipFuncAttributes fa{};
-    size_t stat = 0;
-    if (hipFuncGetAttributes(&fa, (const void*)K) == hipSuccess) stat = fa.sharedSizeBytes;
-    else (void)hipGetLastError();
-    if (hipFuncSetAttribute((const void*)K, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)(160 * 1024 - stat)) != hipSuccess)
-      (void)hipGetLastError();
-    done = true;
-  }
-}
-
 template <typename T, int MODE, int KIND>
 static void launch_fan(const PassArgs& a, dim3 grid, hipStream_t s) {
   allow_lds<k_fan<T, MODE, KIND>>();
@@ -1242,14 +1225,12 @@ static void launch_t(const PassArgs& a, dim3 grid, hipStream_t s) {
 // Radices of the register stages (fft_lds); a larger one runs the prime stage.
 int max_radix(int prec) { return prec == 0 ? 16 : 10; }
 
-static int gen_mode(const PassArgs& a, int prec) {
+int general_mode(const PassArgs& a, int prec) {
   if (a.big) return GM_BIG;
   for (int s = 0; s < a.nstage; ++s)
     if (a.radix[s] > max_radix(prec)) return GM_PRIME;
   return GM_SMALL;
 }
-
-int general_mode(const PassArgs& a, int prec) { return gen_mode(a, prec); }
 
 template <typename T>
 static void launch_mode(const PassArgs& a, int mode, dim3 grid, hipStream_t s) {
@@ -1347,7 +1328,7 @@ hipError_t launch_pass(const PassArgs& pass, int prec, int grid_y, hipStream_t s
     grid_y = a.nfan;
   }
   dim3 grid(tiles, grid_y);
-  const int mode = gen_mode(a, prec);
+  const int mode = general_mode(a, prec);
   if (prec == 0) launch_mode<float>(a, mode, grid, s);
   else launch_mode<double>(a, mode, grid, s);
   return hipGetLastError();
