@@ -95,8 +95,9 @@ int mode_tiles(hp_plan p, const PassArgs& a) { return p->batch_wf ? batched_wf_t
 
 // One tile (strided wavefront items: one per group of wavefronts) per item:
 // more lengthen the chain of a workgroup and pay only where many rounds of
-// workgroups share the tables (8 problems: 85 us with 1, 95 with 2 tiles per
-// item; 64 problems: 484 and 467).
+// workgroups share the tables (FP32, 32 to 128 cells per axis: 8 problems 75 us with 1,
+// 92 with 2 tiles per item, 16 problems 116 and 130; 64 problems 372 and 371, 404 and
+// 396 with other sizes.  FP64: 8 problems 179 and 195, 64 problems 1318 and 1280).
 int batch_tiles_per_item() {
   if (const char* e = std::getenv("HP_BATCH_TILES")) {
     const int v = std::atoi(e);
