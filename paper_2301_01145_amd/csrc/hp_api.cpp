@@ -198,7 +198,10 @@ bool choose_radices(PassArgs& a, int prec) {
 //
 // The widest tile up to `want` pencils that fits 64 KB of LDS (two workgroups
 // per CU at least) with the smaller register budget, then 160 KB, then the
-// larger budget for the tiles of long transforms.  Where that leaves the chip
+// larger budget for the tiles of long transforms.  The LDS counts with padded rows:
+// chosen for rows without the pad, a wider tile leaves half the workgroups (adjoint of
+// a free-space 2D gradient of 1024^2 cells, x pass: 88 us with one pencil of 2048 points
+// per tile, 115 with two).  Where that leaves the chip
 // short of workgroups the tile is narrowed (kFillTiles): a pass of fewer tiles
 // than CUs takes as long as one tile does (FP64 periodic 2D of about 200 x 250
 // points, 16 and 5 tiles: 151 -> 38 us together with the stages above).
@@ -215,8 +218,8 @@ bool choose_tile(PassArgs& a, int prec, int want, int minP) {
         a.P = P;
         a.big = big;
         if (!choose_radices(a, prec)) continue;
+        if (general_lds_bytes(a, P, prec, true) > budget) continue;
         a.lds_bytes = general_lds_bytes(a, P, prec);
-        if (a.lds_bytes > budget) continue;
         while (P / 2 >= std::max(minP, kNarrowest) && (long long)((a.Np + P - 1) / P) * a.No < kFillTiles) {
           P >>= 1;
           a.P = P;

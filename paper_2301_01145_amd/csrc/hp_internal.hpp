@@ -243,7 +243,7 @@ bool fast_tile_ok(int fast, int L, int P, int prec);
 int max_radix(int prec);
 bool stages_fit(int L, long long nf, const int* radix, int nstage, int big, int prec);
 bool general_fits(const PassArgs& a, int prec);
-int general_lds_bytes(const PassArgs& a, int P, int prec);
+int general_lds_bytes(const PassArgs& a, int P, int prec, bool padded = false);
 int general_mode(const PassArgs& a, int prec);
 // Launch one pass over `grid_y` independent field groups.
 hipError_t launch_pass(const PassArgs& a, int prec, int grid_y, hipStream_t s);

@@ -1295,17 +1295,17 @@ static bool pass_tight(const PassArgs& a, int P, int prec) {
   return with <= 4 && lds / (row * nf) > with && (long long)((a.Np + P - 1) / P) * a.No > with * kCUs;
 }
 
-// LDS bytes of a general pass of tile width P: its FFT tiles and the table of the
-// largest prime stage (left out where it would not fit; the kernel sees the
-// room that is left).
-int general_lds_bytes(const PassArgs& a, int P, int prec) {
+// LDS bytes of a general pass of tile width P: its FFT tiles (`padded`: with padded
+// rows, also where the kernel leaves the pad out) and the table of the largest prime
+// stage (left out where it would not fit; the kernel sees the room that is left).
+int general_lds_bytes(const PassArgs& a, int P, int prec, bool padded) {
   const bool cplx = a.xf == X_C2C_F || a.xf == X_C2C_B;
   const int nf = cplx ? P : P / 2;
   int table = 0;
   for (int s = 0; s < a.nstage; ++s)
     if (a.radix[s] > max_radix(prec)) table = std::max(table, a.radix[s]);
   const long long cs = prec == 0 ? 8 : 16;
-  const long long data = (long long)pass_tiles(a) * a.L * tile_row(nf, !pass_tight(a, P, prec)) * cs;
+  const long long data = (long long)pass_tiles(a) * a.L * tile_row(nf, padded || !pass_tight(a, P, prec)) * cs;
   if (a.big && data + table * cs > 160 * 1024) table = 0;
   return (int)std::min<long long>(data + table * cs, 1 << 30);
 }
