@@ -1760,13 +1760,13 @@ bool fast_unbounded_ok(hp_plan p, const Problem& P) {
 //            301; 193 MB 587, 604.  Periodic plans only: the x pass of a free-space
 //            plan keeps its Green's rows in the caches (even at every size)
 //   x:       8 MB 33.9, 37.3; 32 MB 66.1, 62.7; 81 MB 115, 109; 129 MB 185, 194 and 199,
-//            204; 161 MB 207, 212; periodic plans 40 MB 84.1, 82.3; 65 MB 154, 160;
-//            81 MB 137, 144
+//            204; 161 MB 207, 212; adjoint 193 MB 430, 420; periodic plans 40 MB 84.1,
+//            82.3; 65 MB 154, 160; 81 MB 137, 144
 //   y back:  8 MB 33.9, 36.3; 12 MB 48.9, 47.9; 49 MB 89.5, 82.3; 130 MB 172, 154; 193 MB
 //            388, 379; 258 MB 288, 296
 // The fields that the C2R pass writes leave the solve and stay streaming (no
 // reader; cached they displace the next solve's input: R2C 82 -> 89 us).
-bool stream_out(int kind, bool periodic, double bytes) {
+bool stream_out(int kind, bool periodic, bool adjoint, double bytes) {
   constexpr double kMiB = 1024.0 * 1024.0;
   double lo = 20, hi = 256;
   switch (kind) {
@@ -1775,7 +1775,7 @@ bool stream_out(int kind, bool periodic, double bytes) {
       if (!periodic) return true;
       hi = 110;
       break;
-    case FAST_SANDWICH: hi = periodic ? 60 : 100; break;
+    case FAST_SANDWICH: hi = periodic ? 60 : adjoint ? 256 : 100; break;
     case FAST_INV_Y: lo = 10; break;
     default: return true;
   }
@@ -1861,7 +1861,7 @@ hp_status passes_unbounded_fast(hp_plan p, Problem& P, bool adjoint, std::vector
     for (int f = 0; f < n_src; ++f) { r.a.in[f] = src[f]; r.a.out[f] = P.a1[f]; }
     r.grid_y = n_src;
     r.bytes = n_live * ((double)n0 * n1 * n2 * es + (double)n0 * K2 * n1 * cs);
-    r.a.stream = stream_out(FAST_R2C, periodic, n_live * (double)n0 * K2 * n1 * cs);
+    r.a.stream = stream_out(FAST_R2C, periodic, adjoint, n_live * (double)n0 * K2 * n1 * cs);
   }
   // P2 - P4 per kz slab (one slab covering all K2 planes unless HP_SLAB set)
   for (const auto& slab : P.slabs) {
@@ -1875,7 +1875,7 @@ hp_status passes_unbounded_fast(hp_plan p, Problem& P, bool adjoint, std::vector
       for (int f = 0; f < n_src; ++f) { r.a.in[f] = src[f] ? P.a1[f] : nullptr; r.a.out[f] = P.b2[f]; }
       r.grid_y = n_src;
       r.bytes = n_live * ((double)n0 * kc * n1 * cs + (double)kc * M1 * n0 * cs);
-      r.a.stream = stream_out(FAST_FWD_Y, periodic, n_live * (double)kc * M1 * n0 * cs);
+      r.a.stream = stream_out(FAST_FWD_Y, periodic, adjoint, n_live * (double)kc * M1 * n0 * cs);
     }
     // P3: sandwich along x into C2
     HP_TRY(base(FAST_SANDWICH, M0));
@@ -1901,7 +1901,7 @@ hp_status passes_unbounded_fast(hp_plan p, Problem& P, bool adjoint, std::vector
                      ? nc : 1;
       const double oct = periodic ? 0.0 : (double)(M0 / 2 + 1) * (M1 / 2 + 1) * kc * es;
       r.bytes = (n_live + n_mid) * (double)kc * M1 * n0 * cs + oct;
-      a.stream = stream_out(FAST_SANDWICH, periodic, n_mid * (double)kc * M1 * n0 * cs);
+      a.stream = stream_out(FAST_SANDWICH, periodic, adjoint, n_mid * (double)kc * M1 * n0 * cs);
     }
     // P4: backward C2C along y (with derivative completion) into C1 (= A1 buffers)
     HP_TRY(base(FAST_INV_Y, M1));
@@ -1914,7 +1914,7 @@ hp_status passes_unbounded_fast(hp_plan p, Problem& P, bool adjoint, std::vector
       for (int f = 0; f < n_dst; ++f) r.a.out[f] = P.c1.empty() ? P.a1[f] : P.c1[f];
       r.grid_y = iy_mode == IY_PLAIN ? n_mid : (iy_mode == IY_CURL5 ? 2 : 1);
       r.bytes = n_mid * (double)kc * n0 * M1 * cs + n_dst * (double)n1 * n0 * kc * cs;
-      r.a.stream = stream_out(FAST_INV_Y, periodic, n_dst * (double)n1 * n0 * K2 * cs);
+      r.a.stream = stream_out(FAST_INV_Y, periodic, adjoint, n_dst * (double)n1 * n0 * K2 * cs);
     }
   }
   // P5: C2R along z into the destination arrays
@@ -1924,7 +1924,7 @@ hp_status passes_unbounded_fast(hp_plan p, Problem& P, bool adjoint, std::vector
     for (int f = 0; f < n_dst; ++f) { r.a.in[f] = P.c1.empty() ? P.a1[f] : P.c1[f]; r.a.out[f] = dst[f]; }
     r.grid_y = n_dst;
     r.bytes = n_dst * ((double)n1 * n0 * K2 * cs + (double)n0 * n1 * n2 * es);
-    r.a.stream = stream_out(FAST_C2R, periodic, 0.0);
+    r.a.stream = stream_out(FAST_C2R, periodic, adjoint, 0.0);
   }
   return HP_OK;
 }

@@ -201,7 +201,10 @@ __global__ void __launch_bounds__(64 * (P / WF<L>::PPW)) kf_fwd_y(const PassArgs
 // of psi, the gradient and the curl only.  They always stream below 256 points;
 // from there they branch (with_stream), where that takes no wavefront from a CU in
 // FP64 and the compiler's other schedule is the faster one (128^3 divergence, x
-// pass: FP64 240 us without the branch, 227 with; FP32 111, 102).
+// pass: FP64 240 us without the branch, 227 with; FP32 111, 102).  The adjoint of the
+// gradient and the curl branches too: FP32 instances of 128 and 256 points take
+// 170 and 172 registers without the branch, two wavefronts per SIMD instead of
+// three (128^3 curl adjoint, x pass: 148 us without, 134 with).
 template <typename T, int L, int P, bool ADJ, bool DBL, bool PAD, bool EXT, bool STREAM>
 __global__ void __launch_bounds__(64 * (P / WF<L>::PPW),
                                   (sizeof(T) == 4 && P == 8 && L == 512 && !ADJ && !EXT) ? 4 : 1)
@@ -369,7 +372,7 @@ __global__ void __launch_bounds__(64 * (P / WF<L>::PPW),
           st_out<decltype(ST)::value>(&d[x * M1 + c], tile[row(x) * TS + c]);
         }
       };
-      if constexpr (EXT && L >= 256) with_stream(a, put);
+      if constexpr (EXT ? L >= 256 : ADJ) with_stream(a, put);
       else put(std::integral_constant<bool, STREAM>{});
       if (DBL) tb ^= 1;
       else __syncthreads();
@@ -789,8 +792,7 @@ static hipError_t launch_LP(const PassArgs& a0, int grid_y, hipStream_t s) {
     constexpr bool kPlan = P == 8 && DBL == (sizeof(T) == 8);     \
     if (ext && adj) HP_SW(true, DBL, true, true);                 \
     else if (ext) HP_SW(false, DBL, true, true);                  \
-    else if (adj && (a.stream || !kPlan)) HP_SW(true, DBL, false, true); \
-    else if (adj) HP_SW(true, DBL, false, !kPlan);                \
+    else if (adj) HP_SW(true, DBL, false, true);                  \
     else if (a.stream || !kPlan) HP_SW(false, DBL, false, true);  \
     else HP_SW(false, DBL, false, !kPlan);                        \
   } while (0)
