@@ -1760,7 +1760,7 @@ bool fast_unbounded_ok(hp_plan p, const Problem& P) {
 //            301; 193 MB 587, 604.  Periodic plans only: the x pass of a free-space
 //            plan keeps its Green's rows in the caches (even at every size)
 //   x:       8 MB 33.9, 37.3; 32 MB 66.1, 62.7; 81 MB 115, 109; 129 MB 185, 194 and 199,
-//            204; 161 MB 207, 212; adjoint 193 MB 430, 420; periodic plans 40 MB 84.1,
+//            204; 161 MB 207, 212; adjoint 193 MB 441, 426; periodic plans 40 MB 84.1,
 //            82.3; 65 MB 154, 160; 81 MB 137, 144
 //   y back:  8 MB 33.9, 36.3; 12 MB 48.9, 47.9; 49 MB 89.5, 82.3; 130 MB 172, 154; 193 MB
 //            388, 379; 258 MB 288, 296
