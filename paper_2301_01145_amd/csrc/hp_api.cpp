@@ -1086,20 +1086,22 @@ void boundary_fill(const Problem& P, std::vector<PassRec>& out) {
   r.a.fast = FAST_FILL;
   r.a.Np = r.a.No = 1;
   r.bytes = 0.0;  // surfaces: not in the byte model
-  r.fill.ndim = P.nd;
-  for (int a = 0; a < 3; ++a) r.fill.N[a] = a < P.nd ? P.nout[a] : 1;
+  FillArgs f{};
+  f.ndim = P.nd;
+  for (int a = 0; a < 3; ++a) f.N[a] = a < P.nd ? P.nout[a] : 1;
+  auto flush = [&] {
+    r.fill.assign(1, f);
+    out.push_back(r);
+    f.nf = 0;
+  };
   auto add = [&](void* dst, int axes, int comp) {
     if (!axes) return;
-    FillArgs& f = r.fill;
     f.out[f.nf] = dst;
     f.axes[f.nf] = axes;
     for (int a = 0; a < 3; ++a)
       for (int s = 0; s < 2; ++s)
         f.face[f.nf][a][s] = comp >= 0 && P.d.inhomogeneous && a < P.nd ? P.face[a][s][comp] : nullptr;
-    if (++f.nf == kMaxFill) {
-      out.push_back(r);
-      f.nf = 0;
-    }
+    if (++f.nf == kMaxFill) flush();
   };
   for (int c = 0; c < P.ncomp; ++c) add(P.out[c], dmask, c);
   for (const DerivTerm& t : derivative_terms(P)) {
@@ -1110,7 +1112,7 @@ void boundary_fill(const Problem& P, std::vector<PassRec>& out) {
     }
     add(t.dst, axes, -1);
   }
-  if (r.fill.nf > 0) out.push_back(r);
+  if (f.nf > 0) flush();
 }
 
 // DIV / 3D CURL: the second terms added into the outputs (elementwise)
@@ -2207,6 +2209,8 @@ hp_status passes_semi(hp_plan p, Problem& P, std::vector<PassRec>& out) {
 }
 
 hp_status build_passes(hp_plan p, Problem& P, bool adjoint, std::vector<PassRec>& out) {
+  // every solve builds its list: the records, 1 KB each, are not moved as it grows
+  out.reserve(out.size() + 16);
   if (P.d.bc == HP_UNBOUNDED) {
     if (P.nd < 3) return passes_unbounded_low(p, P, adjoint, out);
     if (fast_unbounded_ok(p, P)) return passes_unbounded_fast(p, P, adjoint, out);
@@ -2283,7 +2287,7 @@ hp_status next_event(hp_plan p, hipEvent_t* e) {
 }
 
 hipError_t launch_one(hp_plan p, const PassRec& r) {
-  return r.a.fast == FAST_FILL    ? launch_boundary_fill(r.fill, p->prec, p->stream)
+  return r.a.fast == FAST_FILL    ? launch_boundary_fill(r.fill[0], p->prec, p->stream)
          : r.a.fast >= FAST_R2R_C ? launch_bounded(r.a, p->prec, p->stream)
          : r.a.fast               ? launch_fast(r.a, p->prec, r.grid_y, p->stream)
                                   : launch_pass(r.a, p->prec, r.grid_y, p->stream);

@@ -24,7 +24,7 @@ struct PassRec {
   PassArgs a;
   int grid_y;
   double bytes = -1.0;  // algorithmic bytes when set by the planner
-  FillArgs fill{};      // FAST_FILL
+  std::vector<FillArgs> fill{};  // FAST_FILL: its arguments
 };
 
 struct Problem {
